@@ -2995,9 +2995,10 @@ struct ccut_mlp {
   uint64_t work_rows = 0;
   float *p = nullptr, *g = nullptr, *m = nullptr, *v = nullptr;
   uint16_t *pb = nullptr;  // bf16 copy of the parameters used by the products
+  uint16_t *w1 = nullptr, *w2 = nullptr, *w3 = nullptr, *w2t = nullptr, *w3t = nullptr;  // weights in lane order (training)
   uint64_t t = 0;          // Adam step count
   uint16_t *xb = nullptr, *h1 = nullptr, *h2 = nullptr, *h3 = nullptr, *d1 = nullptr, *d2 = nullptr, *d3 = nullptr;
-  float *y = nullptr, *tb = nullptr, *dy = nullptr, *sq = nullptr, *part = nullptr;
+  float *dy = nullptr, *sq = nullptr, *part = nullptr;
   ~ccut_mlp() {
     if (ctx && ctx->device >= 0) {
       (void)hipSetDevice(ctx->device);
@@ -3068,12 +3069,10 @@ ccut_status sync_call(ccut_ctx *c) {
   return CCUT_OK;
 }
 
-ccut_status mlp_gemm(ccut_ctx *c, const uint16_t *A, uint64_t sam, uint64_t sak, const uint16_t *B, uint64_t sbk,
-                     uint64_t sbn, uint64_t M, uint32_t N, uint32_t K, void *C, uint64_t ldc, int epi,
-                     const float *bias = nullptr, const uint16_t *mask = nullptr, uint64_t ldm = 0) {
-  MlpGemm g{A, sam, sak, B, sbk, sbn, M, N, K, C, ldc, bias, mask, ldm};
-  HIP_TRY(c, launch_mlp_gemm(g, epi, c->cur));
-  return CCUT_OK;
+// The network's parameters and their copies, as the training kernels take them.
+TrainParams mlp_params(const ccut_mlp *M) {
+  return {M->n_params, M->F, M->H, M->off_b1, M->off_w2, M->off_b2, M->off_w3, M->off_b3, M->off_w4, M->off_b4,
+          M->p, M->g, M->m, M->v, M->part, M->pb, M->w1, M->w2, M->w3, M->w2t, M->w3t};
 }
 
 ccut_status mlp_ensure_work(ccut_mlp *M, uint64_t rows) {
@@ -3091,13 +3090,10 @@ ccut_status mlp_ensure_work(ccut_mlp *M, uint64_t rows) {
   M->d1 = b16(rows * H);
   M->d2 = b16(rows * H);
   M->d3 = b16(rows * H);
-  M->y = f32(rows);
-  M->tb = f32(rows);
   M->dy = f32(rows);
   M->sq = f32(rows);
-  M->part = f32((uint64_t)colsum_chunks(rows) * std::max(H, F));
-  if (!M->xb || !M->h1 || !M->h2 || !M->h3 || !M->d1 || !M->d2 || !M->d3 || !M->y || !M->tb || !M->dy || !M->sq ||
-      !M->part) {
+  M->part = f32(4 * train_chunks(rows) * H);
+  if (!M->xb || !M->h1 || !M->h2 || !M->h3 || !M->d1 || !M->d2 || !M->d3 || !M->dy || !M->sq || !M->part) {
     M->work.release();
     M->work_rows = 0;
     return fail(c, CCUT_E_OOM, "device allocation failed");
@@ -3106,50 +3102,73 @@ ccut_status mlp_ensure_work(ccut_mlp *M, uint64_t rows) {
   return CCUT_OK;
 }
 
-// h1..h3 and y for rows of x (rows <= work_rows)
+// y for rows of x (rows <= work_rows); leaves the layers' outputs in h1..h3
 ccut_status mlp_forward_rows(ccut_mlp *M, const uint16_t *x, uint64_t rows, float *y, float scale = 1.f) {
   ccut_ctx *c = M->ctx;
   const uint32_t F = M->F, H = M->H;
-  ccut_status st;
   KTimer t(c, CCUT_K_MLP);
-  if ((st = mlp_gemm(c, x, F, 1, M->pb + M->off_w1, 1, F, rows, H, F, M->h1, H, MLP_EPI_BIAS_RELU,
-                     M->p + M->off_b1)) != CCUT_OK)
-    return st;
-  if ((st = mlp_gemm(c, M->h1, H, 1, M->pb + M->off_w2, 1, H, rows, H, H, M->h2, H, MLP_EPI_BIAS_RELU,
-                     M->p + M->off_b2)) != CCUT_OK)
-    return st;
-  if ((st = mlp_gemm(c, M->h2, H, 1, M->pb + M->off_w3, 1, H, rows, H, H, M->h3, H, MLP_EPI_BIAS_RELU,
-                     M->p + M->off_b3)) != CCUT_OK)
-    return st;
+  HIP_TRY(c, launch_mlp_gemm({x, M->pb + M->off_w1, rows, H, F, M->h1, M->p + M->off_b1}, c->cur));
+  HIP_TRY(c, launch_mlp_gemm({M->h1, M->pb + M->off_w2, rows, H, H, M->h2, M->p + M->off_b2}, c->cur));
+  HIP_TRY(c, launch_mlp_gemm({M->h2, M->pb + M->off_w3, rows, H, H, M->h3, M->p + M->off_b3}, c->cur));
   HIP_TRY(c, launch_head_forward(M->h3, H, rows, M->pb + M->off_w4, M->p + M->off_b4, scale, y, c->cur));
   return CCUT_OK;
 }
 
-// Gradient of the mean squared error into M->g after mlp_forward_rows on
-// the same rows; loss_sum (device) receives sum (y - t)^2.
-ccut_status mlp_backward_rows(ccut_mlp *M, const uint16_t *x, const float *t, uint64_t rows, float *loss_sum) {
+// Forward and backward of one batch of `rows` rows (a multiple of 64, at
+// most work_rows): the weight gradients and the head bias's into M->g, the
+// column sums of the others into M->part; loss_sum (device) receives
+// sum (y - t)^2.  The rows are data rows drawn for `step` (gather), or rows
+// 0 .. rows - 1; x bf16, or xf fp32 (rounded).
+ccut_status mlp_batch_grads(ccut_mlp *M, const uint16_t *x, const float *xf, const float *t, uint64_t n, uint64_t rows,
+                            bool gather, uint32_t step, uint64_t seed, float *loss_sum) {
   ccut_ctx *c = M->ctx;
-  const uint32_t F = M->F, H = M->H;
-  const uint32_t R = (uint32_t)rows;
-  ccut_status st;
+  TrainRows r{};
+  r.x = x;
+  r.xf = xf;
+  r.t = t;
+  r.n = n;
+  r.rows = rows;
+  r.F = M->F;
+  r.H = M->H;
+  r.step = step;
+  r.gather = gather;
+  r.seed = seed;
+  r.w1 = M->w1;
+  r.w2 = M->w2;
+  r.w3 = M->w3;
+  r.w2t = M->w2t;
+  r.w3t = M->w3t;
+  r.w4 = M->pb + M->off_w4;
+  r.b1 = M->p + M->off_b1;
+  r.b2 = M->p + M->off_b2;
+  r.b3 = M->p + M->off_b3;
+  r.b4 = M->p + M->off_b4;
+  r.inv_b2 = 2.0f / (float)rows;
+  r.xb = M->xb;
+  r.h1 = M->h1;
+  r.h2 = M->h2;
+  r.h3 = M->h3;
+  r.d1 = M->d1;
+  r.d2 = M->d2;
+  r.d3 = M->d3;
+  r.dy = M->dy;
+  r.sq = M->sq;
   KTimer tm(c, CCUT_K_MLP);
-  HIP_TRY(c, launch_head_backward(M->h3, H, rows, M->pb + M->off_w4, M->y, t, M->dy, M->sq, M->d3, c->cur));
-  HIP_TRY(c, launch_colsum(M->h3, H, rows, M->dy, M->part, M->g + M->off_w4, c->cur));
-  HIP_TRY(c, launch_vsum(M->dy, rows, M->g + M->off_b4, c->cur));
-  HIP_TRY(c, launch_vsum(M->sq, rows, loss_sum, c->cur));
-  // layer 3: dW3 = dZ3^T H2, db3 = colsum dZ3, dZ2 = (dZ3 W3) [H2 > 0]
-  const uint16_t *hin[3] = {x, M->h1, M->h2};
-  uint16_t *dz[3] = {M->d1, M->d2, M->d3};
-  const uint64_t offw[3] = {M->off_w1, M->off_w2, M->off_w3}, offb[3] = {M->off_b1, M->off_b2, M->off_b3};
-  for (int l = 2; l >= 0; --l) {
-    const uint32_t in = l == 0 ? F : H;
-    if ((st = mlp_gemm(c, dz[l], 1, H, hin[l], in, 1, H, in, R, M->g + offw[l], in, MLP_EPI_F32)) != CCUT_OK)
-      return st;
-    HIP_TRY(c, launch_colsum(dz[l], H, rows, nullptr, M->part, M->g + offb[l], c->cur));
-    if (l > 0 && (st = mlp_gemm(c, dz[l], H, 1, M->pb + offw[l], H, 1, rows, H, H, dz[l - 1], H, MLP_EPI_MASK,
-                                nullptr, hin[l], H)) != CCUT_OK)
-      return st;
-  }
+  HIP_TRY(c, launch_train_rows(r, c->cur));
+  TrainGrads g{M->F, M->H, rows, M->xb, M->h1, M->h2, M->h3, M->d1, M->d2, M->d3, M->dy, M->sq,
+               M->g + M->off_w1, M->g + M->off_w2, M->g + M->off_w3, M->g + M->off_b4, loss_sum, M->part};
+  HIP_TRY(c, launch_train_grads(g, c->cur));
+  return CCUT_OK;
+}
+
+// One Adam step from the gradients of mlp_batch_grads over `rows` rows.
+ccut_status mlp_update(ccut_mlp *M, uint64_t rows, float lr) {
+  ccut_ctx *c = M->ctx;
+  M->t += 1;
+  const float c1 = (float)(1.0 - std::pow(0.9, (double)M->t));
+  const float c2 = (float)(1.0 - std::pow(0.999, (double)M->t));
+  KTimer tm(c, CCUT_K_MLP);
+  HIP_TRY(c, launch_train_update(mlp_params(M), rows, lr, 0.9f, 0.999f, c1, c2, 1e-8f, c->cur));
   return CCUT_OK;
 }
 
@@ -3202,7 +3221,10 @@ ccut_status ccut_mlp_create(ccut_ctx *c, uint32_t F, uint32_t H, ccut_mlp **out)
   M->m = (float *)M->arena.get(o * 4);
   M->v = (float *)M->arena.get(o * 4);
   M->pb = (uint16_t *)M->arena.get(o * 2);
-  if (!M->p || !M->g || !M->m || !M->v || !M->pb) return fail(c, CCUT_E_OOM, "device allocation failed");
+  M->w1 = (uint16_t *)M->arena.get((uint64_t)H * F * 2);
+  for (uint16_t **w : {&M->w2, &M->w3, &M->w2t, &M->w3t}) *w = (uint16_t *)M->arena.get((uint64_t)H * H * 2);
+  if (!M->p || !M->g || !M->m || !M->v || !M->pb || !M->w1 || !M->w2 || !M->w3 || !M->w2t || !M->w3t)
+    return fail(c, CCUT_E_OOM, "device allocation failed");
   // He-style uniform initialisation (limits sqrt(6 / fan_in), output layer
   // sqrt(3 / fan_in)), biases zero
   std::vector<float> init(o, 0.f);
@@ -3234,7 +3256,7 @@ ccut_status ccut_mlp_set_params(ccut_mlp *M, const float *params, size_t count) 
   HIP_TRY(c, hipMemcpyAsync(M->p, params, count * 4, hipMemcpyHostToDevice, c->stream));
   HIP_TRY(c, hipMemsetAsync(M->m, 0, count * 4, c->stream));
   HIP_TRY(c, hipMemsetAsync(M->v, 0, count * 4, c->stream));
-  HIP_TRY(c, launch_to_bf16(M->p, M->pb, count, c->stream));
+  HIP_TRY(c, launch_train_copies(mlp_params(M), c->stream));
   M->t = 0;
   return sync_call(c);
 }
@@ -3273,8 +3295,8 @@ ccut_status ccut_mlp_gradients(ccut_mlp *M, const uint16_t *x, const float *t, u
   if ((st = mlp_ensure_work(M, n)) != CCUT_OK) return st;
   float *lsum = aget<float>(c, 1);
   if (!lsum) return fail(c, CCUT_E_OOM, "device allocation failed");
-  if ((st = mlp_forward_rows(M, x, n, M->y)) != CCUT_OK) return st;
-  if ((st = mlp_backward_rows(M, x, t, n, lsum)) != CCUT_OK) return st;
+  if ((st = mlp_batch_grads(M, x, nullptr, t, n, n, false, 0, 0, lsum)) != CCUT_OK) return st;
+  HIP_TRY(c, launch_train_gradients(mlp_params(M), n, c->cur));
   float hl = 0.f;
   HIP_TRY(c, hipMemcpyAsync(grads, M->g, M->n_params * 4, hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipMemcpyAsync(&hl, lsum, 4, hipMemcpyDeviceToHost, c->stream));
@@ -3295,16 +3317,9 @@ ccut_status ccut_mlp_train(ccut_mlp *M, const uint16_t *x, const float *t, uint6
   if ((st = mlp_ensure_work(M, batch)) != CCUT_OK) return st;
   float *lsum = aget<float>(c, std::max<uint32_t>(steps, 1));
   if (!lsum) return fail(c, CCUT_E_OOM, "device allocation failed");
-  const int in_order = batch == n;
   for (uint32_t s = 0; s < steps; ++s) {
-    HIP_TRY(c, launch_gather_rows(x, t, n, M->F, batch, s, seed, in_order, M->xb, M->tb, c->stream));
-    if ((st = mlp_forward_rows(M, M->xb, batch, M->y)) != CCUT_OK) return st;
-    if ((st = mlp_backward_rows(M, M->xb, M->tb, batch, lsum + s)) != CCUT_OK) return st;
-    M->t += 1;
-    const float c1 = (float)(1.0 - std::pow(0.9, (double)M->t));
-    const float c2 = (float)(1.0 - std::pow(0.999, (double)M->t));
-    KTimer tm(c, CCUT_K_MLP);
-    HIP_TRY(c, launch_adam(M->p, M->g, M->m, M->v, M->pb, M->n_params, lr, 0.9f, 0.999f, c1, c2, 1e-8f, c->stream));
+    if ((st = mlp_batch_grads(M, x, nullptr, t, n, batch, batch != n, s, seed, lsum + s)) != CCUT_OK) return st;
+    if ((st = mlp_update(M, batch, lr)) != CCUT_OK) return st;
   }
   if (losses && steps) {
     HIP_TRY(c, hipMemcpyAsync(losses, lsum, steps * 4, hipMemcpyDeviceToHost, c->stream));
@@ -3676,17 +3691,8 @@ ccut_status ccut_mlp_train_step(ccut_mlp *M, const float *x, const float *t, uin
   float *lsum = aget<float>(c, 1);
   if (!lsum) return fail(c, CCUT_E_OOM, "device allocation failed");
   // the batch is every row, in order: features rounded to bf16, targets as given
-  HIP_TRY(c, launch_to_bf16(x, M->xb, n * M->F, c->stream));
-  HIP_TRY(c, hipMemcpyAsync(M->tb, t, n * 4, hipMemcpyDeviceToDevice, c->stream));
-  if ((st = mlp_forward_rows(M, M->xb, n, M->y)) != CCUT_OK) return st;
-  if ((st = mlp_backward_rows(M, M->xb, M->tb, n, lsum)) != CCUT_OK) return st;
-  M->t += 1;
-  const float c1 = (float)(1.0 - std::pow(0.9, (double)M->t));
-  const float c2 = (float)(1.0 - std::pow(0.999, (double)M->t));
-  {
-    KTimer tm(c, CCUT_K_MLP);
-    HIP_TRY(c, launch_adam(M->p, M->g, M->m, M->v, M->pb, M->n_params, lr, 0.9f, 0.999f, c1, c2, 1e-8f, c->stream));
-  }
+  if ((st = mlp_batch_grads(M, nullptr, x, t, n, n, false, 0, 0, lsum)) != CCUT_OK) return st;
+  if ((st = mlp_update(M, n, lr)) != CCUT_OK) return st;
   if (loss) {
     HIP_TRY(c, hipMemcpyAsync(loss, lsum, 4, hipMemcpyDeviceToHost, c->stream));
     if ((st = sync_call(c)) != CCUT_OK) return st;

@@ -562,34 +562,64 @@ hipError_t launch_recombine_gemm(const GemmArgs &h, const GemmArgs *d_args, bool
 
 
 // ------------------------------------------------- learned term proposal
-enum MlpEpilogue : int { MLP_EPI_F32 = 0, MLP_EPI_BIAS_RELU = 1, MLP_EPI_MASK = 2 };
+// C = relu(A B + bias) as bf16 (fp32 accumulation); A and B with the inner
+// index contiguous.
 struct MlpGemm {
-  const uint16_t *A;  // bf16, A(m, k) = A[m sam + k sak]
-  uint64_t sam, sak;
-  const uint16_t *B;  // bf16, B(k, n) = B[k sbk + n sbn]
-  uint64_t sbk, sbn;
+  const uint16_t *A;  // bf16 [M][K]
+  const uint16_t *B;  // bf16 [N][K]
   uint64_t M;
   uint32_t N, K;
-  void *C;             // fp32 (MLP_EPI_F32) or bf16
-  uint64_t ldc;
-  const float *bias;   // MLP_EPI_BIAS_RELU
-  const uint16_t *mask;  // MLP_EPI_MASK: bf16 layer output, row stride ldm
-  uint64_t ldm;
+  uint16_t *C;        // bf16 [M][N]
+  const float *bias;
 };
-hipError_t launch_mlp_gemm(const MlpGemm &g, int epi, hipStream_t s);
+hipError_t launch_mlp_gemm(const MlpGemm &g, hipStream_t s);
 hipError_t launch_head_forward(const uint16_t *H, uint32_t width, uint64_t rows, const uint16_t *w, const float *b,
                                float scale, float *y, hipStream_t s);
-hipError_t launch_head_backward(const uint16_t *H, uint32_t width, uint64_t rows, const uint16_t *w, const float *y,
-                                const float *t, float *dy, float *sq, uint16_t *dZ, hipStream_t s);
-uint32_t colsum_chunks(uint64_t rows);
-hipError_t launch_colsum(const uint16_t *X, uint32_t width, uint64_t rows, const float *sc, float *part, float *out,
-                         hipStream_t s);
-hipError_t launch_vsum(const float *x, uint64_t n, float *out, hipStream_t s);
-hipError_t launch_adam(float *p, const float *g, float *m, float *v, uint16_t *pb, uint64_t n, float lr, float b1,
-                       float b2, float c1, float c2, float eps, hipStream_t s);
-hipError_t launch_to_bf16(const float *p, uint16_t *pb, uint64_t n, hipStream_t s);
-hipError_t launch_gather_rows(const uint16_t *X, const float *y, uint64_t n, uint32_t width, uint32_t batch,
-                              uint32_t step, uint64_t seed, int in_order, uint16_t *Xb, float *yb, hipStream_t s);
+
+// Training (k_train.hip).  Weights in lane order: see lane_order there.
+constexpr uint32_t kColChunkRows = 256;  // rows of one column-sum chunk
+inline uint64_t train_chunks(uint64_t rows) { return (rows + kColChunkRows - 1) / kColChunkRows; }
+// One step's rows: the batch gathered (row i = data row philox(i, step) mod
+// n, or row i), forward, loss terms, gradients at every pre-activation.
+struct TrainRows {
+  const uint16_t *x;  // data set [n][F] (bf16), or
+  const float *xf;    // [n][F] fp32, rounded to bf16 when read (x unused)
+  const float *t;     // [n]
+  uint64_t n, rows;
+  uint32_t F, H, step, gather;
+  uint64_t seed;
+  const uint16_t *w1, *w2, *w3, *w3t, *w2t;  // lane order
+  const uint16_t *w4;
+  const float *b1, *b2, *b3, *b4;
+  float inv_b2;  // 2 / rows
+  uint16_t *xb, *h1, *h2, *h3, *d1, *d2, *d3;
+  float *dy, *sq;
+};
+hipError_t launch_train_rows(const TrainRows &g, hipStream_t s);
+// The sums over the batch: weight gradients, column-sum chunks
+// part[kind][chunk][H] (kind 0: h3 weighted by dy, 1..3: d3, d2, d1), the
+// head bias gradient and the summed loss.
+struct TrainGrads {
+  uint32_t F, H;
+  uint64_t rows;
+  const uint16_t *xb, *h1, *h2, *h3, *d1, *d2, *d3;
+  const float *dy, *sq;
+  float *gw1, *gw2, *gw3, *gb4, *loss, *part;
+};
+hipError_t launch_train_grads(const TrainGrads &g, hipStream_t s);
+struct TrainParams {
+  uint64_t n;  // parameters
+  uint32_t F, H;
+  uint64_t off_b1, off_w2, off_b2, off_w3, off_b3, off_w4, off_b4;
+  float *p, *g, *m, *v;
+  const float *part;
+  uint16_t *pb, *w1, *w2, *w3, *w2t, *w3t;  // bf16 copies: row-major, and in lane order
+};
+// g completed by the column sums; Adam and the bf16 copies; the copies alone
+hipError_t launch_train_gradients(const TrainParams &P, uint64_t rows, hipStream_t s);
+hipError_t launch_train_update(const TrainParams &P, uint64_t rows, float lr, float b1, float b2, float c1, float c2,
+                               float eps, hipStream_t s);
+hipError_t launch_train_copies(const TrainParams &P, hipStream_t s);
 
 // The network regresses ln-weights divided by this scale (targets in
 // [-1.04, 0]); its logits are the scale times its output.

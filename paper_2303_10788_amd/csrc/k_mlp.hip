@@ -12,6 +12,7 @@
 #include <cmath>
 #include <mutex>
 
+#include "bf16.hpp"
 #include "ccut.h"
 #include "common.hpp"
 
@@ -19,26 +20,11 @@ namespace ccut {
 
 namespace {
 
-typedef short short4v __attribute__((ext_vector_type(4)));
-typedef float float4v __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
-// fp32 -> bf16, round to nearest even (NaN kept quiet)
-__device__ inline uint16_t f2bf(float x) {
-  uint32_t u = __float_as_uint(x);
-  if ((u & 0x7F800000u) == 0x7F800000u && (u & 0x7FFFFFu)) return (uint16_t)((u >> 16) | 0x40u);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
-__device__ inline float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-
 constexpr int MG_T = 64, MG_K = 32, MG_PAD = 8, MG_THREADS = 256;
 
-// C[M x N] = sum_k A(m, k) B(k, n), A(m, k) = A[m sam + k sak],
-// B(k, n) = B[k sbk + n sbn] (bf16), fp32 accumulation; one of the
-// strides of each operand is 1.  Rows m >= M read as zero and are not
-// written; N % 64 == 0 and K % 32 == 0.
-template <int EPI>
+// C[m][n] = relu(sum_k A[m][k] B[n][k] + bias[n]) as bf16, fp32
+// accumulation.  Rows m >= M read as zero and are not written; N % 64 == 0
+// and K % 32 == 0.
 __global__ __launch_bounds__(MG_THREADS) void mlp_gemm_kernel(const MlpGemm g) {
   __shared__ __attribute__((aligned(16))) uint16_t As[MG_T][MG_K + MG_PAD];  // [m][k]
   __shared__ __attribute__((aligned(16))) uint16_t Bs[MG_T][MG_K + MG_PAD];  // [n][k]
@@ -52,38 +38,12 @@ __global__ __launch_bounds__(MG_THREADS) void mlp_gemm_kernel(const MlpGemm g) {
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = float4v{0.f, 0.f, 0.f, 0.f};
   for (uint32_t k0 = 0; k0 < g.K; k0 += MG_K) {
-    // A tile: 64 rows x 32 k, eight contiguous elements per thread
-    if (g.sak == 1) {
-      const uint32_t mm = tid >> 2, kc = (tid & 3) * 8;
-      uint4 v = make_uint4(0, 0, 0, 0);
-      if (m0 + mm < g.M) v = *(const uint4 *)(g.A + (m0 + mm) * g.sam + k0 + kc);
-      *(uint4 *)&As[mm][kc] = v;
-    } else {
-      const uint32_t kk = tid >> 3, mc = (tid & 7) * 8;
-      uint16_t e[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-      if (m0 + mc + 8 <= g.M) {
-        const uint4 v = *(const uint4 *)(g.A + (m0 + mc) + (uint64_t)(k0 + kk) * g.sak);
-        const uint16_t *pv = (const uint16_t *)&v;
-#pragma unroll
-        for (int t = 0; t < 8; ++t) e[t] = pv[t];
-      } else {
-        for (int t = 0; t < 8; ++t)
-          if (m0 + mc + t < g.M) e[t] = g.A[(m0 + mc + t) + (uint64_t)(k0 + kk) * g.sak];
-      }
-#pragma unroll
-      for (int t = 0; t < 8; ++t) As[mc + t][kk] = e[t];
-    }
-    // B tile: 32 k x 64 columns, stored [n][k]
-    if (g.sbk == 1) {
-      const uint32_t nn = tid >> 2, kc = (tid & 3) * 8;
-      *(uint4 *)&Bs[nn][kc] = *(const uint4 *)(g.B + (uint64_t)(n0 + nn) * g.sbn + k0 + kc);
-    } else {
-      const uint32_t kk = tid >> 3, nc = (tid & 7) * 8;
-      const uint4 v = *(const uint4 *)(g.B + (uint64_t)(k0 + kk) * g.sbk + n0 + nc);
-      const uint16_t *pv = (const uint16_t *)&v;
-#pragma unroll
-      for (int t = 0; t < 8; ++t) Bs[nc + t][kk] = pv[t];
-    }
+    // 64 rows x 32 k of each operand, eight contiguous elements per thread
+    const uint32_t rr = tid >> 2, kc = (tid & 3) * 8;
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (m0 + rr < g.M) v = *(const uint4 *)(g.A + (m0 + rr) * g.K + k0 + kc);
+    *(uint4 *)&As[rr][kc] = v;
+    *(uint4 *)&Bs[rr][kc] = *(const uint4 *)(g.B + (uint64_t)(n0 + rr) * g.K + k0 + kc);
     __syncthreads();
 #pragma unroll
     for (int ks = 0; ks < MG_K; ks += 16) {
@@ -107,17 +67,7 @@ __global__ __launch_bounds__(MG_THREADS) void mlp_gemm_kernel(const MlpGemm g) {
       for (int r = 0; r < 4; ++r) {
         const uint64_t m = m0 + wm + 16 * i + 4 * (lane >> 4) + r;
         const uint32_t n = n0 + wn + 16 * j + (lane & 15);
-        if (m >= g.M) continue;
-        float v = acc[i][j][r];
-        if (EPI == MLP_EPI_F32) {
-          ((float *)g.C)[m * g.ldc + n] = v;
-        } else if (EPI == MLP_EPI_BIAS_RELU) {
-          v = fmaxf(v + g.bias[n], 0.f);
-          ((uint16_t *)g.C)[m * g.ldc + n] = f2bf(v);
-        } else {  // MLP_EPI_MASK: gradient through the ReLU of the layer output stored in mask
-          v = bf2f(g.mask[m * g.ldm + n]) > 0.f ? v : 0.f;
-          ((uint16_t *)g.C)[m * g.ldc + n] = f2bf(v);
-        }
+        if (m < g.M) g.C[m * g.N + n] = f2bf(fmaxf(acc[i][j][r] + g.bias[n], 0.f));
       }
 }
 
@@ -140,99 +90,6 @@ __global__ void head_forward_kernel(const uint16_t *__restrict__ H, uint32_t wid
 #pragma unroll
   for (int o = 16; o > 0; o >>= 1) s += __shfl_xor(s, o, 32);
   if (row < rows && l == 0) y[row] = scale * (s + b[0]);
-}
-
-// Loss terms and the output-layer backward: r = y - t, dy = 2 r / B,
-// sq[m] = r^2, dZ[m][n] = dy w[n] [H[m][n] > 0] (bf16).
-__global__ void head_backward_kernel(const uint16_t *__restrict__ H, uint32_t width, uint64_t rows,
-                                     const uint16_t *__restrict__ w, const float *__restrict__ y,
-                                     const float *__restrict__ t, float inv_b2, float *__restrict__ dy,
-                                     float *__restrict__ sq, uint16_t *__restrict__ dZ) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= rows * width) return;
-  const uint64_t m = i / width;
-  const uint32_t n = (uint32_t)(i % width);
-  const float r = y[m] - t[m];
-  const float d = r * inv_b2;
-  if (n == 0) {
-    dy[m] = d;
-    sq[m] = r * r;
-  }
-  dZ[i] = f2bf(bf2f(H[i]) > 0.f ? d * bf2f(w[n]) : 0.f);
-}
-
-// Column sums out[n] = sum_m s[m] X[m][n] (s == nullptr: 1) in two
-// ordered passes: per-chunk partials, then the chunks in order.
-constexpr uint32_t kColChunk = 256;
-__global__ void colsum_partial_kernel(const uint16_t *__restrict__ X, uint32_t width, uint64_t rows,
-                                      const float *__restrict__ s, float *__restrict__ part) {
-  const uint32_t n = threadIdx.x;
-  if (n >= width) return;
-  const uint64_t r0 = (uint64_t)blockIdx.x * kColChunk;
-  const uint64_t r1 = r0 + kColChunk < rows ? r0 + kColChunk : rows;
-  float acc = 0.f;
-  for (uint64_t m = r0; m < r1; ++m) acc += (s ? s[m] : 1.f) * bf2f(X[m * width + n]);
-  part[(uint64_t)blockIdx.x * width + n] = acc;
-}
-__global__ void colsum_final_kernel(const float *__restrict__ part, uint32_t width, uint32_t chunks,
-                                    float *__restrict__ out) {
-  const uint32_t n = blockIdx.x * blockDim.x + threadIdx.x;
-  if (n >= width) return;
-  float acc = 0.f;
-  for (uint32_t c = 0; c < chunks; ++c) acc += part[(uint64_t)c * width + n];
-  out[n] = acc;
-}
-
-// *out = sum of x[0..n) (one workgroup, fixed-order tree)
-__global__ __launch_bounds__(256) void vsum_kernel(const float *__restrict__ x, uint64_t n, float *__restrict__ out) {
-  __shared__ float red[256];
-  float acc = 0.f;
-  for (uint64_t i = threadIdx.x; i < n; i += 256) acc += x[i];
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (uint32_t w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) *out = red[0];
-}
-
-// Adam (Kingma & Ba) on the flat fp32 parameters; c1 = 1 - b1^t,
-// c2 = 1 - b2^t.  Also refreshes the bf16 copy used by the products.
-__global__ void adam_kernel(float *__restrict__ p, const float *__restrict__ g, float *__restrict__ m,
-                            float *__restrict__ v, uint16_t *__restrict__ pb, uint64_t n, float lr, float b1,
-                            float b2, float c1, float c2, float eps) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const float gi = g[i];
-  const float mi = b1 * m[i] + (1.f - b1) * gi;
-  const float vi = b2 * v[i] + (1.f - b2) * gi * gi;
-  m[i] = mi;
-  v[i] = vi;
-  const float np = p[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
-  p[i] = np;
-  pb[i] = f2bf(np);
-}
-
-__global__ void to_bf16_kernel(const float *__restrict__ p, uint16_t *__restrict__ pb, uint64_t n) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) pb[i] = f2bf(p[i]);
-}
-
-// Mini-batch rows: row i of step `step` is row (philox bits mod n) of the
-// data set, or row i itself when the batch covers the data set in order.
-__global__ void gather_rows_kernel(const uint16_t *__restrict__ X, const float *__restrict__ y, uint64_t n,
-                                   uint32_t width, uint32_t batch, uint32_t step, uint64_t seed, int in_order,
-                                   uint16_t *__restrict__ Xb, float *__restrict__ yb) {
-  const uint32_t i = blockIdx.x;
-  if (i >= batch) return;
-  uint64_t src = i;
-  if (!in_order) {
-    const U4 o = philox10(i, step, 0x4D4C5000u, 0u, (uint32_t)seed, (uint32_t)(seed >> 32));
-    src = (((uint64_t)o.w[1] << 32) | o.w[0]) % n;
-  }
-  for (uint32_t c = threadIdx.x; c < width; c += blockDim.x) Xb[(uint64_t)i * width + c] = X[src * width + c];
-  if (threadIdx.x == 0) yb[i] = y[src];
 }
 
 // ------------------------------------------------------------ term model
@@ -654,21 +511,12 @@ inline unsigned blocks(uint64_t n, uint32_t b) { return (unsigned)((n + b - 1) /
 
 }  // namespace
 
-hipError_t launch_mlp_gemm(const MlpGemm &g, int epi, hipStream_t s) {
-  if (g.N % MG_T || g.K % MG_K || (g.sak != 1 && g.sam != 1) || (g.sbk != 1 && g.sbn != 1))
-    return hipErrorInvalidValue;
+hipError_t launch_mlp_gemm(const MlpGemm &g, hipStream_t s) {
+  if (g.N % MG_T || g.K % MG_K) return hipErrorInvalidValue;
   const uint64_t tm = (g.M + MG_T - 1) / MG_T;
   if (tm == 0) return hipSuccess;
   if (tm > 0x7FFFFFFFull) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)tm, g.N / MG_T);
-  switch (epi) {
-    case MLP_EPI_F32: hipLaunchKernelGGL(mlp_gemm_kernel<MLP_EPI_F32>, grid, dim3(MG_THREADS), 0, s, g); break;
-    case MLP_EPI_BIAS_RELU:
-      hipLaunchKernelGGL(mlp_gemm_kernel<MLP_EPI_BIAS_RELU>, grid, dim3(MG_THREADS), 0, s, g);
-      break;
-    case MLP_EPI_MASK: hipLaunchKernelGGL(mlp_gemm_kernel<MLP_EPI_MASK>, grid, dim3(MG_THREADS), 0, s, g); break;
-    default: return hipErrorInvalidValue;
-  }
+  hipLaunchKernelGGL(mlp_gemm_kernel, dim3((unsigned)tm, g.N / MG_T), dim3(MG_THREADS), 0, s, g);
   return hipGetLastError();
 }
 
@@ -692,47 +540,6 @@ hipError_t launch_head_forward(const uint16_t *H, uint32_t width, uint64_t rows,
   if (width % 8 || rows == 0) return rows == 0 ? hipSuccess : hipErrorInvalidValue;
   hipLaunchKernelGGL(head_forward_kernel, dim3(blocks(rows * 32, 256)), dim3(256), 0, s, H, width, rows, w, b, scale,
                      y);
-  return hipGetLastError();
-}
-
-hipError_t launch_head_backward(const uint16_t *H, uint32_t width, uint64_t rows, const uint16_t *w, const float *y,
-                                const float *t, float *dy, float *sq, uint16_t *dZ, hipStream_t s) {
-  hipLaunchKernelGGL(head_backward_kernel, dim3(blocks(rows * width, 256)), dim3(256), 0, s, H, width, rows, w, y, t,
-                     2.0f / (float)rows, dy, sq, dZ);
-  return hipGetLastError();
-}
-
-uint32_t colsum_chunks(uint64_t rows) { return (uint32_t)((rows + kColChunk - 1) / kColChunk); }
-
-hipError_t launch_colsum(const uint16_t *X, uint32_t width, uint64_t rows, const float *sc, float *part, float *out,
-                         hipStream_t s) {
-  if (width > 256) return hipErrorInvalidValue;
-  const uint32_t ch = colsum_chunks(rows);
-  hipLaunchKernelGGL(colsum_partial_kernel, dim3(ch), dim3(256), 0, s, X, width, rows, sc, part);
-  hipLaunchKernelGGL(colsum_final_kernel, dim3(blocks(width, 256)), dim3(256), 0, s, part, width, ch, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_vsum(const float *x, uint64_t n, float *out, hipStream_t s) {
-  hipLaunchKernelGGL(vsum_kernel, dim3(1), dim3(256), 0, s, x, n, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_adam(float *p, const float *g, float *m, float *v, uint16_t *pb, uint64_t n, float lr, float b1,
-                       float b2, float c1, float c2, float eps, hipStream_t s) {
-  hipLaunchKernelGGL(adam_kernel, dim3(blocks(n, 256)), dim3(256), 0, s, p, g, m, v, pb, n, lr, b1, b2, c1, c2, eps);
-  return hipGetLastError();
-}
-
-hipError_t launch_to_bf16(const float *p, uint16_t *pb, uint64_t n, hipStream_t s) {
-  hipLaunchKernelGGL(to_bf16_kernel, dim3(blocks(n, 256)), dim3(256), 0, s, p, pb, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_gather_rows(const uint16_t *X, const float *y, uint64_t n, uint32_t width, uint32_t batch,
-                              uint32_t step, uint64_t seed, int in_order, uint16_t *Xb, float *yb, hipStream_t s) {
-  hipLaunchKernelGGL(gather_rows_kernel, dim3(batch), dim3(64), 0, s, X, y, n, width, batch, step, seed, in_order, Xb,
-                     yb);
   return hipGetLastError();
 }
 
