@@ -155,12 +155,13 @@ struct CallGraph {
 struct ccut_plan {
   ccut_ctx *ctx = nullptr;
   PlanData pd;
-  std::vector<uint32_t *> d_ops;   // per fragment, uploaded on first evaluation
-  std::vector<double *> d_mats;
-  std::vector<uint32_t *> d_back;  // Clifford fragments: the carry-back stream
-  std::vector<uint32_t> n_back;
-  std::vector<uint32_t *> d_layers, d_back_layers;  // layer offsets of both streams
-  std::vector<uint32_t> n_layers, n_back_layers;
+  // the fragments' programs, uploaded on first evaluation: one device block
+  char *d_block = nullptr;
+  std::vector<const uint32_t *> d_ops;    // state-vector program (non-Clifford), else null
+  std::vector<const double *> d_mats;
+  std::vector<const uint32_t *> d_lanes;  // carry-back lane program, or
+  std::vector<const uint32_t *> d_back, d_back_layers;  // layered stream
+  std::vector<uint32_t> n_steps, n_back, n_back_layers;
   std::vector<CallGraph> graphs;  // least recently used first out, at most kMaxCallGraphs
   uint64_t graph_tick = 0;
   static constexpr size_t kMaxCallGraphs = 8;
@@ -168,16 +169,7 @@ struct ccut_plan {
     // a replay may still be reading the graphs' upload blocks
     if (!graphs.empty() && ctx && ctx->device >= 0) (void)hipStreamSynchronize(ctx->stream);
     for (auto &g : graphs) g.release();
-    for (auto p : d_ops)
-      if (p) (void)hipFree(p);
-    for (auto p : d_mats)
-      if (p) (void)hipFree(p);
-    for (auto p : d_back)
-      if (p) (void)hipFree(p);
-    for (auto p : d_layers)
-      if (p) (void)hipFree(p);
-    for (auto p : d_back_layers)
-      if (p) (void)hipFree(p);
+    if (d_block) (void)hipFree(d_block);
   }
 };
 
@@ -237,52 +229,62 @@ T *aget(ccut_ctx *c, size_t count) {
   return (T *)c->arena.get(count * sizeof(T));
 }
 
-// Upload each fragment's op streams once per plan: for Clifford fragments
-// the fused forward stream and the carry-back stream, for non-Clifford ones
-// the state-vector program with its matrices; padded with no-ops
-// (identities) to a multiple of 16 words so kernels can fetch ops sixteen at
-// a time.
+// Upload each fragment's programs once per plan, in one block: the carry-back
+// of a Clifford fragment (lane program, or the layered stream padded with
+// no-ops to a multiple of 16 words), the state-vector program of a
+// non-Clifford one with its matrices.
 ccut_status ensure_ops(ccut_plan *p) {
   ccut_ctx *c = p->ctx;
-  if (!p->d_ops.empty()) return CCUT_OK;
-  for (const Fragment &f : p->pd.frags) {
-    uint32_t *bk = nullptr;
-    std::vector<uint32_t> back = f.cl_back;
-    while (back.size() % 16 || back.empty()) back.push_back(pack_op(G_NOP, 0, 0));
-    if (f.clifford) {
-      HIP_TRY(c, hipMalloc(&bk, back.size() * sizeof(uint32_t)));
-      HIP_TRY(c, hipMemcpy(bk, back.data(), back.size() * 4, hipMemcpyHostToDevice));
+  if (p->d_block) return CCUT_OK;
+  std::vector<char> block;
+  auto add = [&](const void *src, size_t bytes) {
+    const size_t off = block.size();
+    block.resize(off + ((std::max<size_t>(bytes, 1) + 255) & ~size_t(255)), 0);
+    if (bytes) std::memcpy(block.data() + off, src, bytes);
+    return off;
+  };
+  const size_t none = ~size_t(0), nf = p->pd.frags.size();
+  std::vector<size_t> ops(nf, none), mats(nf, none), lanes(nf, none), back(nf, none), lay(nf, none);
+  p->n_steps.assign(nf, 0);
+  p->n_back.assign(nf, 0);
+  p->n_back_layers.assign(nf, 0);
+  for (size_t i = 0; i < nf; ++i) {
+    const Fragment &f = p->pd.frags[i];
+    if (f.clifford && f.cl_back.empty()) {
+      lanes[i] = add(f.cl_lanes.data(), f.cl_lanes.size() * 4);
+      p->n_steps[i] = (uint32_t)(f.cl_lanes.size() / (64 * carry_waves(f.m())));
+    } else if (f.clifford) {
+      std::vector<uint32_t> words = f.cl_back;
+      while (words.size() % 16) words.push_back(pack_op(G_NOP, 0, 0));
+      back[i] = add(words.data(), words.size() * 4);
+      lay[i] = add(f.cl_back_layers.data(), f.cl_back_layers.size() * 4);
+      p->n_back[i] = (uint32_t)f.cl_back.size();
+      p->n_back_layers[i] = (uint32_t)f.cl_back_layers.size() - 1;
+    } else {
+      std::vector<uint32_t> words = f.sv_prog;
+      std::vector<double> m = f.sv_prog_mats;
+      while (words.size() % 16 || words.empty()) {
+        words.push_back(pack_op(G_NOP, 0, 0));
+        m.insert(m.end(), 8, 0.0);
+      }
+      ops[i] = add(words.data(), words.size() * 4);
+      mats[i] = add(m.data(), m.size() * 8);
     }
-    p->d_back.push_back(bk);
-    p->n_back.push_back((uint32_t)f.cl_back.size());
-    uint32_t *dl = nullptr, *dbl = nullptr;
-    if (f.clifford) {
-      HIP_TRY(c, hipMalloc(&dl, std::max<size_t>(f.cl_layers.size(), 1) * 4));
-      HIP_TRY(c, hipMalloc(&dbl, std::max<size_t>(f.cl_back_layers.size(), 1) * 4));
-      if (!f.cl_layers.empty())
-        HIP_TRY(c, hipMemcpy(dl, f.cl_layers.data(), f.cl_layers.size() * 4, hipMemcpyHostToDevice));
-      if (!f.cl_back_layers.empty())
-        HIP_TRY(c, hipMemcpy(dbl, f.cl_back_layers.data(), f.cl_back_layers.size() * 4, hipMemcpyHostToDevice));
-    }
-    p->d_layers.push_back(dl);
-    p->d_back_layers.push_back(dbl);
-    p->n_layers.push_back(f.cl_layers.empty() ? 0u : (uint32_t)f.cl_layers.size() - 1);
-    p->n_back_layers.push_back(f.cl_back_layers.empty() ? 0u : (uint32_t)f.cl_back_layers.size() - 1);
-    std::vector<uint32_t> words = f.clifford ? f.cl_words : f.sv_prog;
-    std::vector<double> mats = f.clifford ? std::vector<double>() : f.sv_prog_mats;
-    while (words.size() % 16 || words.empty()) {
-      words.push_back(pack_op(G_NOP, 0, 0));
-      if (!f.clifford) mats.insert(mats.end(), 8, 0.0);
-    }
-    if (mats.empty()) mats.assign(8, 0.0);
-    uint32_t *o = nullptr;
-    double *t = nullptr;
-    HIP_TRY(c, hipMalloc(&o, words.size() * sizeof(uint32_t)));
-    HIP_TRY(c, hipMalloc(&t, mats.size() * sizeof(double)));
-    HIP_TRY(c, hipMemcpy(o, words.data(), words.size() * 4, hipMemcpyHostToDevice));
-    HIP_TRY(c, hipMemcpy(t, mats.data(), mats.size() * 8, hipMemcpyHostToDevice));
-    p->d_ops.push_back(o);
-    p->d_mats.push_back(t);
+  }
+  char *d = nullptr;
+  HIP_TRY(c, hipMalloc(&d, std::max<size_t>(block.size(), 256)));
+  if (const hipError_t e = hipMemcpy(d, block.data(), block.size(), hipMemcpyHostToDevice); e != hipSuccess) {
+    (void)hipFree(d);
+    return fail(c, CCUT_E_DEVICE, std::string("program upload: ") + hipGetErrorString(e));
+  }
+  p->d_block = d;
+  auto at = [&](size_t off) { return off == none ? nullptr : d + off; };
+  for (size_t i = 0; i < nf; ++i) {
+    p->d_ops.push_back((const uint32_t *)at(ops[i]));
+    p->d_mats.push_back((const double *)at(mats[i]));
+    p->d_lanes.push_back((const uint32_t *)at(lanes[i]));
+    p->d_back.push_back((const uint32_t *)at(back[i]));
+    p->d_back_layers.push_back((const uint32_t *)at(lay[i]));
   }
   return CCUT_OK;
 }
@@ -450,9 +452,19 @@ FragDev frag_desc(ccut_plan *p, const Fragment &f, const FragRequest &r, uint32_
   FragDev h = make_frag_dev(f, r, ((uint64_t)circuit << 40) | ((uint64_t)f.index << 32));
   h.ops = p->d_ops[f.index];
   h.mats = p->d_mats[f.index];
-  h.layers = p->d_layers[f.index];
-  h.n_layers = p->n_layers[f.index];
   return h;
+}
+
+// The same with a Clifford fragment's carry-back programs.
+FragDev carry_desc(const ccut_plan *p, const Fragment &f, const FragDev &h) {
+  FragDev b = h;
+  b.lanes = p->d_lanes[f.index];
+  b.n_steps = p->n_steps[f.index];
+  b.ops = p->d_back[f.index];
+  b.n_ops = p->n_back[f.index];
+  b.layers = p->d_back_layers[f.index];
+  b.n_layers = p->n_back_layers[f.index];
+  return b;
 }
 
 // The measured Paulis of a Clifford fragment before the pull-back through
@@ -522,11 +534,7 @@ ccut_status tableau_models(ccut_plan *p, const Fragment &f, const FragDev &h, co
   uint64_t *d_in = (uint64_t *)upload(c, rows.data(), rows.size() * 8);
   uint64_t *d_out = aget<uint64_t>(c, rows.size());
   if (!d_in || !d_out) return fail(c, CCUT_E_OOM, "device allocation failed");
-  FragDev hb = h;
-  hb.ops = p->d_back[f.index];
-  hb.n_ops = p->n_back[f.index];
-  hb.layers = p->d_back_layers[f.index];
-  hb.n_layers = p->n_back_layers[f.index];
+  const FragDev hb = carry_desc(p, f, h);
   int8_t *d_axis = nullptr;
   uint16_t *d_row = nullptr;
   if (nm > (uint32_t)kMaxMeas) {
@@ -866,12 +874,7 @@ ccut_status heis_tensor(ccut_plan *p, const Fragment &f, const FragRequest &r, u
   uint64_t *d_out = aget<uint64_t>(c, rows.size());
   uint64_t *d_in = (uint64_t *)upload(c, rows.data(), rows.size() * 8);
   if (!tau || !d_out || !d_in) return fail(c, CCUT_E_OOM, "device allocation failed");
-  FragRequest rq = r;
-  FragDev h = frag_desc(p, f, rq, circuit);
-  h.ops = p->d_back[f.index];  // the carry-back stream
-  h.n_ops = p->n_back[f.index];
-  h.layers = p->d_back_layers[f.index];
-  h.n_layers = p->n_back_layers[f.index];
+  const FragDev h = carry_desc(p, f, frag_desc(p, f, r, circuit));
   {
     KTimer t(c, CCUT_K_HEISENBERG);
     HIP_TRY(c, launch_heisenberg(h, W, n_in, n_out, strings ? 0 : nreq, strings ? (uint32_t)strings->size() : 0,
@@ -1967,10 +1970,10 @@ struct ccut_batch {
   // descriptors back to back), their carry-back jobs, the descriptors with
   // the carry-back stream, and each descriptor's row width
   std::vector<uint64_t> carry_rows;
-  std::vector<CarryJob> carry_jobs;
+  std::vector<CarryJob> carry_jobs, stream_jobs;  // by lane program, by layered stream
   std::vector<FragDev> back_descs;
   std::vector<uint32_t> desc_w;
-  uint32_t max_rows = 0;
+  uint32_t lane_waves = 0, max_m = 0, max_rows = 0;  // of the lane jobs; of the stream jobs
   // independent per-plan steps run on a pool of streams (default priority),
   // forked from and joined back into the batch stream
   std::vector<hipStream_t> pool;
@@ -1984,7 +1987,7 @@ struct ccut_batch {
   std::vector<Ref> samp;  // sampled Clifford fragments (desc indexes descs)
   std::vector<Ref> nc;    // non-Clifford fragments (desc indexes sv_descs)
   std::vector<FragDev> sv_descs;
-  uint32_t max_m = 0, block = 64, grid = 0, tune_cached = 0;
+  uint32_t block = 64, grid = 0, tune_cached = 0;
   double tuned_ms = 0.0;
   // device outputs: the copy list of the last run (pinned and on the
   // device), reused while the caller passes the same output addresses, and
@@ -2082,12 +2085,14 @@ ccut_status batch_carry(ccut_batch *b, uint64_t **d_rows_out) {
   uint64_t *d_in = (uint64_t *)upload(c, b->carry_rows.data(), std::max<size_t>(b->carry_rows.size(), 1) * 8);
   uint64_t *d_out = aget<uint64_t>(c, std::max<size_t>(b->carry_rows.size(), 1));
   FragDev *d_back = (FragDev *)upload(c, b->back_descs.data(), b->back_descs.size() * sizeof(FragDev));
-  CarryJob *d_jobs = (CarryJob *)upload(c, b->carry_jobs.data(), b->carry_jobs.size() * sizeof(CarryJob));
+  std::vector<CarryJob> jobs = b->carry_jobs;
+  jobs.insert(jobs.end(), b->stream_jobs.begin(), b->stream_jobs.end());
+  CarryJob *d_jobs = (CarryJob *)upload(c, jobs.data(), jobs.size() * sizeof(CarryJob));
   if (!d_in || !d_out || !d_back || !d_jobs) return fail(c, CCUT_E_OOM, "device allocation failed");
   {
     KTimer t(c, CCUT_K_CARRY);
-    HIP_TRY(c, launch_carry_batch(d_back, d_jobs, (uint32_t)b->carry_jobs.size(), b->max_m, b->max_rows, d_in, d_out,
-                                  c->cur));
+    HIP_TRY(c, launch_carry_batch(d_back, d_jobs, (uint32_t)b->carry_jobs.size(), b->lane_waves,
+                                  (uint32_t)b->stream_jobs.size(), b->max_m, b->max_rows, d_in, d_out, c->cur));
   }
   *d_rows_out = d_out;
   return CCUT_OK;
@@ -2799,15 +2804,20 @@ ccut_status ccut_batch_create(ccut_ctx *c, ccut_plan *const *plans, size_t n, co
       const uint64_t boff = b->carry_rows.size();
       const uint32_t n_rows = (uint32_t)(rows.size() / (2 * Wb + 1));
       b->carry_rows.insert(b->carry_rows.end(), rows.begin(), rows.end());
-      b->carry_jobs.push_back({di, Wb, n_rows, 0u, boff, boff});
-      FragDev hb = h;
-      hb.ops = p->d_back[f.index];
-      hb.n_ops = p->n_back[f.index];
-      hb.layers = p->d_back_layers[f.index];
-      hb.n_layers = p->n_back_layers[f.index];
+      const FragDev hb = carry_desc(p, f, h);
+      if (hb.lanes) {  // 64 rows a job
+        for (uint32_t r0 = 0; r0 < n_rows; r0 += 64) {
+          const uint64_t off = boff + (uint64_t)r0 * (2 * Wb + 1);
+          b->carry_jobs.push_back({di, Wb, std::min(64u, n_rows - r0), 0u, off, off});
+        }
+        b->lane_waves = std::max(b->lane_waves, carry_waves(f.m()));
+      } else {
+        b->stream_jobs.push_back({di, Wb, n_rows, 0u, boff, boff});
+        b->max_m = std::max(b->max_m, f.m());
+        b->max_rows = std::max(b->max_rows, n_rows);
+      }
       b->back_descs.push_back(hb);
       b->desc_w.push_back(Wb);
-      b->max_rows = std::max(b->max_rows, n_rows);
       offs[f.index] = (int64_t)b->model_words_total;
       if (eo->shots_per_variant) {
         if (nm > (uint32_t)kMaxTableBits)
@@ -2817,7 +2827,6 @@ ccut_status ccut_batch_create(ccut_ctx *c, ccut_plan *const *plans, size_t n, co
       for (uint64_t v = 0; v < f.n_variants; ++v)
         b->items.push_back({di, 0u, v, b->model_words_total + v * model_words(nm), boff});
       b->model_words_total += f.n_variants * model_words(nm);
-      b->max_m = std::max(b->max_m, f.m());
     }
     b->model_off.push_back(offs);
   }

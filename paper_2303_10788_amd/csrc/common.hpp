@@ -132,6 +132,20 @@ __host__ __device__ inline uint32_t c1_then(uint32_t pa, uint32_t pb) {
   return c1_encode(C);
 }
 
+// The Heisenberg carry-back as a lane program: lane q holds qubit q's x and z
+// bits of 64 rows, and step s gives each lane one word: a one-qubit map
+// applied first (bits 0-6, c1_encode), the lane's part in a two-qubit gate
+// (bits 7-10) and, from bit 16, its partner's LDS offset (16 bytes a qubit).
+// A zero word is the identity.
+constexpr uint32_t kCarryControl = 1u << 7, kCarryTarget = 1u << 8, kCarryCz = 1u << 9;
+constexpr uint32_t kCarryLead = 1u << 10;  // the lane of a CZ that takes its sign
+constexpr uint32_t kCarryChunk = 16;       // steps fetched at a time
+constexpr uint64_t kLaneWordsMax = 1ull << 24;
+__host__ __device__ inline uint32_t carry_word(uint32_t c1, uint32_t role, uint32_t partner) {
+  return (c1 & 127u) | role | (partner << 20);
+}
+__host__ __device__ inline uint32_t carry_waves(uint32_t m) { return m ? (m + 63) / 64 : 1; }
+
 // Global-address-space views: loads through them with a wave-uniform index
 // compile to scalar (SMEM) loads, so op decoding stays in SGPRs.
 typedef __attribute__((address_space(1))) const uint32_t g_u32;
@@ -174,12 +188,13 @@ struct FragDev {
   uint16_t meas[kMaxMeas];         // local qubit of measurement j (ascending)
   const uint32_t *ops;             // packed op words, padded with G_NOP to a multiple of 16
   const double *mats;              // per op 2x2 complex matrix (re00 im00 re01 im01 re10 im10 re11 im11), G_U2 only
-  // Clifford streams come in ASAP layers of ops on disjoint qubits (layer L
-  // is ops[layers[L] .. layers[L + 1])); reordering commuting ops changes
-  // no row and no sign
+  // A Clifford fragment's carry-back as a stream: ASAP layers of ops on
+  // disjoint qubits (layer L is ops[layers[L] .. layers[L + 1])); reordering
+  // commuting ops changes no row and no sign
   const uint32_t *layers;
   uint32_t n_layers;
-  uint32_t pad_;
+  uint32_t n_steps;      // steps of the carry-back's lane program (a multiple of kCarryChunk)
+  const uint32_t *lanes; // the lane program (null: the layered stream `ops` instead)
 };
 
 // Per-variant affine sample model of a Clifford variant: a shot's outcome
@@ -385,20 +400,22 @@ hipError_t launch_transform_pass(const double *in, double *out, uint64_t outer, 
 
 // Exact Pauli-basis tensor of a Clifford fragment without enumerating
 // variants (Heisenberg picture); see k_heis.hip for the row layout.
-// Rows carried through F.ops (F.n_ops words), column-sliced (k_heis.hip):
-// rows_in null starts from the identity tableau (X_r for r < m, then
-// Z_{r-m}); rows are (x[W], z[W], sign) u64 each.
+// Rows carried back through the fragment (k_heis.hip); rows are (x[W], z[W],
+// sign) u64 each.
 hipError_t launch_rows(const FragDev &F, uint32_t W, const uint64_t *in, uint64_t *out, uint32_t n_rows,
                        hipStream_t s);
 // One fragment's carry-back in a batched launch: n_rows rows of width W
-// words per half at in + in_off, carried through the descriptor's stream
-// into out + out_off.
+// words per half at in + in_off, carried back through the descriptor's
+// fragment into out + out_off (lane programs: at most 64 rows a job).
 struct CarryJob {
   uint32_t desc, W, n_rows, pad_;
   uint64_t in_off, out_off;
 };
-hipError_t launch_carry_batch(const FragDev *descs, const CarryJob *jobs, uint32_t n_jobs, uint32_t max_m,
-                              uint32_t max_rows, const uint64_t *in, uint64_t *out, hipStream_t s);
+// Jobs [0, n_lanes) by lane programs of at most `waves` waves, the others
+// (max_m qubits, max_rows rows) by their streams.
+hipError_t launch_carry_batch(const FragDev *descs, const CarryJob *jobs, uint32_t n_lanes, uint32_t waves,
+                              uint32_t n_stream, uint32_t max_m, uint32_t max_rows, const uint64_t *in, uint64_t *out,
+                              hipStream_t s);
 // Affine sample models from carried-back measured Paulis (one wave per
 // variant): rows as built by measured_rows on the host, W words per half.
 hipError_t launch_affine(const FragDev &F, uint32_t W, const uint64_t *rows, uint64_t v0, uint64_t nv,

@@ -35,11 +35,7 @@ typedef __attribute__((address_space(1))) const FragDev g_FragDevH;
 // changes of its ops into one private word (XOR commutes, and an op reads
 // the columns as they are before it: earlier layers are complete and its
 // own layer never touches its qubits); one reduction over the lanes of each
-// row word adds them up at the end.  One wave, so LDS accesses complete in
-// issue order; a compiler fence keeps the layers in order.  Columns live in
-// LDS ([m][RW] for x, then for z); rows are transposed in (or start as the
-// identity tableau when `in` is null) and back out in the (x[W], z[W],
-// sign) row layout.  At most 1024 rows per wave.
+// row word adds them up at the end.
 constexpr uint32_t kSlicedRows = 1024;
 constexpr uint32_t kOpStage = 1024;  // op words staged in LDS (a layer has at most 512)
 constexpr uint32_t kLayStage = 256;  // layer offsets staged in LDS
@@ -61,16 +57,16 @@ __device__ inline void stage_words(uint32_t *dst, const uint32_t *src, uint32_t 
     if (lane + 64 * k < CAP) dst[lane + 64 * k] = t[k];
 }
 
-// NW waves per workgroup: a layer's ops are spread over all 64 NW lanes and
+// kCarryWaves waves per workgroup: a layer's ops are spread over all lanes and
 // the waves meet at a barrier after each layer (a lane reads columns other
 // waves wrote in the previous layer); wave 0 stages op words and layer
 // offsets and transposes rows in and out, and the lanes' sign shares are
-// XOR-reduced within each wave, then across the waves through LDS.  NW = 1:
-// no barriers (one wave's LDS accesses complete in issue order).
-template <uint32_t NW, class D>
+// XOR-reduced within each wave, then across the waves through LDS.
+constexpr uint32_t kCarryWaves = 4;
+template <class D>
 __device__ void rows_sliced_body(const D &F, uint32_t W, const uint64_t *__restrict__ in, uint64_t *__restrict__ out,
                                  uint32_t n_rows, uint64_t *cols) {
-  constexpr uint32_t T = 64 * NW;
+  constexpr uint32_t NW = kCarryWaves, T = 64 * NW;
   const uint32_t m = F.m;
   const uint32_t RW = (n_rows + 63) / 64;
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
@@ -81,16 +77,7 @@ __device__ void rows_sliced_body(const D &F, uint32_t W, const uint64_t *__restr
   uint32_t *sops = reinterpret_cast<uint32_t *>(Zc + (size_t)m * RW);
   const uint32_t RS = 2 * W + 1;  // row stride in words
   uint64_t sg = 0;  // this lane's share of sign word w
-  auto sync = [] {
-    if (NW > 1) __syncthreads();
-  };
-  if (!in) {
-    for (uint32_t idx = tid; idx < m * RW; idx += T) {  // X_r for rows r < m, then Z_{r - m}
-      const uint32_t q = idx / RW, iw = idx % RW;
-      Xc[idx] = q >> 6 == iw ? 1ull << (q & 63) : 0ull;
-      Zc[idx] = (m + q) >> 6 == iw ? 1ull << ((m + q) & 63) : 0ull;
-    }
-  } else if (wave == 0) {
+  if (wave == 0) {
     // transpose in, 64 rows at a time: lane l loads row 64 iw + l whole,
     // and column word (q, iw) is the ballot of bit q over the lanes
     for (uint32_t iw = 0; iw < RW; ++iw) {
@@ -142,7 +129,7 @@ __device__ void rows_sliced_body(const D &F, uint32_t W, const uint64_t *__restr
         for (uint32_t i = lane; i <= nl; i += 64) slay[i] = L0 + i;
       }
     }
-    sync();  // the staged words (and, the first time, the op window) are in place
+    __syncthreads();  // the staged words (and, the first time, the op window) are in place
     uint32_t v_s1 = slay[1];
     uint32_t v_wd = sops[s0 + o - stage0];  // this lane's first op word of the current layer
     for (uint32_t L = 0; L < nl; ++L) {
@@ -178,30 +165,28 @@ __device__ void rows_sliced_body(const D &F, uint32_t W, const uint64_t *__restr
         }
       }
       asm volatile("" ::: "memory");
-      sync();  // every wave is done with this layer's columns (and op words)
+      __syncthreads();  // every wave is done with this layer's columns (and op words)
       if (!keep) {  // restage from the next layer's start (in issue order after this layer's reads)
         stage0 = s1;
         if (wave == 0) stage_words<kOpStage>(sops, F.ops + s1, F.n_ops - s1, lane);
-        sync();
+        __syncthreads();
         v_wdn = sops[o];
       }
       s0 = s1;
       v_s1 = v_s1n;
       v_wd = v_wdn;
     }
-    sync();  // every wave has read this stage's layer offsets
+    __syncthreads();  // every wave has read this stage's layer offsets
   }
   // sign word w: XOR of the shares of every lane on row word w (lane w of
   // wave 0 ends with it)
   for (uint32_t off = RWp; off < 64; off <<= 1) sg ^= __shfl_xor(sg, off);
   __syncthreads();
-  if (NW > 1) {
-    uint64_t *red = reinterpret_cast<uint64_t *>(sops);  // the op window is no longer read
-    if (lane < RWp) red[wave * 64 + lane] = sg;
-    __syncthreads();
-    if (wave == 0 && lane < RWp)
-      for (uint32_t v = 1; v < NW; ++v) sg ^= red[v * 64 + lane];
-  }
+  uint64_t *red = reinterpret_cast<uint64_t *>(sops);  // the op window is no longer read
+  if (lane < RWp) red[wave * 64 + lane] = sg;
+  __syncthreads();
+  if (wave == 0 && lane < RWp)
+    for (uint32_t v = 1; v < NW; ++v) sg ^= red[v * 64 + lane];
   if (wave != 0) return;
   // transpose out, 64 rows at a time: lane l gathers row 64 rw + l from the
   // column words (each read is the same address for every lane)
@@ -230,25 +215,170 @@ __device__ void rows_sliced_body(const D &F, uint32_t W, const uint64_t *__restr
 }
 
 // Block x carries rows [1024 x, 1024 x + 1024) (rows are independent).
-__global__ __launch_bounds__(64) void rows_sliced_kernel(const FragDev F, uint32_t W, const uint64_t *__restrict__ in,
-                                                          uint64_t *__restrict__ out, uint32_t n_rows) {
+__global__ __launch_bounds__(64 * kCarryWaves) void rows_sliced_kernel(const FragDev F, uint32_t W,
+                                                                       const uint64_t *__restrict__ in,
+                                                                       uint64_t *__restrict__ out, uint32_t n_rows) {
   extern __shared__ uint64_t cols[];
   const uint32_t r0 = blockIdx.x * kSlicedRows;
   const size_t RS = 2 * W + 1;
-  rows_sliced_body<1>(F, W, in ? in + r0 * RS : nullptr, out + r0 * RS, min(kSlicedRows, n_rows - r0), cols);
+  rows_sliced_body(F, W, in + r0 * RS, out + r0 * RS, min(kSlicedRows, n_rows - r0), cols);
 }
 
-// Carry-back of many fragments' rows: block x carries job x's n_rows input
-// rows (row width W words per half) through its descriptor's stream, with
-// kCarryWaves waves spreading each layer's ops.
-constexpr uint32_t kCarryWaves = 4;
-__global__ __launch_bounds__(64 * kCarryWaves) void carry_batch_kernel(const FragDev *__restrict__ descs,
-                                                          const CarryJob *__restrict__ jobs,
-                                                          const uint64_t *__restrict__ in, uint64_t *__restrict__ out) {
+// The stream jobs of a batch: block x carries job x's rows.
+__global__ __launch_bounds__(64 * kCarryWaves) void sliced_batch_kernel(const FragDev *__restrict__ descs,
+                                                                        const CarryJob *__restrict__ jobs,
+                                                                        const uint64_t *__restrict__ in,
+                                                                        uint64_t *__restrict__ out) {
   extern __shared__ uint64_t cols[];
   const CarryJob &J = jobs[blockIdx.x];
   const g_FragDevH &F = ((const g_FragDevH *)descs)[J.desc];
-  rows_sliced_body<kCarryWaves>(F, J.W, in + J.in_off, out + J.out_off, J.n_rows, cols);
+  rows_sliced_body(F, J.W, in + J.in_off, out + J.out_off, J.n_rows, cols);
+}
+
+// 64 x 64 bits held one row per lane, transposed: bit c of lane r goes to bit
+// r of lane c (swaps of the index bits, one lane exchange each).
+__device__ inline uint64_t transpose64(uint64_t v, uint32_t lane) {
+  constexpr uint64_t low[6] = {0x5555555555555555ull, 0x3333333333333333ull, 0x0F0F0F0F0F0F0F0Full,
+                               0x00FF00FF00FF00FFull, 0x0000FFFF0000FFFFull, 0x00000000FFFFFFFFull};
+#pragma unroll
+  for (int b = 5; b >= 0; --b) {
+    const uint32_t j = 1u << b;
+    const uint64_t p = __shfl_xor((unsigned long long)v, j);
+    v = lane & j ? (v & ~low[b]) | ((p & ~low[b]) >> j) : (v & low[b]) | ((p & low[b]) << j);
+  }
+  return v;
+}
+
+// One bit of a program word as a mask (0 or all ones).
+__device__ inline uint64_t word_mask(uint32_t w, uint32_t bit) {
+  return (uint64_t)(int64_t)((int32_t)(w << (31 - bit)) >> 31);
+}
+
+// The carry-back with qubits in lanes: lane q of the workgroup holds qubit
+// q's x and z bits of 64 rows in registers for the whole program, so a step
+// is a few dozen logical operations per lane and one exchange with the
+// partner lane: within a wave (up to 64 qubits) a lane exchange, else one LDS
+// write, a barrier and one LDS read (two buffers in turn, so one barrier a
+// step is enough).  Every lane runs the same instructions whatever its gate.
+// Bound by that chain of steps: the program's words are fetched kCarryChunk
+// steps ahead, one-qubit runs cost no step of their own, and 64 rows to a
+// workgroup keep the workgroups independent.  Signs: each lane collects its
+// share of the 64 rows' sign bits, XORed over the lanes at the end.
+// Measured on MI355X (a layered stream of gates on LDS columns before): see
+// the dispatch below.
+template <bool MULTI, class D>
+__device__ void carry_lanes_body(const D &F, uint32_t W, const uint64_t *__restrict__ in, uint64_t *__restrict__ out,
+                                 uint32_t n_rows, ulonglong2 *ex) {
+  const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, mp = blockDim.x;
+  const uint32_t own = carry_waves(F.m);  // waves that hold qubits (a batch's blocks may have more)
+  const uint32_t RS = 2 * W + 1;
+  const uint32_t n_steps = F.n_steps, stride = 64 * own;
+  const bool mine = wave < own;
+  const uint32_t *prog = F.lanes + tid;
+  uint32_t nxt[kCarryChunk];
+#pragma unroll
+  for (uint32_t i = 0; i < kCarryChunk; ++i) nxt[i] = mine && n_steps ? prog[(size_t)i * stride] : 0u;
+  // lane r reads row r's words of this wave's qubits; transposed, lane q
+  // holds qubit q's bits over the rows
+  uint64_t x = 0, z = 0, sg = 0;
+  const bool row = lane < n_rows;
+  if (mine && row) {
+    x = in[(size_t)lane * RS + wave];
+    z = in[(size_t)lane * RS + W + wave];
+  }
+  const uint64_t s0 = __ballot(wave == 0 && row && (in[(size_t)lane * RS + 2 * W] & 1ull));
+  if (tid == 0) sg = s0;
+  x = transpose64(x, lane);
+  z = transpose64(z, lane);
+  uint32_t buf = 0;
+  for (uint32_t c = 0; c < n_steps; c += kCarryChunk) {
+    uint32_t cur[kCarryChunk];
+#pragma unroll
+    for (uint32_t i = 0; i < kCarryChunk; ++i) cur[i] = nxt[i];
+    if (c + kCarryChunk < n_steps) {
+      prog += (size_t)kCarryChunk * stride;
+#pragma unroll
+      for (uint32_t i = 0; i < kCarryChunk; ++i) nxt[i] = mine ? prog[(size_t)i * stride] : 0u;
+    }
+#pragma unroll
+    for (uint32_t i = 0; i < kCarryChunk; ++i) {
+      const uint32_t w = cur[i];
+      {  // the one-qubit map (c1_decode; the diagonal is stored inverted)
+        const uint64_t i00 = word_mask(w, 0), m01 = word_mask(w, 1), m10 = word_mask(w, 2), i11 = word_mask(w, 3);
+        sg ^= (x & word_mask(w, 4)) ^ (z & word_mask(w, 5)) ^ (x & z & word_mask(w, 6));
+        const uint64_t x1 = (x & ~i00) ^ (z & m01);
+        z = (z & ~i11) ^ (x & m10);
+        x = x1;
+      }
+      uint64_t px, pz;
+      if (MULTI) {
+        ulonglong2 *e = ex + buf * mp;
+        e[tid] = make_ulonglong2(x, z);
+        __syncthreads();
+        const ulonglong2 p = *reinterpret_cast<const ulonglong2 *>(reinterpret_cast<const char *>(e) + (w >> 16));
+        px = p.x;
+        pz = p.y;
+        buf ^= 1;
+      } else {
+        const int addr = (int)(w >> 18);  // four bytes a lane
+        const uint32_t x0 = __builtin_amdgcn_ds_bpermute(addr, (int)(uint32_t)x);
+        const uint32_t x1 = __builtin_amdgcn_ds_bpermute(addr, (int)(uint32_t)(x >> 32));
+        const uint32_t z0 = __builtin_amdgcn_ds_bpermute(addr, (int)(uint32_t)z);
+        const uint32_t z1 = __builtin_amdgcn_ds_bpermute(addr, (int)(uint32_t)(z >> 32));
+        px = (uint64_t)x1 << 32 | x0;
+        pz = (uint64_t)z1 << 32 | z0;
+      }
+      // CX (control 1, target 2): sign x1 z2 ~(x2 ^ z1), x2 ^= x1, z1 ^= z2;
+      // CZ: sign x1 x2 (z1 ^ z2), z1 ^= x2, z2 ^= x1
+      const uint64_t mc = word_mask(w, 7), mt = word_mask(w, 8), mz = word_mask(w, 9), ml = word_mask(w, 10);
+      sg ^= x & ((pz & ~(px ^ z) & mc) ^ (px & (z ^ pz) & ml));
+      x ^= px & mt;
+      z ^= (pz & mc) ^ (px & mz);
+    }
+  }
+  x = transpose64(x, lane);
+  z = transpose64(z, lane);
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) sg ^= __shfl_xor((unsigned long long)sg, off);
+  if (MULTI) {
+    __syncthreads();  // the last exchange is read
+    if (lane == 0) ex[wave].x = sg;
+    __syncthreads();
+    sg = 0;
+    for (uint32_t v = 0; v < mp / 64; ++v) sg ^= ex[v].x;
+  }
+  if (!row) return;
+  if (mine) {
+    out[(size_t)lane * RS + wave] = x;
+    out[(size_t)lane * RS + W + wave] = z;
+  }
+  if (wave == 0) {
+    for (uint32_t w = own; w < W; ++w) out[(size_t)lane * RS + w] = out[(size_t)lane * RS + W + w] = 0;
+    out[(size_t)lane * RS + 2 * W] = (sg >> lane) & 1ull;
+  }
+}
+
+// Block x carries rows [64 x, 64 x + 64).
+template <bool MULTI>
+__global__ __launch_bounds__(MULTI ? 512 : 64) void carry_lanes_kernel(const FragDev F, uint32_t W,
+                                                                       const uint64_t *__restrict__ in,
+                                                                       uint64_t *__restrict__ out, uint32_t n_rows) {
+  __shared__ ulonglong2 ex[MULTI ? 2 * 512 : 1];
+  const uint32_t r0 = blockIdx.x * 64;
+  const size_t RS = 2 * W + 1;
+  carry_lanes_body<MULTI>(F, W, in + r0 * RS, out + r0 * RS, min(64u, n_rows - r0), ex);
+}
+
+// Block x carries job x's rows (at most 64).
+template <bool MULTI>
+__global__ __launch_bounds__(MULTI ? 512 : 64) void carry_batch_kernel(const FragDev *__restrict__ descs,
+                                                                       const CarryJob *__restrict__ jobs,
+                                                                       const uint64_t *__restrict__ in,
+                                                                       uint64_t *__restrict__ out) {
+  __shared__ ulonglong2 ex[MULTI ? 2 * 512 : 1];
+  const CarryJob &J = jobs[blockIdx.x];
+  const g_FragDevH &F = ((const g_FragDevH *)descs)[J.desc];
+  carry_lanes_body<MULTI>(F, J.W, in + J.in_off, out + J.out_off, J.n_rows, ex);
 }
 
 struct HeisArgs {
@@ -423,28 +553,47 @@ size_t rows_sliced_lds(uint32_t m, uint32_t n_rows) {
 hipError_t launch_rows(const FragDev &F, uint32_t W, const uint64_t *in, uint64_t *out, uint32_t n_rows,
                        hipStream_t s) {
   if (n_rows == 0) return hipSuccess;
-  if ((W != 1 && W != 2 && W != 4 && W != 8) || F.m > 64 * W || (!in && n_rows > kSlicedRows))
-    return hipErrorInvalidValue;
+  if (!in || (W != 1 && W != 2 && W != 4 && W != 8) || F.m > 64 * W) return hipErrorInvalidValue;
+  if (F.lanes) {
+    if (F.n_steps % kCarryChunk) return hipErrorInvalidValue;
+    const dim3 grid((n_rows + 63) / 64), block(64 * carry_waves(F.m));
+    if (F.m <= 64)
+      hipLaunchKernelGGL(carry_lanes_kernel<false>, grid, block, 0, s, F, W, in, out, n_rows);
+    else
+      hipLaunchKernelGGL(carry_lanes_kernel<true>, grid, block, 0, s, F, W, in, out, n_rows);
+    return hipGetLastError();
+  }
   const size_t lds = rows_sliced_lds(F.m, std::min(n_rows, kSlicedRows));
   if (lds > 160 * 1024) return hipErrorInvalidValue;
   hipError_t e = hipFuncSetAttribute((const void *)rows_sliced_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(rows_sliced_kernel, dim3((n_rows + kSlicedRows - 1) / kSlicedRows), dim3(64), lds, s, F, W, in,
-                     out, n_rows);
+  hipLaunchKernelGGL(rows_sliced_kernel, dim3((n_rows + kSlicedRows - 1) / kSlicedRows), dim3(64 * kCarryWaves), lds, s,
+                     F, W, in, out, n_rows);
   return hipGetLastError();
 }
 
-hipError_t launch_carry_batch(const FragDev *descs, const CarryJob *jobs, uint32_t n_jobs, uint32_t max_m,
-                              uint32_t max_rows, const uint64_t *in, uint64_t *out, hipStream_t s) {
-  if (n_jobs == 0) return hipSuccess;
+hipError_t launch_carry_batch(const FragDev *descs, const CarryJob *jobs, uint32_t n_lanes, uint32_t waves,
+                              uint32_t n_stream, uint32_t max_m, uint32_t max_rows, const uint64_t *in, uint64_t *out,
+                              hipStream_t s) {
+  if (n_lanes) {
+    if (waves == 0 || waves > 8) return hipErrorInvalidValue;
+    if (waves == 1)
+      hipLaunchKernelGGL(carry_batch_kernel<false>, dim3(n_lanes), dim3(64), 0, s, descs, jobs, in, out);
+    else
+      hipLaunchKernelGGL(carry_batch_kernel<true>, dim3(n_lanes), dim3(64 * waves), 0, s, descs, jobs, in, out);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  if (n_stream == 0) return hipSuccess;
   if (max_rows > kSlicedRows) return hipErrorInvalidValue;
   const size_t lds = rows_sliced_lds(max_m, max_rows);
   if (lds > 160 * 1024) return hipErrorInvalidValue;
-  hipError_t e = hipFuncSetAttribute((const void *)carry_batch_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+  hipError_t e = hipFuncSetAttribute((const void *)sliced_batch_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(carry_batch_kernel, dim3(n_jobs), dim3(64 * kCarryWaves), lds, s, descs, jobs, in, out);
+  hipLaunchKernelGGL(sliced_batch_kernel, dim3(n_stream), dim3(64 * kCarryWaves), lds, s, descs, jobs + n_lanes, in,
+                     out);
   return hipGetLastError();
 }
 

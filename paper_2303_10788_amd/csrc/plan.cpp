@@ -196,9 +196,49 @@ void layer_stream(std::vector<uint32_t> &words, std::vector<uint32_t> &starts, u
   words.swap(out);
 }
 
+// The carry-back stream as a lane program: step s holds one word per qubit,
+// a two-qubit gate at the first step after both its qubits' earlier gates, a
+// one-qubit run merged into the word of the gate it precedes (or in a step of
+// its own after the last one).  Steps are padded to a multiple of 16, qubits
+// to whole waves.  False (and no program) where it would take more than
+// kLaneWordsMax words: deep streams that keep few qubits busy at a time.
+bool lane_program(const std::vector<uint32_t> &stream, uint32_t m, std::vector<uint32_t> &prog) {
+  const uint64_t mp = 64 * carry_waves(m);
+  std::vector<uint64_t> next(m, 0);
+  std::vector<uint32_t> run(m, 0u);  // pending one-qubit map
+  auto put = [&](uint64_t s, uint32_t q, uint32_t word) {
+    const uint64_t need = (s / kCarryChunk + 1) * kCarryChunk * mp;
+    if (need > kLaneWordsMax) return false;
+    if (prog.size() < need) prog.resize(need, 0u);
+    prog[s * mp + q] = word;
+    return true;
+  };
+  for (const uint32_t w : stream) {
+    const uint32_t k = op_kind(w), a = op_q0(w), b = op_q1(w);
+    if (!is_two_qubit(k)) {
+      run[a] = c1_then(run[a], b);
+      continue;
+    }
+    const uint64_t s = std::max(next[a], next[b]);
+    const uint32_t ra = k == G_CX ? kCarryControl : kCarryCz | kCarryLead, rb = k == G_CX ? kCarryTarget : kCarryCz;
+    if (!put(s, a, carry_word(run[a], ra, b)) || !put(s, b, carry_word(run[b], rb, a))) {
+      prog.clear();
+      return false;
+    }
+    run[a] = run[b] = 0u;
+    next[a] = next[b] = s + 1;
+  }
+  for (uint32_t q = 0; q < m; ++q)
+    if (run[q] && !put(next[q], q, carry_word(run[q], 0, q))) {
+      prog.clear();
+      return false;
+    }
+  return true;
+}
+
 // Fuse every run of one-qubit Cliffords on a qubit into one G_C1 word,
 // emitted just before the next two-qubit gate on that qubit (or at the
-// end): the forward stream for tableau passes and, from the same runs, the
+// end): the forward stream (gate counts) and, from the same runs, the
 // reversed stream of inverse gates for the Heisenberg carry-back.
 void fuse_clifford_runs(Fragment &F) {
   const uint32_t m = F.m();
@@ -227,8 +267,9 @@ void fuse_clifford_runs(Fragment &F) {
     }
   }
   for (uint32_t q = 0; q < m; ++q) flush(q);
-  F.cl_back.assign(back.rbegin(), back.rend());
-  layer_stream(F.cl_words, F.cl_layers, m);
+  std::reverse(back.begin(), back.end());
+  if (m <= 512 && lane_program(back, m, F.cl_lanes)) return;
+  F.cl_back = std::move(back);
   layer_stream(F.cl_back, F.cl_back_layers, m);
 }
 

@@ -32,11 +32,12 @@ struct Fragment {
   std::vector<double> op_theta;
   // Clifford fragments: runs of one-qubit gates on a qubit fused into one
   // G_C1 word (cl_words, circuit order), and the inverse stream for the
-  // Heisenberg carry-back (cl_back: last gate first, each gate inverted)
-  std::vector<uint32_t> cl_words, cl_back;
-  // both streams are ordered by ASAP layer; layer L of a stream spans
-  // words [layers[L], layers[L + 1])
-  std::vector<uint32_t> cl_layers, cl_back_layers;
+  // Heisenberg carry-back (last gate first, each gate inverted) as a lane
+  // program (cl_lanes, see carry_word in common.hpp) or, where that would
+  // take more than kLaneWordsMax words, as a stream cl_back ordered by ASAP
+  // layer (layer L spans words [layers[L], layers[L + 1]))
+  std::vector<uint32_t> cl_words, cl_lanes;
+  std::vector<uint32_t> cl_back, cl_back_layers;
   // non-Clifford fragments: the same ops with runs of one-qubit gates on a
   // qubit fused into one 2x2 unitary (G_U2) for the state-vector kernel
   std::vector<uint32_t> sv_words;
