@@ -136,10 +136,11 @@ __host__ __device__ inline uint32_t c1_then(uint32_t pa, uint32_t pb) {
 // bits of 64 rows, and step s gives each lane one word: a one-qubit map
 // applied first (bits 0-6, c1_encode), the lane's part in a two-qubit gate
 // (bits 7-10) and, from bit 16, its partner's LDS offset (16 bytes a qubit).
-// A zero word is the identity.
+// A zero word is the identity.  A lane's words of kCarryChunk steps are
+// adjacent: word (s, q) is at ((s / 4) * lanes + q) * 4 + s % 4.
 constexpr uint32_t kCarryControl = 1u << 7, kCarryTarget = 1u << 8, kCarryCz = 1u << 9;
 constexpr uint32_t kCarryLead = 1u << 10;  // the lane of a CZ that takes its sign
-constexpr uint32_t kCarryChunk = 16;       // steps fetched at a time
+constexpr uint32_t kCarryChunk = 4;        // steps fetched at a time (one 16-byte load a lane)
 constexpr uint64_t kLaneWordsMax = 1ull << 24;
 __host__ __device__ inline uint32_t carry_word(uint32_t c1, uint32_t role, uint32_t partner) {
   return (c1 & 127u) | role | (partner << 20);

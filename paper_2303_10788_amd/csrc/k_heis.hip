@@ -260,24 +260,31 @@ __device__ inline uint64_t word_mask(uint32_t w, uint32_t bit) {
 // partner lane: within a wave (up to 64 qubits) a lane exchange, else one LDS
 // write, a barrier and one LDS read (two buffers in turn, so one barrier a
 // step is enough).  Every lane runs the same instructions whatever its gate.
-// Bound by that chain of steps: the program's words are fetched kCarryChunk
-// steps ahead, one-qubit runs cost no step of their own, and 64 rows to a
-// workgroup keep the workgroups independent.  Signs: each lane collects its
-// share of the 64 rows' sign bits, XORed over the lanes at the end.
-// Measured on MI355X (a layered stream of gates on LDS columns before): see
-// the dispatch below.
+// Bound by that chain of steps: the program's words are fetched kCarryAhead
+// chunks ahead, one-qubit runs cost no step of their own, and 64 rows to a
+// workgroup keep the workgroups independent.  The loop is unrolled by one
+// chunk only: a launch runs few iterations, and its instructions come cold.
+// Signs: each lane collects its share of the 64 rows' sign bits, XORed over
+// the lanes at the end.  Measured on MI355X against the layered stream below
+// (LDS columns, a divergent round trip per gate kind and layer, one workgroup
+// for all rows): 24 qubits 25 -> 11 us, 156 qubits and 160 rows 114 -> 14 us,
+// 394 qubits 90 -> 17 us, a 256-circuit batch 65 -> 21 us; unrolled by 16
+// steps the first two took 13 and 17 us.
+constexpr uint32_t kCarryAhead = 4;
 template <bool MULTI, class D>
 __device__ void carry_lanes_body(const D &F, uint32_t W, const uint64_t *__restrict__ in, uint64_t *__restrict__ out,
                                  uint32_t n_rows, ulonglong2 *ex) {
   const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, mp = blockDim.x;
   const uint32_t own = carry_waves(F.m);  // waves that hold qubits (a batch's blocks may have more)
   const uint32_t RS = 2 * W + 1;
-  const uint32_t n_steps = F.n_steps, stride = 64 * own;
+  const uint32_t n_chunks = F.n_steps / kCarryChunk, stride = 64 * own;
   const bool mine = wave < own;
-  const uint32_t *prog = F.lanes + tid;
-  uint32_t nxt[kCarryChunk];
+  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+  const u32x4 *prog = reinterpret_cast<const u32x4 *>(F.lanes) + tid;
+  u32x4 queue[kCarryAhead];
 #pragma unroll
-  for (uint32_t i = 0; i < kCarryChunk; ++i) nxt[i] = mine && n_steps ? prog[(size_t)i * stride] : 0u;
+  for (uint32_t i = 0; i < kCarryAhead; ++i)
+    queue[i] = mine && i < n_chunks ? prog[(size_t)i * stride] : u32x4{0u, 0u, 0u, 0u};
   // lane r reads row r's words of this wave's qubits; transposed, lane q
   // holds qubit q's bits over the rows
   uint64_t x = 0, z = 0, sg = 0;
@@ -291,15 +298,12 @@ __device__ void carry_lanes_body(const D &F, uint32_t W, const uint64_t *__restr
   x = transpose64(x, lane);
   z = transpose64(z, lane);
   uint32_t buf = 0;
-  for (uint32_t c = 0; c < n_steps; c += kCarryChunk) {
-    uint32_t cur[kCarryChunk];
+#pragma unroll 1
+  for (uint32_t c = 0; c < n_chunks; ++c) {
+    const u32x4 cur = queue[0];
 #pragma unroll
-    for (uint32_t i = 0; i < kCarryChunk; ++i) cur[i] = nxt[i];
-    if (c + kCarryChunk < n_steps) {
-      prog += (size_t)kCarryChunk * stride;
-#pragma unroll
-      for (uint32_t i = 0; i < kCarryChunk; ++i) nxt[i] = mine ? prog[(size_t)i * stride] : 0u;
-    }
+    for (uint32_t i = 0; i + 1 < kCarryAhead; ++i) queue[i] = queue[i + 1];
+    if (mine && c + kCarryAhead < n_chunks) queue[kCarryAhead - 1] = prog[(size_t)(c + kCarryAhead) * stride];
 #pragma unroll
     for (uint32_t i = 0; i < kCarryChunk; ++i) {
       const uint32_t w = cur[i];
@@ -554,6 +558,9 @@ hipError_t launch_rows(const FragDev &F, uint32_t W, const uint64_t *in, uint64_
                        hipStream_t s) {
   if (n_rows == 0) return hipSuccess;
   if (!in || (W != 1 && W != 2 && W != 4 && W != 8) || F.m > 64 * W) return hipErrorInvalidValue;
+  // a lane program wherever the plan built one: it stands for every stream but
+  // those of more than 64 MB of program (a word per qubit and step, against
+  // one per gate), which the layered kernel takes
   if (F.lanes) {
     if (F.n_steps % kCarryChunk) return hipErrorInvalidValue;
     const dim3 grid((n_rows + 63) / 64), block(64 * carry_waves(F.m));

@@ -199,7 +199,7 @@ void layer_stream(std::vector<uint32_t> &words, std::vector<uint32_t> &starts, u
 // The carry-back stream as a lane program: step s holds one word per qubit,
 // a two-qubit gate at the first step after both its qubits' earlier gates, a
 // one-qubit run merged into the word of the gate it precedes (or in a step of
-// its own after the last one).  Steps are padded to a multiple of 16, qubits
+// its own after the last one).  Steps are padded to a multiple of 4, qubits
 // to whole waves.  False (and no program) where it would take more than
 // kLaneWordsMax words: deep streams that keep few qubits busy at a time.
 bool lane_program(const std::vector<uint32_t> &stream, uint32_t m, std::vector<uint32_t> &prog) {
@@ -210,7 +210,7 @@ bool lane_program(const std::vector<uint32_t> &stream, uint32_t m, std::vector<u
     const uint64_t need = (s / kCarryChunk + 1) * kCarryChunk * mp;
     if (need > kLaneWordsMax) return false;
     if (prog.size() < need) prog.resize(need, 0u);
-    prog[s * mp + q] = word;
+    prog[(s / kCarryChunk * mp + q) * kCarryChunk + s % kCarryChunk] = word;
     return true;
   };
   for (const uint32_t w : stream) {
