@@ -261,14 +261,8 @@ ccut_status ensure_ops(ccut_plan *p) {
       p->n_back[i] = (uint32_t)f.cl_back.size();
       p->n_back_layers[i] = (uint32_t)f.cl_back_layers.size() - 1;
     } else {
-      std::vector<uint32_t> words = f.sv_prog;
-      std::vector<double> m = f.sv_prog_mats;
-      while (words.size() % 16 || words.empty()) {
-        words.push_back(pack_op(G_NOP, 0, 0));
-        m.insert(m.end(), 8, 0.0);
-      }
-      ops[i] = add(words.data(), words.size() * 4);
-      mats[i] = add(m.data(), m.size() * 8);
+      ops[i] = add(f.sv_prog.data(), f.sv_prog.size() * 4);
+      mats[i] = add(f.sv_prog_mats.data(), f.sv_prog_mats.size() * 8);
     }
   }
   char *d = nullptr;
@@ -610,9 +604,8 @@ ccut_status variant_dists(ccut_plan *p, const ccut_eval_opts *eo, const Fragment
   if (!dist && !cnt16) return fail(c, CCUT_E_OOM, "device allocation failed");
   if (cnt_out) *cnt_out = cnt16;
   if (!f.clifford) {
-    const size_t sb = sv_states_bytes(h);
-    double *states = sb ? aget<double>(c, sb / sizeof(double)) : nullptr;
-    if (sb && !states) return fail(c, CCUT_E_OOM, "device allocation failed");
+    double *states = aget<double>(c, sv_states_bytes(h) / sizeof(double));
+    if (!states) return fail(c, CCUT_E_OOM, "device allocation failed");
     KTimer t(c, CCUT_K_SV);
     HIP_TRY(c, launch_sv(h, dist, states, c->cur));
   } else {
@@ -1755,9 +1748,8 @@ ccut_status zexpect_call(ccut_plan *p, const ccut_eval_opts *eo, const uint64_t 
     const FragDev h = frag_desc(p, f, r, eo->circuit);
     if (!f.clifford) {
       double *dist = aget<double>(c, nv << nm);
-      const size_t sb = sv_states_bytes(h);
-      double *states = sb ? aget<double>(c, sb / sizeof(double)) : nullptr;
-      if (!dist || (sb && !states)) return fail(c, CCUT_E_OOM, "device allocation failed");
+      double *states = aget<double>(c, sv_states_bytes(h) / sizeof(double));
+      if (!dist || !states) return fail(c, CCUT_E_OOM, "device allocation failed");
       {
         KTimer t(c, CCUT_K_SV);
         HIP_TRY(c, launch_sv(h, dist, states, c->cur));
@@ -2229,43 +2221,33 @@ ccut_status batch_enqueue(ccut_batch *b, bool tune) {
     size_t lds[2] = {0, 0};
     double cost = 0.0;
   };
-  // one class per launch shape (register and wave bits): every state of
-  // up to 8 qubits shares one; C.m is the class's widest state
+  // one class per launch shape (number of waves): every state of up to 7
+  // qubits shares one, and those of 11 and 12; C.m is the class's widest state
   std::vector<SvClass> classes;
-  auto shape_key = [](uint32_t m) {
-    const SvShape sh = sv_shape(m);
-    return sh.rb * 64u + sh.wb;
-  };
   for (uint32_t m = 1; m <= (uint32_t)kMaxNcQubits; ++m) {
-    if (m > 1 && shape_key(m - 1) == shape_key(m)) continue;  // handled with the class's first width
+    if (m > 1 && sv_waves(m - 1) == sv_waves(m)) continue;  // handled with the class's first width
     SvClass C;
     C.m = m;
     for (const auto &ref : b->nc) {
       const FragDev &h = b->sv_descs[ref.desc];
-      if (shape_key(h.m) != shape_key(m)) continue;
+      if (sv_waves(h.m) != sv_waves(m)) continue;
       C.m = std::max(C.m, h.m);
       double *dist = aget<double>(c, h.n_variants << ref.n_meas);
-      const size_t sb = sv_states_bytes(h);
-      double *states = sb ? aget<double>(c, sb / sizeof(double)) : nullptr;
-      if (!dist || (sb && !states)) return fail(c, CCUT_E_OOM, "device allocation failed");
+      double *states = aget<double>(c, sv_states_bytes(h) / sizeof(double));
+      if (!dist || !states) return fail(c, CCUT_E_OOM, "device allocation failed");
       pre_dist[ref.plan][ref.frag] = dist;
-      const uint32_t passes[2] = {sb ? 1u : 0u, 2u};
-      for (int k = 0; k < (sb ? 2 : 1); ++k) {
+      for (int k = 0; k < 2; ++k) {  // evolve, combine
         uint64_t n_wg;
-        uint32_t bs;
         size_t l;
-        bool split;
-        sv_pass_shape(h, passes[k], n_wg, bs, l, split);
+        sv_pass_shape(h, k == 1, n_wg, l);
         SvJob J{};
         J.desc = ref.desc;
-        J.split = split ? 1u : 0u;
         J.wg0 = C.wg[k];
         J.dist = dist;
-        J.mode = passes[k];
         J.states = states;
         C.wg[k] += n_wg;
         C.lds[k] = std::max(C.lds[k], l);
-        C.cost += (double)n_wg * (double)(1u << h.m) * (passes[k] == 2 ? 8.0 : (double)h.n_ops);
+        C.cost += k ? (double)n_wg * 1024 : (double)n_wg * (double)(1u << h.m) * (double)h.n_ops;
         C.jobs[k].push_back(J);
       }
     }
@@ -2285,9 +2267,8 @@ ccut_status batch_enqueue(ccut_batch *b, bool tune) {
     if (!b->nc.empty()) {
       // (the fork point was recorded before the sampling chain)
       for (size_t k = 0; k < n_sv_streams; ++k) HIP_TRY(c, hipStreamWaitEvent(b->pool[k], b->fork_ev, 0));
-      // two launches per shape class: the first runs fragments without
-      // quantum inputs in full and evolves the computational-basis inputs of
-      // the others, the second combines those into their preparations; the
+      // two launches per shape class: the computational-basis inputs evolved,
+      // then combined into every variant's outcomes; the
       // classes go to the streams longest first, each to the stream with the
       // least work so far (work: amplitudes times program length, summed over
       // workgroups)
@@ -2311,7 +2292,8 @@ ccut_status batch_enqueue(ccut_batch *b, bool tune) {
         for (int k = 0; k < 2; ++k) {
           if (C.jobs[k].empty()) continue;
           KTimer tm(c, CCUT_K_SV);
-          HIP_TRY(c, launch_sv_batch(d_sv, C.d_jobs[k], (uint32_t)C.jobs[k].size(), C.wg[k], C.m, C.lds[k], c->cur));
+          HIP_TRY(c, launch_sv_batch(d_sv, C.d_jobs[k], (uint32_t)C.jobs[k].size(), C.wg[k], k == 1, C.m, C.lds[k],
+                                     c->cur));
         }
         span_end(sp, c->cur);
       }

@@ -11,37 +11,10 @@ constexpr int kMaxAxes = 16;   // cut axes incident to one fragment
 constexpr int kMaxMeas = 64;   // measured qubits of one Clifford fragment (one u64 record)
 constexpr int kMaxNcQubits = 12;  // state vector of 2^12 complex doubles = 64 KiB of LDS
 
-// State-vector programs.  A non-Clifford fragment's state of 2^m amplitudes
-// is spread over registers: amplitude index bits [0, RB) select one of a
-// thread's 2^RB registers, the next min(m, 6) bits the lane of a wave and
-// the top WB bits the wave.  A program maps each logical qubit to one of
-// these bit positions; ops whose matrix mixes amplitudes (a general 2x2 or
-// a CX target) act on register or lane positions only, so they need no
-// barrier; diagonal ops, CZ and CX controls act anywhere.  SV_SWAP exchanges
-// a register or lane position with a wave position through LDS.
-enum : uint32_t {
-  SV_U2 = 0,    // general 2x2 unitary on position a (register or lane), matrix in mats
-  SV_DIAG = 1,  // diagonal unitary on position a (any): diag(m00, m11)
-  SV_CX = 2,    // control position a (any), target position b (register or lane)
-  SV_CZ = 3,    // positions a, b (any)
-  SV_SWAP = 4,  // exchange positions a (register or lane) and b (wave)
-  SV_END = 5,   // final layout: bits 4q..4q+3 of the first matrix word = position of qubit q
-};
-struct SvShape {
-  uint32_t rb, lb, wb;  // register, lane and wave bits
-};
-// Up to 4 amplitudes per thread (more spill registers): one wave up to 8
-// qubits (register bits first, so ops on the two lowest positions need no
-// exchange), and from 9 qubits on the state spreads over 2^(m - 8) waves,
-// up to 16 (1024 threads).  Every state of up to 8 qubits (from 2) has the
-// same shape, so a batch runs them in one launch.
-__host__ __device__ inline SvShape sv_shape(uint32_t m) {
-  if (m <= 8) {
-    const uint32_t rb = m < 2 ? m : 2u;
-    return {rb, m - rb, 0u};
-  }
-  return {2u, 6u, m - 8};
-}
+// Waves of a state-vector workgroup: one per 128 amplitudes (a step's tile of
+// 16 columns by 8 states), at least one, at most 16 (12 qubits: two tiles a
+// wave).  States of up to 7 qubits have the same launch shape.
+__host__ __device__ inline uint32_t sv_waves(uint32_t m) { return m <= 7 ? 1u : m >= 11 ? 16u : 1u << (m - 7); }
 constexpr int kMaxTableBits = 24;
 
 enum GateKind : uint32_t {
@@ -175,7 +148,7 @@ __device__ inline Ops16 load_ops16(const uint32_t *ops, uint32_t g16) {
 // the kernel-argument segment, so every field read is a scalar load).
 struct FragDev {
   uint32_t m;          // local qubits
-  uint32_t n_ops;      // fragment gates (preparations and rotations are implied by the variant)
+  uint32_t n_ops;      // steps of the state-vector program, or words of a carry-back stream
   uint32_t n_axes;
   uint32_t n_meas;     // measured set: requested circuit outputs + quantum outputs
   uint32_t n_req;      // requested circuit outputs among the measured set
@@ -187,8 +160,8 @@ struct FragDev {
   uint32_t axis_radix[kMaxAxes];
   uint32_t axis_cut[kMaxAxes];
   uint16_t meas[kMaxMeas];         // local qubit of measurement j (ascending)
-  const uint32_t *ops;             // packed op words, padded with G_NOP to a multiple of 16
-  const double *mats;              // per op 2x2 complex matrix (re00 im00 re01 im01 re10 im10 re11 im11), G_U2 only
+  const uint32_t *ops;             // state-vector program (256 words a step), or packed op words of a stream
+  const double *mats;              // state-vector program: 256 doubles a step
   // A Clifford fragment's carry-back as a stream: ASAP layers of ops on
   // disjoint qubits (layer L is ops[layers[L] .. layers[L + 1])); reordering
   // commuting ops changes no row and no sign
@@ -196,6 +169,12 @@ struct FragDev {
   uint32_t n_layers;
   uint32_t n_steps;      // steps of the carry-back's lane program (a multiple of kCarryChunk)
   const uint32_t *lanes; // the lane program (null: the layered stream `ops` instead)
+  // non-Clifford fragments, for the combine pass: input axes (bit j: axis j),
+  // the requested and the unmeasured qubits, and per axis the distance of its
+  // two values in the stored states, the outcome bit (outputs; else 0) and the
+  // stride in the variant index
+  uint32_t in_axes, req_mask, rest_mask;
+  uint32_t axis_dist[kMaxAxes], axis_obit[kMaxAxes], axis_stride[kMaxAxes];
 };
 
 // Per-variant affine sample model of a Clifford variant: a shot's outcome
@@ -262,16 +241,12 @@ constexpr size_t kSampleLdsMax = 8 * 256 * 8 + (size_t(2) << kLdsHistBits);
 
 // One non-Clifford fragment in a batched state-vector launch: descriptor
 // descs[desc], tables in dist, wg0 = its first workgroup.
-// One fragment's pass of a batched state-vector launch: mode 0 runs every
-// preparation combination in full (fragments without quantum inputs),
-// mode 1 evolves the computational-basis inputs into `states`, mode 2
-// combines them into the preparation combinations' tables.
+// One fragment's evolve or combine pass in a batched state-vector launch.
 struct SvJob {
-  uint32_t desc, split;
+  uint32_t desc, pad_;
   uint64_t wg0;
   double *dist;
-  uint32_t mode, pad_;
-  double *states;  // [2^n_in][2^m] complex amplitudes (modes 1 and 2)
+  double *states;  // [2^n_in][2^m] complex amplitudes
 };
 
 // The job whose range [start, next start) holds idx (starts ascending, first 0).
@@ -310,20 +285,16 @@ hipError_t launch_hist_reduce(const uint32_t *partial, uint64_t nv, uint32_t nbl
                               uint64_t shots, double *dist, hipStream_t s, uint16_t *cnt16 = nullptr);
 hipError_t launch_exact_tables(const uint64_t *models, uint32_t n_meas, uint64_t nv, double *dist,
                                hipStream_t s);
-// prog: the fragment's state-vector program (words + 8 doubles per word)
-// states: scratch of sv_states_bytes(frag) (may be NULL when it is 0).
+// states: scratch of sv_states_bytes(frag).
 hipError_t launch_sv(const FragDev &frag, double *dist, void *states, hipStream_t s);
 uint32_t sv_inputs(const FragDev &h);
 size_t sv_states_bytes(const FragDev &h);
-// Launch shape of one pass (0 full, 1 evolve, 2 combine) of a fragment.
-void sv_pass_shape(const FragDev &h, uint32_t pass, uint64_t &n_wg, uint32_t &block, size_t &lds, bool &split);
-// State-vector launch shape of a fragment: workgroups, threads, LDS bytes,
-// whether basis combinations get workgroups of their own.
-void sv_launch_shape(const FragDev &h, uint64_t &n_wg, uint32_t &block, size_t &lds, bool &split);
-// Many non-Clifford fragments of one shape (same m class: register bits and
-// waves) in one launch; lds = the largest of theirs.
-hipError_t launch_sv_batch(const FragDev *descs, const SvJob *jobs, uint32_t n_jobs, uint64_t total_wg, uint32_t m,
-                           size_t lds, hipStream_t s);
+// Workgroups and LDS of one pass of a fragment.
+void sv_pass_shape(const FragDev &h, bool combine, uint64_t &n_wg, size_t &lds);
+// One pass of many non-Clifford fragments of one shape (same number of waves;
+// m: the widest) in one launch; lds = the largest of theirs.
+hipError_t launch_sv_batch(const FragDev *descs, const SvJob *jobs, uint32_t n_jobs, uint64_t total_wg, bool combine,
+                           uint32_t m, size_t lds, hipStream_t s);
 // Batched sampling over jobs (see SampleJob; wg0 numbers the units of this
 // launch's jobs from 0); lds = the largest sample_lds_bytes among them.  The
 // reduction runs over all jobs of a batch (rb0 numbering) in one launch.

@@ -103,74 +103,152 @@ void fuse_one_qubit_runs(Fragment &F) {
   for (uint32_t q = 0; q < m; ++q) flush(q);
 }
 
-// Lay the fused stream out for the register-resident state-vector kernel
-// (positions as in sv_shape).  Qubit q starts at position q.  Before an op
-// that mixes amplitudes along a qubit that sits at a wave position, that
-// qubit swaps places with the register or lane qubit whose next such use
-// lies furthest ahead (Belady's rule), so swaps stay rare.  One-qubit
-// unitaries with zero off-diagonal entries become SV_DIAG, which runs at any
-// position.  The program ends with SV_END carrying the final layout.
-void build_sv_program(Fragment &F) {
-  const uint32_t m = F.m();
-  const SvShape sh = sv_shape(m);
-  const uint32_t inner = sh.rb + sh.lb;  // positions below this are register or lane bits
+// The state-vector program: the fused stream cut into three-qubit unitaries.
+// A block starts at the first op not yet taken and takes, in order, every
+// later op on its three qubits that no skipped op comes before on any of its
+// qubits (an op is skipped when it leaves the block's qubits; ops on disjoint
+// qubits commute).  Its first two qubits are the starting op's (a one-qubit
+// op's partner in its next two-qubit gate), the third is the one that lets it
+// take most ops.
+struct SvBlock {
+  uint32_t q[3];
+  std::vector<size_t> ops;
+};
+
+void sv_blocks(const Fragment &F, uint32_t mm, std::vector<SvBlock> &blocks) {
   const size_t n = F.sv_words.size();
-  std::vector<int32_t> need(n, -1);
-  std::vector<char> diag(n, 0);
+  std::vector<uint32_t> mask(n);
+  std::vector<char> two(n);
   for (size_t g = 0; g < n; ++g) {
-    const uint32_t w = F.sv_words[g], k = op_kind(w);
-    if (k == G_U2) {
-      const double *M = &F.sv_mats[8 * g];
-      diag[g] = M[2] == 0.0 && M[3] == 0.0 && M[4] == 0.0 && M[5] == 0.0;
-      if (!diag[g]) need[g] = (int32_t)op_q0(w);
-    } else if (k == G_CX) {
-      need[g] = (int32_t)op_q1(w);  // the target
-    }
+    const uint32_t w = F.sv_words[g];
+    two[g] = is_two_qubit(op_kind(w));
+    mask[g] = 1u << op_q0(w) | (two[g] ? 1u << op_q1(w) : 0u);
   }
-  std::vector<std::vector<size_t>> uses(m);
-  for (size_t g = 0; g < n; ++g)
-    if (need[g] >= 0) uses[need[g]].push_back(g);
-  std::vector<size_t> next(m, 0);
-  auto next_use = [&](uint32_t q, size_t g) {  // first use after op g
-    while (next[q] < uses[q].size() && uses[q][next[q]] <= g) ++next[q];
-    return next[q] < uses[q].size() ? uses[q][next[q]] : SIZE_MAX;
+  std::vector<char> done(n, 0);
+  auto scan = [&](size_t g0, uint32_t set, std::vector<size_t> *take) {
+    uint32_t blocked = 0;
+    size_t count = 0;
+    for (size_t g = g0; g < n && (set & ~blocked); ++g) {
+      if (done[g]) continue;
+      if (!(mask[g] & blocked) && !(mask[g] & ~set)) {
+        ++count;
+        if (take) take->push_back(g);
+      } else {
+        blocked |= mask[g];
+      }
+    }
+    return count;
   };
-  std::vector<uint32_t> pos(m), at(m);
-  for (uint32_t q = 0; q < m; ++q) pos[q] = at[q] = q;
-  auto emit = [&](uint32_t kind, uint32_t a, uint32_t b, const double *M) {
-    F.sv_prog.push_back(pack_op(kind, a, b));
-    for (int t = 0; t < 8; ++t) F.sv_prog_mats.push_back(M ? M[t] : 0.0);
-  };
-  for (size_t g = 0; g < n; ++g) {
-    const uint32_t w = F.sv_words[g], k = op_kind(w), a = op_q0(w), b = op_q1(w);
-    if (k != G_U2 && k != G_CX && k != G_CZ) continue;
-    if (need[g] >= 0 && pos[need[g]] >= inner) {
-      const uint32_t q = (uint32_t)need[g];
-      uint32_t victim = 0;
-      size_t far = 0;
-      for (uint32_t p = 0; p < inner; ++p) {
-        const size_t u = next_use(at[p], g);
-        if (p == 0 || u > far) {
-          far = u;
-          victim = p;
+  for (size_t g0 = 0; g0 < n; ++g0) {
+    if (done[g0]) continue;
+    uint32_t pair = mask[g0];
+    for (size_t g = g0 + 1; g < n && !two[g0]; ++g)
+      if (!done[g] && two[g] && (mask[g] & pair)) {
+        pair |= mask[g];
+        break;
+      }
+    for (uint32_t q = 0; __builtin_popcount(pair) < 2; ++q) pair |= 1u << q;
+    uint32_t best = 0;
+    size_t most = 0;
+    for (uint32_t q = 0; q < mm; ++q) {
+      if (pair >> q & 1u) continue;
+      const size_t c = scan(g0, pair | 1u << q, nullptr);
+      if (c > most) {
+        most = c;
+        best = q;
+      }
+    }
+    const uint32_t set = pair | 1u << best;
+    SvBlock B;
+    for (uint32_t q = 0, i = 0; q < mm; ++q)
+      if (set >> q & 1u) B.q[i++] = q;
+    scan(g0, set, &B.ops);
+    for (size_t g : B.ops) done[g] = 1;
+    blocks.push_back(std::move(B));
+  }
+}
+
+// The block's 8 x 8 unitary, bit i of a basis index = qubit q[i].
+void sv_block_matrix(const Fragment &F, const SvBlock &B, cplx (&U)[8][8]) {
+  for (uint32_t i = 0; i < 8; ++i)
+    for (uint32_t j = 0; j < 8; ++j) U[i][j] = i == j ? 1.0 : 0.0;
+  auto local = [&](uint32_t q) { return 1u << (q == B.q[0] ? 0 : q == B.q[1] ? 1 : 2); };
+  for (size_t g : B.ops) {
+    const uint32_t w = F.sv_words[g], k = op_kind(w), a = local(op_q0(w));
+    if (k == G_U2) {
+      const double *e = &F.sv_mats[8 * g];
+      const cplx m00(e[0], e[1]), m01(e[2], e[3]), m10(e[4], e[5]), m11(e[6], e[7]);
+      for (uint32_t i = 0; i < 8; ++i) {
+        if (i & a) continue;
+        for (uint32_t j = 0; j < 8; ++j) {
+          const cplx x = U[i][j], y = U[i | a][j];
+          U[i][j] = m00 * x + m01 * y;
+          U[i | a][j] = m10 * x + m11 * y;
         }
       }
-      const uint32_t pw = pos[q], qv = at[victim];
-      emit(SV_SWAP, victim, pw, nullptr);
-      std::swap(at[victim], at[pw]);
-      pos[q] = victim;
-      pos[qv] = pw;
+    } else {
+      const uint32_t b = local(op_q1(w));
+      for (uint32_t i = 0; i < 8; ++i) {
+        if (!(i & a) || (i & b)) continue;
+        for (uint32_t j = 0; j < 8; ++j) {
+          if (k == G_CX)
+            std::swap(U[i][j], U[i | b][j]);
+          else
+            U[i | b][j] = -U[i | b][j];
+        }
+      }
     }
-    if (k == G_U2)
-      emit(diag[g] ? SV_DIAG : SV_U2, pos[a], 0, &F.sv_mats[8 * g]);
-    else
-      emit(k == G_CX ? SV_CX : SV_CZ, pos[a], pos[b], nullptr);
   }
-  uint64_t layout = 0;
-  for (uint32_t q = 0; q < m; ++q) layout |= (uint64_t)pos[q] << (4 * q);
-  double M[8] = {};
-  std::memcpy(&M[0], &layout, 8);
-  emit(SV_END, 0, 0, M);
+}
+
+// Per step four words and four doubles a lane (sv_prog, sv_prog_mats).  Words:
+// LDS byte offsets (16 bits each) of the lane's index bits and of the register
+// bit, then of tile bits 0-1, 2-3 and 4.  Doubles: lane l's matrix elements
+// A[l % 16][4 c + l / 16], c < 4.  The block's qubits are lane bits 4 and 5 and
+// the register; the other qubits fill lane bits 0-3 (residues 0, 1, 2, 3 mod 4
+// where they can: different LDS banks), then the tile.
+void build_sv_program(Fragment &F) {
+  const uint32_t m = F.m(), mm = std::max(m, 3u);
+  std::vector<SvBlock> blocks;
+  sv_blocks(F, mm, blocks);
+  F.sv_prog.reserve(256 * blocks.size());
+  F.sv_prog_mats.reserve(256 * blocks.size());
+  auto slot = [](uint32_t p) { return ((1u << p) | (p >= 4 ? 1u << (p & 3u) : 0u)) * 16u; };  // p < 12: sv_slot(2^p)
+  for (const SvBlock &B : blocks) {
+    std::vector<uint32_t> rest;
+    for (uint32_t q = 0; q < mm; ++q)
+      if (q != B.q[0] && q != B.q[1] && q != B.q[2]) rest.push_back(q);
+    std::vector<uint32_t> cols;
+    for (uint32_t r = 0; r < 4 && !rest.empty(); ++r) {
+      size_t at = 0;
+      for (size_t i = 0; i < rest.size(); ++i)
+        if ((rest[i] & 3u) == r) {
+          at = i;
+          break;
+        }
+      cols.push_back(rest[at]);
+      rest.erase(rest.begin() + (long)at);
+    }
+    uint32_t off[12] = {};  // lane 0-5, register, tile 0-4
+    for (size_t i = 0; i < cols.size(); ++i) off[i] = slot(cols[i]);
+    off[4] = slot(B.q[0]);
+    off[5] = slot(B.q[1]);
+    off[6] = slot(B.q[2]);
+    for (size_t i = 0; i < rest.size(); ++i) off[7 + i] = slot(rest[i]);
+    for (uint32_t l = 0; l < 64; ++l) {
+      uint32_t o = 0;
+      for (uint32_t j = 0; j < 6; ++j) o ^= l >> j & 1u ? off[j] : 0u;
+      F.sv_prog.insert(F.sv_prog.end(), {o | off[6] << 16, off[7] | off[8] << 16, off[9] | off[10] << 16, off[11]});
+    }
+    cplx U[8][8];
+    sv_block_matrix(F, B, U);
+    for (uint32_t l = 0; l < 64; ++l)
+      for (uint32_t c = 0; c < 4; ++c) {
+        const uint32_t row = l % 16, k = 4 * c + l / 16;
+        const cplx u = U[row & 7u][k & 7u];
+        F.sv_prog_mats.push_back(row < 8 ? (k < 8 ? u.real() : -u.imag()) : (k < 8 ? u.imag() : u.real()));
+      }
+  }
 }
 
 // Order a Clifford stream by ASAP layer: op g goes one layer after the
@@ -488,7 +566,7 @@ FragRequest zstring_request(const Fragment &f, const std::vector<uint64_t> &anym
 FragDev make_frag_dev(const Fragment &f, const FragRequest &r, uint64_t vid_base) {
   FragDev d{};
   d.m = f.m();
-  d.n_ops = (uint32_t)(f.clifford ? f.cl_words.size() : f.sv_prog.size());
+  d.n_ops = f.clifford ? 0u : (uint32_t)(f.sv_prog.size() / 256);
   d.n_axes = (uint32_t)f.axes.size();
   d.n_meas = (uint32_t)r.meas.size();
   d.n_req = (uint32_t)r.req_pos.size();
@@ -502,6 +580,25 @@ FragDev make_frag_dev(const Fragment &f, const FragRequest &r, uint64_t vid_base
     d.axis_cut[j] = f.axes[j].cut;
   }
   for (size_t j = 0; j < r.meas.size() && j < (size_t)kMaxMeas; ++j) d.meas[j] = (uint16_t)r.meas[j];
+  if (!f.clifford && d.m <= (uint32_t)kMaxNcQubits) {
+    uint32_t n_in = 0, stride = 1, outs = 0;
+    for (size_t j = 0; j < f.axes.size(); ++j) {
+      const Axis &a = f.axes[j];
+      d.axis_stride[j] = stride;
+      stride *= a.radix();
+      if (a.side == 1) {
+        d.in_axes |= 1u << j;
+        d.axis_dist[j] = 1u << (d.m + n_in++);
+      } else {
+        d.axis_dist[j] = 1u << a.local;
+        d.axis_obit[j] = 1u << r.axis_outpos[j];
+        outs |= 1u << a.local;
+      }
+    }
+    for (uint32_t q : r.meas) d.req_mask |= 1u << q;
+    d.req_mask &= ~outs;
+    d.rest_mask = ((1u << d.m) - 1) & ~(d.req_mask | outs);
+  }
   return d;
 }
 

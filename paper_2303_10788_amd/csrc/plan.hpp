@@ -42,8 +42,8 @@ struct Fragment {
   // qubit fused into one 2x2 unitary (G_U2) for the state-vector kernel
   std::vector<uint32_t> sv_words;
   std::vector<double> sv_mats;              // 8 doubles per sv word
-  // the same stream laid out for the state-vector kernel (SV_* words, 8
-  // doubles per word)
+  // the same stream as three-qubit unitaries for the state-vector kernel (256
+  // words and 256 doubles a step, build_sv_program)
   std::vector<uint32_t> sv_prog;
   std::vector<double> sv_prog_mats;
   bool clifford = true;
