@@ -820,13 +820,28 @@ ccut_status pauli_passes(ccut_ctx *c, const Fragment &f, const FragRequest &r, d
 }
 
 
-// Exact Pauli-basis tensor of a Clifford fragment in the Heisenberg picture.
-// Marginal mode (strings == nullptr): T[p_f][b] over the requested outputs.
-// String mode: t[p_f][s] for Z strings given as local z masks (W words each).
-ccut_status heis_tensor(ccut_plan *p, const Fragment &f, const FragRequest &r, uint32_t circuit,
-                        const std::vector<std::vector<uint64_t>> *strings, double **out) {
+// Exact-mode Clifford fragments take the Heisenberg picture unless told
+// otherwise; a marginal request of more than 14 bits on the fragment
+// (req_bits) takes the variant path, since the transform to the Pauli basis
+// runs one LDS block of 2^req_bits entries per row (Z strings: req_bits 0).
+constexpr uint32_t kHeisMaxReqBits = 14;
+bool use_heisenberg(const Fragment &f, const ccut_eval_opts *eo, size_t req_bits) {
+  return f.clifford && eo->shots_per_variant == 0 && eo->method != CCUT_METHOD_VARIANTS &&
+         req_bits <= kHeisMaxReqBits;
+}
+
+// A Clifford fragment's observables carried back through it (Heisenberg
+// picture): the Z's of its requested outputs, or Z strings given as local z
+// masks (W words each), then X and Z of each quantum output.
+struct HeisRows {
+  uint32_t W = 0, n_in = 0, n_out = 0;
+  uint64_t cin[8] = {};  // local qubits that are circuit inputs
+  uint64_t *rows = nullptr;
+};
+ccut_status heis_rows(ccut_plan *p, const Fragment &f, const FragRequest &r, uint32_t circuit,
+                      const std::vector<std::vector<uint64_t>> *strings, HeisRows &H) {
   ccut_ctx *c = p->ctx;
-  const uint32_t W = row_words(f.m());
+  const uint32_t W = H.W = row_words(f.m());
   if (!W) return fail(c, CCUT_E_UNSUPPORTED, "Clifford fragment wider than 512 qubits");
   const uint32_t RW = 2 * W + 1;
   std::vector<uint64_t> rows;
@@ -838,45 +853,130 @@ ccut_status heis_tensor(ccut_plan *p, const Fragment &f, const FragRequest &r, u
       for (uint32_t w = 0; w < W; ++w) row[W + w] |= (*zmask)[w];
     rows.insert(rows.end(), row.begin(), row.end());
   };
-  const uint32_t nreq = (uint32_t)r.req_pos.size();
   if (!strings) {
-    for (uint32_t i = 0; i < nreq; ++i) add_row(-1, (int)r.meas[r.req_pos[i]], nullptr);
+    for (uint32_t q : r.req_pos) add_row(-1, (int)r.meas[q], nullptr);
   } else {
     for (const auto &z : *strings) add_row(-1, -1, &z);
   }
-  uint32_t n_in = 0, n_out = 0;
   for (const Axis &a : f.axes) {
     if (a.side == 0) {
       add_row((int)a.local, -1, nullptr);
       add_row(-1, (int)a.local, nullptr);
-      ++n_out;
+      ++H.n_out;
     } else {
-      ++n_in;
+      ++H.n_in;
     }
   }
-  if (n_out > 8) return fail(c, CCUT_E_UNSUPPORTED, "more than 8 quantum outputs on a Clifford fragment");
-  std::vector<uint64_t> cin(8, 0);
+  if (H.n_out > 8) return fail(c, CCUT_E_UNSUPPORTED, "more than 8 quantum outputs on a Clifford fragment");
   for (uint32_t i = 0; i < f.m(); ++i)
-    if (f.segs[i] == 0) cin[i >> 6] |= 1ull << (i & 63);
+    if (f.segs[i] == 0) H.cin[i >> 6] |= 1ull << (i & 63);
   const uint32_t n_rows = (uint32_t)(rows.size() / RW);
   if (rows.empty()) rows.assign(RW, 0);  // a fragment with nothing to carry back still gets a valid buffer
+  H.rows = aget<uint64_t>(c, rows.size());
+  uint64_t *d_in = (uint64_t *)upload(c, rows.data(), rows.size() * 8);
+  if (!H.rows || !d_in) return fail(c, CCUT_E_OOM, "device allocation failed");
+  KTimer t(c, CCUT_K_HEISENBERG);
+  HIP_TRY(c, launch_rows(carry_desc(p, f, frag_desc(p, f, r, circuit)), W, d_in, H.rows, n_rows, c->cur));
+  return CCUT_OK;
+}
+
+// The size limit of a fragment's exact tensor (ncols outcomes or strings); it
+// holds for evaluations that never form the tensor too.
+ccut_status heis_size(ccut_ctx *c, const Fragment &f, uint64_t ncols) {
+  if ((ncols << (2 * f.axes.size())) > (1ull << 34))
+    return fail(c, CCUT_E_UNSUPPORTED, "Pauli-basis tensor exceeds 2^34 entries");
+  return CCUT_OK;
+}
+
+// Exact Pauli-basis tensor of a Clifford fragment in the Heisenberg picture.
+// Marginal mode (strings == nullptr): T[p_f][b] over the requested outputs.
+// String mode: t[p_f][s].
+ccut_status heis_tensor(ccut_plan *p, const Fragment &f, const FragRequest &r, uint32_t circuit,
+                        const std::vector<std::vector<uint64_t>> *strings, double **out) {
+  ccut_ctx *c = p->ctx;
+  const uint32_t nreq = (uint32_t)r.req_pos.size();
   const uint64_t ncols = strings ? strings->size() : (1ull << nreq);
   const uint64_t total = ncols << (2 * f.axes.size());
-  if (total > (1ull << 34)) return fail(c, CCUT_E_UNSUPPORTED, "Pauli-basis tensor exceeds 2^34 entries");
+  const ccut_status size_st = heis_size(c, f, ncols);
+  if (size_st != CCUT_OK) return size_st;
   double *tau = aget<double>(c, total);
-  uint64_t *d_out = aget<uint64_t>(c, rows.size());
-  uint64_t *d_in = (uint64_t *)upload(c, rows.data(), rows.size() * 8);
-  if (!tau || !d_out || !d_in) return fail(c, CCUT_E_OOM, "device allocation failed");
-  const FragDev h = carry_desc(p, f, frag_desc(p, f, r, circuit));
+  if (!tau) return fail(c, CCUT_E_OOM, "device allocation failed");
+  HeisRows H;
+  const ccut_status st = heis_rows(p, f, r, circuit, strings, H);
+  if (st != CCUT_OK) return st;
   {
     KTimer t(c, CCUT_K_HEISENBERG);
-    HIP_TRY(c, launch_heisenberg(h, W, n_in, n_out, strings ? 0 : nreq, strings ? (uint32_t)strings->size() : 0,
-                                 cin.data(), d_in, d_out, n_rows, tau, c->cur));
+    HIP_TRY(c, launch_heisenberg(frag_desc(p, f, r, circuit), H.W, H.n_in, H.n_out, strings ? 0 : nreq,
+                                 strings ? (uint32_t)strings->size() : 0, H.cin, H.rows, tau, c->cur));
   }
   *out = tau;
   return cancelled(c);
 }
 
+// The Clifford fragment an exact contraction goes through (k_exact.hip): the
+// one with most quantum inputs, at least min_in, all but max_free cuts its
+// inputs and no cut on both its sides (there the output Pauli would have
+// to match the input's).  -1: none.
+int exact_fragment(const PlanData &pd, const ccut_eval_opts *eo, const std::vector<FragRequest> &reqs, bool strings,
+                   uint32_t min_in, uint32_t max_free) {
+  int best = -1;
+  uint32_t most = 0;
+  for (const Fragment &f : pd.frags) {
+    const size_t r = strings ? 0 : reqs[f.index].req_pos.size();
+    if (!use_heisenberg(f, eo, r) || r > kExactMaxReq || !row_words(f.m())) continue;
+    uint32_t n_in = 0;
+    std::vector<char> seen(pd.k, 0);
+    bool twice = false;
+    for (const Axis &a : f.axes) {
+      n_in += a.side == 1;
+      twice |= seen[a.cut] != 0;
+      seen[a.cut] = 1;
+    }
+    if (!twice && n_in >= min_in && n_in + max_free >= pd.k && n_in > most) {
+      best = (int)f.index;
+      most = n_in;
+    }
+  }
+  return best;
+}
+
+// Whether a marginal goes through exact_fragment: from three inputs on (64
+// terms of the dense sum for each one here) and where the dense contraction
+// would take the matrix paths (the plain sum's bits are those of the sparse
+// one); the sparse and skipping sums of exact data are the same sum.  fp64
+// only: the fp32 modes round sums of eight terms in the dense order.
+int exact_marginal_fragment(const PlanData &pd, const ccut_eval_opts *eo, const std::vector<FragRequest> &reqs,
+                            uint32_t nq) {
+  if (eo->precision != CCUT_FP64 || ((1ull << (2 * pd.k)) << nq) <= (1ull << 20)) return -1;
+  return exact_fragment(pd, eo, reqs, false, 3, kExactMaxFree);
+}
+
+ExactArgs exact_args(const PlanData &pd, const Fragment &f, const HeisRows &H, uint32_t first_out_row, uint32_t r,
+                     uint32_t nq) {
+  ExactArgs A{};
+  A.frag = f.index;
+  A.r = r;
+  A.nq = nq;
+  std::vector<char> input(pd.k, 0);
+  std::vector<uint32_t> row(pd.k, ~0u);
+  uint32_t oc = 0;
+  for (const Axis &a : f.axes) {
+    if (a.side == 1) {
+      A.in_local[A.n_in] = a.local;
+      A.in_cut[A.n_in++] = a.cut;
+      input[a.cut] = 1;
+    } else {
+      row[a.cut] = first_out_row + 2 * oc++;
+    }
+  }
+  for (uint32_t c = 0; c < pd.k; ++c)
+    if (!input[c]) {
+      A.free_cut[A.n_free] = c;
+      A.free_row[A.n_free++] = row[c];
+    }
+  std::copy(H.cin, H.cin + 8, A.cin_mask);
+  return A;
+}
 
 // Operands of the dense contraction: the fragment with the most requested
 // bits forms the column side, the others the row side.
@@ -984,7 +1084,6 @@ bool plain_contraction(const RecombArgs &args, uint32_t nq, bool fp32) {
 ccut_status recombine(ccut_ctx *c, const RecombArgs &args, uint32_t nq, bool fp32, double *res,
                       bool sparse = false) {
   if (sparse) return recombine_sparse(c, args, nq, fp32, res);
-  const uint64_t K = 1ull << (2 * args.k);
   if (plain_contraction(args, nq, fp32)) {
     RecombArgs *dargs = (RecombArgs *)upload(c, &args, sizeof(args));
     if (!dargs) return fail(c, CCUT_E_OOM, "device allocation failed");
@@ -995,16 +1094,6 @@ ccut_status recombine(ccut_ctx *c, const RecombArgs &args, uint32_t nq, bool fp3
   GemmArgs g;
   make_gemm_args(args, g);
   return run_gemm(c, g, fp32, res, true);
-}
-
-// Exact-mode Clifford fragments take the Heisenberg picture unless told
-// otherwise; a marginal request of more than 14 bits on the fragment
-// (req_bits) takes the variant path, since the transform to the Pauli basis
-// runs one LDS block of 2^req_bits entries per row (Z strings: req_bits 0).
-constexpr uint32_t kHeisMaxReqBits = 14;
-bool use_heisenberg(const Fragment &f, const ccut_eval_opts *eo, size_t req_bits) {
-  return f.clifford && eo->shots_per_variant == 0 && eo->method != CCUT_METHOD_VARIANTS &&
-         req_bits <= kHeisMaxReqBits;
 }
 
 // Results to the caller: into host memory with a final synchronization, or
@@ -1498,13 +1587,20 @@ ccut_status marginal_enqueue(ccut_plan *p, const ccut_eval_opts *eo, const uint3
   args.n_frags = (uint32_t)pd.frags.size();
   args.k = pd.k;
   args.lo_parts = eo->precision == CCUT_FP32X3_MFMA_FP64SUM;
-  const int g = fold_target(pd, eo, qubits, nq);
+  std::vector<FragRequest> reqs;
+  for (const Fragment &f : pd.frags) reqs.push_back(marginal_request(f, qubits, nq));
+  const int ef = exact_marginal_fragment(pd, eo, reqs, nq);
+  const int g = ef >= 0 ? -1 : fold_target(pd, eo, qubits, nq);
   const bool counts_ok = counts_contraction(pd, eo, nq);
+  HeisRows H;
   for (const Fragment &f : pd.frags) {
     route(c, f);
-    FragRequest r = marginal_request(f, qubits, nq);
+    const FragRequest &r = reqs[f.index];
     double *dist = nullptr, *T = nullptr;
-    if (use_heisenberg(f, eo, r.req_pos.size())) {
+    if ((int)f.index == ef) {
+      if ((st = heis_size(c, f, 1ull << r.req_pos.size())) != CCUT_OK) return st;
+      if ((st = heis_rows(p, f, r, eo->circuit, nullptr, H)) != CCUT_OK) return st;
+    } else if (use_heisenberg(f, eo, r.req_pos.size())) {
       if ((st = heis_tensor(p, f, r, eo->circuit, nullptr, &T)) != CCUT_OK) return st;
     } else {
       uint64_t *pm = pre_models ? (*pre_models)[f.index] : nullptr;
@@ -1531,6 +1627,15 @@ ccut_status marginal_enqueue(ccut_plan *p, const ccut_eval_opts *eo, const uint3
     if ((st = cancelled(c)) != CCUT_OK) return st;
   }
   if ((st = join(c)) != CCUT_OK) return st;
+  if (ef >= 0) {
+    const Fragment &f = pd.frags[ef];
+    const uint32_t r = (uint32_t)reqs[ef].req_pos.size();
+    RecombArgs *dargs = (RecombArgs *)upload(c, &args, sizeof(args));
+    if (!dargs) return fail(c, CCUT_E_OOM, "device allocation failed");
+    KTimer t(c, CCUT_K_RECOMBINE);
+    HIP_TRY(c, launch_exact_marginal(exact_args(pd, f, H, r, r, nq), dargs, H.W, H.rows, res, c->cur));
+    return CCUT_OK;
+  }
   std::vector<FoldJob> fj;
   fold_jobs(pd, g, args, fj);
   if (!fj.empty()) {
@@ -1658,7 +1763,10 @@ ccut_status marginal_call(ccut_plan *p, const ccut_eval_opts *eo, const uint32_t
   if (eo->flags & CCUT_FLAG_SKIP) {
     if (eo->flags & CCUT_FLAG_ML)
       return fail(c, CCUT_E_UNSUPPORTED, "the maximum-likelihood correction needs every variant (no skipping)");
-    st = marginal_skip_enqueue(p, eo, qubits, nq, res);
+    std::vector<FragRequest> reqs;
+    for (const Fragment &f : p->pd.frags) reqs.push_back(marginal_request(f, qubits, nq));
+    st = exact_marginal_fragment(p->pd, eo, reqs, nq) >= 0 ? marginal_enqueue(p, eo, qubits, nq, res, nullptr)
+                                                           : marginal_skip_enqueue(p, eo, qubits, nq, res);
   } else {
     st = marginal_enqueue(p, eo, qubits, nq, res, nullptr);
   }
@@ -1688,6 +1796,9 @@ ccut_status zexpect_call(ccut_plan *p, const ccut_eval_opts *eo, const uint64_t 
   args.n_frags = (uint32_t)pd.frags.size();
   args.k = pd.k;
   args.lo_parts = eo->precision == CCUT_FP32X3_MFMA_FP64SUM;
+  // (in fp32 only where a single term is left: its product rounds the same way)
+  const int ef = exact_fragment(pd, eo, {}, true, 1, eo->precision == CCUT_FP64 ? kExactMaxFree : 0);
+  HeisRows H;
   for (const Fragment &f : pd.frags) {
     route(c, f);
     FragRequest r = zstring_request(f, anymask);
@@ -1704,7 +1815,11 @@ ccut_status zexpect_call(ccut_plan *p, const ccut_eval_opts *eo, const uint64_t 
             zs[s2][l >> 6] |= 1ull << (l & 63);
         }
       double *T = nullptr;
-      if ((st = heis_tensor(p, f, r, eo->circuit, &zs, &T)) != CCUT_OK) return st;
+      if ((int)f.index == ef)
+        st = heis_size(c, f, n_strings) == CCUT_OK ? heis_rows(p, f, r, eo->circuit, &zs, H) : CCUT_E_UNSUPPORTED;
+      else
+        st = heis_tensor(p, f, r, eo->circuit, &zs, &T);
+      if (st != CCUT_OK) return st;
       RecombFrag &rf = args.f[f.index];
       rf.T = T;
       rf.n_axes = (uint32_t)f.axes.size();
@@ -1802,10 +1917,15 @@ ccut_status zexpect_call(ccut_plan *p, const ccut_eval_opts *eo, const uint64_t 
   if ((st = join(c)) != CCUT_OK) return st;
   RecombArgs *dargs = (RecombArgs *)upload(c, &args, sizeof(args));
   double *res = on_device ? out : aget<double>(c, n_strings);  // a device output receives the sums directly
-  const uint32_t zsplits = zrecombine_splits(pd.k, n_strings);
-  double *zpart = aget<double>(c, (size_t)zsplits * n_strings);
-  if (!dargs || !res || !zpart) return fail(c, CCUT_E_OOM, "device allocation failed");
-  {
+  if (!dargs || !res) return fail(c, CCUT_E_OOM, "device allocation failed");
+  if (ef >= 0) {
+    KTimer t(c, CCUT_K_ZRECOMBINE);
+    HIP_TRY(c, launch_exact_strings(exact_args(pd, pd.frags[ef], H, n_strings, 0, 0), dargs, H.W, H.rows, n_strings,
+                                    eo->precision != CCUT_FP64, res, c->cur));
+  } else {
+    const uint32_t zsplits = zrecombine_splits(pd.k, n_strings);
+    double *zpart = aget<double>(c, (size_t)zsplits * n_strings);
+    if (!zpart) return fail(c, CCUT_E_OOM, "device allocation failed");
     KTimer t(c, CCUT_K_ZRECOMBINE);
     HIP_TRY(c, launch_zrecombine(dargs, args.n_frags, pd.k, n_strings, eo->precision != CCUT_FP64,
                                  zpart, zsplits, res, c->cur));
@@ -2501,7 +2621,9 @@ ccut_status batch_enqueue(ccut_batch *b, bool tune) {
   std::vector<TileJob> tjobs;
   std::vector<FoldJob> fjobs;
   std::vector<RecombArgs> rargs(np);
-  std::vector<uint8_t> kind(np);  // 0 plain (batched), 1 plain (own launch), 2 MFMA
+  std::vector<uint8_t> kind(np);  // 0 plain (batched), 1 plain (own launch), 2 MFMA, 3 exact through a fragment (own launch)
+  std::vector<int> exact_of(np, -1);
+  std::vector<HeisRows> exact_rows(np);
   for (size_t i = 0; i < np; ++i) {
     ccut_plan *p = b->plans[i];
     const PlanData &pd = p->pd;
@@ -2520,12 +2642,18 @@ ccut_status batch_enqueue(ccut_batch *b, bool tune) {
     args.k = pd.k;
     args.lo_parts = b->eo.precision == CCUT_FP32X3_MFMA_FP64SUM;
     c->stream = c->cur = P ? b->pool[i % P] : b->stream;
-    const int g = fold_target(pd, &eo, qubits, nq);
+    std::vector<FragRequest> reqs;
+    for (const Fragment &f : pd.frags) reqs.push_back(marginal_request(f, qubits, nq));
+    const int ef = exact_of[i] = exact_marginal_fragment(pd, &eo, reqs, nq);
+    const int g = ef >= 0 ? -1 : fold_target(pd, &eo, qubits, nq);
     std::vector<char> folded(pd.frags.size(), 0);
     for (const Fragment &f : pd.frags) {
-      FragRequest r = marginal_request(f, qubits, nq);
+      const FragRequest &r = reqs[f.index];
       double *T = nullptr;
-      if (use_heisenberg(f, &eo, r.req_pos.size())) {
+      if ((int)f.index == ef) {
+        st = heis_size(c, f, 1ull << r.req_pos.size());
+        if (st == CCUT_OK) st = heis_rows(p, f, r, eo.circuit, nullptr, exact_rows[i]);
+      } else if (use_heisenberg(f, &eo, r.req_pos.size())) {
         st = heis_tensor(p, f, r, eo.circuit, nullptr, &T);
       } else {
         double *dist = pre_dist[i][f.index];
@@ -2566,8 +2694,7 @@ ccut_status batch_enqueue(ccut_batch *b, bool tune) {
     if (st != CCUT_OK) return st;
     fold_jobs(pd, g, args, fjobs, &folded);
     // the contraction recombine() would take
-    const uint64_t K = 1ull << (2 * pd.k);
-    kind[i] = plain_contraction(args, nq, fp32) ? (args.n_frags <= 8 ? 0 : 1) : 2;
+    kind[i] = ef >= 0 ? 3 : plain_contraction(args, nq, fp32) ? (args.n_frags <= 8 ? 0 : 1) : 2;
   }
   for (size_t k = 0; k < P; ++k) {
     HIP_TRY(c, hipEventRecord(b->join_ev[k], b->pool[k]));
@@ -2593,7 +2720,7 @@ ccut_status batch_enqueue(ccut_batch *b, bool tune) {
   // the output table: res while enqueuing eagerly; a captured graph reads
   // whatever the run call has put there
   b->job_out.assign(np, 0);
-  for (size_t i = 0; i < np; ++i) b->job_out[i] = kind[i] != 1;
+  for (size_t i = 0; i < np; ++i) b->job_out[i] = kind[i] != 1 && kind[i] != 3;
   if (!b->capturing && b->cur_tab != b->res) {
     HIP_TRY(c, hipStreamSynchronize(b->stream));  // an earlier copy may still read the pinned table
     for (size_t i = 0; i < np; ++i) b->h_out_tab[i] = b->res[i];
@@ -2606,7 +2733,7 @@ ccut_status batch_enqueue(ccut_batch *b, bool tune) {
   std::vector<size_t> plain_of(np, 0);
   std::vector<GemmArgs> gargs;
   for (size_t i = 0; i < np; ++i) {
-    if (kind[i] < 2) {
+    if (kind[i] != 2) {
       plain_of[i] = plain.size();
       plain.push_back(rargs[i]);
     } else {
@@ -2722,6 +2849,17 @@ ccut_status batch_enqueue(ccut_batch *b, bool tune) {
                                    sk ? 1u << ((sk - 1) / 3) : 0u, sk ? 1u << ((sk - 1) % 3) : 0u, c->cur));
     }
     span_end(sp, c->cur);
+  }
+  for (size_t i = 0, at = 0; i < np; ++i) {
+    if (kind[i] != 3) continue;
+    c->cur = at ? b->pool[at - 1] : b->stream;
+    at = (at + 1) % n_str;
+    const Fragment &f = b->plans[i]->pd.frags[exact_of[i]];
+    const uint32_t nq = (uint32_t)b->qubits[i].size(), r = rargs[i].f[f.index].n_req;
+    const HeisRows &H = exact_rows[i];
+    KTimer t(c, CCUT_K_RECOMBINE);
+    HIP_TRY(c, launch_exact_marginal(exact_args(b->plans[i]->pd, f, H, r, r, nq), d_plain + plain_of[i], H.W, H.rows,
+                                     b->res[i], c->cur));
   }
   c->cur = b->stream;
   for (size_t k = 0; k < n_side; ++k) {

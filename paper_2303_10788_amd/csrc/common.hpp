@@ -402,9 +402,10 @@ hipError_t launch_affine_wide(const FragDev &F, uint32_t W, const int8_t *meas_a
 // the item's fragment rows; block threads (a multiple of 64), grid blocks.
 hipError_t launch_affine_batch(const FragDev *descs, const uint32_t *desc_w, const BatchItem *items, uint32_t n_items,
                                const uint64_t *rows, uint64_t *models, uint32_t block, uint32_t grid, hipStream_t s);
+// rows: carried back (launch_rows), see k_heis.hip for their order.
 hipError_t launch_heisenberg(const FragDev &F, uint32_t W, uint32_t n_in, uint32_t n_out, uint32_t r,
-                             uint32_t n_str, const uint64_t *cin_mask, const uint64_t *rows_in, uint64_t *rows_out,
-                             uint32_t n_rows, double *tau, hipStream_t s);
+                             uint32_t n_str, const uint64_t *cin_mask, const uint64_t *rows, double *tau,
+                             hipStream_t s);
 
 // A fragment tensor to be rewritten along cut axes `mask` (bit j = axis j)
 // into the preparation basis of the fragments downstream (launch_fold).
@@ -485,6 +486,22 @@ struct OutCopy {
 hipError_t launch_gather_f64(const OutCopy *d_jobs, uint32_t n_jobs, uint64_t max_n, hipStream_t s);
 hipError_t launch_support_terms(const RecombArgs *d_args, const SupportArgs &sa, const uint8_t *nz, uint64_t K,
                                 uint64_t *pos, uint64_t *scratch, uint64_t *terms, hipStream_t s);
+// Exact contractions through Clifford fragment `frag` (k_exact.hip), whose
+// carried-back rows are the r requested Z's (marginals) or the strings, then
+// X and Z of each quantum output.  The other fragments' tensors are in the
+// RecombArgs, in the Pauli basis.
+constexpr uint32_t kExactMaxReq = 14, kExactMaxFree = 3;
+struct ExactArgs {
+  uint32_t frag, r, nq, n_in, n_free;
+  uint32_t in_local[kMaxAxes], in_cut[kMaxAxes];  // the fragment's quantum inputs
+  uint32_t free_cut[kExactMaxFree];               // the cuts that are not inputs of it, and the first row of
+  uint32_t free_row[kExactMaxFree];               // its quantum output there (~0: it has none there)
+  uint64_t cin_mask[8];                           // local qubits that are circuit inputs
+};
+hipError_t launch_exact_marginal(const ExactArgs &A, const RecombArgs *d_args, uint32_t W, const uint64_t *rows,
+                                 double *out, hipStream_t s);
+hipError_t launch_exact_strings(const ExactArgs &A, const RecombArgs *d_args, uint32_t W, const uint64_t *rows,
+                                uint32_t n_strings, bool fp32, double *out, hipStream_t s);
 constexpr uint32_t kRcChunkOut = 128;  // outputs per workgroup of the plain recombination
 // Z strings: fp64 products and sum, or (fp32 = true) fp32 products summed
 // in fp32 over chunks of 32 terms and in fp64 across chunks.

@@ -16,6 +16,7 @@
 #include <algorithm>
 
 #include "common.hpp"
+#include "pauli.hpp"
 
 namespace ccut {
 
@@ -393,38 +394,6 @@ struct HeisArgs {
   uint32_t n_str;        // Z-string mode: number of string rows (0 = marginal mode)
 };
 
-// Phase-tracked product: P = i^a X^x Z^z.
-template <int W>
-struct PAcc {
-  uint64_t x[W], z[W];
-  uint32_t a;
-};
-
-template <int W>
-__device__ inline void pmul(PAcc<W> &L, const uint64_t *R) {  // L <- L * R (R a Hermitian row)
-  uint32_t cross = 0, pr = 0;
-#pragma unroll
-  for (int w = 0; w < W; ++w) {
-    cross += __popcll(L.z[w] & R[w]);
-    pr += __popcll(R[w] & R[W + w]);
-  }
-  L.a = (L.a + 2u * (uint32_t)R[2 * W] + pr + 2u * cross) & 3u;
-#pragma unroll
-  for (int w = 0; w < W; ++w) {
-    L.x[w] ^= R[w];
-    L.z[w] ^= R[W + w];
-  }
-}
-
-template <int W>
-__device__ inline uint32_t pbit(const uint64_t (&v)[W], uint32_t q) {
-  uint64_t word = v[0];
-#pragma unroll
-  for (int w = 1; w < W; ++w)
-    if ((q >> 6) == (uint32_t)w) word = v[w];
-  return (uint32_t)(word >> (q & 63)) & 1u;
-}
-
 // One thread per (S or string, P_out combination).  rows: for the marginal
 // mode the r requested Z images followed by (X_c, Z_c) images per output;
 // for the string mode n_str string images followed by the output images.
@@ -440,9 +409,7 @@ __global__ void tau_kernel(const HeisArgs A, const uint64_t *__restrict__ rows, 
   const uint64_t pc = t / ncols;
   const uint32_t RW = 2 * W + 1;
   PAcc<W> acc;
-#pragma unroll
-  for (int w = 0; w < W; ++w) acc.x[w] = acc.z[w] = 0;
-  acc.a = 0;
+  pclear(acc);
   uint32_t out_base;
   if (A.n_str == 0) {
     for (uint32_t j = 0; j < A.r; ++j)
@@ -452,21 +419,13 @@ __global__ void tau_kernel(const HeisArgs A, const uint64_t *__restrict__ rows, 
     pmul<W>(acc, rows + (size_t)col * RW);
     out_base = A.n_str;
   }
-  // output Paulis, in output-axis order; Y = i X Z
+  // output Paulis, in output-axis order
   uint32_t oc = 0;
   uint64_t pf = 0;
   for (uint32_t j = 0; j < A.n_axes; ++j) {
     if (A.axis_side[j] != 0) continue;
     const uint32_t P = (uint32_t)((pc >> (2 * oc)) & 3ull);  // I, X, Y, Z
-    const uint64_t *rx = rows + (size_t)(out_base + 2 * oc) * RW;
-    const uint64_t *rz = rx + RW;
-    if (P == 1) pmul<W>(acc, rx);
-    if (P == 3) pmul<W>(acc, rz);
-    if (P == 2) {
-      acc.a = (acc.a + 1u) & 3u;
-      pmul<W>(acc, rx);
-      pmul<W>(acc, rz);
-    }
+    pmul_out<W>(acc, P, rows + (size_t)(out_base + 2 * oc) * RW);
     pf |= (uint64_t)P << (2 * j);
     ++oc;
   }
@@ -474,18 +433,9 @@ __global__ void tau_kernel(const HeisArgs A, const uint64_t *__restrict__ rows, 
 #pragma unroll
   for (int w = 0; w < W; ++w)
     if (acc.x[w] & A.cin_mask[w]) return;
-  for (uint32_t j = 0; j < A.n_axes; ++j) {
-    if (A.axis_side[j] != 1) continue;
-    const uint32_t q = A.axis_local[j];
-    const uint32_t xq = pbit<W>(acc.x, q), zq = pbit<W>(acc.z, q);
-    const uint32_t P = xq ? (zq ? 2u : 1u) : (zq ? 3u : 0u);
-    pf |= (uint64_t)P << (2 * j);
-  }
-  uint32_t pxz = 0;
-#pragma unroll
-  for (int w = 0; w < W; ++w) pxz += __popcll(acc.x[w] & acc.z[w]);
-  const uint32_t sgn = ((acc.a - pxz) & 3u) >> 1;  // acc is Hermitian: a - x.z in {0, 2}
-  tau[pf * ncols + col] = ldexp(sgn ? -1.0 : 1.0, (int)A.n_in);
+  for (uint32_t j = 0; j < A.n_axes; ++j)
+    if (A.axis_side[j] == 1) pf |= (uint64_t)pdigit<W>(acc, A.axis_local[j]) << (2 * j);
+  tau[pf * ncols + col] = ldexp(psign<W>(acc) ? -1.0 : 1.0, (int)A.n_in);
 }
 
 // T[row][b] = 2^-r sum_S (-1)^{b.S} tau[row][S]: in-place WHT per row in LDS.
@@ -530,23 +480,21 @@ __global__ void fill_zero_kernel(double *p, uint64_t n) {
 }
 
 template <int W>
-hipError_t run_w(const FragDev &F, const HeisArgs &A, const uint64_t *rows_in, uint64_t *rows_out, uint32_t n_rows,
-                 double *tau, uint64_t ncols, hipStream_t s) {
+hipError_t run_w(const HeisArgs &A, const uint64_t *rows, double *tau, uint64_t ncols, hipStream_t s) {
   hipError_t e;
-  if (n_rows && (e = launch_rows(F, W, rows_in, rows_out, n_rows, s)) != hipSuccess) return e;
   const uint64_t total_tau = ncols << (2 * A.n_axes);
   hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)std::min<uint64_t>((total_tau + 255) / 256, 65536)), dim3(256),
                      0, s, tau, total_tau);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const uint64_t nt = ncols << (2 * A.n_out);
-  hipLaunchKernelGGL((tau_kernel<W>), dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, s, A, rows_out, tau, ncols);
+  hipLaunchKernelGGL((tau_kernel<W>), dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, s, A, rows, tau, ncols);
   return hipGetLastError();
 }
 
 }  // namespace
 
-// rows_in: host-built Pauli rows [n_rows][2W+1] with W = words(m) rounded up
-// to {1, 2, 4, 8}; see k_heis layout.  Marginal mode (n_str == 0): rows are
+// rows: carried-back Pauli rows [n_rows][2W+1] with W = words(m) rounded up
+// to {1, 2, 4, 8}.  Marginal mode (n_str == 0): rows are
 // r requested Z's then (X_c, Z_c) per output axis; tau is [4^n_axes][2^r] and
 // is turned into T[p_f][b] in place.  String mode: rows are n_str strings then
 // the output pairs; tau is [4^n_axes][n_str] = t_f[p_f][string].
@@ -605,8 +553,8 @@ hipError_t launch_carry_batch(const FragDev *descs, const CarryJob *jobs, uint32
 }
 
 hipError_t launch_heisenberg(const FragDev &F, uint32_t W, uint32_t n_in, uint32_t n_out, uint32_t r,
-                             uint32_t n_str, const uint64_t *cin_mask, const uint64_t *rows_in, uint64_t *rows_out,
-                             uint32_t n_rows, double *tau, hipStream_t s) {
+                             uint32_t n_str, const uint64_t *cin_mask, const uint64_t *rows, double *tau,
+                             hipStream_t s) {
   HeisArgs A{};
   A.m = F.m;
   A.W = W;
@@ -623,10 +571,10 @@ hipError_t launch_heisenberg(const FragDev &F, uint32_t W, uint32_t n_in, uint32
   const uint64_t ncols = n_str ? n_str : (1ull << r);
   hipError_t e;
   switch (W) {
-    case 1: e = run_w<1>(F, A, rows_in, rows_out, n_rows, tau, ncols, s); break;
-    case 2: e = run_w<2>(F, A, rows_in, rows_out, n_rows, tau, ncols, s); break;
-    case 4: e = run_w<4>(F, A, rows_in, rows_out, n_rows, tau, ncols, s); break;
-    case 8: e = run_w<8>(F, A, rows_in, rows_out, n_rows, tau, ncols, s); break;
+    case 1: e = run_w<1>(A, rows, tau, ncols, s); break;
+    case 2: e = run_w<2>(A, rows, tau, ncols, s); break;
+    case 4: e = run_w<4>(A, rows, tau, ncols, s); break;
+    case 8: e = run_w<8>(A, rows, tau, ncols, s); break;
     default: return hipErrorInvalidValue;
   }
   if (e != hipSuccess || n_str) return e;
