@@ -978,6 +978,60 @@ ExactArgs exact_args(const PlanData &pd, const Fragment &f, const HeisRows &H, u
   return A;
 }
 
+// Whether fragment f's tensor is evaluated by its nonzero columns only: exact
+// Heisenberg data, an axis on every cut (each once), and few enough subsets
+// and output Paulis (ColumnSet).  From five cuts on: below, its 256 columns
+// cost less than finding them.
+bool column_fragment(const PlanData &pd, const ccut_eval_opts *eo, const Fragment &f, size_t r) {
+  if (!use_heisenberg(f, eo, r) || !row_words(f.m()) || pd.frags.size() > 8) return false;
+  if (pd.k < 5 || pd.k > kMaxColumnCuts || f.axes.size() != pd.k) return false;
+  uint32_t n_out = 0;
+  for (size_t j = 0; j < f.axes.size(); ++j) {
+    if (f.axes[j].cut != j) return false;
+    n_out += f.axes[j].side == 0;
+  }
+  return n_out <= kExactMaxFree && r + 2 * n_out <= 12;
+}
+
+// A fragment's nonzero columns, with their tensor (device buffers of the
+// call).  term_mask: keep the lookup tables of sampled terms.
+struct Columns {
+  HeisRows H;
+  ExactArgs A{};
+  ColumnSet S{};
+  double *T = nullptr;
+};
+ccut_status column_set(ccut_plan *p, const Fragment &f, const FragRequest &r, uint32_t circuit, bool group8,
+                       bool term_mask, double *norm, Columns &C) {
+  ccut_ctx *c = p->ctx;
+  const uint32_t nr = (uint32_t)r.req_pos.size();
+  ccut_status st;
+  if ((st = heis_size(c, f, 1ull << nr)) != CCUT_OK) return st;
+  if ((st = heis_rows(p, f, r, circuit, nullptr, C.H)) != CCUT_OK) return st;
+  C.A = exact_args(p->pd, f, C.H, nr, nr, nr);
+  const uint32_t k = p->pd.k, pairs = 1u << (nr + 2 * C.A.n_free);
+  ColumnSet &S = C.S;
+  S.k = k;
+  S.zero = (uint32_t)std::min<uint64_t>(pairs, 1ull << (2 * k));
+  S.group8 = group8;
+  S.count = aget<uint64_t>(c, 2);
+  S.cols = aget<uint64_t>(c, S.zero);
+  S.entries = aget<uint32_t>(c, pairs);
+  S.terms = aget<uint64_t>(c, (size_t)S.zero * (group8 ? 8 : 1));
+  S.term_col = aget<uint32_t>(c, (size_t)S.zero * (group8 ? 8 : 1));
+  if (term_mask) {
+    S.mask = aget<uint32_t>(c, 1ull << (2 * k - 5));
+    S.rank = aget<uint32_t>(c, 1ull << (2 * k - 5));
+  }
+  C.T = aget<double>(c, ((size_t)S.zero + 1) << nr);
+  if (!S.count || !S.cols || !S.entries || !S.terms || !S.term_col || (term_mask && (!S.mask || !S.rank)) || !C.T)
+    return fail(c, CCUT_E_OOM, "device allocation failed");
+  KTimer t(c, CCUT_K_HEISENBERG);
+  HIP_TRY(c, launch_columns(C.A, S, C.H.W, C.H.rows, c->cur));
+  HIP_TRY(c, launch_column_tensor(C.A, S, C.T, norm, c->cur));
+  return cancelled(c);
+}
+
 // Operands of the dense contraction: the fragment with the most requested
 // bits forms the column side, the others the row side.
 void make_gemm_args(const RecombArgs &args, GemmArgs &g) {
@@ -1017,6 +1071,22 @@ ccut_status run_gemm(ccut_ctx *c, const GemmArgs &g, bool fp32, double *res, boo
   KTimer t(c, CCUT_K_RECOMBINE);
   HIP_TRY(c, launch_recombine_gemm(g, dg, fp32, partial, splits, res, c->cur, skinny));
   return CCUT_OK;
+}
+
+// The contraction over a column set's terms (args.f of its fragment: the
+// column tensor); their number stays on the device.
+ccut_status column_contract(ccut_ctx *c, const RecombArgs &args, const Columns &C, bool fp32, double *res,
+                            const double *tscale = nullptr, bool square = false) {
+  GemmArgs g;
+  make_gemm_args(args, g);
+  g.terms = C.S.terms;
+  g.col_of = C.S.term_col;
+  g.col_frag = C.A.frag;
+  g.K_dev = C.S.count + 1;
+  g.K = (uint64_t)C.S.zero * (C.S.group8 ? 8 : 1);
+  g.tscale = tscale;
+  g.square = square;
+  return run_gemm(c, g, fp32, res);
 }
 
 // The sparse contraction: the support (cut terms whose column is nonzero in
@@ -1590,9 +1660,17 @@ ccut_status marginal_enqueue(ccut_plan *p, const ccut_eval_opts *eo, const uint3
   std::vector<FragRequest> reqs;
   for (const Fragment &f : pd.frags) reqs.push_back(marginal_request(f, qubits, nq));
   const int ef = exact_marginal_fragment(pd, eo, reqs, nq);
-  const int g = ef >= 0 ? -1 : fold_target(pd, eo, qubits, nq);
+  // fp32: over the nonzero columns of a fragment on every cut (the dense sum
+  // in groups of eight aligned terms, the sparse one over its support)
+  int cf = -1;
+  if (eo->precision != CCUT_FP64 && !(eo->flags & CCUT_FLAG_SKIP))
+    for (const Fragment &f : pd.frags)
+      if (cf < 0 && column_fragment(pd, eo, f, reqs[f.index].req_pos.size())) cf = (int)f.index;
+  const bool sparse = (eo->flags & CCUT_FLAG_SPARSE) != 0;
+  const int g = ef >= 0 || cf >= 0 ? -1 : fold_target(pd, eo, qubits, nq);
   const bool counts_ok = counts_contraction(pd, eo, nq);
   HeisRows H;
+  Columns C;
   for (const Fragment &f : pd.frags) {
     route(c, f);
     const FragRequest &r = reqs[f.index];
@@ -1600,6 +1678,9 @@ ccut_status marginal_enqueue(ccut_plan *p, const ccut_eval_opts *eo, const uint3
     if ((int)f.index == ef) {
       if ((st = heis_size(c, f, 1ull << r.req_pos.size())) != CCUT_OK) return st;
       if ((st = heis_rows(p, f, r, eo->circuit, nullptr, H)) != CCUT_OK) return st;
+    } else if ((int)f.index == cf) {
+      if ((st = column_set(p, f, r, eo->circuit, !sparse, false, nullptr, C)) != CCUT_OK) return st;
+      T = C.T;
     } else if (use_heisenberg(f, eo, r.req_pos.size())) {
       if ((st = heis_tensor(p, f, r, eo->circuit, nullptr, &T)) != CCUT_OK) return st;
     } else {
@@ -1636,6 +1717,26 @@ ccut_status marginal_enqueue(ccut_plan *p, const ccut_eval_opts *eo, const uint3
     HIP_TRY(c, launch_exact_marginal(exact_args(pd, f, H, r, r, nq), dargs, H.W, H.rows, res, c->cur));
     return CCUT_OK;
   }
+  if (cf >= 0) {
+    if (sparse) {
+      RecombArgs *dargs = (RecombArgs *)upload(c, &args, sizeof(args));
+      SupportArgs sa{};
+      uint64_t cols = 0;
+      for (const Fragment &f : pd.frags) {
+        sa.off[f.index] = cols;
+        if ((int)f.index != cf) cols += 1ull << (2 * f.axes.size());
+      }
+      uint8_t *nz = aget<uint8_t>(c, std::max<uint64_t>(cols, 1));
+      if (!dargs || !nz) return fail(c, CCUT_E_OOM, "device allocation failed");
+      KTimer t(c, CCUT_K_RECOMBINE);
+      for (const Fragment &f : pd.frags)
+        if ((int)f.index != cf)
+          HIP_TRY(c, launch_colnz(args.f[f.index].T, args.f[f.index].rows, 1ull << (2 * f.axes.size()),
+                                  nz + sa.off[f.index], c->cur));
+      HIP_TRY(c, launch_column_support(dargs, C.A, sa, nz, C.S, c->cur));
+    }
+    return column_contract(c, args, C, true, res);
+  }
   std::vector<FoldJob> fj;
   fold_jobs(pd, g, args, fj);
   if (!fj.empty()) {
@@ -1644,7 +1745,7 @@ ccut_status marginal_enqueue(ccut_plan *p, const ccut_eval_opts *eo, const uint3
     KTimer t(c, CCUT_K_TRANSFORM);
     HIP_TRY(c, launch_fold(d_fj, (uint32_t)fj.size(), c->cur));
   }
-  return recombine(c, args, nq, eo->precision != CCUT_FP64, res, (eo->flags & CCUT_FLAG_SPARSE) != 0);
+  return recombine(c, args, nq, eo->precision != CCUT_FP64, res, sparse);
 }
 }  // namespace
 
@@ -3149,6 +3250,8 @@ struct ccut_learned {
   RecombArgs args{};
   LearnedDev h{};
   LearnedDev *d = nullptr;
+  bool by_columns = false;  // one fragment's tensor kept by its nonzero columns
+  Columns cols;
   ~ccut_learned() {
     if (ctx && ctx->device >= 0) {
       (void)hipSetDevice(ctx->device);
@@ -3466,8 +3569,12 @@ void ccut_mlp_destroy(ccut_mlp *M) {
   ctx_release(c);
 }
 
-ccut_status ccut_learned_create(ccut_plan *p, const ccut_eval_opts *eo, const uint32_t *qubits, uint32_t nq,
-                                ccut_learned **out) {
+}  // extern "C"
+
+namespace {
+// ccut_learned_create without its final synchronization.
+ccut_status learned_enqueue(ccut_plan *p, const ccut_eval_opts *eo, const uint32_t *qubits, uint32_t nq,
+                            ccut_learned **out) {
   if (!p || !out) return CCUT_E_INVALID;
   *out = nullptr;
   ccut_status st = check_eval(p, eo);
@@ -3510,8 +3617,19 @@ ccut_status ccut_learned_create(ccut_plan *p, const ccut_eval_opts *eo, const ui
     h.n_frags = args.n_frags;
     for (const Fragment &f : pd.frags) {
       FragRequest r = marginal_request(f, qubits, nq);
+      const uint32_t a = (uint32_t)f.axes.size();
+      const uint64_t ncols = 1ull << (2 * a);
+      double *norm = aget<double>(c, ncols);
+      double *part = aget<double>(c, (uint64_t)4 * std::max<uint32_t>(a, 1) * share_chunks(a));
+      if (!norm || !part) return fail(c, CCUT_E_OOM, "device allocation failed");
       double *dist = nullptr, *T = nullptr;
-      if (use_heisenberg(f, eo, r.req_pos.size())) {
+      const bool columns = !L->by_columns && column_fragment(pd, eo, f, r.req_pos.size());
+      if (columns) {  // its column norms come with the columns
+        HIP_TRY(c, launch_fill_u32(reinterpret_cast<uint32_t *>(norm), 2 * ncols, 0u, c->cur));  // +0.0
+        if ((st = column_set(p, f, r, eo->circuit, false, true, norm, L->cols)) != CCUT_OK) return st;
+        T = L->cols.T;
+        L->by_columns = true;
+      } else if (use_heisenberg(f, eo, r.req_pos.size())) {
         if ((st = heis_tensor(p, f, r, eo->circuit, nullptr, &T)) != CCUT_OK) return st;
       } else {
         if ((st = variant_dists(p, eo, f, r, &dist)) != CCUT_OK) return st;
@@ -3524,14 +3642,9 @@ ccut_status ccut_learned_create(ccut_plan *p, const ccut_eval_opts *eo, const ui
       rf.n_req = (uint32_t)r.req_pos.size();
       for (size_t j = 0; j < f.axes.size(); ++j) rf.axis_cut[j] = f.axes[j].cut;
       for (size_t i = 0; i < r.req_user.size(); ++i) rf.req_user[i] = r.req_user[i];
-      const uint32_t a = (uint32_t)f.axes.size();
-      const uint64_t ncols = 1ull << (2 * a);
-      double *norm = aget<double>(c, ncols);
-      double *part = aget<double>(c, (uint64_t)4 * std::max<uint32_t>(a, 1) * share_chunks(a));
-      if (!norm || !part) return fail(c, CCUT_E_OOM, "device allocation failed");
       {
         KTimer t(c, CCUT_K_TERMS);
-        HIP_TRY(c, launch_colnorm(T, rf.rows, ncols, norm, c->cur));
+        if (!columns) HIP_TRY(c, launch_colnorm(T, rf.rows, ncols, norm, c->cur));
         HIP_TRY(c, launch_shares(norm, a, part, shares + slot_off[f.index], c->cur));
       }
       h.norm[f.index] = norm;
@@ -3548,11 +3661,19 @@ ccut_status ccut_learned_create(ccut_plan *p, const ccut_eval_opts *eo, const ui
     h.phi = phi;
     L->d = (LearnedDev *)upload(c, &h, sizeof(h));
     if (!L->d) return fail(c, CCUT_E_OOM, "device allocation failed");
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
   }
   *out = L.release();
   ctx_retain(c);
   return CCUT_OK;
+}
+}  // namespace
+
+extern "C" {
+
+ccut_status ccut_learned_create(ccut_plan *p, const ccut_eval_opts *eo, const uint32_t *qubits, uint32_t nq,
+                                ccut_learned **out) {
+  const ccut_status st = learned_enqueue(p, eo, qubits, nq, out);
+  return st == CCUT_OK ? sync_call(p->ctx) : st;
 }
 
 ccut_status ccut_learned_info(const ccut_learned *L, uint32_t *k, uint64_t *n_terms, uint32_t *width) {
@@ -3694,6 +3815,73 @@ ccut_status draw_terms(ccut_ctx *c, const double *q, uint64_t K, uint64_t n, uin
   HIP_TRY(c, launch_sample_terms(cdf, K, n, seed, cid, out, c->cur));
   return CCUT_OK;
 }
+
+// The estimate of n terms drawn from q into res and, when res2 is set, its
+// second moment: with Y_j the j-th term of the estimate,
+// sum_j Y_j^2 = 2^-k res2[b].  By columns: the draws are counted per nonzero
+// column (a term outside them weighs nothing) and each column contracted once.
+ccut_status sampled_estimate(ccut_learned *L, const double *q, uint64_t n, uint64_t seed, uint64_t *terms, double *res,
+                             double *res2) {
+  ccut_ctx *c = L->ctx;
+  ccut_status st;
+  if ((st = draw_terms(c, q, L->K, n, seed, L->circuit, terms)) != CCUT_OK) return st;
+  if (L->by_columns) {
+    const ColumnSet &S = L->cols.S;
+    uint32_t *counts = aget<uint32_t>(c, S.zero);
+    double *scale = aget<double>(c, S.zero), *scale2 = aget<double>(c, S.zero);
+    if (!counts || !scale || !scale2) return fail(c, CCUT_E_OOM, "device allocation failed");
+    {
+      KTimer t(c, CCUT_K_TERMS);
+      HIP_TRY(c, launch_column_weights(S, terms, n, q, counts, scale, scale2, c->cur));
+    }
+    if ((st = column_contract(c, L->args, L->cols, false, res, scale)) != CCUT_OK) return st;
+    return res2 ? column_contract(c, L->args, L->cols, false, res2, scale2, true) : CCUT_OK;
+  }
+  double *scale = aget<double>(c, n);
+  if (!scale) return fail(c, CCUT_E_OOM, "device allocation failed");
+  {
+    KTimer t(c, CCUT_K_TERMS);
+    HIP_TRY(c, launch_is_scale(terms, q, n, scale, c->cur));
+  }
+  GemmArgs g;
+  make_gemm_args(L->args, g);
+  g.terms = terms;
+  g.tscale = scale;
+  g.K = n;
+  if ((st = run_gemm(c, g, false, res)) != CCUT_OK || !res2) return st;
+  g.square = 1;
+  return run_gemm(c, g, false, res2);
+}
+
+// The exhaustive contraction by columns: the exact sum over subsets in fp64,
+// the aligned groups of eight terms in the fp32 modes.
+ccut_status columns_exhaustive(ccut_learned *L, const RecombArgs &args, double *res) {
+  ccut_ctx *c = L->ctx;
+  Columns C = L->cols;
+  if (L->precision == CCUT_FP64) {
+    RecombArgs *dargs = (RecombArgs *)upload(c, &args, sizeof(args));
+    if (!dargs) return fail(c, CCUT_E_OOM, "device allocation failed");
+    C.A.nq = L->nq;
+    KTimer t(c, CCUT_K_RECOMBINE);
+    HIP_TRY(c, launch_exact_marginal(C.A, dargs, C.H.W, C.H.rows, res, c->cur));
+    return CCUT_OK;
+  }
+  ColumnSet &S = C.S;
+  S.group8 = 1;
+  S.mask = S.rank = nullptr;
+  S.count = aget<uint64_t>(c, 2);
+  S.cols = aget<uint64_t>(c, S.zero);
+  S.entries = aget<uint32_t>(c, kMaxColumnEntries);
+  S.terms = aget<uint64_t>(c, (size_t)S.zero * 8);
+  S.term_col = aget<uint32_t>(c, (size_t)S.zero * 8);
+  if (!S.count || !S.cols || !S.entries || !S.terms || !S.term_col)
+    return fail(c, CCUT_E_OOM, "device allocation failed");
+  {
+    KTimer t(c, CCUT_K_HEISENBERG);
+    HIP_TRY(c, launch_columns(C.A, S, C.H.W, C.H.rows, c->cur));
+  }
+  return column_contract(c, args, C, true, res);
+}
 }  // namespace
 
 extern "C" {
@@ -3717,19 +3905,9 @@ ccut_status ccut_learned_estimate(ccut_learned *L, const double *q, uint64_t n, 
   if (!q || !out) return fail(c, CCUT_E_INVALID, "NULL argument");
   if (n == 0 || n > 0xFFFFFFFFull) return fail(c, CCUT_E_INVALID, "n must be in [1, 2^32)");
   uint64_t *terms = terms_out ? terms_out : aget<uint64_t>(c, n);
-  double *scale = aget<double>(c, n), *res = aget<double>(c, (size_t)1 << L->nq);
-  if (!terms || !scale || !res) return fail(c, CCUT_E_OOM, "device allocation failed");
-  if ((st = draw_terms(c, q, L->K, n, seed, L->circuit, terms)) != CCUT_OK) return st;
-  {
-    KTimer t(c, CCUT_K_TERMS);
-    HIP_TRY(c, launch_is_scale(terms, q, n, scale, c->cur));
-  }
-  GemmArgs g;
-  make_gemm_args(L->args, g);
-  g.terms = terms;
-  g.tscale = scale;
-  g.K = n;
-  if ((st = run_gemm(c, g, false, res)) != CCUT_OK) return st;
+  double *res = aget<double>(c, (size_t)1 << L->nq);
+  if (!terms || !res) return fail(c, CCUT_E_OOM, "device allocation failed");
+  if ((st = sampled_estimate(L, q, n, seed, terms, res, nullptr)) != CCUT_OK) return st;
   return finish_out(c, res, out, (size_t)1 << L->nq, on_device);
 }
 
@@ -3743,7 +3921,8 @@ ccut_status ccut_learned_exhaustive(ccut_learned *L, double *out, int on_device)
   if (!res) return fail(c, CCUT_E_OOM, "device allocation failed");
   RecombArgs args = L->args;
   args.lo_parts = L->precision == CCUT_FP32X3_MFMA_FP64SUM;
-  if ((st = recombine(c, args, L->nq, L->precision != CCUT_FP64, res)) != CCUT_OK) return st;
+  st = L->by_columns ? columns_exhaustive(L, args, res) : recombine(c, args, L->nq, L->precision != CCUT_FP64, res);
+  if (st != CCUT_OK) return st;
   return finish_out(c, res, out, (size_t)1 << L->nq, on_device);
 }
 
@@ -3762,7 +3941,7 @@ ccut_status ccut_learned_marginal(ccut_plan *p, const ccut_eval_opts *eo, ccut_m
   if (!out) return fail(c, CCUT_E_INVALID, "out is NULL");
   if (n_terms == 0 || n_terms > 0xFFFFFFFFull) return fail(c, CCUT_E_INVALID, "n_terms must be in [1, 2^32)");
   ccut_learned *L = nullptr;
-  ccut_status st = ccut_learned_create(p, eo, qubits, nq, &L);
+  ccut_status st = learned_enqueue(p, eo, qubits, nq, &L);
   if (st != CCUT_OK) return st;
   std::unique_ptr<ccut_learned, void (*)(ccut_learned *)> hold(L, ccut_learned_destroy);
   if ((st = begin_call(c)) != CCUT_OK) return st;
@@ -3771,40 +3950,21 @@ ccut_status ccut_learned_marginal(ccut_plan *p, const ccut_eval_opts *eo, ccut_m
   float *logits = aget<float>(c, K), *mpart = aget<float>(c, nb);
   double *q = aget<double>(c, K), *spart = aget<double>(c, nb), *stats = aget<double>(c, 2);
   uint64_t *terms = aget<uint64_t>(c, n_terms);
-  double *scale = aget<double>(c, n_terms), *res = aget<double>(c, bins);
-  double *res2 = out_stderr_l1 ? aget<double>(c, bins) : nullptr;
-  if (!logits || !mpart || !q || !spart || !stats || !terms || !scale || !res || (out_stderr_l1 && !res2))
+  double *res = aget<double>(c, bins), *res2 = out_stderr_l1 ? aget<double>(c, bins) : nullptr;
+  double *l1 = aget<double>(c, kStderrBlocks + 1);
+  if (!logits || !mpart || !q || !spart || !stats || !terms || !res || (out_stderr_l1 && !res2) || !l1)
     return fail(c, CCUT_E_OOM, "device allocation failed");
   if ((st = learned_logits_enqueue(L, net, logits)) != CCUT_OK) return st;
   {
     KTimer t(c, CCUT_K_TERMS);
     HIP_TRY(c, launch_proposal(logits, K, 0.05, mpart, spart, stats, q, c->cur));
   }
-  if ((st = draw_terms(c, q, K, n_terms, eo->seed, L->circuit, terms)) != CCUT_OK) return st;
-  {
-    KTimer t(c, CCUT_K_TERMS);
-    HIP_TRY(c, launch_is_scale(terms, q, n_terms, scale, c->cur));
-  }
-  GemmArgs g;
-  make_gemm_args(L->args, g);
-  g.terms = terms;
-  g.tscale = scale;
-  g.K = n_terms;
-  if ((st = run_gemm(c, g, false, res)) != CCUT_OK) return st;
+  if ((st = sampled_estimate(L, q, n_terms, eo->seed, terms, res, res2)) != CCUT_OK) return st;
   if (out_stderr_l1) {
-    // second moment: res2 = 2^-k sum_j (w_j / (N q_j))^2 2^2k, so with
-    // Y_j the j-th term of the estimate, sum_j Y_j^2 = 2^-k res2 and the
-    // standard error of entry b is sqrt(sum_j Y_j^2 - est_b^2 / N)
-    g.square = 1;
-    if ((st = run_gemm(c, g, false, res2)) != CCUT_OK) return st;
-    std::vector<double> e(bins), e2(bins);
-    HIP_TRY(c, hipMemcpyAsync(e.data(), res, bins * 8, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(c, hipMemcpyAsync(e2.data(), res2, bins * 8, hipMemcpyDeviceToHost, c->stream));
+    // the standard error of entry b is sqrt(sum_j Y_j^2 - est_b^2 / N)
+    HIP_TRY(c, launch_stderr_l1(res, res2, bins, L->k, (double)n_terms, l1 + 1, l1, c->stream));
+    HIP_TRY(c, hipMemcpyAsync(out_stderr_l1, l1, 8, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
-    double l1 = 0.0;
-    for (uint64_t b = 0; b < bins; ++b)
-      l1 += std::sqrt(std::max(0.0, std::ldexp(e2[b], -(int)L->k) - e[b] * e[b] / (double)n_terms));
-    *out_stderr_l1 = l1;
   }
   return finish_out(c, res, out, bins, out_on_device);
 }

@@ -502,6 +502,32 @@ hipError_t launch_exact_marginal(const ExactArgs &A, const RecombArgs *d_args, u
                                  double *out, hipStream_t s);
 hipError_t launch_exact_strings(const ExactArgs &A, const RecombArgs *d_args, uint32_t W, const uint64_t *rows,
                                 uint32_t n_strings, bool fp32, double *out, hipStream_t s);
+// The nonzero columns of fragment A.frag's tensor, found from its rows.  Its
+// axes are cuts 0 .. k-1 in order (a column index is a cut term), its outputs
+// the free cuts; at most kMaxColumnEntries (subset, output Paulis) pairs.
+constexpr uint32_t kMaxColumnCuts = 10, kMaxColumnEntries = 4096;
+struct ColumnSet {
+  uint32_t k, zero;        // cuts; index of the all-zero column (>= every column count)
+  uint32_t group8;         // terms: the 8-aligned groups of terms with a nonzero column, else the columns alone
+  uint64_t *count;         // [2] nonzero columns, terms
+  uint64_t *cols;          // [zero] column i's cut term, ascending
+  uint32_t *entries;       // per pair: 2 column + sign, or ~0
+  uint64_t *terms;         // [group8 ? 8 zero : zero], ascending
+  uint32_t *term_col;      // their columns (`zero` for a term outside the set)
+  uint32_t *mask, *rank;   // optional, [4^k / 32]: bit per term; columns below each thread's run of words
+};
+hipError_t launch_columns(const ExactArgs &A, const ColumnSet &S, uint32_t W, const uint64_t *rows, hipStream_t s);
+// T[column][2^r] (column `zero`: zeros); norm (optional): norm[term] of every
+// nonzero column, the root of its summed squares.
+hipError_t launch_column_tensor(const ExactArgs &A, const ColumnSet &S, double *T, double *norm, hipStream_t s);
+// The terms of S (group8 = 0) whose column is nonzero in every other fragment
+// too (nz as in launch_support_terms), compacted in place.
+hipError_t launch_column_support(const RecombArgs *d_args, const ExactArgs &A, const SupportArgs &sa, const uint8_t *nz,
+                                 const ColumnSet &S, hipStream_t s);
+// Draws terms[0..n) counted per column, and the columns' weights: scale =
+// count / (n q), scale2 = sqrt(count) / (n q), 0 where nothing was drawn.
+hipError_t launch_column_weights(const ColumnSet &S, const uint64_t *terms, uint64_t n, const double *q,
+                                 uint32_t *counts, double *scale, double *scale2, hipStream_t s);
 constexpr uint32_t kRcChunkOut = 128;  // outputs per workgroup of the plain recombination
 // Z strings: fp64 products and sum, or (fp32 = true) fp32 products summed
 // in fp32 over chunks of 32 terms and in fp64 across chunks.
@@ -524,6 +550,11 @@ struct GemmArgs {
   // term's row-side value is multiplied by tscale[kk] when set
   const uint64_t *terms;
   const double *tscale;
+  // the column tensor of fragment col_frag holds some columns only: K index
+  // -> column col_of[kk] (set together with terms)
+  const uint32_t *col_of;
+  const uint64_t *K_dev;  // the number of terms when only the device knows it (K: its bound)
+  uint32_t col_frag;
   uint32_t square;  // 1: every operand value squared (second moment of the sampled estimate)
   uint32_t lo_parts;  // fp32 mode: 1 = operands split hi + lo, three MFMA products; 0 = one fp32 product
   GemmSide L, R;
@@ -671,5 +702,10 @@ hipError_t launch_int_cdf(const double *q, uint64_t n, uint64_t *cdf, uint64_t *
 hipError_t launch_sample_terms(const uint64_t *cdf, uint64_t K, uint64_t n, uint64_t seed, uint64_t cid,
                                uint64_t *out, hipStream_t s);
 hipError_t launch_is_scale(const uint64_t *terms, const double *q, uint64_t n, double *scale, hipStream_t s);
+// *out = sum_b sqrt(max(0, 2^-k e2[b] - e[b]^2 / n)), in a fixed order; part:
+// kStderrBlocks doubles
+constexpr uint32_t kStderrBlocks = 256;
+hipError_t launch_stderr_l1(const double *e, const double *e2, uint64_t bins, uint32_t k, double n, double *part,
+                            double *out, hipStream_t s);
 
 }  // namespace ccut

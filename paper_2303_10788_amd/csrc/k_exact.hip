@@ -179,7 +179,276 @@ __global__ __launch_bounds__(64) void exact_strings_kernel(const ExactArgs A, co
   out[s] = ldexp(sum, (int)A.n_in - (int)R.k);
 }
 
+// ------------------------------------------------- the nonzero columns
+// Where the columns of C's tensor are needed themselves (fp32 contractions,
+// whose sums of eight terms are rounded in cut-term order, and sampled term
+// lists): one workgroup marks the column of every (subset, output Paulis) pair
+// in a bit mask in LDS (4^10 terms: 128 KB), counts the bits below each thread's
+// words and lists the columns in ascending order; a workgroup per column then
+// gathers its pairs and transforms them.  A few of the 4^k columns are
+// nonzero (1 to 16 in the 6- and 10-cut workloads).  Measured at 10 cuts: 19 +
+// 4 us where filling and transforming every column took 1590 us, its column
+// norms another 3400 us and each contraction of 16384 drawn terms 220 us
+// (their counts 5, the columns' contraction 16 us); at 6 cuts, 1024 subsets of
+// 7 words 20 + 6 us and an fp32 contraction of 15 + 5 us, for 94 us.
+constexpr uint32_t kColThreads = 1024;
+
+// Inclusive scan over the workgroup of two counts packed in one word.
+__device__ inline uint32_t block_scan(uint32_t v, uint32_t *wave_sum) {
+  const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (uint32_t o = 1; o < 64; o <<= 1) {
+    const uint32_t p = __shfl_up(v, o);
+    if (lane >= o) v += p;
+  }
+  __syncthreads();  // wave_sum is free
+  if (lane == 63) wave_sum[wave] = v;
+  __syncthreads();
+  for (uint32_t w = 0; w < wave; ++w) v += wave_sum[w];
+  return v;
+}
+
+// Words of the mask per thread, and a word's place in LDS: a thread walks its
+// own words in order, so each thread's run is one word longer than its words
+// (lanes on different banks).
+__host__ __device__ inline uint32_t col_per(uint32_t k) { return 2 * k > 15 ? 1u << (2 * k - 15) : 1u; }
+__device__ inline uint32_t col_at(uint32_t w, uint32_t per) { return per > 1 ? w + w / per : w; }
+
+template <int W>
+__global__ __launch_bounds__(kColThreads) void columns_kernel(const ExactArgs A, const ColumnSet S,
+                                                              const uint64_t *d_rows) {
+  extern __shared__ uint32_t mask[];  // [4^k / 32], col_at
+  __shared__ uint32_t base[kColThreads], wave_sum[kColThreads / 64];
+  c_u64 *rows = (c_u64 *)(uintptr_t)d_rows;
+  const uint32_t tid = threadIdx.x;
+  const uint32_t n_words = 1u << (2 * S.k - 5), per = col_per(S.k);
+  for (uint32_t i = tid; i < n_words; i += kColThreads) mask[col_at(i, per)] = 0;
+  __syncthreads();
+  const uint32_t n_pairs = 1u << (A.r + 2 * A.n_free);
+  constexpr uint32_t kMost = kMaxColumnEntries / kColThreads;
+  uint32_t pair[kMost];  // this thread's pairs: sign << 31 | term, or ~0
+#pragma unroll
+  for (uint32_t i = 0; i < kMost; ++i) {
+    const uint32_t e = tid + i * kColThreads;
+    pair[i] = ~0u;
+    if (e >= n_pairs) continue;
+    PAcc<W> acc;
+    pclear(acc);
+    for (uint32_t j = 0; j < A.r; ++j)
+      if (e >> j & 1u) pmul<W>(acc, rows + (size_t)j * (2 * W + 1));
+    uint32_t P = free_paulis<W>(A, e >> A.r, acc, rows);
+    if (!input_paulis<W>(A, acc, P)) continue;
+    pair[i] = P | psign<W>(acc) << 31;
+    atomicOr(&mask[col_at(P >> 5, per)], 1u << (P & 31));
+  }
+  __syncthreads();
+  // columns (low half) and 8-aligned groups (high half) in this thread's words
+  uint32_t own = 0;
+  const uint32_t w0 = tid * per, w1 = w0 < n_words ? w0 + per : w0;
+  auto groups = [](uint32_t m) {  // nonzero bytes
+    return ((m & 0xFFu) != 0) + ((m & 0xFF00u) != 0) + ((m & 0xFF0000u) != 0) + ((m & 0xFF000000u) != 0);
+  };
+  for (uint32_t w = w0; w < w1; ++w) {
+    const uint32_t m = mask[col_at(w, per)];
+    own += __popc(m) | (uint32_t)groups(m) << 16;
+  }
+  const uint32_t incl = block_scan(own, wave_sum);
+  base[tid] = (incl - own) & 0xFFFFu;
+  uint32_t col = (incl - own) & 0xFFFFu, grp = (incl - own) >> 16;
+  if (tid == kColThreads - 1) {
+    S.count[0] = incl & 0xFFFFu;
+    S.count[1] = S.group8 ? 8ull * (incl >> 16) : incl & 0xFFFFu;
+  }
+  if (S.mask) {
+    for (uint32_t i = tid; i < n_words; i += kColThreads) S.mask[i] = mask[col_at(i, per)];
+    if (w0 < n_words) S.rank[tid] = col;
+  }
+  for (uint32_t w = w0; own && w < w1; ++w) {
+    const uint32_t m = mask[col_at(w, per)];
+    for (uint32_t g = 0; m && g < 4; ++g) {
+      const uint32_t byte = m >> (8 * g) & 0xFFu;
+      if (!byte) continue;
+      for (uint32_t i = 0; i < 8; ++i) {
+        const uint64_t P = 32ull * w + 8 * g + i;
+        const bool in = byte >> i & 1u;
+        if (S.group8) {
+          S.terms[8 * grp + i] = P;
+          S.term_col[8 * grp + i] = in ? col : S.zero;
+        } else if (in) {
+          S.terms[col] = P;
+          S.term_col[col] = col;
+        }
+        if (in) S.cols[col++] = P;
+      }
+      ++grp;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (uint32_t i = 0; i < kMost; ++i) {
+    const uint32_t e = tid + i * kColThreads;
+    if (e >= n_pairs) continue;
+    uint32_t out = ~0u;
+    if (pair[i] != ~0u) {
+      const uint32_t P = pair[i] & 0x7FFFFFFFu, w = P >> 5, t = w / per;
+      uint32_t c = base[t] + __popc(mask[col_at(w, per)] & ((1u << (P & 31)) - 1));
+      for (uint32_t v = t * per; v < w; ++v) c += __popc(mask[col_at(v, per)]);
+      out = 2 * c | pair[i] >> 31;
+    }
+    S.entries[e] = out;
+  }
+}
+
+// Block c: column c (blocks past the columns end at once; block `zero` writes
+// the zero column).
+__global__ __launch_bounds__(256) void column_tensor_kernel(const ExactArgs A, const ColumnSet S,
+                                                            double *__restrict__ T, double *__restrict__ norm) {
+  extern __shared__ double h[];
+  __shared__ uint32_t size;
+  const uint32_t c = blockIdx.x, tid = threadIdx.x, r = A.r, n = 1u << r;
+  double *row = T + (size_t)c * n;
+  if (c == S.zero) {
+    for (uint32_t i = tid; i < n; i += 256) row[i] = 0.0;
+    return;
+  }
+  if (c >= S.count[0]) return;
+  if (tid == 0) size = 0;
+  for (uint32_t i = tid; i < n; i += 256) h[i] = 0.0;
+  __syncthreads();
+  const uint32_t n_pairs = n << (2 * A.n_free);
+  const double v = ldexp(1.0, (int)A.n_in);
+  uint32_t found = 0;
+  for (uint32_t e = tid; e < n_pairs; e += 256) {
+    const uint32_t x = S.entries[e];
+    if (x >> 1 != c || x == ~0u) continue;
+    h[e & (n - 1)] = x & 1u ? -v : v;  // (a column has one output Pauli combination: its subsets differ)
+    ++found;
+  }
+  if (norm && found) atomicAdd(&size, found);
+  __syncthreads();
+  for (uint32_t s = 0; s < r; ++s) {
+    for (uint32_t k = tid; k < n / 2; k += 256) {
+      const uint32_t i0 = ((k >> s) << (s + 1)) | (k & ((1u << s) - 1)), i1 = i0 | (1u << s);
+      const double a = h[i0], b = h[i1];
+      h[i0] = a + b;
+      h[i1] = a - b;
+    }
+    __syncthreads();
+  }
+  for (uint32_t i = tid; i < n; i += 256) row[i] = ldexp(h[i], -(int)r);
+  // sum_b T[b]^2 = 2^-r sum_S tau[S]^2 (every value is a power of two times an
+  // integer: the sum over b is exact too)
+  if (norm && tid == 0) norm[S.cols[c]] = sqrt(ldexp((double)size, 2 * (int)A.n_in - (int)r));
+}
+
+__global__ __launch_bounds__(kColThreads) void column_support_kernel(const RecombArgs *d_args, const ExactArgs A,
+                                                                     const SupportArgs sa,
+                                                                     const uint8_t *__restrict__ nz, const ColumnSet S) {
+  __shared__ uint32_t wave_sum[kColThreads / 64];
+  c_RecombArgs &R = *(c_RecombArgs *)(uintptr_t)d_args;
+  const uint32_t n = (uint32_t)S.count[0];
+  uint32_t done = 0;
+  for (uint32_t i0 = 0; i0 < n; i0 += kColThreads) {
+    const uint32_t i = i0 + threadIdx.x;
+    bool ok = i < n;
+    const uint64_t P = ok ? S.cols[i] : 0;
+    for (uint32_t f = 0; ok && f < R.n_frags; ++f) {
+      if (f == A.frag) continue;
+      auto &F = R.f[f];
+      ok = nz[sa.off[f] + frag_column(F, (uint32_t)P)] != 0;
+    }
+    const uint32_t incl = block_scan(ok ? 1u : 0u, wave_sum);
+    uint32_t total = 0;
+    __syncthreads();
+    if (threadIdx.x == kColThreads - 1) wave_sum[0] = incl;
+    __syncthreads();
+    total = wave_sum[0];
+    if (ok) {
+      S.terms[done + incl - 1] = P;
+      S.term_col[done + incl - 1] = i;
+    }
+    done += total;
+  }
+  if (threadIdx.x == 0) S.count[1] = done;
+}
+
+// Draws per column, counted in LDS first: most draws fall on a handful of
+// columns (16384 global atomics on one counter took 178 us).
+__global__ __launch_bounds__(kColThreads) void column_count_kernel(const ColumnSet S, const uint64_t *__restrict__ terms,
+                                                                   uint64_t n, uint32_t *__restrict__ counts) {
+  __shared__ uint32_t own[kMaxColumnEntries];
+  for (uint32_t i = threadIdx.x; i < S.zero; i += kColThreads) own[i] = 0;
+  __syncthreads();
+  const uint32_t per = col_per(S.k);
+  for (uint64_t j = (uint64_t)blockIdx.x * kColThreads + threadIdx.x; j < n; j += (uint64_t)gridDim.x * kColThreads) {
+    const uint64_t P = terms[j];
+    const uint32_t w = (uint32_t)(P >> 5), m = S.mask[w], b = 1u << (P & 31);
+    if (!(m & b)) continue;
+    uint32_t c = S.rank[w / per] + __popc(m & (b - 1));
+    for (uint32_t v = w / per * per; v < w; ++v) c += __popc(S.mask[v]);
+    atomicAdd(&own[c], 1u);
+  }
+  __syncthreads();
+  for (uint32_t i = threadIdx.x; i < S.zero; i += kColThreads)
+    if (own[i]) atomicAdd(&counts[i], own[i]);
+}
+
+__global__ void column_weight_kernel(const ColumnSet S, uint64_t n, const double *__restrict__ q,
+                                     const uint32_t *__restrict__ counts, double *__restrict__ scale,
+                                     double *__restrict__ scale2) {
+  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= S.count[0]) return;
+  const double c = counts[i], s = counts[i] ? 1.0 / ((double)n * q[S.cols[i]]) : 0.0;
+  scale[i] = c * s;
+  scale2[i] = sqrt(c) * s;
+}
+
 }  // namespace
+
+hipError_t launch_columns(const ExactArgs &A, const ColumnSet &S, uint32_t W, const uint64_t *rows, hipStream_t s) {
+  if (S.k < 3 || S.k > kMaxColumnCuts || A.r + 2 * A.n_free > 12 || A.n_free > kExactMaxFree)
+    return hipErrorInvalidValue;
+  static_assert(kMaxColumnEntries == 1u << 12, "pairs per workgroup");
+  const uint32_t n_words = 1u << (2 * S.k - 5);
+  const size_t lds = sizeof(uint32_t) * (n_words + n_words / col_per(S.k));
+  const void *kernel = W == 1 ? (const void *)columns_kernel<1>
+                       : W == 2 ? (const void *)columns_kernel<2>
+                       : W == 4 ? (const void *)columns_kernel<4>
+                                : (const void *)columns_kernel<8>;
+  hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  const dim3 grid(1), block(kColThreads);
+  switch (W) {
+    case 1: hipLaunchKernelGGL(columns_kernel<1>, grid, block, lds, s, A, S, rows); break;
+    case 2: hipLaunchKernelGGL(columns_kernel<2>, grid, block, lds, s, A, S, rows); break;
+    case 4: hipLaunchKernelGGL(columns_kernel<4>, grid, block, lds, s, A, S, rows); break;
+    case 8: hipLaunchKernelGGL(columns_kernel<8>, grid, block, lds, s, A, S, rows); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_column_tensor(const ExactArgs &A, const ColumnSet &S, double *T, double *norm, hipStream_t s) {
+  if (A.r + 2 * A.n_free > 12) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(column_tensor_kernel, dim3(S.zero + 1), dim3(256), sizeof(double) << A.r, s, A, S, T, norm);
+  return hipGetLastError();
+}
+
+hipError_t launch_column_support(const RecombArgs *d_args, const ExactArgs &A, const SupportArgs &sa, const uint8_t *nz,
+                                 const ColumnSet &S, hipStream_t s) {
+  hipLaunchKernelGGL(column_support_kernel, dim3(1), dim3(kColThreads), 0, s, d_args, A, sa, nz, S);
+  return hipGetLastError();
+}
+
+hipError_t launch_column_weights(const ColumnSet &S, const uint64_t *terms, uint64_t n, const double *q,
+                                 uint32_t *counts, double *scale, double *scale2, hipStream_t s) {
+  hipError_t e = launch_fill_u32(counts, S.zero, 0u, s);
+  if (e != hipSuccess) return e;
+  if (n) hipLaunchKernelGGL(column_count_kernel, dim3((unsigned)std::min<uint64_t>((n + kColThreads - 1) / kColThreads, 256)),
+                       dim3(kColThreads), 0, s, S, terms, n, counts);
+  hipLaunchKernelGGL(column_weight_kernel, dim3((S.zero + 255) / 256), dim3(256), 0, s, S, n, q, counts, scale, scale2);
+  return hipGetLastError();
+}
 
 hipError_t launch_exact_marginal(const ExactArgs &A, const RecombArgs *d_args, uint32_t W, const uint64_t *rows,
                                  double *out, hipStream_t s) {

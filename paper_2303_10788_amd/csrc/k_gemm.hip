@@ -224,7 +224,8 @@ __device__ inline void fac_fill(const GemmArgs *__restrict__ G, bool left, uint3
       const uint64_t j = kb + kk;
       double v = 0.0;
       if (j < k1) {
-        const uint64_t idx = frag_p(G, f, C->terms ? C->terms[j] : j) * F.rows + (fixed | r);
+        const uint64_t p = C->col_of && f == C->col_frag ? C->col_of[j] : frag_p(G, f, C->terms ? C->terms[j] : j);
+        const uint64_t idx = p * F.rows + (fixed | r);
         v = F.cnt16 ? (double)reinterpret_cast<const uint16_t *>(F.T)[idx] * (1.0 / F.shots) : F.T[idx];
       }
       fac[off + e] = v;
@@ -268,7 +269,7 @@ __device__ __attribute__((always_inline)) inline void gemm_body(const GemmArgs *
   __shared__ TS Al[LO ? KC : 1][MT + 1];  // hi/lo mode: low parts of the split operands
   __shared__ TS Bl[LO ? KC : 1][NT + 1];
   const uint32_t M = G->M, N = G->N;
-  const uint64_t K = G->K;
+  const uint64_t K = G->K_dev ? *G->K_dev : G->K;
   const uint32_t tilesM = (M + MT - 1) / MT;
   const uint32_t tm = tile % tilesM, tn = tile / tilesM;
   const uint64_t k0 = (uint64_t)split * k_per_split;
@@ -484,6 +485,10 @@ __device__ __attribute__((always_inline)) inline void gemm_body(const GemmArgs *
 template <int MODE, bool GEN>
 __global__ __launch_bounds__(GEMM_THREADS, 3) void gemm_kernel(const GemmArgs *__restrict__ G, uint64_t k_per_split,
                                                             double *__restrict__ partial, double *__restrict__ out) {
+  if (G->K_dev) {  // the splits share the terms that there are
+    const uint64_t chunks = (*G->K_dev + KC - 1) / KC;
+    k_per_split = (chunks + gridDim.y - 1) / gridDim.y * KC;
+  }
   gemm_body<MODE, GEN>(G, k_per_split, partial, blockIdx.x, blockIdx.y, out);
 }
 
@@ -785,6 +790,8 @@ __global__ void gemm_reduce_batch_kernel(const GemmJob *__restrict__ jobs, uint3
 // terms), so short contractions take one split and write their outputs
 // directly (no partial sums, no reduction pass).
 uint32_t gemm_splits(const GemmArgs &h) {
+  // a count only the device knows: usually a few chunks, so a few splits
+  if (h.K_dev) return 4;
   const uint64_t tiles = (uint64_t)((h.M + MT - 1) / MT) * ((h.N + NT - 1) / NT);
   const uint64_t kchunks = (h.K + KC - 1) / KC;
   uint64_t s = std::max<uint64_t>(1, 1024 / std::max<uint64_t>(tiles, 1));

@@ -9,6 +9,7 @@
 // MFMA lane layout of v_mfma_f32_16x16x16_bf16 (checked on gfx950): lane l
 // supplies A[row l % 16][k 4 (l / 16) + i] and B[k 4 (l / 16) + i][col l % 16]
 // for i < 4; accumulator register g holds D[row 4 (l / 16) + g][col l % 16].
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 
@@ -507,6 +508,35 @@ __global__ void is_scale_kernel(const uint64_t *__restrict__ terms, const double
   if (j < n) scale[j] = 1.0 / ((double)n * q[terms[j]]);
 }
 
+// the estimate's summed standard error: partial sums of a fixed stride, a
+// fixed tree, then a tree over the blocks
+__global__ __launch_bounds__(256) void stderr_partial_kernel(const double *__restrict__ e, const double *__restrict__ e2,
+                                                             uint64_t bins, uint32_t k, double n,
+                                                             double *__restrict__ part) {
+  __shared__ double red[256];
+  double s = 0.0;
+  for (uint64_t b = (uint64_t)blockIdx.x * 256 + threadIdx.x; b < bins; b += (uint64_t)gridDim.x * 256)
+    s += sqrt(fmax(0.0, ldexp(e2[b], -(int)k) - e[b] * e[b] / n));
+  red[threadIdx.x] = s;
+  __syncthreads();
+  for (uint32_t w = 128; w > 0; w >>= 1) {
+    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
+}
+__global__ __launch_bounds__(kStderrBlocks) void stderr_final_kernel(const double *__restrict__ part, uint32_t n,
+                                                                     double *__restrict__ out) {
+  __shared__ double red[kStderrBlocks];
+  red[threadIdx.x] = threadIdx.x < n ? part[threadIdx.x] : 0.0;
+  __syncthreads();
+  for (uint32_t w = kStderrBlocks / 2; w > 0; w >>= 1) {
+    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) *out = red[0];
+}
+
 inline unsigned blocks(uint64_t n, uint32_t b) { return (unsigned)((n + b - 1) / b); }
 
 }  // namespace
@@ -657,6 +687,14 @@ hipError_t launch_sample_terms(const uint64_t *cdf, uint64_t K, uint64_t n, uint
 
 hipError_t launch_is_scale(const uint64_t *terms, const double *q, uint64_t n, double *scale, hipStream_t s) {
   hipLaunchKernelGGL(is_scale_kernel, dim3(blocks(n, 256)), dim3(256), 0, s, terms, q, n, scale);
+  return hipGetLastError();
+}
+
+hipError_t launch_stderr_l1(const double *e, const double *e2, uint64_t bins, uint32_t k, double n, double *part,
+                            double *out, hipStream_t s) {
+  const unsigned nb = std::min(blocks(bins, 256), kStderrBlocks);
+  hipLaunchKernelGGL(stderr_partial_kernel, dim3(nb), dim3(256), 0, s, e, e2, bins, k, n, part);
+  hipLaunchKernelGGL(stderr_final_kernel, dim3(1), dim3(kStderrBlocks), 0, s, part, nb, out);
   return hipGetLastError();
 }
 

@@ -107,3 +107,75 @@ def test_wide_against_variants(ctx, n, r):
     assert np.abs(plan.zexpect(words) - ref).max() <= 1e-10
     for prec in (cc.CCUT_FP32_MFMA_FP64SUM, cc.CCUT_FP32X3_MFMA_FP64SUM):
         assert np.abs(plan.zexpect(words, precision=prec) - ref).max() <= 1e-5
+
+
+def _blocks(exits, n, depth, seed, n_t=4, tail_near=True):
+    """Blocks of 4 wires with the given exit counts, evenly placed, cut one layer before the end where `tail_near` (the
+    requested exit wires then keep many columns nonzero)."""
+    gap = n // len(exits)
+    blocks = [W.Block(list(range(i * gap, i * gap + 4)), list(range(i * gap + 4 - c, i * gap + 4)))
+              for i, c in enumerate(exits)]
+    ops, cuts = W.block_circuit(n, depth, blocks, t_c=depth - 2 if tail_near else depth // 2, p_cx=0.4, seed=seed, n_t=n_t)
+    exits_ = [q for b in blocks for q in b.exits]
+    inner = [b.wires[0] for b in blocks]
+    return ops, cuts, inner, exits_
+
+
+@pytest.mark.parametrize("exits,n", [((3, 2), 20), ((3, 3), 40), ((3, 3, 3), 70), ((3, 3, 2, 2), 120)])
+def test_columns_fp32_and_learned(ctx, exits, n):
+    """Contractions over the nonzero columns (5 to 10 cuts; one and many words of the mask per thread): the fp32 modes
+    against fp64, dense and sparse; the term model's norms, support and estimate against the dense tensors' values.  fp32
+    bar: the suite's 1e-5; the others as for the dense path (1e-10; norms of exact data exactly)."""
+    import torch
+    ops, cuts, inner, ex = _blocks(exits, n, 14, n)
+    k = len(cuts)
+    print(f"columns k={k} n={n}", flush=True)
+    plan = cc.Plan(ctx, n, ops, cuts)
+    big = max(range(len(exits) + 1), key=lambda f: plan.fragments()[f]["m"])
+    for qubits in (sorted(inner + ex[:6]), sorted(inner + ex[:2]), sorted(inner)):
+        T = plan.fragment_tensor(qubits, big)
+        cols = np.nonzero(np.abs(T).max(axis=1))[0]
+        ref = plan.marginal(qubits)
+        for flag in (0, cc.CCUT_FLAG_SPARSE):
+            for prec in (cc.CCUT_FP32_MFMA_FP64SUM, cc.CCUT_FP32X3_MFMA_FP64SUM):
+                got = plan.marginal(qubits, precision=prec, flags=flag)
+                assert np.abs(got - ref).max() <= 1e-5
+                assert np.array_equal(got, plan.marginal(qubits, precision=prec, flags=flag))
+        L = cc.Learned(plan, qubits)
+        assert np.abs(L.exhaustive() - ref).max() <= 1e-10
+        sup, count = L.support()
+        sup = sup.cpu().numpy()
+        assert set(sup) <= set(cols) and list(sup) == sorted(sup)
+        assert np.abs(cc.Learned(plan, qubits, precision=cc.CCUT_FP32_MFMA_FP64SUM).exhaustive() - ref).max() <= 1e-5
+        # a proposal of weights 1..4 over all terms, more on the support: the estimate against the drawn terms' sum
+        q = torch.ones(L.K, dtype=torch.float64) / (2 * L.K)
+        q[torch.from_numpy(sup.astype(np.int64))] += 0.5 / max(count, 1)
+        q = q.cuda()
+        terms = torch.empty(700, dtype=torch.int64, device="cuda")
+        est = L.estimate(q, 700, seed=3, terms_out=terms)
+        w = {}
+        frags = plan.fragments()
+        tens = {f: plan.fragment_tensor(qubits, f) for f in range(len(frags))}
+        exp = np.zeros(1 << len(qubits))
+        req = {f: cc.ccut_request_info(plan.handle, qubits, f)[1] for f in tens}
+        drawn, times = np.unique(terms.cpu().numpy(), return_counts=True)
+        qh = q.cpu().numpy()
+        users = {}
+        for f, fr in enumerate(frags):
+            loc = {wire: i for i, (wire, seg) in enumerate(fr["segments"])}
+            last = {}
+            for wire, seg in fr["segments"]:
+                last[wire] = max(seg, last.get(wire, -1))
+            ends = [i for i, (wire, seg) in enumerate(fr["segments"])
+                    if seg == sum(1 for c in cuts if c[0] == wire) and wire in qubits]
+            users[f] = [qubits.index(fr["segments"][i][0]) for i in ends]
+            assert len(users[f]) == req[f]
+        idx = np.arange(1 << len(qubits))
+        for P, c in zip(drawn, times):
+            v = np.full(1 << len(qubits), 0.5 ** k)
+            for f, fr in enumerate(frags):
+                p = sum(((int(P) >> (2 * a[0])) & 3) << (2 * j) for j, a in enumerate(fr["axes"]))
+                b = sum(((idx >> u) & 1) << i for i, u in enumerate(users[f]))
+                v = v * tens[f][p][b]
+            exp += c * v / (700 * qh[P])
+        assert np.abs(est - exp).max() <= 1e-10 * max(1.0, np.abs(exp).max())
