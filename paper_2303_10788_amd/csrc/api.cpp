@@ -3225,7 +3225,7 @@ struct ccut_mlp {
   uint64_t work_rows = 0;
   float *p = nullptr, *g = nullptr, *m = nullptr, *v = nullptr;
   uint16_t *pb = nullptr;  // bf16 copy of the parameters used by the products
-  uint16_t *w1 = nullptr, *w2 = nullptr, *w3 = nullptr, *w2t = nullptr, *w3t = nullptr;  // weights in lane order (training)
+  uint16_t *w1 = nullptr, *w2 = nullptr, *w3 = nullptr, *w2t = nullptr, *w3t = nullptr;  // weights in lane order
   uint64_t t = 0;          // Adam step count
   uint16_t *xb = nullptr, *h1 = nullptr, *h2 = nullptr, *h3 = nullptr, *d1 = nullptr, *d2 = nullptr, *d3 = nullptr;
   float *dy = nullptr, *sq = nullptr, *part = nullptr;
@@ -3743,13 +3743,13 @@ ccut_status learned_logits_enqueue(ccut_learned *L, ccut_mlp *M, float *logits) 
   if (M->ctx != c || M->F != L->width) return fail(c, CCUT_E_INVALID, "network input width differs from the features");
   if (M->F == 64 && M->H == 256) {  // the whole pass in one launch, activations on chip
     MlpFused net{};
-    net.w1 = M->pb + M->off_w1;
-    net.w2 = M->pb + M->off_w2;
-    net.w3 = M->pb + M->off_w3;
+    net.w[0] = M->w1;
+    net.w[1] = M->w2;
+    net.w[2] = M->w3;
     net.w4 = M->pb + M->off_w4;
-    net.b1 = M->p + M->off_b1;
-    net.b2 = M->p + M->off_b2;
-    net.b3 = M->p + M->off_b3;
+    net.b[0] = M->p + M->off_b1;
+    net.b[1] = M->p + M->off_b2;
+    net.b[2] = M->p + M->off_b3;
     net.b4 = M->p + M->off_b4;
     net.F = M->F;
     net.H = M->H;

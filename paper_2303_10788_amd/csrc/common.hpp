@@ -613,7 +613,7 @@ hipError_t launch_mlp_gemm(const MlpGemm &g, hipStream_t s);
 hipError_t launch_head_forward(const uint16_t *H, uint32_t width, uint64_t rows, const uint16_t *w, const float *b,
                                float scale, float *y, hipStream_t s);
 
-// Training (k_train.hip).  Weights in lane order: see lane_order there.
+// Training (k_train.hip).  Weights in lane order: see lane_order (bf16.hpp).
 constexpr uint32_t kColChunkRows = 256;  // rows of one column-sum chunk
 inline uint64_t train_chunks(uint64_t rows) { return (rows + kColChunkRows - 1) / kColChunkRows; }
 // One step's rows: the batch gathered (row i = data row philox(i, step) mod
@@ -681,8 +681,8 @@ hipError_t launch_features(const LearnedDev *L, const uint64_t *terms, uint64_t 
 // y = scale (b4 + h3 . w4) summed as the separate head kernel does; the
 // activations never leave the workgroup.  F = 64 inputs, H = 256.
 struct MlpFused {
-  const uint16_t *w1, *w2, *w3, *w4;  // bf16 [H][F], [H][H], [H][H], [H]
-  const float *b1, *b2, *b3, *b4;
+  const uint16_t *w[3], *w4;  // bf16 [H][F], [H][H], [H][H] in lane order (bf16.hpp), [H]
+  const float *b[3], *b4;
   uint32_t F, H;
 };
 hipError_t launch_mlp_logits_fused(const LearnedDev *L, const MlpFused &net, uint64_t first, uint64_t n, float scale,

@@ -5,10 +5,6 @@
 // q = (1 - eps) softmax + eps / K, its integer CDF, Philox inverse-CDF term
 // sampling, and the per-term inputs (features, labels, support) computed
 // from the fragment tensors.
-//
-// MFMA lane layout of v_mfma_f32_16x16x16_bf16 (checked on gfx950): lane l
-// supplies A[row l % 16][k 4 (l / 16) + i] and B[k 4 (l / 16) + i][col l % 16]
-// for i < 4; accumulator register g holds D[row 4 (l / 16) + g][col l % 16].
 #include <algorithm>
 #include <cmath>
 #include <mutex>
@@ -46,18 +42,15 @@ __global__ __launch_bounds__(MG_THREADS) void mlp_gemm_kernel(const MlpGemm g) {
     *(uint4 *)&As[rr][kc] = v;
     *(uint4 *)&Bs[rr][kc] = *(const uint4 *)(g.B + (uint64_t)(n0 + rr) * g.K + k0 + kc);
     __syncthreads();
+    u32x4 a[2], b[2];
 #pragma unroll
-    for (int ks = 0; ks < MG_K; ks += 16) {
-      short4v a[2], b[2];
+    for (int i = 0; i < 2; ++i) a[i] = *(const u32x4 *)&As[wm + 16 * i + (lane & 15)][8 * (lane >> 4)];
 #pragma unroll
-      for (int i = 0; i < 2; ++i) a[i] = *(const short4v *)&As[wm + 16 * i + (lane & 15)][ks + 4 * (lane >> 4)];
+    for (int j = 0; j < 2; ++j) b[j] = *(const u32x4 *)&Bs[wn + 16 * j + (lane & 15)][8 * (lane >> 4)];
 #pragma unroll
-      for (int j = 0; j < 2; ++j) b[j] = *(const short4v *)&Bs[wn + 16 * j + (lane & 15)][ks + 4 * (lane >> 4)];
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[i], b[j], acc[i][j], 0, 0, 0);
-    }
+      for (int j = 0; j < 2; ++j) acc[i][j] = mfma_bf16(a[i], b[j], acc[i][j]);
     __syncthreads();
   }
 #pragma unroll
@@ -223,103 +216,124 @@ __global__ void features_kernel(const LearnedDev *__restrict__ L, const uint64_t
   X[i] = f2bf(v);
 }
 
-// Fused forward pass: a workgroup of 8 waves takes 128 term rows.  The
-// rows' features are built in LDS (as features_kernel does); each layer's
-// weights stream through LDS in chunks of 64 input columns; wave w
-// accumulates rows 64 (w & 1) .. + 63 by columns 64 (w >> 1) .. + 63 with
-// v_mfma_f32_16x16x16_bf16 in increasing k, adds the bias, applies the
-// ReLU and rounds to bf16 into the activation tile (in place, after a
-// barrier); the head then sums each row as head_forward_kernel does.
-constexpr uint32_t FF_TM = 128, FF_H = 256, FF_F = 64, FF_KC = 64, FF_THREADS = 512;
-constexpr uint32_t FF_AS = FF_H + 8, FF_WS = FF_KC + 8;  // padded row strides (bf16)
+// Fused forward pass: a workgroup of four waves takes 128 term rows.  The
+// rows' features are built in LDS (as features_kernel does); wave w then forms
+// columns 64 w .. + 63 of each layer for all rows with increasing k, adds the
+// bias, applies the ReLU and rounds to bf16 into the activation tile (in place,
+// after a barrier); the head sums each row as head_forward_kernel does.
+//
+// The products are transposed (weights as the left operand), so that a lane
+// holds four consecutive columns of a row and stores them at once.  No other
+// wave of the workgroup reads a wave's weights: they come from L2 in lane order
+// straight into registers, 4 KB a wave and 32 inner indices, loaded a step
+// ahead, and the loop over k has no barrier.  Through LDS they would double its
+// traffic, which at 64 columns by 128 rows a wave is 64 bytes a clock for the
+// activations alone, half of what LDS delivers.  68 KB of LDS and at most 256
+// registers let two workgroups share a CU: one's epilogue, features and head
+// run beside the other's products.  2^20 rows (312 GFLOP), F 64, H 256: 358 us,
+// 870 TFLOP/s (833 us with 16-deep products and the weights through LDS in
+// chunks of 64 columns, a barrier on each side of a chunk).
+constexpr uint32_t FF_TM = 128, FF_H = 256, FF_F = 64, FF_THREADS = 256;
+constexpr uint32_t FF_AS = FF_H + 8;  // padded row stride (bf16)
+constexpr uint32_t FF_LAYERS = 3;
 
-__device__ __attribute__((always_inline)) inline void ff_layer(uint16_t *act, uint16_t *ws, const uint16_t *__restrict__ W, const float *__restrict__ b,
-                                uint32_t K, uint32_t tid) {
-  const uint32_t lane = tid & 63, wave = tid >> 6;
-  const uint32_t wm = (wave & 1) * 64, wn = (wave >> 1) * 64;
-  float4v acc[4][4];
+struct FFWeights {
+  u32x4 w[4];  // a wave's 64 columns, 32 inner indices
+};
+
+__device__ inline void ff_load(FFWeights &B, const uint16_t *__restrict__ W, uint32_t nc, uint32_t c, uint32_t tid) {
+  const u32x4 *src = reinterpret_cast<const u32x4 *>(W) + ((size_t)(4 * (tid >> 6)) * nc + c) * 64 + (tid & 63);
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = float4v{0.f, 0.f, 0.f, 0.f};
-  for (uint32_t kc = 0; kc < K; kc += FF_KC) {
-    // weight chunk: ws[n][kk] = W[n][kc + kk], 256 rows of 128 B, four 16 B loads per thread
-    u32x4 v0, v1, v2, v3;
-    {
-      const uint32_t i0 = tid, i1 = tid + FF_THREADS, i2 = tid + 2 * FF_THREADS, i3 = tid + 3 * FF_THREADS;
-      v0 = *(const u32x4 *)(W + (uint64_t)(i0 >> 3) * K + kc + (i0 & 7) * 8);
-      v1 = *(const u32x4 *)(W + (uint64_t)(i1 >> 3) * K + kc + (i1 & 7) * 8);
-      v2 = *(const u32x4 *)(W + (uint64_t)(i2 >> 3) * K + kc + (i2 & 7) * 8);
-      v3 = *(const u32x4 *)(W + (uint64_t)(i3 >> 3) * K + kc + (i3 & 7) * 8);
-      __syncthreads();  // the previous chunk is consumed
-      *(u32x4 *)&ws[(i0 >> 3) * FF_WS + (i0 & 7) * 8] = v0;
-      *(u32x4 *)&ws[(i1 >> 3) * FF_WS + (i1 & 7) * 8] = v1;
-      *(u32x4 *)&ws[(i2 >> 3) * FF_WS + (i2 & 7) * 8] = v2;
-      *(u32x4 *)&ws[(i3 >> 3) * FF_WS + (i3 & 7) * 8] = v3;
-    }
-    __syncthreads();
-#pragma unroll
-    for (uint32_t ks = 0; ks < FF_KC; ks += 16) {
-      short4v a[4], bb[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        a[i] = *(const short4v *)&act[(wm + 16 * i + (lane & 15)) * FF_AS + kc + ks + 4 * (lane >> 4)];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) bb[j] = *(const short4v *)&ws[(wn + 16 * j + (lane & 15)) * FF_WS + ks + 4 * (lane >> 4)];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[i], bb[j], acc[i][j], 0, 0, 0);
-    }
-  }
-  __syncthreads();  // every wave is done reading this layer's input
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const uint32_t m = wm + 16 * i + 4 * (lane >> 4) + r, n = wn + 16 * j + (lane & 15);
-        act[m * FF_AS + n] = f2bf(fmaxf(acc[i][j][r] + b[n], 0.f));
-      }
-  __syncthreads();
+  for (uint32_t i = 0; i < 4; ++i) B.w[i] = src[(size_t)i * nc * 64];
 }
 
-__global__ __launch_bounds__(FF_THREADS) void mlp_fused_forward_kernel(const LearnedDev *__restrict__ L,
-                                                                       const MlpFused net, uint64_t first, uint64_t n,
-                                                                       float scale, float *__restrict__ y) {
-  extern __shared__ uint16_t ff_smem[];
-  uint16_t *act = ff_smem;                     // [FF_TM][FF_AS]
-  uint16_t *ws = ff_smem + FF_TM * FF_AS;      // [FF_H][FF_WS]
-  const uint32_t tid = threadIdx.x;
+// acc[i][j] += the wave's columns 16 i .. + 15 by rows 16 j .. + 15
+__device__ __attribute__((always_inline)) inline void ff_products(const FFWeights &B, const uint16_t *act,
+                                                                  float4v (&acc)[4][8]) {
+#pragma unroll
+  for (uint32_t j = 0; j < 8; ++j) {
+    const u32x4 x = *(const u32x4 *)(act + 16 * j * FF_AS);
+#pragma unroll
+    for (uint32_t i = 0; i < 4; ++i) acc[i][j] = mfma_bf16(B.w[i], x, acc[i][j]);
+  }
+}
+
+__global__ __launch_bounds__(FF_THREADS, 2) void mlp_fused_forward_kernel(const LearnedDev *__restrict__ L,
+                                                                          const MlpFused net, uint64_t first,
+                                                                          uint64_t n, float scale,
+                                                                          float *__restrict__ y) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t act[];  // [FF_TM][FF_AS]
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const uint64_t r0 = (uint64_t)blockIdx.x * FF_TM;
-  // features of rows r0 .. r0 + 127 (zero rows past n)
-  for (uint32_t i = tid; i < FF_TM * FF_F; i += FF_THREADS) {
-    const uint32_t t = i / FF_F, col = i % FF_F;
-    float v = 0.f;
-    if (r0 + t < n) {
-      const uint64_t P = first + r0 + t;
-      const uint32_t c = col / 6, rr = col % 6;
-      if (c < L->k) {
-        const uint32_t p = (uint32_t)((P >> (2 * c)) & 3u);
-        v = rr < 4 ? (rr == p ? 1.f : 0.f) : (float)L->phi[(c * 2 + (rr - 4)) * 4 + p];
-      }
+  FFWeights cur;
+  ff_load(cur, net.w[0], FF_F / 32, 0, tid);
+  // features of rows r0 .. r0 + 127 (zero rows past n), a column per lane
+  {
+    const uint32_t c = lane / 6, rr = lane % 6;
+    uint64_t v = 0;  // the feature's bf16 by P_c
+    if (c < L->k) {
+#pragma unroll
+      for (uint32_t p = 0; p < 4; ++p)
+        v |= (uint64_t)f2bf(rr < 4 ? (rr == p ? 1.f : 0.f) : (float)L->phi[(c * 2 + (rr - 4)) * 4 + p]) << (16 * p);
     }
-    act[t * FF_AS + col] = f2bf(v);
+    for (uint32_t t = wave; t < FF_TM; t += FF_THREADS / 64) {
+      const uint32_t p = (uint32_t)((first + r0 + t) >> (2 * c)) & 3u;
+      act[t * FF_AS + lane] = r0 + t < n ? (uint16_t)(v >> (16 * p)) : (uint16_t)0;
+    }
   }
   __syncthreads();
-  ff_layer(act, ws, net.w1, net.b1, FF_F, tid);
-  ff_layer(act, ws, net.w2, net.b2, FF_H, tid);
-  ff_layer(act, ws, net.w3, net.b3, FF_H, tid);
+  const uint16_t *in = act + (lane & 15) * FF_AS + 8 * (lane >> 4);
+#pragma unroll 1
+  for (uint32_t layer = 0; layer < FF_LAYERS; ++layer) {
+    const uint16_t *W = net.w[layer];
+    const uint32_t nc = layer ? FF_H / 32 : FF_F / 32;
+    const uint32_t after = layer + 1 < FF_LAYERS ? layer + 1 : layer;  // (the last layer's own, unused)
+    float4v acc[4][8];
+#pragma unroll
+    for (uint32_t i = 0; i < 4; ++i)
+#pragma unroll
+      for (uint32_t j = 0; j < 8; ++j) acc[i][j] = float4v{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (uint32_t c = 0; c < nc; c += 2) {
+      FFWeights odd;
+      ff_load(odd, W, nc, c + 1, tid);
+      ff_products(cur, in + 32 * c, acc);
+      const bool more = c + 2 < nc;
+      ff_load(cur, more ? W : net.w[after], more ? nc : FF_H / 32, more ? c + 2 : 0, tid);
+      ff_products(odd, in + 32 * c + 32, acc);
+    }
+    float4v b[4];
+#pragma unroll
+    for (uint32_t i = 0; i < 4; ++i)
+      b[i] = *(const float4v *)(net.b[layer] + 64 * wave + 16 * i + 4 * (lane >> 4));
+    __syncthreads();  // every wave is done reading this layer's input
+#pragma unroll
+    for (uint32_t j = 0; j < 8; ++j)
+#pragma unroll
+      for (uint32_t i = 0; i < 4; ++i) {
+        float r[4];
+#pragma unroll
+        for (uint32_t e = 0; e < 4; ++e) r[e] = fmaxf(acc[i][j][e] + b[i][e], 0.f);
+        *(uint64_t *)(act + (16 * j + (lane & 15)) * FF_AS + 64 * wave + 16 * i + 4 * (lane >> 4)) =
+            ((uint64_t)f2bf2(r[2], r[3]) << 32) | f2bf2(r[0], r[1]);
+      }
+    __syncthreads();
+  }
   // head: 32 lanes per row, eight consecutive elements per lane, butterfly
   const uint32_t l = tid & 31;
+  float w4[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) w4[e] = bf2f(net.w4[l * 8 + e]);
+  const float b4 = net.b4[0];
+#pragma unroll 4
   for (uint32_t t = tid >> 5; t < FF_TM; t += FF_THREADS / 32) {
+    const u32x4 h = *(const u32x4 *)(act + t * FF_AS + l * 8);
     float sacc = 0.f;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) sacc += bf2f(act[t * FF_AS + l * 8 + e]) * bf2f(net.w4[l * 8 + e]);
+    for (int e = 0; e < 8; ++e) sacc += bf2f((uint16_t)(h[e >> 1] >> (16 * (e & 1)))) * w4[e];
 #pragma unroll
     for (int o = 16; o > 0; o >>= 1) sacc += __shfl_xor(sacc, o, 32);
-    if (l == 0 && r0 + t < n) y[r0 + t] = scale * (sacc + net.b4[0]);
+    if (l == 0 && r0 + t < n) y[r0 + t] = scale * (sacc + b4);
   }
 }
 
@@ -554,7 +568,7 @@ hipError_t launch_mlp_logits_fused(const LearnedDev *L, const MlpFused &net, uin
                                    float *y, hipStream_t s) {
   if (net.F != FF_F || net.H != FF_H) return hipErrorInvalidValue;
   if (n == 0) return hipSuccess;
-  const size_t lds = (size_t)(FF_TM * FF_AS + FF_H * FF_WS) * sizeof(uint16_t);
+  const size_t lds = (size_t)FF_TM * FF_AS * sizeof(uint16_t);
   hipError_t e = hipFuncSetAttribute((const void *)mlp_fused_forward_kernel,
                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;

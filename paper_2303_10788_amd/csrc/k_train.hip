@@ -20,31 +20,19 @@
 // loaded before the epilogue and the barrier of the current one, and the
 // weights are kept a second time in the order the lanes read them (16 bytes a
 // lane, 1 KB a wave and load: rows of a row-major weight would be fetched in
-// 32-byte pieces).  The ordered sums over 1024 rows (64 dependent products of a
+// 32-byte pieces).  The ordered sums over 1024 rows (32 dependent products of a
 // weight gradient's element, 256 dependent additions of a column-sum chunk) are
 // staged through LDS ahead of their use, and no sum is split further: every
 // result has the same bits as one launch per operation gave.  Measured at 1024
-// rows, F 64, H 256: 36 us a step, against 411 us for 27 launches per step with
+// rows, F 64, H 256: 35 us a step, against 411 us for 27 launches per step with
 // a memory access per row and column in the column sums (58 us each) and
 // 64 x 64 tiles for the weight gradients (16 workgroups, 35 us each).
-//
-// MFMA lane layout of v_mfma_f32_16x16x16_bf16: lane l supplies A[row l % 16]
-// [k 4 (l / 16) + i] and B[k 4 (l / 16) + i][col l % 16] for i < 4;
-// accumulator register g holds D[row 4 (l / 16) + g][col l % 16].
 #include "bf16.hpp"
 #include "common.hpp"
 
 namespace ccut {
 
 namespace {
-
-// Position of element (n, k) of an N x K weight in lane order: per 16 columns
-// n and 32 inner indices k one 1 KB block, lane l's 16 bytes holding its four
-// k of each of the block's two 16-wide chunks.
-__host__ __device__ inline uint32_t lane_order(uint32_t n, uint32_t k, uint32_t K) {
-  const uint32_t lane = ((k >> 2) & 3u) * 16 + (n & 15u);
-  return (((n >> 4) * (K >> 5) + (k >> 5)) * 64 + lane) * 8 + ((k >> 4) & 1u) * 4 + (k & 3u);
-}
 
 constexpr uint32_t kRows = 16, kRowThreads = 512, kRowWaves = kRowThreads / 64;
 constexpr uint32_t kPad = 8;       // row padding of the LDS tiles (bf16)
@@ -70,26 +58,20 @@ __device__ inline void load_weights(WaveWeights &B, const uint16_t *__restrict__
 }
 
 // acc[t] = rows (16 x K in LDS, row stride lda) times the wave's columns, the
-// inner index ascending in steps of 16.
+// inner index ascending in steps of 32.
 __device__ inline void row_products(const uint16_t *A, uint32_t lda, const WaveWeights &B, uint32_t N, uint32_t K,
                                     uint32_t wave, uint32_t lane, float4v (&acc)[kWaveTiles]) {
   const uint32_t nc = K >> 5;
 #pragma unroll
   for (uint32_t t = 0; t < kWaveTiles; ++t) acc[t] = float4v{0.f, 0.f, 0.f, 0.f};
-  const uint16_t *a = A + (lane & 15) * lda + 4 * (lane >> 4);
+  const uint16_t *a = A + (lane & 15) * lda + 8 * (lane >> 4);
 #pragma unroll
   for (uint32_t c = 0; c < kMaxChunks; ++c) {
     if (c >= nc) break;
-    const short4v a0 = *(const short4v *)(a + 32 * c), a1 = *(const short4v *)(a + 32 * c + 16);
+    const u32x4 av = *(const u32x4 *)(a + 32 * c);
 #pragma unroll
-    for (uint32_t t = 0; t < kWaveTiles; ++t) {
-      if ((wave + kRowWaves * t) * 16 >= N) continue;
-      const u32x4 w = B.w[t][c];
-      const short4v b0 = __builtin_bit_cast(short4v, ((uint64_t)w.y << 32) | w.x);
-      const short4v b1 = __builtin_bit_cast(short4v, ((uint64_t)w.w << 32) | w.z);
-      acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a0, b0, acc[t], 0, 0, 0);
-      acc[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a1, b1, acc[t], 0, 0, 0);
-    }
+    for (uint32_t t = 0; t < kWaveTiles; ++t)
+      if ((wave + kRowWaves * t) * 16 < N) acc[t] = mfma_bf16(av, B.w[t][c], acc[t]);
   }
 }
 
@@ -232,8 +214,8 @@ __device__ inline void grad_store(const GradRegs &R, uint16_t *tile, uint32_t t)
 }
 
 // dW[m][n] = sum over rows of D[row][m] X[row][n], one 32 x 32 tile per
-// workgroup, one 16 x 16 block per wave, rows ascending in steps of 16.  Bound
-// by the chain of `rows` / 16 dependent products; the next 128 rows are loaded
+// workgroup, one 16 x 16 block per wave, rows ascending in steps of 32.  Bound
+// by the chain of `rows` / 32 dependent products; the next 128 rows are loaded
 // while the current ones are summed.
 __device__ void grad_tile(const TrainGrads &g, const uint16_t *__restrict__ D, const uint16_t *__restrict__ X,
                           uint32_t in, uint32_t m0, uint32_t n0, float *__restrict__ out, uint16_t *smem) {
@@ -251,18 +233,16 @@ __device__ void grad_tile(const TrainGrads &g, const uint16_t *__restrict__ D, c
     grad_store(R, half ? Bs : As, t);
     __syncthreads();  // (two buffers: the other one's readers passed this barrier's predecessor)
     if (k0 + kGradK < rows) grad_load(R, src, width, k0 + kGradK, rows, c0, t);
-    const uint16_t *a = As + ((wave & 1) * 16 + (lane & 15)) * kGradLd + 4 * (lane >> 4);
-    const uint16_t *b = Bs + ((wave >> 1) * 16 + (lane & 15)) * kGradLd + 4 * (lane >> 4);
+    const uint16_t *a = As + ((wave & 1) * 16 + (lane & 15)) * kGradLd + 8 * (lane >> 4);
+    const uint16_t *b = Bs + ((wave >> 1) * 16 + (lane & 15)) * kGradLd + 8 * (lane >> 4);
     if (rows - k0 >= kGradK) {
 #pragma unroll
-      for (uint32_t c = 0; c < kGradK / 16; ++c)
-        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(*(const short4v *)(a + 16 * c), *(const short4v *)(b + 16 * c),
-                                                        acc, 0, 0, 0);
+      for (uint32_t c = 0; c < kGradK / 32; ++c)
+        acc = mfma_bf16(*(const u32x4 *)(a + 32 * c), *(const u32x4 *)(b + 32 * c), acc);
     } else {  // the last 64 rows
 #pragma unroll
-      for (uint32_t c = 0; c < 4; ++c)
-        acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(*(const short4v *)(a + 16 * c), *(const short4v *)(b + 16 * c),
-                                                        acc, 0, 0, 0);
+      for (uint32_t c = 0; c < 2; ++c)
+        acc = mfma_bf16(*(const u32x4 *)(a + 32 * c), *(const u32x4 *)(b + 32 * c), acc);
     }
   }
 #pragma unroll
