@@ -3228,7 +3228,7 @@ struct ccut_mlp {
   uint16_t *w1 = nullptr, *w2 = nullptr, *w3 = nullptr, *w2t = nullptr, *w3t = nullptr;  // weights in lane order
   uint64_t t = 0;          // Adam step count
   uint16_t *xb = nullptr, *h1 = nullptr, *h2 = nullptr, *h3 = nullptr, *d1 = nullptr, *d2 = nullptr, *d3 = nullptr;
-  float *dy = nullptr, *sq = nullptr, *part = nullptr;
+  float *dy = nullptr, *sq = nullptr;
   ~ccut_mlp() {
     if (ctx && ctx->device >= 0) {
       (void)hipSetDevice(ctx->device);
@@ -3304,7 +3304,7 @@ ccut_status sync_call(ccut_ctx *c) {
 // The network's parameters and their copies, as the training kernels take them.
 TrainParams mlp_params(const ccut_mlp *M) {
   return {M->n_params, M->F, M->H, M->off_b1, M->off_w2, M->off_b2, M->off_w3, M->off_b3, M->off_w4, M->off_b4,
-          M->p, M->g, M->m, M->v, M->part, M->pb, M->w1, M->w2, M->w3, M->w2t, M->w3t};
+          M->p, M->g, M->m, M->v, M->pb, M->w1, M->w2, M->w3, M->w2t, M->w3t};
 }
 
 ccut_status mlp_ensure_work(ccut_mlp *M, uint64_t rows) {
@@ -3324,8 +3324,7 @@ ccut_status mlp_ensure_work(ccut_mlp *M, uint64_t rows) {
   M->d3 = b16(rows * H);
   M->dy = f32(rows);
   M->sq = f32(rows);
-  M->part = f32(4 * train_chunks(rows) * H);
-  if (!M->xb || !M->h1 || !M->h2 || !M->h3 || !M->d1 || !M->d2 || !M->d3 || !M->dy || !M->sq || !M->part) {
+  if (!M->xb || !M->h1 || !M->h2 || !M->h3 || !M->d1 || !M->d2 || !M->d3 || !M->dy || !M->sq) {
     M->work.release();
     M->work_rows = 0;
     return fail(c, CCUT_E_OOM, "device allocation failed");
@@ -3347,60 +3346,48 @@ ccut_status mlp_forward_rows(ccut_mlp *M, const uint16_t *x, uint64_t rows, floa
 }
 
 // Forward and backward of one batch of `rows` rows (a multiple of 64, at
-// most work_rows): the weight gradients and the head bias's into M->g, the
-// column sums of the others into M->part; loss_sum (device) receives
-// sum (y - t)^2.  The rows are data rows drawn for `step` (gather), or rows
-// 0 .. rows - 1; x bf16, or xf fp32 (rounded).
-ccut_status mlp_batch_grads(ccut_mlp *M, const uint16_t *x, const float *xf, const float *t, uint64_t n, uint64_t rows,
-                            bool gather, uint32_t step, uint64_t seed, float *loss_sum) {
+// most work_rows), and one Adam step with it (update) or the gradients into
+// M->g; loss_sum (device) receives sum (y - t)^2.  The rows are data rows drawn
+// for `step` (gather), or rows 0 .. rows - 1; x bf16, or xf fp32 (rounded).
+ccut_status mlp_batch(ccut_mlp *M, const uint16_t *x, const float *xf, const float *t, uint64_t n, uint64_t rows,
+                      bool gather, uint32_t step, uint64_t seed, bool update, float lr, float *loss_sum) {
   ccut_ctx *c = M->ctx;
   TrainRows r{};
   r.x = x;
   r.xf = xf;
   r.t = t;
   r.n = n;
+  r.inv_n = n ? ~0ull / n : 0;
   r.rows = rows;
   r.F = M->F;
   r.H = M->H;
   r.step = step;
   r.gather = gather;
   r.seed = seed;
-  r.w1 = M->w1;
-  r.w2 = M->w2;
-  r.w3 = M->w3;
-  r.w2t = M->w2t;
-  r.w3t = M->w3t;
+  const uint16_t *w[5] = {M->w1, M->w2, M->w3, M->w3t, M->w2t};
+  const float *b[3] = {M->p + M->off_b1, M->p + M->off_b2, M->p + M->off_b3};
+  uint16_t *out[5] = {M->h1, M->h2, M->h3, M->d2, M->d1};
+  std::copy(w, w + 5, r.w);
+  std::copy(b, b + 3, r.b);
+  std::copy(out, out + 5, r.out);
   r.w4 = M->pb + M->off_w4;
-  r.b1 = M->p + M->off_b1;
-  r.b2 = M->p + M->off_b2;
-  r.b3 = M->p + M->off_b3;
   r.b4 = M->p + M->off_b4;
   r.inv_b2 = 2.0f / (float)rows;
   r.xb = M->xb;
-  r.h1 = M->h1;
-  r.h2 = M->h2;
-  r.h3 = M->h3;
-  r.d1 = M->d1;
-  r.d2 = M->d2;
   r.d3 = M->d3;
   r.dy = M->dy;
   r.sq = M->sq;
   KTimer tm(c, CCUT_K_MLP);
   HIP_TRY(c, launch_train_rows(r, c->cur));
-  TrainGrads g{M->F, M->H, rows, M->xb, M->h1, M->h2, M->h3, M->d1, M->d2, M->d3, M->dy, M->sq,
-               M->g + M->off_w1, M->g + M->off_w2, M->g + M->off_w3, M->g + M->off_b4, loss_sum, M->part};
-  HIP_TRY(c, launch_train_grads(g, c->cur));
-  return CCUT_OK;
-}
-
-// One Adam step from the gradients of mlp_batch_grads over `rows` rows.
-ccut_status mlp_update(ccut_mlp *M, uint64_t rows, float lr) {
-  ccut_ctx *c = M->ctx;
-  M->t += 1;
-  const float c1 = (float)(1.0 - std::pow(0.9, (double)M->t));
-  const float c2 = (float)(1.0 - std::pow(0.999, (double)M->t));
-  KTimer tm(c, CCUT_K_MLP);
-  HIP_TRY(c, launch_train_update(mlp_params(M), rows, lr, 0.9f, 0.999f, c1, c2, 1e-8f, c->cur));
+  TrainGrads g{rows, M->xb, M->h1, M->h2, M->h3, M->d1, M->d2, M->d3, M->dy, M->sq, loss_sum};
+  TrainAdam A{0, lr, 0.9f, 0.999f, 0.f, 0.f, 1e-8f};
+  if (update) {
+    M->t += 1;
+    A.update = 1;
+    A.c1 = (float)(1.0 - std::pow(0.9, (double)M->t));
+    A.c2 = (float)(1.0 - std::pow(0.999, (double)M->t));
+  }
+  HIP_TRY(c, launch_train_grads(g, mlp_params(M), A, c->cur));
   return CCUT_OK;
 }
 
@@ -3527,8 +3514,7 @@ ccut_status ccut_mlp_gradients(ccut_mlp *M, const uint16_t *x, const float *t, u
   if ((st = mlp_ensure_work(M, n)) != CCUT_OK) return st;
   float *lsum = aget<float>(c, 1);
   if (!lsum) return fail(c, CCUT_E_OOM, "device allocation failed");
-  if ((st = mlp_batch_grads(M, x, nullptr, t, n, n, false, 0, 0, lsum)) != CCUT_OK) return st;
-  HIP_TRY(c, launch_train_gradients(mlp_params(M), n, c->cur));
+  if ((st = mlp_batch(M, x, nullptr, t, n, n, false, 0, 0, false, 0.f, lsum)) != CCUT_OK) return st;
   float hl = 0.f;
   HIP_TRY(c, hipMemcpyAsync(grads, M->g, M->n_params * 4, hipMemcpyDeviceToHost, c->stream));
   HIP_TRY(c, hipMemcpyAsync(&hl, lsum, 4, hipMemcpyDeviceToHost, c->stream));
@@ -3550,8 +3536,7 @@ ccut_status ccut_mlp_train(ccut_mlp *M, const uint16_t *x, const float *t, uint6
   float *lsum = aget<float>(c, std::max<uint32_t>(steps, 1));
   if (!lsum) return fail(c, CCUT_E_OOM, "device allocation failed");
   for (uint32_t s = 0; s < steps; ++s) {
-    if ((st = mlp_batch_grads(M, x, nullptr, t, n, batch, batch != n, s, seed, lsum + s)) != CCUT_OK) return st;
-    if ((st = mlp_update(M, batch, lr)) != CCUT_OK) return st;
+    if ((st = mlp_batch(M, x, nullptr, t, n, batch, batch != n, s, seed, true, lr, lsum + s)) != CCUT_OK) return st;
   }
   if (losses && steps) {
     HIP_TRY(c, hipMemcpyAsync(losses, lsum, steps * 4, hipMemcpyDeviceToHost, c->stream));
@@ -3980,8 +3965,7 @@ ccut_status ccut_mlp_train_step(ccut_mlp *M, const float *x, const float *t, uin
   float *lsum = aget<float>(c, 1);
   if (!lsum) return fail(c, CCUT_E_OOM, "device allocation failed");
   // the batch is every row, in order: features rounded to bf16, targets as given
-  if ((st = mlp_batch_grads(M, nullptr, x, t, n, n, false, 0, 0, lsum)) != CCUT_OK) return st;
-  if ((st = mlp_update(M, n, lr)) != CCUT_OK) return st;
+  if ((st = mlp_batch(M, nullptr, x, t, n, n, false, 0, 0, true, lr, lsum)) != CCUT_OK) return st;
   if (loss) {
     HIP_TRY(c, hipMemcpyAsync(loss, lsum, 4, hipMemcpyDeviceToHost, c->stream));
     if ((st = sync_call(c)) != CCUT_OK) return st;

@@ -615,47 +615,45 @@ hipError_t launch_head_forward(const uint16_t *H, uint32_t width, uint64_t rows,
 
 // Training (k_train.hip).  Weights in lane order: see lane_order (bf16.hpp).
 constexpr uint32_t kColChunkRows = 256;  // rows of one column-sum chunk
-inline uint64_t train_chunks(uint64_t rows) { return (rows + kColChunkRows - 1) / kColChunkRows; }
 // One step's rows: the batch gathered (row i = data row philox(i, step) mod
 // n, or row i), forward, loss terms, gradients at every pre-activation.
 struct TrainRows {
   const uint16_t *x;  // data set [n][F] (bf16), or
   const float *xf;    // [n][F] fp32, rounded to bf16 when read (x unused)
   const float *t;     // [n]
-  uint64_t n, rows;
+  uint64_t n, inv_n, rows;  // inv_n = (2^64 - 1) / n
   uint32_t F, H, step, gather;
   uint64_t seed;
-  const uint16_t *w1, *w2, *w3, *w3t, *w2t;  // lane order
+  const uint16_t *w[5];  // W1, W2, W3, W3^T, W2^T in lane order
   const uint16_t *w4;
-  const float *b1, *b2, *b3, *b4;
+  const float *b[3], *b4;
   float inv_b2;  // 2 / rows
-  uint16_t *xb, *h1, *h2, *h3, *d1, *d2, *d3;
+  uint16_t *xb, *out[5], *d3;  // out: h1, h2, h3, d2, d1
   float *dy, *sq;
 };
 hipError_t launch_train_rows(const TrainRows &g, hipStream_t s);
-// The sums over the batch: weight gradients, column-sum chunks
-// part[kind][chunk][H] (kind 0: h3 weighted by dy, 1..3: d3, d2, d1), the
-// head bias gradient and the summed loss.
+// The sums over the batch, and with them the parameters' step (or, without
+// `update`, their gradients into g): the weight gradients, the column sums of h3
+// weighted by dy and of d3, d2, d1, the sums of dy and sq.
 struct TrainGrads {
-  uint32_t F, H;
   uint64_t rows;
   const uint16_t *xb, *h1, *h2, *h3, *d1, *d2, *d3;
   const float *dy, *sq;
-  float *gw1, *gw2, *gw3, *gb4, *loss, *part;
+  float *loss;  // sum of sq
 };
-hipError_t launch_train_grads(const TrainGrads &g, hipStream_t s);
 struct TrainParams {
-  uint64_t n;  // parameters
+  uint64_t n;  // parameters, W1 first
   uint32_t F, H;
   uint64_t off_b1, off_w2, off_b2, off_w3, off_b3, off_w4, off_b4;
   float *p, *g, *m, *v;
-  const float *part;
   uint16_t *pb, *w1, *w2, *w3, *w2t, *w3t;  // bf16 copies: row-major, and in lane order
 };
-// g completed by the column sums; Adam and the bf16 copies; the copies alone
-hipError_t launch_train_gradients(const TrainParams &P, uint64_t rows, hipStream_t s);
-hipError_t launch_train_update(const TrainParams &P, uint64_t rows, float lr, float b1, float b2, float c1, float c2,
-                               float eps, hipStream_t s);
+struct TrainAdam {
+  uint32_t update;
+  float lr, b1, b2, c1, c2, eps;
+};
+hipError_t launch_train_grads(const TrainGrads &g, const TrainParams &P, const TrainAdam &A, hipStream_t s);
+// the bf16 copies from p
 hipError_t launch_train_copies(const TrainParams &P, hipStream_t s);
 
 // The network regresses ln-weights divided by this scale (targets in

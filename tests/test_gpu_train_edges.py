@@ -40,7 +40,11 @@ def _case(F, H, rows, seed):
     return params, x, t, torch.tensor(x).to(torch.bfloat16).cuda(), torch.tensor(t).cuda()
 
 
-@pytest.mark.parametrize("F,H,rows", [(64, 64, 64), (256, 64, 192), (64, 256, 320), (192, 128, 1088), (256, 256, 64)])
+EDGES = [(64, 64, 64), (256, 64, 192), (64, 256, 320), (192, 128, 1088), (256, 256, 64), (64, 256, 1216)]
+PAIRS = [(F, H, 128) for F in (64, 128, 192, 256) for H in (64, 128, 192, 256)]  # one kernel each
+
+
+@pytest.mark.parametrize("F,H,rows", EDGES + PAIRS)
 def test_gradients_at_edges(ctx, F, H, rows):
     print(f"gradients F={F} H={H} rows={rows}", flush=True)
     params, x, t, xd, td = _case(F, H, rows, 3)
