@@ -9,10 +9,12 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG, "csrc")
 OUT = os.path.join(PKG, "libccut.so")
+PACK_OUT = os.path.join(PKG, "libccut_pack.so")
 BUILD_DIR = os.path.join(PKG, "_build")
 SOURCES = ["plan.cpp", "cutfind.cpp", "api.cpp", "k_sample.hip", "k_sv.hip", "k_contract.hip", "k_heis.hip",
            "k_exact.hip", "k_gemm.hip", "k_mlp.hip", "k_train.hip", "k_mlc.hip", "k_affine.hip"]
@@ -41,11 +43,26 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _build_pack() -> None:
+    """libccut_pack.so: the binding's conversion of Python circuits (its
+    symbols of the interpreter resolve in the process that loads it)."""
+    tmp = PACK_OUT + f".tmp{os.getpid()}"
+    cmd = [hipcc(), "-no-hip-rt", "-x", "c++", "-O3", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-I", os.path.join(PKG, "..", "include"), "-I", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "pack.cpp"), "-o", tmp]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"compile failed: {' '.join(cmd)}\n{r.stdout}\n{r.stderr}")
+    os.replace(tmp, PACK_OUT)
+
+
 def build(verbose: bool = False, jobs: int = 8) -> str:
     """Compile every source and link libccut.so; returns its path."""
     os.makedirs(BUILD_DIR, exist_ok=True)
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
+        pack = ex.submit(_build_pack)
         objs = list(ex.map(_compile, SOURCES))
+        pack.result()
     tmp = OUT + f".tmp{os.getpid()}"
     # -z defs: an unresolved symbol fails the link instead of the first load
     cmd = [hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", "-Wl,-z,defs", *objs, "-o", tmp]

@@ -29,8 +29,9 @@ namespace {
 struct Circuit {
   uint32_t n;
   std::vector<ccut_op> ops;
-  std::vector<std::vector<uint32_t>> wire_ops;    // per wire: op indices in order
-  std::vector<std::map<uint32_t, uint32_t>> pos;  // per wire: op index -> position
+  uint32_t max_width;
+  std::vector<std::vector<uint32_t>> wire_ops;  // per wire: op indices in order
+  std::vector<uint32_t> pos0, pos1;             // per op: its position on wire q0, on wire q1
 };
 
 bool two_qubit(uint32_t k) { return k == CCUT_CX || k == CCUT_CZ; }
@@ -38,12 +39,13 @@ bool non_clifford(uint32_t k) { return k == CCUT_T || k == CCUT_TDG || k == CCUT
 
 using Region = std::map<uint32_t, std::pair<uint32_t, uint32_t>>;  // wire -> [lo, hi]
 
-// Extend r until closed.
+// Extend r until closed, or wider than any region may be (every caller drops
+// such a region; its closure may be the whole circuit).
 void close_region(const Circuit &C, Region &r) {
   std::vector<uint32_t> todo;
   for (auto &kv : r) todo.push_back(kv.first);
   std::map<uint32_t, std::pair<uint32_t, uint32_t>> done;  // wire -> interval already scanned
-  while (!todo.empty()) {
+  while (!todo.empty() && r.size() <= C.max_width) {
     const uint32_t w = todo.back();
     todo.pop_back();
     const auto iv = r[w];
@@ -51,10 +53,11 @@ void close_region(const Circuit &C, Region &r) {
     const bool seen = it != done.end();
     for (uint32_t p = iv.first; p <= iv.second; ++p) {
       if (seen && p >= it->second.first && p <= it->second.second) continue;
-      const ccut_op &o = C.ops[C.wire_ops[w][p]];
+      const uint32_t i = C.wire_ops[w][p];
+      const ccut_op &o = C.ops[i];
       if (!two_qubit(o.kind)) continue;
       const uint32_t u = o.q0 == w ? o.q1 : o.q0;
-      const uint32_t pu = C.pos[u].at(C.wire_ops[w][p]);
+      const uint32_t pu = o.q0 == w ? C.pos1[i] : C.pos0[i];
       auto ru = r.find(u);
       if (ru == r.end()) {
         r[u] = {pu, pu};
@@ -184,22 +187,24 @@ extern "C" ccut_status ccut_find_cuts(uint32_t n_qubits, const ccut_op *ops, siz
   C.n = n_qubits;
   C.ops.assign(ops, ops + n_ops);
   C.wire_ops.assign(n_qubits, {});
-  C.pos.assign(n_qubits, {});
+  C.max_width = max_width;
+  C.pos0.resize(n_ops);
+  C.pos1.resize(n_ops);
   for (uint32_t i = 0; i < (uint32_t)n_ops; ++i) {
     const ccut_op &o = ops[i];
     if (o.kind > CCUT_RZ || o.q0 >= n_qubits) return CCUT_E_INVALID;
     if (two_qubit(o.kind) && (o.q1 >= n_qubits || o.q1 == o.q0)) return CCUT_E_INVALID;
-    for (uint32_t w : {o.q0, o.q1}) {
-      C.pos[w][i] = (uint32_t)C.wire_ops[w].size();
-      C.wire_ops[w].push_back(i);
-      if (!two_qubit(o.kind)) break;
-    }
+    C.pos0[i] = (uint32_t)C.wire_ops[o.q0].size();
+    C.wire_ops[o.q0].push_back(i);
+    if (!two_qubit(o.kind)) continue;
+    C.pos1[i] = (uint32_t)C.wire_ops[o.q1].size();
+    C.wire_ops[o.q1].push_back(i);
   }
   // one region per non-Clifford op (one wire wide)
   std::vector<Region> regs;
   for (uint32_t i = 0; i < (uint32_t)n_ops; ++i)
     if (non_clifford(ops[i].kind)) {
-      const uint32_t p = C.pos[ops[i].q0][i];
+      const uint32_t p = C.pos0[i];
       regs.push_back(Region{{ops[i].q0, {p, p}}});
     }
   auto width_ok = [&](const Region &r) { return r.size() <= max_width; };
