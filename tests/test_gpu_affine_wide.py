@@ -47,3 +47,21 @@ def test_records_at_word_edges(ctx, m, measured, gates):
             assert np.array_equal(got[v], words), (f, v)
             compared += 1
     assert compared >= 3
+
+
+@pytest.mark.parametrize("m,n_ext,shots", [(40, 65, 7), (40, 129, 300), (70, 64, 257), (100, 70, 5), (130, 130, 3)])
+def test_parities_at_mask_and_shot_edges(ctx, m, n_ext, shots):
+    """Sampled Z strings on both sides of 64 measurements, with mask counts around the groups of 64 and shots that
+    fill neither a quad nor a wave, against the oracle: exact parity counts, contraction rounding 1e-12."""
+    print(f"parities m={m} masks={n_ext} shots={shots}", flush=True)
+    chain = [("CX" if q % 3 else "CZ", q, q + 1, 0.0) for q in range(m - 1)]
+    ops = [("H", 0, -1, 0.0)] + W.random_circuit(m, 2 * m, 70 + m, kinds=CLIFF) + chain
+    cuts = [(0, 0)]
+    rng = np.random.default_rng(m)
+    masks = [sum(1 << int(q) for q in rng.choice(m, size=int(rng.integers(1, m + 1)), replace=False))
+             for _ in range(n_ext)]
+    words = np.array([[(z >> (64 * w)) & 0xFFFFFFFFFFFFFFFF for w in range((m + 63) // 64)] for z in masks],
+                     dtype=np.uint64)
+    want = C.zexpect(m, ops, cuts, masks, shots=shots, seed=13)
+    got = cc.Plan(ctx, m, ops, cuts).zexpect(words, shots=shots, seed=13)
+    assert np.abs(got - want).max() <= 1e-12
