@@ -228,12 +228,16 @@ constexpr uint32_t kSampleThreads = 256;  // threads of a sampling workgroup (51
 constexpr uint32_t kMaxUnitQpt = 63;      // 63 quads x 256 threads x 4 shots = 64512 < 2^16
 static_assert(kMaxUnitQpt * kSampleThreads * 4 < 65536, "16-bit LDS counts");
 __host__ __device__ inline uint32_t sample_tab_groups(uint32_t n_meas) { return (n_meas + 7) / 8; }
+// A variant with at most kFewBits random measurements is counted by them, in
+// kFewCopies copies of its counts in the same memory instead.
+constexpr uint32_t kFewBits = 6, kFewCopies = 32;
 inline size_t sample_lds_bytes(uint32_t n_meas, bool hist, bool sliced = false) {
   const size_t tab = (size_t)sample_tab_groups(n_meas) * 256 * 8;
   if (!hist) return tab;
+  const size_t few = (size_t(4) * kFewCopies) << (n_meas < kFewBits ? n_meas : kFewBits);
   const uint32_t lb = sliced ? kLdsHistBits : n_meas;
-  if (lb > kLdsHistBits) return tab;
-  return tab + 4 * (((size_t(1) << lb) + 1) / 2);
+  const size_t all = lb > kLdsHistBits ? tab : tab + 4 * (((size_t(1) << lb) + 1) / 2);
+  return all > few ? all : few;
 }
 constexpr size_t kSampleLdsMax = 8 * 256 * 8 + (size_t(2) << kLdsHistBits);
 

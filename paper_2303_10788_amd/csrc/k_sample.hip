@@ -94,6 +94,69 @@ __device__ __attribute__((always_inline)) void narrow_lds_shots(uint32_t *lds, u
   }
 }
 
+// Shots of a variant with at most kFewBits random measurements: each is counted
+// by its random bits alone, 32 copies of the 2^R counts in LDS by lane, so that
+// no two lanes of a half wave meet in a bank or a word (up to 64 lanes on one
+// word otherwise); then each outcome gets its sum once, by add(x, count).
+// `hist` (may overlap the copies): zeroed before add is called.  Measured for
+// the 6-bit tables of 16 variants at 50000 shots: 7 us; 79 us with a ballot
+// and an add per distinct outcome of a wave.
+template <class Add>
+__device__ __attribute__((always_inline)) inline void few_bits_shots(const uint64_t *s_model, uint64_t rmask,
+                                                                     uint64_t shots, uint64_t vid, uint64_t seed, uint64_t q0,
+                                                                     uint32_t q_end, bool wide, uint32_t *copies,
+                                                                     Add add, uint32_t *hist, uint32_t hist_words) {
+  const uint32_t r_lo = __builtin_amdgcn_readfirstlane((uint32_t)rmask);
+  const uint32_t r_hi = __builtin_amdgcn_readfirstlane((uint32_t)(rmask >> 32));
+  const uint32_t outcomes = 1u << (__popc(r_lo) + __popc(r_hi));
+  for (uint32_t i = threadIdx.x; i < outcomes * kFewCopies; i += kSampleBlock) copies[i] = 0;
+  __syncthreads();
+  const uint64_t nquads = (shots + 3) >> 2;
+  for (uint32_t q = 0; q < q_end; ++q) {
+    const uint64_t quad = (q0 + q) * kSampleBlock + threadIdx.x;
+    if (quad >= nquads) break;
+    uint64_t u[4];
+    quad_bits(quad, vid, seed, wide, u);
+    uint32_t c[4] = {0, 0, 0, 0}, i = 0;
+    for (uint32_t rem = r_lo; rem; rem &= rem - 1, ++i) {
+      const uint32_t j = (uint32_t)__builtin_ctz(rem);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) c[r] |= __builtin_amdgcn_ubfe((uint32_t)u[r], j, 1) << i;
+    }
+    for (uint32_t rem = r_hi; rem; rem &= rem - 1, ++i) {
+      const uint32_t j = (uint32_t)__builtin_ctz(rem);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) c[r] |= __builtin_amdgcn_ubfe((uint32_t)(u[r] >> 32), j, 1) << i;
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (quad * 4 + r < shots) atomicAdd(&copies[c[r] * kFewCopies + (threadIdx.x & (kFewCopies - 1))], 1u);
+  }
+  __syncthreads();
+  // four threads sum an outcome's copies (at most 64 outcomes: one pass)
+  static_assert((4u << kFewBits) <= kSampleThreads && kFewCopies % 4 == 0, "threads per outcome");
+  const uint32_t o = threadIdx.x >> 2;
+  uint32_t n = 0;
+  if (o < outcomes)
+#pragma unroll
+    for (uint32_t k = 0; k < kFewCopies / 4; ++k)
+      n += copies[o * kFewCopies + ((4 * (k + o) + (threadIdx.x & 3)) & (kFewCopies - 1))];
+  n += __shfl_xor(n, 1);
+  n += __shfl_xor(n, 2);
+  __syncthreads();
+  if (hist) {
+    for (uint32_t i = threadIdx.x; i < hist_words; i += kSampleBlock) hist[i] = 0;
+    __syncthreads();
+  }
+  if (n && (threadIdx.x & 3) == 0) {
+    uint64_t x = s_model[0];
+    uint32_t i = 0;
+    for (uint64_t rem = rmask; rem; rem &= rem - 1, ++i)
+      if ((o >> i) & 1u) x ^= s_model[2 + __builtin_ctzll(rem)];
+    add(x, n);
+  }
+}
+
 // Shots of variant v, block bx of nbx: each thread handles `qpt` quads;
 // quads are interleaved across the workgroup so record writes are
 // contiguous.  With n_meas <= kLdsHistBits (or a slice of the bins) the
@@ -120,7 +183,8 @@ __device__ __attribute__((always_inline)) void sample_body(const uint64_t *__res
   // the model to LDS in one coalesced load, then the tables from LDS
   if (threadIdx.x < mw) s_model[threadIdx.x] = md[threadIdx.x];
   __syncthreads();
-  const uint64_t x0 = s_model[0], rmask = s_model[1];
+  // (a skipped variant has no model: nothing past its measurements is taken from it)
+  const uint64_t x0 = s_model[0], rmask = s_model[1] & (n_meas < 64 ? (1ull << n_meas) - 1 : ~0ull);
   const uint32_t bins = 1u << n_meas;
   // sliced (nslice > 1): this workgroup counts the outcomes whose top bits
   // equal `slice` into an LDS histogram of 2^kLdsHistBits bins
@@ -128,14 +192,21 @@ __device__ __attribute__((always_inline)) void sample_body(const uint64_t *__res
   // dist (one shot block): the workgroup writes the table itself, count x fl(1/shots)
   const bool lds_hist = (partial != nullptr || dist != nullptr || cnt16 != nullptr) && (n_meas <= kLdsHistBits || sliced);
   const bool wide = n_meas > 32;
-  // With few random bits the shots of a wave land on few bins: lanes with
-  // equal outcomes then add their count once (one atomic per distinct
-  // outcome in the wave instead of up to 64 on one address).
-  const bool combine = (lds_hist || partial != nullptr) && __popcll(rmask) <= 6;
-  const bool fast = lds_hist && !wide && records == nullptr && !combine &&
+  // Few random bits: the shots are counted by those bits alone, below.
+  const bool few = (lds_hist || partial != nullptr) && records == nullptr && __popcll(rmask) <= (int)kFewBits;
+  if (few) {
+    few_bits_shots(s_model, rmask, shots, vid0 + v, seed, (uint64_t)bx * qpt, skip ? 0u : qpt, wide,
+                   reinterpret_cast<uint32_t *>(s_dyn), [&](uint64_t x, uint32_t n) {
+                     if (!lds_hist)
+                       atomicAdd(&partial[v * (uint64_t)bins + x], n);
+                     else if (!sliced || (uint32_t)(x >> kLdsHistBits) == slice)
+                       atomicAdd(&s_hist[((uint32_t)x & ((1u << kLdsHistBits) - 1u)) >> 1], n << (16 * ((uint32_t)x & 1u)));
+                   }, lds_hist ? s_hist : nullptr, ((sliced ? 1u << kLdsHistBits : bins) + 1) / 2);
+  }
+  const bool fast = lds_hist && !wide && records == nullptr && !few &&
                     ((!sliced && groups >= 1 && groups <= 2) || (sliced && groups == 3));
   uint32_t *s_tab32 = reinterpret_cast<uint32_t *>(s_dyn);  // the fast path's 32-bit entries
-  for (uint32_t e = threadIdx.x; e < groups * 256; e += kSampleBlock) {
+  for (uint32_t e = threadIdx.x; e < (few ? 0u : groups * 256); e += kSampleBlock) {
     const uint32_t g = e >> 8, b = e & 255u;
     uint64_t t = 0;
 #pragma unroll
@@ -150,7 +221,7 @@ __device__ __attribute__((always_inline)) void sample_body(const uint64_t *__res
   }
   const uint32_t lbins = sliced ? (1u << kLdsHistBits) : bins;
   const uint32_t lwords = (lbins + 1) / 2;  // two 16-bit counts per word
-  if (lds_hist) {
+  if (lds_hist && !few) {
     if (lwords % 4 == 0) {  // 16 bytes per store (the histogram starts 16-byte aligned)
       u32x4 *h4 = reinterpret_cast<u32x4 *>(s_hist);
       for (uint32_t i = threadIdx.x; i < lwords / 4; i += kSampleBlock) h4[i] = u32x4{0u, 0u, 0u, 0u};
@@ -161,7 +232,6 @@ __device__ __attribute__((always_inline)) void sample_body(const uint64_t *__res
   __syncthreads();
   const uint64_t vid = vid0 + v;
   const uint64_t nquads = (shots + 3) >> 2;
-  const uint32_t lane = threadIdx.x & 63u;
   uint32_t *hist = lds_hist ? s_hist : (partial ? partial + v * (uint64_t)bins : nullptr);
   // a skipped variant draws no shots: its (zero) histogram is still written
   const uint32_t q_end = skip ? 0u : qpt;
@@ -174,45 +244,26 @@ __device__ __attribute__((always_inline)) void sample_body(const uint64_t *__res
     else
       narrow_lds_shots<3, true>(s_tab32, (uint32_t)x0, shots, vid, seed, q0, q_end, slice);
   }
-  for (uint32_t q = 0; q < (fast ? 0u : q_end); ++q) {
+  for (uint32_t q = 0; q < (fast || few ? 0u : q_end); ++q) {
     const uint64_t quad = ((uint64_t)bx * qpt + q) * kSampleBlock + threadIdx.x;
-    if (!combine && quad >= nquads) break;
-    if (combine && ((uint64_t)bx * qpt + q) * kSampleBlock >= nquads) break;  // the whole workgroup is done
+    if (quad >= nquads) break;
     uint64_t u[4];
     quad_bits(quad, vid, seed, wide, u);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const uint64_t s = quad * 4 + r;
-      bool valid = quad < nquads && s < shots;
-      if (!combine && !valid) break;
+      if (s >= shots) break;
       uint64_t x = x0;
       for (uint32_t g = 0; g < groups; ++g) x ^= s_tab[(g << 8) | (uint32_t)((u[r] >> (8 * g)) & 255u)];
-      if (records && valid) records[v * shots + s] = x;
+      if (records) records[v * shots + s] = x;
       if (sliced) {
-        if ((uint32_t)(x >> kLdsHistBits) != slice) valid = false;
+        if ((uint32_t)(x >> kLdsHistBits) != slice) continue;
         x &= (1u << kLdsHistBits) - 1u;
-        if (!combine && !valid) continue;
       }
-      if (combine) {
-        // every lane of the wave is here (no early exit on this path)
-        uint64_t todo = __ballot(valid);
-        while (todo) {
-          const uint32_t leader = (uint32_t)__ffsll((unsigned long long)todo) - 1u;
-          const uint32_t xl = __builtin_amdgcn_readlane((uint32_t)x, leader);
-          const uint64_t same = __ballot(valid && (uint32_t)x == xl) & todo;
-          if (lane == leader) {
-            if (lds_hist)
-              atomicAdd(&hist[xl >> 1], (uint32_t)__popcll(same) << (16 * (xl & 1u)));
-            else
-              atomicAdd(&hist[xl], (uint32_t)__popcll(same));
-          }
-          todo &= ~same;
-        }
-      } else if (lds_hist) {
+      if (lds_hist)
         atomicAdd(&hist[(uint32_t)x >> 1], 1u << (16 * ((uint32_t)x & 1u)));
-      } else if (hist) {
+      else if (hist)
         atomicAdd(&hist[x], 1u);
-      }
     }
   }
   if (lds_hist) {
@@ -302,15 +353,27 @@ __global__ __launch_bounds__(kSampleBlock) void sample_batch_kernel(const Sample
   }
 }
 
-// dist[v][b] = (sum over shot blocks of counts) x fl(1/shots)
-__global__ void hist_reduce_kernel(const uint32_t *__restrict__ partial, uint64_t nv, uint32_t nblk,
-                                   uint32_t bins, uint64_t shots, double *__restrict__ dist,
-                                   uint16_t *__restrict__ cnt16) {
-  const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nv * bins) return;
-  const uint64_t v = i / bins, b = i % bins;
+// dist[v][b] = (sum over shot blocks of counts) x fl(1/shots).  `slices`
+// (1, 2, 4 or 8) threads to an entry, each adding every slices-th block: bound
+// by the latency of their loads (49 blocks of 16 x 64 entries one thread to an
+// entry: 16 us; eight to an entry: 4 us).
+__global__ __launch_bounds__(256) void hist_reduce_kernel(const uint32_t *__restrict__ partial, uint64_t nv,
+                                                          uint32_t nblk, uint32_t bins, uint64_t shots, uint32_t slices,
+                                                          double *__restrict__ dist, uint16_t *__restrict__ cnt16) {
+  __shared__ uint64_t part[256];
+  const uint32_t per = 256 / slices, e = threadIdx.x & (per - 1);
+  const uint64_t i = (uint64_t)blockIdx.x * per + e;
   uint64_t c = 0;
-  for (uint32_t k = 0; k < nblk; ++k) c += partial[(v * nblk + k) * (uint64_t)bins + b];
+  if (i < nv * bins) {
+    const uint64_t v = i / bins, b = i % bins;
+    const uint32_t *src = partial + v * nblk * (uint64_t)bins + b;
+#pragma unroll 8
+    for (uint32_t k = threadIdx.x / per; k < nblk; k += slices) c += src[k * (uint64_t)bins];
+  }
+  part[threadIdx.x] = c;
+  __syncthreads();
+  if (threadIdx.x >= per || i >= nv * bins) return;
+  for (uint32_t k = 1; k < slices; ++k) c += part[k * per + e];
   if (cnt16)
     cnt16[i] = (uint16_t)c;
   else
@@ -830,8 +893,9 @@ hipError_t launch_hist_reduce(const uint32_t *partial, uint64_t nv, uint32_t nbl
                               uint64_t shots, double *dist, hipStream_t s, uint16_t *cnt16) {
   const uint64_t n = nv * bins;
   if (cnt16 && shots > 0xFFFFull) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(hist_reduce_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, partial, nv, nblk,
-                     bins, shots, dist, cnt16);
+  const uint32_t slices = nblk >= 8 ? 8 : nblk >= 4 ? 4 : nblk >= 2 ? 2 : 1;
+  hipLaunchKernelGGL(hist_reduce_kernel, dim3(blocks_for(n, 256 / slices)), dim3(256), 0, s, partial, nv, nblk, bins,
+                     shots, slices, dist, cnt16);
   return hipGetLastError();
 }
 
