@@ -757,23 +757,16 @@ ccut_status pauli_passes(ccut_ctx *c, const Fragment &f, const FragRequest &r, d
   uint64_t n_out_axes = 0;
   for (const Axis &ax : f.axes) n_out_axes += ax.side == 0;
   const uint64_t entries_out = (mode2_lo ? mode2_lo : xsize >> n_out_axes) << (2 * a);
-  if (mode2_lo && a >= 2 && a <= 3 && entries_out <= (1ull << 16)) {
+  if (mode2_lo && a >= 2 && a <= kMaxAllAxes && entries_out <= (1ull << 16)) {
     TransformAll A{};
     A.n_axes = a;
     A.x_in = xsize;
     A.n_strings = mode2_lo;
-    uint64_t xo = xsize, nout = 0;
     for (uint32_t j = 0; j < a; ++j) {
-      const bool is_out = f.axes[j].side == 0;
       A.rad[j] = f.axes[j].radix();
-      A.mode[j] = is_out ? (mode2_lo ? 2u : 1u) : 0u;
-      A.pos[j] = is_out && !mode2_lo ? (uint32_t)r.axis_outpos[j] : 0u;
-      if (is_out) ++nout;
+      A.is_out[j] = f.axes[j].side == 0;
     }
-    xo >>= nout;
-    if (mode2_lo) xo = mode2_lo;
-    A.x_out = xo;
-    double *nxt = aget<double>(c, xo << (2 * a));
+    double *nxt = aget<double>(c, mode2_lo << (2 * a));
     if (!nxt) return fail(c, CCUT_E_OOM, "device allocation failed");
     {
       KTimer t(c, CCUT_K_TRANSFORM);

@@ -59,75 +59,59 @@ __global__ void transform_pass_kernel(const double *__restrict__ in, double *__r
   out[i] = acc;
 }
 
-// One thread per output entry; the terms of every axis are enumerated as a
-// mixed-radix counter (at most 3 per input axis, 2 or 1 per output axis).
-__global__ void transform_all_kernel(const TransformAll A, const double *__restrict__ in, double *__restrict__ out) {
-  const uint32_t a = A.n_axes;
-  const uint64_t total = (A.x_out << (2 * a));
+// String-selection tables of at most three axes, one thread per output entry:
+// an input axis contributes 2 or 3 terms (I: p0 + p1; X: 2p+ - p0 - p1; Y: 2p+i
+// - p0 - p1; Z: p0 - p1), an output axis selects one (basis X, Y, Z, its outcome
+// bit in J).  Bound by the latency of the loads: the nine of the first two axes
+// are on their way together (3328 entries: 5 us; 22 us with
+// the terms enumerated one by one through a mixed-radix counter).
+__global__ __launch_bounds__(256) void transform_all_kernel(const TransformAll A, const double *__restrict__ in,
+                                                            double *__restrict__ out) {
+  constexpr uint32_t N = kMaxAllAxes;
   const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= total) return;
-  const uint64_t x = i % A.x_out;
-  const uint64_t P = i / A.x_out;
-  // per axis: number of terms and the term list (digit, outcome bit, coefficient)
-  uint32_t nt[kMaxAxes];
-  for (uint32_t j = 0; j < a; ++j) {
-    const uint32_t p = (uint32_t)((P >> (2 * j)) & 3ull);
-    nt[j] = A.mode[j] == 0 ? (p == 1 || p == 2 ? 3u : 2u) : A.mode[j] == 1 ? 2u : 1u;
-  }
-  // x with the consumed outcome bits (mode 1) as zeros, ascending positions
-  uint64_t xbase = x;
-  if (A.n_strings == 0) {
-    uint32_t ps[kMaxAxes], np = 0;
-    for (uint32_t j = 0; j < a; ++j)
-      if (A.mode[j] == 1) ps[np++] = A.pos[j];
-    for (uint32_t u = 1; u < np; ++u)  // insertion sort, np <= 16
-      for (uint32_t v = u; v > 0 && ps[v - 1] > ps[v]; --v) {
-        const uint32_t t = ps[v];
-        ps[v] = ps[v - 1];
-        ps[v - 1] = t;
-      }
-    for (uint32_t u = 0; u < np; ++u)
-      xbase = ((xbase >> ps[u]) << (ps[u] + 1)) | (xbase & ((1ull << ps[u]) - 1));
+  if (i >= A.n_strings << (2 * A.n_axes)) return;
+  const uint64_t P = i / A.n_strings;
+  uint32_t nt[N], t_out = 0;
+  uint64_t off[N][3], stride = A.x_in, base = i % A.n_strings;
+  double w[N][3];
+#pragma unroll
+  for (uint32_t j = 0; j < N; ++j) {
+    const uint32_t p = j < A.n_axes ? (uint32_t)(P >> (2 * j)) & 3u : 0u;
+    nt[j] = 1;
+    off[j][0] = off[j][1] = off[j][2] = 0;
+    w[j][0] = w[j][1] = w[j][2] = 1.0;
+    if (j >= A.n_axes) continue;
+    if (A.is_out[j]) {
+      off[j][0] = (p == 1 ? 0u : p == 2 ? 1u : 2u) * stride;  // (I reads Z)
+      base += (uint64_t)(p != 0) * (A.n_strings << t_out);
+      ++t_out;
+    } else {
+      const bool three = p == 1 || p == 2;
+      nt[j] = three ? 3u : 2u;
+      off[j][0] = three ? (p + 1) * stride : 0;
+      off[j][1] = three ? 0 : stride;
+      off[j][2] = stride;
+      w[j][0] = three ? 2.0 : 1.0;
+      w[j][1] = p == 0 ? 1.0 : -1.0;
+      w[j][2] = -1.0;
+    }
+    stride *= A.rad[j];
   }
   double acc = 0.0;
-  uint32_t c[kMaxAxes];
-  for (uint32_t j = 0; j < a; ++j) c[j] = 0;
-  for (;;) {
-    double coef = 1.0;
-    uint64_t v = 0, stride = 1, xin = xbase, J = 0;
-    uint32_t t_out = 0;
-    for (uint32_t j = 0; j < a; ++j) {
-      const uint32_t p = (uint32_t)((P >> (2 * j)) & 3ull);
-      uint32_t d, b = 0;
-      double w;
-      if (A.mode[j] == 0) {
-        // I: p0 + p1; X: 2p+ - p0 - p1; Y: 2p+i - p0 - p1; Z: p0 - p1
-        if (p == 0) { d = c[j]; w = 1.0; }
-        else if (p == 3) { d = c[j]; w = c[j] ? -1.0 : 1.0; }
-        else if (c[j] == 0) { d = p + 1; w = 2.0; }
-        else { d = c[j] - 1; w = -1.0; }
-      } else {
-        d = p == 1 ? 0u : p == 2 ? 1u : 2u;  // basis X, Y, Z (I reads Z)
-        if (A.mode[j] == 1) {
-          b = c[j];
-          w = (p != 0 && b) ? -1.0 : 1.0;
-        } else {
-          b = p == 0 ? 0u : 1u;
-          w = 1.0;
-        }
-        if (A.mode[j] == 1) xin |= (uint64_t)b << A.pos[j];
-        else J |= (uint64_t)b << t_out;
-        ++t_out;
-      }
-      coef *= w;
-      v += d * stride;
-      stride *= A.rad[j];
-    }
-    if (A.n_strings) xin = J * A.n_strings + x;
-    acc += coef * in[v * A.x_in + xin];
-    uint32_t j = 0;
-    while (j < a && ++c[j] == nt[j]) c[j++] = 0;
-    if (j == a) break;
+#pragma unroll 1
+  for (uint32_t c2 = 0; c2 < nt[2]; ++c2) {
+    const double *src = in + base + (c2 == 0 ? off[2][0] : c2 == 1 ? off[2][1] : off[2][2]);
+    const double w2 = c2 == 0 ? w[2][0] : c2 == 1 ? w[2][1] : w[2][2];
+    double v[3][3];
+#pragma unroll
+    for (uint32_t c1 = 0; c1 < 3; ++c1)
+#pragma unroll
+      for (uint32_t c0 = 0; c0 < 3; ++c0) v[c1][c0] = src[off[1][c1 < nt[1] ? c1 : 0] + off[0][c0 < nt[0] ? c0 : 0]];
+#pragma unroll
+    for (uint32_t c1 = 0; c1 < 3; ++c1)
+#pragma unroll
+      for (uint32_t c0 = 0; c0 < 3; ++c0)
+        if (c1 < nt[1] && c0 < nt[0]) acc += w[0][c0] * w[1][c1] * w2 * v[c1][c0];
   }
   out[i] = acc;
 }
@@ -397,7 +381,7 @@ __global__ void recombine_fp64_kernel(const RecombArgs *__restrict__ A, uint32_t
 // order: per chunk of 128 terms the column offsets p_f(P) * rows_f are
 // computed once per workgroup into LDS, each thread keeps its rows in
 // registers, and the term loop is unrolled so the gathers overlap.
-constexpr uint32_t kRcFrags = 8, kRcChunk = kRcChunkOut;
+constexpr uint32_t kRcFrags = 8, kRcChunk = kRcChunkOut, kZrWaves = 8;
 typedef const __attribute__((address_space(4))) RecombFrag c_RecombFragK;
 // terms: the cut terms to sum (ascending), or null for all 4^k.
 __device__ inline void recombine_small_body(const RecombArgs *__restrict__ A, uint32_t nq,
@@ -590,18 +574,23 @@ __global__ void zrecombine_kernel(const RecombArgs *__restrict__ A, uint32_t n_s
 
 // The same for at most 8 fragments (same operations, same order): the
 // column offsets of each chunk of 64 terms are computed once per workgroup
-// into LDS; with a single term range the result is written directly
-// (scaled by 2^-k) and no final pass is needed.
+// into LDS and its waves take equal shares of the chunk (multiples of 8 terms, so
+// fp32 groups stay whole), their sums added in order at the end; with a single
+// term range the result is written directly (scaled by 2^-k) and no final pass is
+// needed.  Bound by the latency of the gathers: 64 strings of 3 cuts 5 us,
+// 18.5 us with one wave for the chunk.
 template <bool F32>
-__global__ __launch_bounds__(64) void zrecombine_small_kernel(const RecombArgs *__restrict__ A, uint32_t n_strings,
+__global__ __launch_bounds__(64 * kZrWaves) void zrecombine_small_kernel(const RecombArgs *__restrict__ A, uint32_t n_strings,
                                                               uint64_t per_split, double *__restrict__ partial,
                                                               double *__restrict__ direct) {
   __shared__ uint64_t s_off[kRcFrags][64];
+  __shared__ double s_acc[kZrWaves][64];
   typedef const __attribute__((address_space(4))) RecombArgs c_Args;
   typedef const __attribute__((address_space(1))) double g_f64;
   c_Args *C = (c_Args *)(uint64_t)A;  // uniform descriptors: scalar loads
-  const uint32_t tid = threadIdx.x;
-  const uint32_t s = blockIdx.x * 64 + tid;
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t waves = blockDim.x >> 6, share = 64 / waves;
+  const uint32_t s = blockIdx.x * 64 + lane;
   const bool live = s < n_strings;
   const uint32_t nf = C->n_frags, k = C->k, lo_parts = C->lo_parts;
   g_f64 *T[kRcFrags];
@@ -627,11 +616,12 @@ __global__ __launch_bounds__(64) void zrecombine_small_kernel(const RecombArgs *
     __syncthreads();
     if (!live) continue;
     constexpr uint32_t U = 4;
-    for (uint32_t t0 = 0; t0 < cn; t0 += U) {
+    const uint32_t t_begin = wave * share, t_end = t_begin + share < cn ? t_begin + share : cn;
+    for (uint32_t t0 = t_begin; t0 < t_end; t0 += U) {
       double v[U][kRcFrags];
 #pragma unroll
       for (uint32_t u = 0; u < U; ++u) {
-        const uint32_t t = t0 + u < cn ? t0 + u : t0;
+        const uint32_t t = t0 + u < t_end ? t0 + u : t0;
 #pragma unroll
         for (uint32_t f = 0; f < kRcFrags; ++f)
           if (f < nf) v[u][f] = T[f][s_off[f][t]];
@@ -639,7 +629,7 @@ __global__ __launch_bounds__(64) void zrecombine_small_kernel(const RecombArgs *
       __builtin_amdgcn_sched_barrier(0);  // the gathers stay ahead of their uses
 #pragma unroll
       for (uint32_t u = 0; u < U; ++u) {
-        if (t0 + u >= cn) break;
+        if (t0 + u >= t_end) break;
         const uint64_t P = C0 + t0 + u;
         double term = 1.0;
         float hi = 1.f, corr = 0.f;
@@ -667,7 +657,13 @@ __global__ __launch_bounds__(64) void zrecombine_small_kernel(const RecombArgs *
       }
     }
   }
-  if (!live) return;
+  if (waves > 1) {
+    s_acc[wave][lane] = acc;
+    __syncthreads();
+    acc = 0.0;
+    for (uint32_t w = 0; w < waves; ++w) acc += s_acc[w][lane];
+  }
+  if (!live || wave) return;
   if (direct)
     direct[s] = ldexp(acc, -(int)k);
   else
@@ -732,8 +728,8 @@ hipError_t launch_transform_pass(const double *in, double *out, uint64_t outer, 
 }
 
 hipError_t launch_transform_all(const TransformAll &a, const double *in, double *out, hipStream_t s) {
-  if (a.n_axes == 0 || a.n_axes > (uint32_t)kMaxAxes) return hipErrorInvalidValue;
-  const uint64_t total = a.x_out << (2 * a.n_axes);
+  if (a.n_axes == 0 || a.n_axes > kMaxAllAxes) return hipErrorInvalidValue;
+  const uint64_t total = a.n_strings << (2 * a.n_axes);
   if (total == 0) return hipSuccess;
   hipLaunchKernelGGL(transform_all_kernel, dim3(blocks_for(total, 256)), dim3(256), 0, s, a, in, out);
   return hipGetLastError();
@@ -818,10 +814,12 @@ hipError_t launch_zrecombine(const RecombArgs *d_args, uint32_t n_frags, uint32_
   const dim3 grid(blocks_for(n_strings, 64), splits);
   if (n_frags <= kRcFrags) {
     double *direct = splits == 1 ? out : nullptr;
+    const uint32_t waves = per >= 64 ? 8 : per >= 32 ? 4 : per >= 16 ? 2 : 1;  // shares of 8 terms or more
+    const dim3 block(64 * waves);
     if (fp32)
-      hipLaunchKernelGGL(zrecombine_small_kernel<true>, grid, dim3(64), 0, s, d_args, n_strings, per, partial, direct);
+      hipLaunchKernelGGL(zrecombine_small_kernel<true>, grid, block, 0, s, d_args, n_strings, per, partial, direct);
     else
-      hipLaunchKernelGGL(zrecombine_small_kernel<false>, grid, dim3(64), 0, s, d_args, n_strings, per, partial, direct);
+      hipLaunchKernelGGL(zrecombine_small_kernel<false>, grid, block, 0, s, d_args, n_strings, per, partial, direct);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || direct) return e;
     hipLaunchKernelGGL(zrecombine_final_kernel, dim3(blocks_for(n_strings, 64)), dim3(64), 0, s, partial, n_strings,
