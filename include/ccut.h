@@ -274,12 +274,12 @@ ccut_status ccut_marginal(ccut_plan *plan, const ccut_eval_opts *eo, const uint3
 ccut_status ccut_zexpect(ccut_plan *plan, const ccut_eval_opts *eo, const uint64_t *masks,
                          uint32_t n_strings, double *out, int out_on_device);
 
-/* Call graphs (default on).  A ccut_marginal or ccut_zexpect call with a
- * device output that repeats an earlier call on the same plan exactly (same
- * options, request and output address) is captured as a HIP graph on its
- * second occurrence and replayed from then on: every kernel and copy runs
- * again, only the host-side planning and launch overhead is saved.  Up to 8
- * graphs per plan (least recently used out).  Calls with host outputs, with
+/* Call graphs (default on).  A ccut_marginal or ccut_zexpect call
+ * that repeats an earlier call on the same plan exactly (same
+ * options, request and, on the device, output address) is captured as a HIP
+ * graph on its second occurrence and replayed from then on: every kernel and
+ * copy runs again, only the host-side planning and launch overhead is saved.
+ * Up to 8 graphs per plan (least recently used out).  Calls with
  * kernel timing enabled, or issued while the context's stream is being
  * captured by the caller always run eagerly.  enable = 0 turns replay off
  * (captured graphs are kept until their plan is destroyed).  Errors:

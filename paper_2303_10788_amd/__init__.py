@@ -455,7 +455,7 @@ class Context:
         ccut_timing_enable(self.handle, on)
 
     def call_graphs(self, on: bool = True):
-        """Replay repeated device-output marginal/zexpect calls as captured
+        """Replay repeated marginal/zexpect calls as captured
         HIP graphs (on by default)."""
         ccut_call_graphs(self.handle, on)
 
