@@ -673,7 +673,9 @@ ccut_status variant_dists(ccut_plan *p, const ccut_eval_opts *eo, const Fragment
 // Tile plan of a fragment's marginal-mode transform (variant data in, T out):
 // false when the fragment has no axes, more than kMaxTileAxes, or variant
 // data per x_out entry beyond kTileElems.
-bool tile_job(const Fragment &f, const FragRequest &r, const double *in, uint64_t xsize, double *out, TileJob &J) {
+// elems: of a tile of this launch (every kind takes the same fragments).
+bool tile_job(const Fragment &f, const FragRequest &r, const double *in, uint64_t xsize, double *out, TileJob &J,
+              uint32_t elems = kTileElems) {
   const uint32_t a = (uint32_t)f.axes.size();
   if (a == 0 || a > (uint32_t)kMaxTileAxes) return false;
   J = TileJob{};
@@ -693,8 +695,8 @@ bool tile_job(const Fragment &f, const FragRequest &r, const double *in, uint64_
   uint32_t xb = 0;  // log2 of x_in
   while ((1ull << xb) < xsize) ++xb;
   const uint32_t xo_bits = xb - n_out;
-  uint32_t t = std::min<uint32_t>(xo_bits, kTileMaxT);
-  while ((V << (n_out + t)) > kTileElems) --t;
+  uint32_t t = std::min<uint32_t>(xo_bits, elems > kTileElems ? kTileCountMaxT : kTileMaxT);
+  while ((V << (n_out + t)) > elems) --t;
   std::sort(outpos.begin(), outpos.end());
   auto is_out_pos = [&](uint32_t p) { return std::binary_search(outpos.begin(), outpos.end(), p); };
   uint32_t p = 0, cnt = 0;
@@ -735,6 +737,56 @@ bool tile_job(const Fragment &f, const FragRequest &r, const double *in, uint64_
   return true;
 }
 
+// The transform of a sampled fragment's counts where every axis is a quantum
+// output: false if some is not, there are more than four, or the table exceeds
+// 32-bit byte offsets.
+bool out_job(const Fragment &f, const FragRequest &r, const uint16_t *cnt, uint64_t shots, OutJob &J) {
+  const uint32_t a = (uint32_t)f.axes.size();
+  if (a == 0 || a > kOutAxes) return false;
+  J = OutJob{};
+  for (uint32_t j = 0; j < a; ++j) {
+    if (f.axes[j].side != 0) return false;
+    J.pos[j] = J.asc[j] = (uint32_t)r.axis_outpos[j];
+  }
+  std::sort(J.asc, J.asc + a);
+  J.in = cnt;
+  J.shots = (double)shots;
+  J.n_axes = a;
+  J.xib = (uint32_t)r.meas.size();
+  J.xob = J.xib - a;
+  if ((f.n_variants << J.xib) > 0x7FFFFFFFull) return false;
+  J.t = std::min<uint32_t>(J.xob, a <= 2 ? 8 : 4);
+  J.tiles = 1u << (J.xob - J.t);
+  return true;
+}
+
+// The transform of 16-bit shot counts, into 32-bit ones (*out points to them) or
+// their values.
+ccut_status counts_passes(ccut_ctx *c, const Fragment &f, const FragRequest &r, const uint16_t *cnt, uint64_t shots,
+                          bool values, double **out) {
+  OutJob O;
+  if (out_job(f, r, cnt, shots, O)) {
+    O.out = c->arena.get((1ull << (O.xob + 2 * O.n_axes)) * (values ? sizeof(double) : sizeof(int32_t)));
+    OutJob *dj = O.out ? (OutJob *)upload(c, &O, sizeof(O)) : nullptr;
+    if (!dj) return fail(c, CCUT_E_OOM, "device allocation failed");
+    KTimer t(c, CCUT_K_TRANSFORM);
+    HIP_TRY(c, launch_transform_out(dj, 1, O.tiles, values, c->cur));
+    *out = (double *)O.out;
+    return CCUT_OK;
+  }
+  TileJob J;
+  if (!tile_job(f, r, nullptr, 1ull << r.meas.size(), nullptr, J, kTileCountElems)) return fail(c, CCUT_E_INVALID, "counts beyond a tile");
+  J.in16 = cnt;
+  J.shots = (double)shots;
+  J.out = (double *)c->arena.get((J.x_out << (2 * f.axes.size())) * (values ? sizeof(double) : sizeof(int32_t)));
+  TileJob *dj = J.out ? (TileJob *)upload(c, &J, sizeof(J)) : nullptr;
+  if (!dj) return fail(c, CCUT_E_OOM, "device allocation failed");
+  KTimer t(c, CCUT_K_TRANSFORM);
+  HIP_TRY(c, launch_transform_tiled(dj, 1, J.tiles, values ? kTileCountsF64 : kTileCounts, c->cur));
+  *out = J.out;
+  return CCUT_OK;
+}
+
 ccut_status pauli_passes(ccut_ctx *c, const Fragment &f, const FragRequest &r, double *data,
                          uint64_t xsize, uint64_t mode2_lo, double **out) {
   const uint32_t a = (uint32_t)f.axes.size();
@@ -746,7 +798,7 @@ ccut_status pauli_passes(ccut_ctx *c, const Fragment &f, const FragRequest &r, d
       TileJob *dj = J.out ? (TileJob *)upload(c, &J, sizeof(J)) : nullptr;
       if (!dj) return fail(c, CCUT_E_OOM, "device allocation failed");
       KTimer t(c, CCUT_K_TRANSFORM);
-      HIP_TRY(c, launch_transform_tiled(dj, 1, J.tiles, c->cur));
+      HIP_TRY(c, launch_transform_tiled(dj, 1, J.tiles, kTileF64, c->cur));
       *out = J.out;
       return CCUT_OK;
     }
@@ -1453,6 +1505,28 @@ bool counts_contraction(const PlanData &pd, const ccut_eval_opts *eo, uint32_t n
   return !(!fp32 && pd.frags.size() > 2 && (K << nq) <= (1ull << 20));
 }
 
+// Whether fragment f's transform sums its shot counts themselves: the column
+// side of the contraction (its first fragment with the most requested outputs),
+// sampled, not the fold target, fitting the tiled transform.  The same for every
+// way of summing the terms, so that they agree; a matrix contraction
+// (counts_contraction) reads the transformed counts, the others their values.
+// That tensor is the contraction's traffic: counts are half of it, and half of
+// the transform's output.
+bool counts_transform(const PlanData &pd, const ccut_eval_opts *eo, const std::vector<FragRequest> &reqs,
+                      const Fragment &f, uint32_t nq, const uint32_t *qubits) {
+  if (!f.clifford || eo->shots_per_variant == 0 || eo->shots_per_variant > 0xFFFFull || (eo->flags & CCUT_FLAG_ML))
+    return false;
+  size_t col = 0;
+  for (size_t i = 1; i < reqs.size(); ++i)
+    if (reqs[i].req_pos.size() > reqs[col].req_pos.size()) col = i;
+  const FragRequest &r = reqs[f.index];
+  ccut_eval_opts dense = *eo;
+  dense.flags = 0;
+  TileJob probe;
+  return col == f.index && fold_target(pd, &dense, qubits, nq) < 0 && !use_heisenberg(f, eo, r.req_pos.size()) &&
+         tile_job(f, r, nullptr, 1ull << r.meas.size(), nullptr, probe);
+}
+
 // The axes of fragment f on a cut of fragment g (bit j: axis j).
 uint32_t fold_mask(const PlanData &pd, int g, const Fragment &f) {
   if (g < 0 || (int)f.index == g) return 0;
@@ -1555,9 +1629,11 @@ ccut_status marginal_skip_enqueue(ccut_plan *p, const ccut_eval_opts *eo, const 
   args.n_frags = (uint32_t)pd.frags.size();
   args.k = pd.k;
   args.lo_parts = eo->precision == CCUT_FP32X3_MFMA_FP64SUM;
+  std::vector<FragRequest> reqs;
+  for (const Fragment &f : pd.frags) reqs.push_back(marginal_request(f, qubits, nq));
   for (const Fragment &f : pd.frags) {
     route(c, f);
-    FragRequest r = marginal_request(f, qubits, nq);
+    const FragRequest &r = reqs[f.index];
     double *T = nullptr;
     const bool heis = use_heisenberg(f, eo, r.req_pos.size());
     if (f.clifford && eo->shots_per_variant == 0 && heis == (bool)ex_heis[f.index]) {
@@ -1619,11 +1695,16 @@ ccut_status marginal_skip_enqueue(ccut_plan *p, const ccut_eval_opts *eo, const 
         if (!vmask) return fail(c, CCUT_E_OOM, "device allocation failed");
       }
       double *dist = nullptr;
-      if ((st = variant_dists(p, eo, f, r, &dist, nullptr, nullptr, vmask)) != CCUT_OK) return st;
+      uint16_t *cnt = nullptr;
+      const bool whole = counts_transform(pd, eo, reqs, f, nq, qubits);
+      if ((st = variant_dists(p, eo, f, r, &dist, nullptr, whole ? &cnt : nullptr, vmask)) != CCUT_OK) return st;
       if (f.axes.empty())
         T = dist;
-      else if ((st = pauli_passes(c, f, r, dist, 1ull << r.meas.size(), 0, &T)) != CCUT_OK)
-        return st;
+      else if (cnt)
+        st = counts_passes(c, f, r, cnt, eo->shots_per_variant, true, &T);
+      else
+        st = pauli_passes(c, f, r, dist, 1ull << r.meas.size(), 0, &T);
+      if (st != CCUT_OK) return st;
     }
     RecombFrag &rf = args.f[f.index];
     rf.T = T;
@@ -1681,14 +1762,17 @@ ccut_status marginal_enqueue(ccut_plan *p, const ccut_eval_opts *eo, const uint3
       uint64_t *pm = pre_models ? (*pre_models)[f.index] : nullptr;
       dist = pre_dist ? (*pre_dist)[f.index] : nullptr;
       uint16_t *cnt = nullptr;
-      const bool counts = (int)f.index == g && counts_ok;
+      const bool whole = !dist && (int)f.index != g && counts_transform(pd, eo, reqs, f, nq, qubits);
+      const bool counts = ((int)f.index == g && counts_ok) || whole;
       if (!dist && (st = variant_dists(p, eo, f, r, &dist, pm, counts ? &cnt : nullptr)) != CCUT_OK) return st;
       if ((int)f.index == g)
         T = cnt ? reinterpret_cast<double *>(cnt) : dist;  // tables [preparations][outcomes]: the tensor's layout
-      else if ((st = pauli_passes(c, f, r, dist, 1ull << r.meas.size(), 0, &T)) != CCUT_OK)
+      else if (cnt) {
+        if ((st = counts_passes(c, f, r, cnt, eo->shots_per_variant, !counts_ok, &T)) != CCUT_OK) return st;
+      } else if ((st = pauli_passes(c, f, r, dist, 1ull << r.meas.size(), 0, &T)) != CCUT_OK)
         return st;
-      if (cnt) {
-        args.f[f.index].cnt16 = 1;
+      if (cnt && counts_ok) {
+        args.f[f.index].counts = whole ? 32 : 16;
         args.f[f.index].shots = (double)eo->shots_per_variant;
       }
     }
@@ -2729,7 +2813,8 @@ ccut_status batch_enqueue(ccut_batch *b, bool tune) {
   HIP_TRY(c, hipEventRecord(b->fork_ev, b->stream));
   for (size_t k = 0; k < P; ++k) HIP_TRY(c, hipStreamWaitEvent(b->pool[k], b->fork_ev, 0));
   const bool fp32 = b->eo.precision != CCUT_FP64;
-  std::vector<TileJob> tjobs;
+  std::vector<TileJob> tjobs[3];  // by TileKind
+  std::vector<OutJob> ojobs[2];   // [1]: to values
   std::vector<FoldJob> fjobs;
   std::vector<RecombArgs> rargs(np);
   std::vector<uint8_t> kind(np);  // 0 plain (batched), 1 plain (own launch), 2 MFMA, 3 exact through a fragment (own launch)
@@ -2777,17 +2862,31 @@ ccut_status batch_enqueue(ccut_batch *b, bool tune) {
           // tables [preparations][outcomes] stand in for the tensor (fold_target)
           T = cnt ? reinterpret_cast<double *>(cnt) : dist;
           if (cnt) {
-            args.f[f.index].cnt16 = 1;
+            args.f[f.index].counts = 16;
             args.f[f.index].shots = (double)eo.shots_per_variant;
           }
         } else if (st == CCUT_OK && !f.axes.empty() && tile_job(f, r, dist, xsize, nullptr, J)) {
+          const bool whole = cnt && counts_transform(pd, &eo, reqs, f, nq, qubits);
+          if (whole) (void)tile_job(f, r, dist, xsize, nullptr, J, kTileCountElems);
           J.in16 = cnt;
           J.shots = (double)eo.shots_per_variant;
           J.fold = fold_mask(pd, g, f);  // the fold of fold_jobs, applied in the tile
           folded[f.index] = 1;
-          J.out = T = aget<double>(c, J.x_out << (2 * f.axes.size()));
+          const TileKind tk = !whole ? kTileF64 : counts_contraction(pd, &eo, nq) ? kTileCounts : kTileCountsF64;
+          J.out = T = (double *)c->arena.get((J.x_out << (2 * f.axes.size())) *
+                                             (tk == kTileCounts ? sizeof(int32_t) : sizeof(double)));
           if (!T) st = fail(c, CCUT_E_OOM, "device allocation failed");
-          tjobs.push_back(J);
+          if (tk == kTileCounts) {
+            args.f[f.index].counts = 32;
+            args.f[f.index].shots = J.shots;
+          }
+          OutJob O;
+          if (whole && out_job(f, r, cnt, eo.shots_per_variant, O)) {
+            O.out = T;
+            ojobs[tk == kTileCountsF64].push_back(O);
+          } else {
+            tjobs[tk].push_back(J);
+          }
         } else if (st == CCUT_OK) {
           st = pauli_passes(c, f, r, dist, xsize, 0, &T);
         }
@@ -2807,20 +2906,41 @@ ccut_status batch_enqueue(ccut_batch *b, bool tune) {
     // the contraction recombine() would take
     kind[i] = ef >= 0 ? 3 : plain_contraction(args, nq, fp32) ? (args.n_frags <= 8 ? 0 : 1) : 2;
   }
-  for (size_t k = 0; k < P; ++k) {
-    HIP_TRY(c, hipEventRecord(b->join_ev[k], b->pool[k]));
-    HIP_TRY(c, hipStreamWaitEvent(b->stream, b->join_ev[k], 0));
-  }
-  if (!tjobs.empty()) {
+  // the transforms: into counts on the batch stream, the others beside them
+  for (int values = 0; values < 2; ++values) {
+    std::vector<OutJob> &list = ojobs[values];
+    if (list.empty()) continue;
+    // the costly tiles first
+    std::stable_sort(list.begin(), list.end(), [](const OutJob &x, const OutJob &y) { return x.n_axes > y.n_axes; });
     uint64_t wg = 0;
-    for (TileJob &J : tjobs) {
+    for (OutJob &O : list) {
+      O.wg0 = wg;
+      wg += O.tiles;
+    }
+    c->cur = values && P ? b->pool[0] : b->stream;
+    OutJob *d_o = (OutJob *)upload(c, list.data(), list.size() * sizeof(OutJob));
+    if (!d_o) return fail(c, CCUT_E_OOM, "device allocation failed");
+    KTimer t(c, CCUT_K_TRANSFORM);
+    HIP_TRY(c, launch_transform_out(d_o, (uint32_t)list.size(), wg, values != 0, c->cur));
+  }
+  for (TileKind tk : {kTileF64, kTileCountsF64, kTileCounts}) {
+    std::vector<TileJob> &list = tjobs[tk];
+    if (list.empty()) continue;
+    uint64_t wg = 0;
+    for (TileJob &J : list) {
       J.wg0 = wg;
       wg += J.tiles;
     }
-    TileJob *d_t = (TileJob *)upload(c, tjobs.data(), tjobs.size() * sizeof(TileJob));
+    c->cur = tk == kTileCounts || !P ? b->stream : b->pool[0];
+    TileJob *d_t = (TileJob *)upload(c, list.data(), list.size() * sizeof(TileJob));
     if (!d_t) return fail(c, CCUT_E_OOM, "device allocation failed");
     KTimer t(c, CCUT_K_TRANSFORM);
-    HIP_TRY(c, launch_transform_tiled(d_t, (uint32_t)tjobs.size(), wg, c->cur));
+    HIP_TRY(c, launch_transform_tiled(d_t, (uint32_t)list.size(), wg, tk, c->cur));
+  }
+  c->cur = b->stream;
+  for (size_t k = 0; k < P; ++k) {
+    HIP_TRY(c, hipEventRecord(b->join_ev[k], b->pool[k]));
+    HIP_TRY(c, hipStreamWaitEvent(b->stream, b->join_ev[k], 0));
   }
   if (!fjobs.empty()) {
     FoldJob *d_fj = (FoldJob *)upload(c, fjobs.data(), fjobs.size() * sizeof(FoldJob));

@@ -265,14 +265,14 @@ __device__ inline uint32_t find_job(const J *jobs, uint32_t n, uint64_t idx, F s
 
 // The dispatcher hands consecutive workgroups of a launch to the chip's 8
 // XCDs in turn, and each XCD has an L2 of its own.  xcd_block renumbers
-// workgroup `bid` of `n` so that each XCD runs one contiguous range of
-// logical blocks: neighbouring tiles, which share cache lines, then meet in
-// one L2 instead of being fetched from HBM once per XCD.  A bijection of
-// [0, n) for any n.
-constexpr uint32_t kXcds = 8;
+// workgroup `bid` of `n` so that an XCD runs 8 consecutive logical blocks, the
+// next XCD the next 8: neighbouring tiles, which share cache lines, then meet in
+// one L2 instead of being fetched from HBM once per XCD.  (Whole ranges of the
+// grid per XCD leave XCDs idle where a launch's jobs differ in cost: the count
+// transforms of 256 circuits 134 us instead of 64.)  A bijection of [0, n) for any n.
 __device__ inline uint32_t xcd_block(uint32_t bid, uint32_t n) {
-  const uint32_t x = bid % kXcds, local = bid / kXcds, per = n / kXcds, rem = n % kXcds;
-  return x < rem ? x * (per + 1) + local : rem * (per + 1) + (x - rem) * per + local;
+  const uint32_t first = bid & ~63u;
+  return first + 64 <= n ? first + (bid & 7u) * 8 + ((bid >> 3) & 7u) : bid;
 }
 
 // ---------------------------------------------------------------- launchers
@@ -348,9 +348,12 @@ hipError_t launch_transform_all(const TransformAll &a, const double *in, double 
 // bits below thr, then the outcome bits at x_in positions hpos[0..nh).
 constexpr int kMaxTileAxes = 8;
 constexpr uint32_t kTileElems = 4096, kTileMaxT = 8;
+// Tiles of counts: larger, as the 2^t output entries of a term are a tile's
+// contiguous run (2 for four output axes in a tile of 4096, 8 in one of 16384).
+constexpr uint32_t kTileCountElems = 16384, kTileCountMaxT = 10, kTileCountThreads = 1024;
 struct TileJob {
   const double *in;
-  double *out;
+  double *out;           // or (kTileCounts) int32_t
   const uint16_t *in16;  // when set: the variant data as 16-bit shot counts, value = count / shots
   double shots;
   uint64_t x_in, x_out;
@@ -361,10 +364,29 @@ struct TileJob {
   uint32_t rad[kMaxTileAxes];   // 4 quantum input, 3 quantum output
   uint32_t lpos[kMaxTileAxes];  // output axis: its outcome bit's position in the tile's x
   uint32_t hpos[kMaxTileAxes];  // x_in positions of the outcome bits at or above thr, ascending
-  uint32_t xpos[kTileMaxT];     // the t positions below thr that carry the tile's x_out bits, ascending
+  uint32_t xpos[kTileCountMaxT];  // the t positions below thr that carry the tile's x_out bits, ascending
   uint32_t rmag[kMaxTileAxes];  // floor(2^32 / R_j) + 1, R_j the product of the radices below axis j (0: R_j = 1)
 };
-hipError_t launch_transform_tiled(const TileJob *d_jobs, uint32_t n_jobs, uint64_t total_wg, hipStream_t s);
+// How a launch computes: kTileF64 in fp64; else every job reads in16, folds
+// nothing and sums the counts themselves, writing them (int32_t) or their values.
+enum TileKind { kTileF64, kTileCounts, kTileCountsF64 };
+hipError_t launch_transform_tiled(const TileJob *d_jobs, uint32_t n_jobs, uint64_t total_wg, TileKind kind,
+                                  hipStream_t s);
+
+// The transform of counts of a fragment whose axes are all quantum outputs:
+// out[P][x] (int32_t counts, or their values), the table 3^a variants (axis 0
+// fastest) of 2^xib counts, at most 2^32 bytes.
+constexpr uint32_t kOutAxes = 4;
+struct OutJob {
+  const uint16_t *in;
+  void *out;
+  double shots;
+  uint64_t wg0;                          // first tile of the job in the launch
+  uint32_t n_axes, xib, xob, t, tiles;   // 2^xob outcomes x, 2^t of them a tile
+  uint32_t pos[kOutAxes], asc[kOutAxes]; // the axes' outcome bits, and ascending
+};
+hipError_t launch_transform_out(const OutJob *d_jobs, uint32_t n_jobs, uint64_t total_tiles, bool values,
+                                hipStream_t s);
 
 hipError_t launch_transform_pass(const double *in, double *out, uint64_t outer, uint64_t inner_digits,
                                  uint64_t xsize_in, uint64_t lo, int mode, hipStream_t s);
@@ -435,7 +457,7 @@ hipError_t launch_ml_correct(const MlJob &h, const MlJob *d_job, hipStream_t s);
 
 struct RecombFrag {
   const double *T;          // T_f[p_f][row], row count `rows`
-  uint32_t cnt16;           // 1: T holds 16-bit shot counts, the value is count / shots
+  uint32_t counts;          // 16, 32: T holds whole shot counts of so many bits (32: signed), the value is count / shots
   uint32_t pad_;
   double shots;
   uint32_t n_axes;

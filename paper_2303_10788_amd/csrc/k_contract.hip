@@ -11,6 +11,8 @@
 // applied one axis at a time; the fragment tensor ends as T_f[p_f][b_f].
 #include <algorithm>
 
+#include <type_traits>
+
 #include "common.hpp"
 
 // products and sums exactly as written (no contraction into fma), so every
@@ -127,17 +129,24 @@ __global__ __launch_bounds__(256) void transform_all_kernel(const TransformAll A
 // slots of bases X, Y, Z and Z in the outcome-1 slot of basis X.
 // A workgroup takes `per_wg` consecutive tiles of the launch in turn (fewer,
 // longer workgroups: the dispatcher, not the tiles, limits short ones), and
-// the workgroups of one XCD take consecutive ranges (xcd_block): the tiles
+// the workgroups of one XCD take consecutive tiles (xcd_block): the tiles
 // of a variant row share its cache lines.
-constexpr uint32_t kTileThreads = 256;
-__device__ __attribute__((always_inline)) void tile_body(const TileJob &J, uint64_t u, double *s, uint32_t *s_xdep,
+template <class V>
+constexpr uint32_t kTileThreads = std::is_same<V, double>::value ? 256 : kTileCountThreads;
+template <class V, class O>
+__device__ __attribute__((always_inline)) void tile_body(const TileJob &J, uint64_t u, V *s, uint32_t *s_xdep,
                                                          uint32_t (*s_pv)[256]);
 
-__global__ __launch_bounds__(kTileThreads) void transform_tiled_kernel(const TileJob *__restrict__ jobs,
+// V double, or int32_t: sampled tables as the whole counts they are (sums and
+// differences of counts below 2^16 over a tile's axes are exact, so the values
+// are no further from the exact ones).  A tile takes half the LDS, and written
+// as counts (O int32_t; the contraction scales them) half the bytes.
+template <class V, class O>
+__global__ __launch_bounds__(kTileThreads<V>) void transform_tiled_kernel(const TileJob *__restrict__ jobs,
                                                                        uint32_t n_jobs, uint64_t total,
                                                                        uint32_t per_wg) {
-  __shared__ double s[kTileElems];
-  __shared__ uint32_t s_xdep[1u << kTileMaxT];
+  __shared__ V s[std::is_same<V, double>::value ? kTileElems : kTileCountElems];
+  __shared__ uint32_t s_xdep[1u << (std::is_same<V, double>::value ? kTileMaxT : kTileCountMaxT)];
   __shared__ uint32_t s_pv[2][256];
   const uint64_t g0 = (uint64_t)xcd_block(blockIdx.x, gridDim.x) * per_wg;
   const uint64_t g1 = g0 + per_wg < total ? g0 + per_wg : total;
@@ -145,7 +154,7 @@ __global__ __launch_bounds__(kTileThreads) void transform_tiled_kernel(const Til
   for (uint64_t g = g0; g < g1; ++g) {
     while (jb + 1 < n_jobs && jobs[jb + 1].wg0 <= g) ++jb;
     if (g > g0) __syncthreads();  // the previous tile's LDS is consumed
-    tile_body(jobs[jb], g - jobs[jb].wg0, s, s_xdep, s_pv);
+    tile_body<V, O>(jobs[jb], g - jobs[jb].wg0, s, s_xdep, s_pv);
   }
 }
 
@@ -168,20 +177,24 @@ __device__ inline uint32_t pv_byte(uint32_t pb, const uint32_t *Rv, const uint32
   return (v << lb) | l;
 }
 
-__device__ __attribute__((always_inline)) void tile_body(const TileJob &J, uint64_t u, double *s, uint32_t *s_xdep,
+template <class V, class O>
+__device__ __attribute__((always_inline)) void tile_body(const TileJob &J, uint64_t u, V *s, uint32_t *s_xdep,
                                                          uint32_t (*s_pv)[256]) {
-  static_assert(kTileThreads == 256, "one byte of P per thread in the offset tables");
+  constexpr bool kCounts = !std::is_same<V, double>::value;
+  constexpr uint32_t kThreads = kTileThreads<V>;
+  static_assert(kThreads >= 256, "one byte of P per thread in the offset tables");
   const uint32_t tid = threadIdx.x;
-  const uint32_t a = J.n_axes, V = J.v_count, lb = J.lbits, t = J.t, thr = J.thr, nh = J.nh;
+  const uint32_t a = J.n_axes, nv = J.v_count, lb = J.lbits, t = J.t, thr = J.thr, nh = J.nh;
   const uint32_t XL = 1u << lb, XT = 1u << t;
   // the job's per-axis positions in registers, read once (uniform).  Slots
   // past the job's axes hold 0 and are never selected: the bits and digits
   // they would place are 0, so the index arithmetic below needs no guards.
-  uint32_t hp[kMaxTileAxes], xp[kTileMaxT];
+  constexpr uint32_t kMaxT = kCounts ? kTileCountMaxT : kTileMaxT;
+  uint32_t hp[kMaxTileAxes], xp[kMaxT];
 #pragma unroll
   for (uint32_t h = 0; h < (uint32_t)kMaxTileAxes; ++h) hp[h] = J.hpos[h];
 #pragma unroll
-  for (uint32_t i = 0; i < kTileMaxT; ++i) xp[i] = J.xpos[i];
+  for (uint32_t i = 0; i < kMaxT; ++i) xp[i] = J.xpos[i];
   // the tile's fixed x_in bits: u's bits in the non-outcome positions from
   // thr up, i.e. u << thr with a zero inserted at each outcome position at
   // or above thr (ascending)
@@ -189,10 +202,10 @@ __device__ __attribute__((always_inline)) void tile_body(const TileJob &J, uint6
 #pragma unroll
   for (uint32_t h = 0; h < (uint32_t)kMaxTileAxes; ++h)
     if (h < nh) base = ((base >> hp[h]) << (hp[h] + 1)) | (base & ((1ull << hp[h]) - 1ull));
-  for (uint32_t xo = tid; xo < XT; xo += kTileThreads) {
+  for (uint32_t xo = tid; xo < XT; xo += kThreads) {
     uint32_t l = 0;
 #pragma unroll
-    for (uint32_t i = 0; i < kTileMaxT; ++i) l |= ((xo >> i) & 1u) << xp[i];
+    for (uint32_t i = 0; i < kMaxT; ++i) l |= ((xo >> i) & 1u) << xp[i];
     s_xdep[xo] = l;
   }
   // per-axis radix products, output flags and outcome positions (slots past
@@ -207,11 +220,13 @@ __device__ __attribute__((always_inline)) void tile_body(const TileJob &J, uint6
       lq[j] = J.lpos[j];
       Rj *= J.rad[j] ? J.rad[j] : 1u;
     }
-    s_pv[0][tid] = pv_byte<0>(tid, Rv, o3, lq, lb);
-    s_pv[1][tid] = pv_byte<1>(tid, Rv, o3, lq, lb);
+    if (kThreads == 256 || tid < 256) {
+      s_pv[0][tid] = pv_byte<0>(tid, Rv, o3, lq, lb);
+      s_pv[1][tid] = pv_byte<1>(tid, Rv, o3, lq, lb);
+    }
   }
   const uint32_t lowmask = (1u << thr) - 1u;
-  const uint32_t n_el = V << lb;
+  const uint32_t n_el = nv << lb;
   // x_in bits of a tile-local index l: bits below thr in place, bit thr + h
   // at the outcome position hp[h] (a bit permutation, so the deposit of
   // disjoint bit sets or's)
@@ -225,39 +240,43 @@ __device__ __attribute__((always_inline)) void tile_body(const TileJob &J, uint6
   // disjoint bits: this thread's part is deposited once, the second part
   // (nonzero only when XL > 256) is uniform
   const uint64_t xt = base | dep(tid & (XL - 1u));
-  // every element's table index first, then all loads, then the
-  // conversions: no load waits on the one before it
-  constexpr uint32_t kPer = kTileElems / kTileThreads;
-  uint64_t idx[kPer];
+  // four elements at a time, their loads before the first use (a tile of few
+  // axes is smaller than the LDS it may take)
+  constexpr uint32_t kPer = (kCounts ? kTileCountElems : kTileElems) / kThreads, kGroup = 4;
+  const double inv = kCounts ? 0.0 : 1.0 / J.shots;  // a table entry is count x fl(1/shots)
+#pragma unroll 2
+  for (uint32_t i0 = 0; i0 < kPer; i0 += kGroup) {
+    if (i0 * kThreads >= n_el) break;
+    uint64_t idx[kGroup];
 #pragma unroll
-  for (uint32_t i = 0; i < kPer; ++i) {
-    const uint32_t e = tid + i * kTileThreads;
-    const uint32_t v = e >> lb;
-    uint64_t x = xt;
-    if (XL > kTileThreads) x |= dep((i * kTileThreads) & (XL - 1u));
-    idx[i] = e < n_el ? (uint64_t)v * J.x_in + x : 0;  // entry 0 stands in for the lanes past the tile
-  }
-  if (J.in16) {
-    const __attribute__((address_space(1))) uint16_t *in16 =
-        (const __attribute__((address_space(1))) uint16_t *)J.in16;
-    const double inv = 1.0 / J.shots;  // a table entry is count x fl(1/shots)
-    uint32_t c[kPer];
-#pragma unroll
-    for (uint32_t i = 0; i < kPer; ++i) c[i] = in16[idx[i]];
-#pragma unroll
-    for (uint32_t i = 0; i < kPer; ++i) {
-      const uint32_t e = tid + i * kTileThreads;
-      if (e < n_el) s[e] = (double)c[i] * inv;
+    for (uint32_t i = 0; i < kGroup; ++i) {
+      const uint32_t e = tid + (i0 + i) * kThreads;
+      const uint32_t v = e >> lb;
+      uint64_t x = xt;
+      if (XL > kThreads) x |= dep(((i0 + i) * kThreads) & (XL - 1u));
+      idx[i] = e < n_el ? (uint64_t)v * J.x_in + x : 0;  // entry 0 stands in for the lanes past the tile
     }
-  } else {
-    const __attribute__((address_space(1))) double *in = (const __attribute__((address_space(1))) double *)J.in;
-    double d[kPer];
+    if (kCounts || J.in16) {
+      const __attribute__((address_space(1))) uint16_t *in16 =
+          (const __attribute__((address_space(1))) uint16_t *)J.in16;
+      uint32_t c[kGroup];
 #pragma unroll
-    for (uint32_t i = 0; i < kPer; ++i) d[i] = in[idx[i]];
+      for (uint32_t i = 0; i < kGroup; ++i) c[i] = in16[idx[i]];
 #pragma unroll
-    for (uint32_t i = 0; i < kPer; ++i) {
-      const uint32_t e = tid + i * kTileThreads;
-      if (e < n_el) s[e] = d[i];
+      for (uint32_t i = 0; i < kGroup; ++i) {
+        const uint32_t e = tid + (i0 + i) * kThreads;
+        if (e < n_el) s[e] = kCounts ? (V)c[i] : (V)((double)c[i] * inv);
+      }
+    } else {
+      const __attribute__((address_space(1))) double *in = (const __attribute__((address_space(1))) double *)J.in;
+      double d[kGroup];
+#pragma unroll
+      for (uint32_t i = 0; i < kGroup; ++i) d[i] = in[idx[i]];
+#pragma unroll
+      for (uint32_t i = 0; i < kGroup; ++i) {
+        const uint32_t e = tid + (i0 + i) * kThreads;
+        if (e < n_el) s[e] = (V)d[i];
+      }
     }
   }
   __syncthreads();
@@ -273,25 +292,25 @@ __device__ __attribute__((always_inline)) void tile_body(const TileJob &J, uint6
       r = ((gh - q * R) << lb) | (g & (XL - 1u));
     };
     if (J.rad[j] == 4) {
-      for (uint32_t g = tid; g < (n_el >> 2); g += kTileThreads) {
+      for (uint32_t g = tid; g < (n_el >> 2); g += kThreads) {
         uint32_t q, r;
         split(g, q, r);
         const uint32_t b = q * 4 * S + r;
-        const double p0 = s[b], p1 = s[b + S], pp = s[b + 2 * S], pi = s[b + 3 * S];
+        const V p0 = s[b], p1 = s[b + S], pp = s[b + 2 * S], pi = s[b + 3 * S];
         s[b] = p0 + p1;
-        s[b + S] = 2.0 * pp - p0 - p1;
-        s[b + 2 * S] = 2.0 * pi - p0 - p1;
+        s[b + S] = (V)2 * pp - p0 - p1;
+        s[b + 2 * S] = (V)2 * pi - p0 - p1;
         s[b + 3 * S] = p0 - p1;
       }
     } else {
       const uint32_t lp = J.lpos[j], half = XL >> 1, o1 = 1u << lp;
-      for (uint32_t g = tid; g < (V / 3) * half; g += kTileThreads) {
+      for (uint32_t g = tid; g < (nv / 3) * half; g += kThreads) {
         const uint32_t li = g & (half - 1u), vg = g >> (lb - 1);
         const uint32_t l = ((li >> lp) << (lp + 1)) | (li & (o1 - 1u));
         const uint32_t vq = __umulhi(vg, mag) + (vg & m1);
         const uint32_t b = ((vq * 3 * R + (vg - vq * R)) << lb) | l;
-        const double x0 = s[b], x1 = s[b + o1], y0 = s[b + S], y1 = s[b + S + o1];
-        const double z0 = s[b + 2 * S], z1 = s[b + 2 * S + o1];
+        const V x0 = s[b], x1 = s[b + o1], y0 = s[b + S], y1 = s[b + S + o1];
+        const V z0 = s[b + 2 * S], z1 = s[b + 2 * S + o1];
         s[b] = z0 + z1;
         s[b + S] = x0 - x1;
         s[b + 2 * S] = y0 - y1;
@@ -304,14 +323,14 @@ __device__ __attribute__((always_inline)) void tile_body(const TileJob &J, uint6
   // folded axes: the four Pauli slots of the axis rewritten into the
   // preparation basis of the fragment downstream of its cut (the map of
   // launch_fold: s=0: I - X - Y + Z, s=1: I - X - Y - Z, s=+: 2X, s=+i: 2Y)
-  if (J.fold) {
+  if (!kCounts && J.fold) {
     R = 1;
     for (uint32_t j = 0; j < a; ++j) {
       if ((J.fold >> j) & 1u) {
         const uint32_t S = R << lb, mag = J.rmag[j];
         const uint32_t m1 = mag ? 0u : ~0u;
-        const uint32_t ngroups = J.rad[j] == 4 ? (n_el >> 2) : (V / 3) * (XL >> 1);
-        for (uint32_t g = tid; g < ngroups; g += kTileThreads) {
+        const uint32_t ngroups = J.rad[j] == 4 ? (n_el >> 2) : (nv / 3) * (XL >> 1);
+        for (uint32_t g = tid; g < ngroups; g += kThreads) {
           uint32_t b, s1, s2, s3;
           if (J.rad[j] == 4) {
             const uint32_t gh = g >> lb, q = __umulhi(gh, mag) + (gh & m1);
@@ -325,11 +344,11 @@ __device__ __attribute__((always_inline)) void tile_body(const TileJob &J, uint6
             b = ((vq * 3 * R + (vg - vq * R)) << lb) | l;
             s1 = b + S, s2 = b + 2 * S, s3 = b + o1;
           }
-          const double vI = s[b], vX = s[s1], vY = s[s2], vZ = s[s3];
+          const V vI = s[b], vX = s[s1], vY = s[s2], vZ = s[s3];
           s[b] = ((vI - vX) - vY) + vZ;
           s[s1] = ((vI - vX) - vY) - vZ;
-          s[s2] = 2.0 * vX;
-          s[s3] = 2.0 * vY;
+          s[s2] = (V)2 * vX;
+          s[s3] = (V)2 * vY;
         }
         __syncthreads();
       }
@@ -340,13 +359,151 @@ __device__ __attribute__((always_inline)) void tile_body(const TileJob &J, uint6
   // source slot from the two byte tables (P < 4^a <= 4096) and s_xdep;
   // stored through a global pointer (a generic store would hold up the next
   // LDS read until it completes)
-  __attribute__((address_space(1))) double *out = (__attribute__((address_space(1))) double *)J.out;
-  const uint64_t x_out = J.x_out, ob = (uint64_t)u << t;
+  __attribute__((address_space(1))) O *out = (__attribute__((address_space(1))) O *)J.out;
+  const double scale = kCounts && !std::is_same<O, V>::value ? 1.0 / J.shots : 1.0;
+  const uint32_t xob = (uint32_t)__builtin_ctzll(J.x_out);  // (x_out is a power of two)
+  const uint64_t ob = (uint64_t)u << t;
   const uint32_t n_out = XT << (2 * a);
-  for (uint32_t e = tid; e < n_out; e += kTileThreads) {
+  for (uint32_t e = tid; e < n_out; e += kThreads) {
     const uint32_t xo = e & (XT - 1u), P = e >> t;
     const uint32_t off = s_pv[0][P & 255u] + s_pv[1][P >> 8] + s_xdep[xo];
-    out[(uint64_t)P * x_out + ob + xo] = s[off];
+    out[((uint64_t)P << xob) + ob + xo] = std::is_same<O, V>::value ? (O)s[off] : (O)((double)s[off] * scale);
+  }
+}
+
+// The transform of a sampled fragment whose axes are all quantum outputs (at
+// most four), on its counts.  A basis' two outcomes of an axis become I, X, Y or
+// Z (I, Z from the Z basis), all exact sums of whole numbers.  Two axes are taken
+// in registers, 36 counts to 16: of one or two axes straight from the table to
+// the tensor; of three or four through LDS once, a tile of 2^t outcomes x with
+// every pair (I, X, Y, Z)^2 of axes 0 and 1 by every basis and outcome of the
+// others.  A thread's 36 loads (and 16 stores) differ by uniform offsets alone,
+// so an entry costs its load and about one addition, where the tiled passes
+// spent some 25 instructions on each load and 40 on each group of six: they were
+// bound by instructions.  Measured for the sampled fragments of 256 circuits (34
+// million counts, 16 million entries): 64 us, 222 us tiled.
+constexpr uint32_t kOutThreads = 256, kOutT = 4;
+constexpr uint32_t kOutRow = 36 * (1u << kOutT) + 16;  // LDS words of one (p0, p1): padded, two rows span the banks
+
+// six counts (basis X, Y, Z; outcome 0, 1) to I, X, Y, Z
+__device__ inline void out_axis(const int32_t (&in)[6], int32_t (&out)[4]) {
+  out[0] = in[4] + in[5];
+  out[1] = in[0] - in[1];
+  out[2] = in[2] - in[3];
+  out[3] = in[4] - in[5];
+}
+
+// load(k): entry k = (2 d0 + c0) + 6 (2 d1 + c1); out[p0 + 4 p1]
+template <class Load>
+__device__ __attribute__((always_inline)) inline void out_pair(Load load, int32_t (&out)[16]) {
+  int32_t v[36], t[4][6];
+#pragma unroll
+  for (uint32_t k = 0; k < 36; ++k) v[k] = load(k);
+#pragma unroll
+  for (uint32_t k1 = 0; k1 < 6; ++k1) {
+    int32_t in[6], o[4];
+#pragma unroll
+    for (uint32_t k0 = 0; k0 < 6; ++k0) in[k0] = v[6 * k1 + k0];
+    out_axis(in, o);
+#pragma unroll
+    for (uint32_t p0 = 0; p0 < 4; ++p0) t[p0][k1] = o[p0];
+  }
+#pragma unroll
+  for (uint32_t p0 = 0; p0 < 4; ++p0) {
+    int32_t o[4];
+    out_axis(t[p0], o);
+#pragma unroll
+    for (uint32_t p1 = 0; p1 < 4; ++p1) out[p0 + 4 * p1] = o[p1];
+  }
+}
+
+template <class O>
+__global__ __launch_bounds__(kOutThreads) void transform_out_kernel(const OutJob *__restrict__ jobs, uint32_t n_jobs,
+                                                                    uint64_t total, uint32_t per_wg) {
+  __shared__ int32_t s[16 * kOutRow];
+  typedef const __attribute__((address_space(4))) OutJob c_OutJob;
+  const uint32_t tid = threadIdx.x;
+  const uint64_t g0 = (uint64_t)xcd_block(blockIdx.x, gridDim.x) * per_wg;
+  const uint64_t g1 = g0 + per_wg < total ? g0 + per_wg : total;
+  uint32_t jb = find_job(jobs, n_jobs, g0, [](const OutJob &J) { return J.wg0; });
+  for (uint64_t g = g0; g < g1; ++g) {
+    while (jb + 1 < n_jobs && jobs[jb + 1].wg0 <= g) ++jb;
+    c_OutJob &J = *(c_OutJob *)(uint64_t)(jobs + jb);
+    const uint32_t a = J.n_axes, xib = J.xib, xob = J.xob, t = J.t, XT = 1u << t;
+    const uint32_t x0 = (uint32_t)(g - J.wg0) << t;
+    const __attribute__((address_space(1))) char *in = (const __attribute__((address_space(1))) char *)J.in;
+    __attribute__((address_space(1))) char *out = (__attribute__((address_space(1))) char *)J.out;
+    const double scale = 1.0 / J.shots;
+    // table index of outcome x with the axes' outcome bits 0 (positions ascending)
+    auto dep = [&](uint32_t x) {
+#pragma unroll
+      for (uint32_t j = 0; j < kOutAxes; ++j)
+        if (j < a) x = ((x >> J.asc[j]) << (J.asc[j] + 1)) | (x & ((1u << J.asc[j]) - 1u));
+      return x;
+    };
+    // byte offset of axis j's entry k = 2 d + c (uniform)
+    auto step = [&](uint32_t j, uint32_t k) {
+      const uint32_t radix = j == 0 ? 1u : j == 1 ? 3u : j == 2 ? 9u : 27u;
+      return ((((k >> 1) * radix) << xib) + ((k & 1u) << J.pos[j])) * 2u;
+    };
+    auto put = [&](uint32_t P, uint32_t off, int32_t c) {  // off: entry offset below the uniform P << xob
+      __attribute__((address_space(1))) char *q = out + ((uint64_t)P << xob) * sizeof(O);
+      *(__attribute__((address_space(1))) O *)(q + (uint32_t)(off * sizeof(O))) =
+          std::is_same<O, int32_t>::value ? (O)c : (O)((double)c * scale);
+    };
+    if (a <= 2) {
+      if (tid < XT) {
+        const uint32_t x = x0 + tid, at = dep(x) * 2u;
+        auto get = [&](uint32_t off) -> int32_t {
+          return *(const __attribute__((address_space(1))) uint16_t *)(in + off + at);
+        };
+        if (a == 2) {
+          int32_t o[16];
+          out_pair([&](uint32_t k) { return get(step(0, k % 6) + step(1, k / 6)); }, o);
+#pragma unroll
+          for (uint32_t P = 0; P < 16; ++P) put(P, x, o[P]);
+        } else {
+          int32_t v[6], o[4];
+#pragma unroll
+          for (uint32_t k = 0; k < 6; ++k) v[k] = get(step(0, k));
+          out_axis(v, o);
+#pragma unroll
+          for (uint32_t P = 0; P < 4; ++P) put(P, x, o[P]);
+        }
+      }
+      continue;
+    }
+    const uint32_t n2 = a == 3 ? 6u : 36u;
+    if (g > g0) __syncthreads();  // the tile before is read
+    for (uint32_t i = tid; i < n2 << t; i += kOutThreads) {
+      const uint32_t x = i & (XT - 1u), k = i >> t, k3 = k / 6, k2 = k - 6 * k3;
+      const uint32_t at = dep(x0 + x) * 2u + step(2, k2) + (a == 4 ? step(3, k3) : 0u);
+      int32_t o[16];
+      out_pair([&](uint32_t q) -> int32_t {
+        return *(const __attribute__((address_space(1))) uint16_t *)(in + (step(0, q % 6) + step(1, q / 6)) + at);
+      }, o);
+#pragma unroll
+      for (uint32_t P = 0; P < 16; ++P) s[P * kOutRow + i] = o[P];
+    }
+    __syncthreads();
+    for (uint32_t i = tid; i < 16u << t; i += kOutThreads) {
+      const uint32_t x = i & (XT - 1u), P = i >> t;
+      const int32_t *row = s + P * kOutRow + x;
+      const uint32_t off = (P << xob) + x0 + x;
+      if (a == 4) {
+        int32_t o[16];
+        out_pair([&](uint32_t q) { return row[q << t]; }, o);
+#pragma unroll
+        for (uint32_t Q = 0; Q < 16; ++Q) put(Q << 4, off, o[Q]);
+      } else {
+        int32_t v[6], o[4];
+#pragma unroll
+        for (uint32_t k = 0; k < 6; ++k) v[k] = row[k << t];
+        out_axis(v, o);
+#pragma unroll
+        for (uint32_t Q = 0; Q < 4; ++Q) put(Q << 4, off, o[Q]);
+      }
+    }
   }
 }
 
@@ -785,14 +942,39 @@ hipError_t launch_recombine_batch(const RcJob *d_jobs, uint32_t n_jobs, uint64_t
   return hipGetLastError();
 }
 
-hipError_t launch_transform_tiled(const TileJob *d_jobs, uint32_t n_jobs, uint64_t total_tiles, hipStream_t s) {
+hipError_t launch_transform_out(const OutJob *d_jobs, uint32_t n_jobs, uint64_t total_tiles, bool values,
+                                hipStream_t s) {
+  if (n_jobs == 0 || total_tiles == 0) return hipSuccess;
+  // about 8192 workgroups, at most 8 tiles each
+  const uint32_t per_wg = (uint32_t)std::min<uint64_t>(8, std::max<uint64_t>(1, total_tiles / 8192));
+  const uint64_t wgs = (total_tiles + per_wg - 1) / per_wg;
+  if (wgs > 0x7FFFFFFFull) return hipErrorInvalidValue;
+  if (values)
+    hipLaunchKernelGGL(transform_out_kernel<double>, dim3((unsigned)wgs), dim3(kOutThreads), 0, s, d_jobs, n_jobs,
+                       total_tiles, per_wg);
+  else
+    hipLaunchKernelGGL(transform_out_kernel<int32_t>, dim3((unsigned)wgs), dim3(kOutThreads), 0, s, d_jobs, n_jobs,
+                       total_tiles, per_wg);
+  return hipGetLastError();
+}
+
+hipError_t launch_transform_tiled(const TileJob *d_jobs, uint32_t n_jobs, uint64_t total_tiles,
+                                  TileKind kind, hipStream_t s) {
   if (n_jobs == 0 || total_tiles == 0) return hipSuccess;
   // about 4096 workgroups, at most 16 tiles each
   const uint32_t per_wg = (uint32_t)std::min<uint64_t>(16, std::max<uint64_t>(1, total_tiles / 4096));
   const uint64_t wgs = (total_tiles + per_wg - 1) / per_wg;
   if (wgs > 0x7FFFFFFFull) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(transform_tiled_kernel, dim3((unsigned)wgs), dim3(kTileThreads), 0, s, d_jobs, n_jobs,
-                     total_tiles, per_wg);
+#define CCUT_TILED(V, O)                                                                                           \
+  hipLaunchKernelGGL((transform_tiled_kernel<V, O>), dim3((unsigned)wgs), dim3(kTileThreads<V>), 0, s, d_jobs, n_jobs, \
+                     total_tiles, per_wg)
+  if (kind == kTileCounts)
+    CCUT_TILED(int32_t, int32_t);
+  else if (kind == kTileCountsF64)
+    CCUT_TILED(int32_t, double);
+  else
+    CCUT_TILED(double, double);
+#undef CCUT_TILED
   return hipGetLastError();
 }
 

@@ -57,10 +57,13 @@ __device__ inline uint64_t frag_p(const GemmArgs *__restrict__ G, uint32_t f, ui
   return p;
 }
 
-// A fragment tensor entry: fp64, or a 16-bit shot count times fl(1/shots)
-// (the value the fp64 table would hold).
-__device__ inline double tval(const RecombFrag &F, uint64_t i) {
-  return F.cnt16 ? (double)reinterpret_cast<const uint16_t *>(F.T)[i] * (1.0 / F.shots) : F.T[i];
+// A fragment tensor entry: fp64, or a whole shot count (of 16 bits, or 32 and
+// signed) times fl(1/shots).
+template <class F>
+__device__ inline double tval(const F &f, uint64_t i) {
+  if (f.counts == 16) return (double)reinterpret_cast<const uint16_t *>(f.T)[i] * (1.0 / f.shots);
+  if (f.counts == 32) return (double)reinterpret_cast<const int32_t *>(f.T)[i] * (1.0 / f.shots);
+  return f.T[i];
 }
 
 __device__ inline double side_value(const GemmArgs *__restrict__ G, const GemmSide &S, uint32_t row, uint64_t P) {
@@ -74,7 +77,7 @@ __device__ inline double side_value(const GemmArgs *__restrict__ G, const GemmSi
     const uint32_t r = (row >> sh) & ((1u << bits) - 1u);
     c_RecombFrag &F = C->f[f];
     const uint64_t idx = frag_p(G, f, P) * F.rows + r;
-    v *= F.cnt16 ? (double)reinterpret_cast<const uint16_t *>(F.T)[idx] * (1.0 / F.shots) : F.T[idx];
+    v *= tval(F, idx);
   }
   return v;
 }
@@ -104,9 +107,13 @@ __device__ inline const RecombFrag *direct_side(const GemmArgs *__restrict__ G, 
 struct DirOp {
   const __attribute__((address_space(1))) double *T64;
   const __attribute__((address_space(1))) uint16_t *T16;
+  const __attribute__((address_space(1))) int32_t *T32;
   double inv;  // fl(1 / shots): a count's value is count x inv
   uint64_t rows;
-  bool c16;
+  uint32_t counts;
+  __device__ double at(uint64_t i) const {
+    return counts == 16 ? (double)T16[i] * inv : counts == 32 ? (double)T32[i] * inv : T64[i];
+  }
 };
 
 __device__ inline DirOp dir_op(const RecombFrag *F) {
@@ -115,9 +122,10 @@ __device__ inline DirOp dir_op(const RecombFrag *F) {
   c_RecombFrag &C = *(c_RecombFrag *)(uint64_t)F;
   D.T64 = (const __attribute__((address_space(1))) double *)(uint64_t)C.T;
   D.T16 = (const __attribute__((address_space(1))) uint16_t *)(uint64_t)C.T;
+  D.T32 = (const __attribute__((address_space(1))) int32_t *)(uint64_t)C.T;
   D.inv = 1.0 / C.shots;
   D.rows = C.rows;
-  D.c16 = C.cnt16 != 0;
+  D.counts = C.counts;
   return D;
 }
 
@@ -136,10 +144,15 @@ __device__ __attribute__((always_inline)) inline void direct_gather(const DirOp 
     ok[i] = col_ok && j < k1;
     ix[i] = ok[i] ? j * D.rows + col : 0;  // entry 0 stands in for the lanes past the range
   }
-  if (D.c16) {
-    uint32_t c[NPER];
+  if (D.counts) {
+    int32_t c[NPER];
+    if (D.counts == 16) {
 #pragma unroll
-    for (uint32_t i = 0; i < NPER; ++i) c[i] = D.T16[ix[i]];
+      for (uint32_t i = 0; i < NPER; ++i) c[i] = D.T16[ix[i]];
+    } else {
+#pragma unroll
+      for (uint32_t i = 0; i < NPER; ++i) c[i] = D.T32[ix[i]];
+    }
 #pragma unroll
     for (uint32_t i = 0; i < NPER; ++i) v[i] = ok[i] ? (double)c[i] * D.inv : 0.0;
   } else {
@@ -151,7 +164,7 @@ __device__ __attribute__((always_inline)) inline void direct_gather(const DirOp 
 }
 
 // direct_gather in two steps, so a chunk's loads can be issued a chunk
-// ahead: the raw entries (16-bit count or fp64 bits) ...
+// ahead: the raw entries (a count or fp64 bits) ...
 template <uint32_t NPER, uint32_t STEP>
 __device__ __attribute__((always_inline)) inline void direct_load(const DirOp &D, uint64_t kb, uint64_t k1,
                                                                   uint32_t kk0, uint32_t col, bool col_ok,
@@ -162,9 +175,12 @@ __device__ __attribute__((always_inline)) inline void direct_load(const DirOp &D
     const uint64_t j = kb + kk0 + STEP * i;
     ix[i] = col_ok && j < k1 ? j * D.rows + col : 0;
   }
-  if (D.c16) {
+  if (D.counts == 16) {
 #pragma unroll
     for (uint32_t i = 0; i < NPER; ++i) raw[i] = D.T16[ix[i]];
+  } else if (D.counts == 32) {
+#pragma unroll
+    for (uint32_t i = 0; i < NPER; ++i) raw[i] = (uint32_t)D.T32[ix[i]];
   } else {
 #pragma unroll
     for (uint32_t i = 0; i < NPER; ++i) raw[i] = (uint64_t)__double_as_longlong(D.T64[ix[i]]);
@@ -178,7 +194,7 @@ __device__ __attribute__((always_inline)) inline void direct_value(const DirOp &
 #pragma unroll
   for (uint32_t i = 0; i < NPER; ++i) {
     const bool ok = col_ok && kb + kk0 + STEP * i < k1;
-    const double x = D.c16 ? (double)(uint32_t)raw[i] * D.inv : __longlong_as_double((long long)raw[i]);
+    const double x = D.counts ? (double)(int32_t)raw[i] * D.inv : __longlong_as_double((long long)raw[i]);
     v[i] = ok ? x : 0.0;
   }
 }
@@ -226,7 +242,7 @@ __device__ inline void fac_fill(const GemmArgs *__restrict__ G, bool left, uint3
       if (j < k1) {
         const uint64_t p = C->col_of && f == C->col_frag ? C->col_of[j] : frag_p(G, f, C->terms ? C->terms[j] : j);
         const uint64_t idx = p * F.rows + (fixed | r);
-        v = F.cnt16 ? (double)reinterpret_cast<const uint16_t *>(F.T)[idx] * (1.0 / F.shots) : F.T[idx];
+        v = tval(F, idx);
       }
       fac[off + e] = v;
     }
@@ -516,6 +532,9 @@ constexpr uint32_t SK_N = 256, SK_M = 32, SK_KC = 64;
 // Column loads through global pointers: vector-memory loads only, so the
 // LDS reads of the loop never wait for them.
 typedef const __attribute__((address_space(1))) uint16_t g_u16;
+typedef const __attribute__((address_space(1))) int32_t g_i32;
+typedef int32_t i2v __attribute__((ext_vector_type(2)));
+typedef int32_t i4v __attribute__((ext_vector_type(4)));
 typedef const __attribute__((address_space(1))) double g_f64;
 typedef double d2v __attribute__((ext_vector_type(2)));
 typedef uint32_t u2v __attribute__((ext_vector_type(2)));
@@ -528,6 +547,9 @@ struct ColLoad<1> {
   typedef double Raw64;
   __device__ static Raw16 cnt(g_u16 *p) { return p[0]; }
   __device__ static void cnt_val(Raw16 w, double inv, double *b) { b[0] = (double)w * inv; }
+  typedef int32_t Raw32;
+  __device__ static Raw32 i32(g_i32 *p) { return p[0]; }
+  __device__ static void i32_val(Raw32 w, double inv, double *b) { b[0] = (double)w * inv; }
   __device__ static Raw64 f64(g_f64 *p) { return p[0]; }
   __device__ static void f64_val(Raw64 v, double *b) { b[0] = v; }
 };
@@ -540,6 +562,9 @@ struct ColLoad<2> {
     b[0] = (double)(w & 0xFFFFu) * inv;
     b[1] = (double)(w >> 16) * inv;
   }
+  typedef i2v Raw32;
+  __device__ static Raw32 i32(g_i32 *p) { return *reinterpret_cast<const __attribute__((address_space(1))) i2v *>(p); }
+  __device__ static void i32_val(Raw32 w, double inv, double *b) { b[0] = (double)w.x * inv, b[1] = (double)w.y * inv; }
   __device__ static Raw64 f64(g_f64 *p) { return *reinterpret_cast<const __attribute__((address_space(1))) d2v *>(p); }
   __device__ static void f64_val(Raw64 v, double *b) { b[0] = v.x, b[1] = v.y; }
 };
@@ -555,6 +580,11 @@ struct ColLoad<4> {
     b[1] = (double)(w.x >> 16) * inv;
     b[2] = (double)(w.y & 0xFFFFu) * inv;
     b[3] = (double)(w.y >> 16) * inv;
+  }
+  typedef i4v Raw32;
+  __device__ static Raw32 i32(g_i32 *p) { return *reinterpret_cast<const __attribute__((address_space(1))) i4v *>(p); }
+  __device__ static void i32_val(Raw32 w, double inv, double *b) {
+    b[0] = (double)w.x * inv, b[1] = (double)w.y * inv, b[2] = (double)w.z * inv, b[3] = (double)w.w * inv;
   }
   __device__ static Raw64 f64(g_f64 *p) {
     const __attribute__((address_space(1))) d2v *q = reinterpret_cast<const __attribute__((address_space(1))) d2v *>(p);
@@ -581,7 +611,8 @@ __device__ __attribute__((always_inline)) inline void skinny_body(const GemmArgs
   c_RecombFrag &FR = cargs(G)->f[rf];
   g_f64 *Tn = (g_f64 *)(uint64_t)FR.T + n;
   g_u16 *Cn = (g_u16 *)(uint64_t)FR.T + n;
-  const bool cnt16 = FR.cnt16 != 0;
+  g_i32 *In = (g_i32 *)(uint64_t)FR.T + n;
+  const uint32_t counts = FR.counts;
   const double inv = 1.0 / FR.shots;  // a count's value is count x fl(1/shots)
   const uint64_t rows = FR.rows;
   const bool square = G->square != 0;
@@ -612,7 +643,7 @@ __device__ __attribute__((always_inline)) inline void skinny_body(const GemmArgs
       double a;
       if (FA) {
         const uint64_t ix = j * DA.rows + m;
-        a = DA.c16 ? (double)DA.T16[ix] * DA.inv : DA.T64[ix];
+        a = DA.at(ix);
       } else {
         a = side_value(G, G->L, m, terms ? terms[j] : j);
       }
@@ -626,17 +657,17 @@ __device__ __attribute__((always_inline)) inline void skinny_body(const GemmArgs
     // before the first is used (fewer for many accumulators, which would
     // crowd the registers)
     constexpr uint32_t U = MC * CPT <= 8 ? 8 : 4;
-    if (cnt16) {  // 16-bit shot counts: a quarter of the bytes, the same values
+    auto sum = [&](auto load, auto value) {
       for (uint32_t k2 = 0; k2 < kn; k2 += U) {
-        typename ColLoad<CPT>::Raw16 w[U];
+        decltype(load(uint64_t(0))) w[U];
 #pragma unroll
-        for (uint32_t u = 0; u < U; ++u) w[u] = ColLoad<CPT>::cnt(Cn + s_boff[k2 + u < kn ? k2 + u : k2]);
+        for (uint32_t u = 0; u < U; ++u) w[u] = load(s_boff[k2 + u < kn ? k2 + u : k2]);
         __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of their uses
 #pragma unroll
         for (uint32_t u = 0; u < U; ++u) {
           if (k2 + u >= kn) break;
           double b[CPT];
-          ColLoad<CPT>::cnt_val(w[u], inv, b);
+          value(w[u], b);
 #pragma unroll
           for (uint32_t c = 0; c < CPT; ++c) {
             if (square) b[c] *= b[c];
@@ -645,26 +676,14 @@ __device__ __attribute__((always_inline)) inline void skinny_body(const GemmArgs
           }
         }
       }
-    } else {
-      for (uint32_t k2 = 0; k2 < kn; k2 += U) {
-        typename ColLoad<CPT>::Raw64 w[U];
-#pragma unroll
-        for (uint32_t u = 0; u < U; ++u) w[u] = ColLoad<CPT>::f64(Tn + s_boff[k2 + u < kn ? k2 + u : k2]);
-        __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of their uses
-#pragma unroll
-        for (uint32_t u = 0; u < U; ++u) {
-          if (k2 + u >= kn) break;
-          double b[CPT];
-          ColLoad<CPT>::f64_val(w[u], b);
-#pragma unroll
-          for (uint32_t c = 0; c < CPT; ++c) {
-            if (square) b[c] *= b[c];
-#pragma unroll
-            for (uint32_t m = 0; m < MC; ++m) acc[m][c] += As[k2 + u][m] * b[c];
-          }
-        }
-      }
-    }
+    };
+    typedef ColLoad<CPT> CL;
+    if (counts == 16)  // a quarter of the bytes, the same values
+      sum([&](uint64_t o) { return CL::cnt(Cn + o); }, [&](typename CL::Raw16 w, double *b) { CL::cnt_val(w, inv, b); });
+    else if (counts == 32)  // half
+      sum([&](uint64_t o) { return CL::i32(In + o); }, [&](typename CL::Raw32 w, double *b) { CL::i32_val(w, inv, b); });
+    else
+      sum([&](uint64_t o) { return CL::f64(Tn + o); }, [&](typename CL::Raw64 w, double *b) { CL::f64_val(w, b); });
   }
   if (n >= N) return;
   if (out) {
