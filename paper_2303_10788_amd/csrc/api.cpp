@@ -1556,6 +1556,117 @@ void fold_jobs(const PlanData &pd, int g, const RecombArgs &args, std::vector<Fo
 // Clifford variant no term of the support reads draws no shots; the
 // tensors are formed in the Pauli basis (no fold) and only the support's
 // terms are summed.  The support size is read back (the call synchronizes).
+// The variant tables of the non-Clifford fragments of a call, where it has at
+// least two: one launch evolves all their states of a launch shape and one
+// combines them, where each fragment took two launches of its own, mostly
+// latency (5.5 us each for states of a few qubits; four such fragments in a
+// chain 44 us, together 11).  dist[f]: fragment f's table, or null if it is left
+// to variant_dists (which reports what it cannot do).  On the current stream.
+ccut_status grouped_tables(ccut_plan *p, const ccut_eval_opts *eo, const std::vector<FragRequest> &reqs,
+                           std::vector<double *> &dist) {
+  ccut_ctx *c = p->ctx;
+  const PlanData &pd = p->pd;
+  dist.assign(pd.frags.size(), nullptr);
+  std::vector<const Fragment *> nc;
+  for (const Fragment &f : pd.frags) {
+    const size_t nm = reqs[f.index].meas.size();
+    if (!f.clifford && nm <= (size_t)kMaxTableBits && (f.n_variants << nm) <= (uint64_t(1) << 34)) nc.push_back(&f);
+  }
+  if (nc.size() < 2 || (eo->flags & CCUT_FLAG_ML)) return CCUT_OK;
+  // descriptors, then the classes' evolve and combine jobs, in one upload
+  std::stable_sort(nc.begin(), nc.end(), [](const Fragment *x, const Fragment *y) { return sv_waves(x->m()) < sv_waves(y->m()); });
+  std::vector<FragDev> descs;
+  std::vector<SvJob> jobs[2];
+  struct Class {
+    uint32_t first, count, m;
+    uint64_t wg[2];
+    size_t lds[2];
+  };
+  std::vector<Class> classes;
+  for (const Fragment *f : nc) {
+    const FragRequest &r = reqs[f->index];
+    const FragDev h = frag_desc(p, *f, r, eo->circuit);
+    if (classes.empty() || sv_waves(classes.back().m) != sv_waves(h.m))
+      classes.push_back(Class{(uint32_t)descs.size(), 0, h.m, {0, 0}, {0, 0}});
+    Class &C = classes.back();
+    double *d = aget<double>(c, f->n_variants << r.meas.size());
+    double *states = aget<double>(c, sv_states_bytes(h) / sizeof(double));
+    if (!d || !states) return fail(c, CCUT_E_OOM, "device allocation failed");
+    for (int k = 0; k < 2; ++k) {  // evolve, combine
+      uint64_t n_wg;
+      size_t lds;
+      sv_pass_shape(h, k == 1, n_wg, lds);
+      SvJob J{};
+      J.desc = (uint32_t)descs.size();
+      J.wg0 = C.wg[k];
+      J.dist = d;
+      J.states = states;
+      C.wg[k] += n_wg;
+      C.lds[k] = std::max(C.lds[k], lds);
+      jobs[k].push_back(J);
+    }
+    C.m = std::max(C.m, h.m);
+    ++C.count;
+    descs.push_back(h);
+    dist[f->index] = d;
+  }
+  const size_t nd = descs.size(), db = (nd * sizeof(FragDev) + 255) & ~size_t(255), jb = nd * sizeof(SvJob);
+  std::vector<char> block(db + 2 * jb, 0);
+  std::memcpy(block.data(), descs.data(), nd * sizeof(FragDev));
+  for (int k = 0; k < 2; ++k) std::memcpy(block.data() + db + k * jb, jobs[k].data(), jb);
+  char *d_block = (char *)upload(c, block.data(), block.size());
+  if (!d_block) return fail(c, CCUT_E_OOM, "device allocation failed");
+  for (const Class &C : classes)
+    for (int k = 0; k < 2; ++k) {
+      KTimer t(c, CCUT_K_SV);
+      HIP_TRY(c, launch_sv_batch((const FragDev *)d_block, (const SvJob *)(d_block + db + k * jb) + C.first, C.count,
+                                 C.wg[k], k == 1, C.m, C.lds[k], c->cur));
+    }
+  return CCUT_OK;
+}
+
+// The Pauli-basis tensors T[f] of those fragments, from one more launch; that
+// of the fold target g (-1: none) is its table, and axes on its cuts are folded
+// (folded[f] set).  Null where grouped_tables left the table.
+ccut_status grouped_tensors(ccut_plan *p, const ccut_eval_opts *eo, const std::vector<FragRequest> &reqs, int g,
+                            std::vector<double *> &T, std::vector<char> &folded) {
+  ccut_ctx *c = p->ctx;
+  const PlanData &pd = p->pd;
+  std::vector<double *> dist;
+  ccut_status st = grouped_tables(p, eo, reqs, dist);
+  if (st != CCUT_OK) return st;
+  T.assign(pd.frags.size(), nullptr);
+  folded.assign(pd.frags.size(), 0);
+  std::vector<TileJob> jobs;
+  uint64_t tiles = 0;
+  for (const Fragment &f : pd.frags) {
+    double *d = dist[f.index];
+    if (!d) continue;
+    const FragRequest &r = reqs[f.index];
+    const uint64_t xsize = 1ull << r.meas.size();
+    TileJob J;
+    if ((int)f.index == g || f.axes.empty()) {
+      T[f.index] = d;
+    } else if (tile_job(f, r, d, xsize, nullptr, J)) {
+      J.fold = fold_mask(pd, g, f);
+      folded[f.index] = 1;
+      J.wg0 = tiles;
+      tiles += J.tiles;
+      J.out = T[f.index] = aget<double>(c, J.x_out << (2 * f.axes.size()));
+      if (!J.out) return fail(c, CCUT_E_OOM, "device allocation failed");
+      jobs.push_back(J);
+    } else if ((st = pauli_passes(c, f, r, d, xsize, 0, &T[f.index])) != CCUT_OK) {
+      return st;
+    }
+  }
+  if (jobs.empty()) return CCUT_OK;
+  TileJob *d_jobs = (TileJob *)upload(c, jobs.data(), jobs.size() * sizeof(TileJob));
+  if (!d_jobs) return fail(c, CCUT_E_OOM, "device allocation failed");
+  KTimer t(c, CCUT_K_TRANSFORM);
+  HIP_TRY(c, launch_transform_tiled(d_jobs, (uint32_t)jobs.size(), tiles, kTileF64, c->cur));
+  return CCUT_OK;
+}
+
 ccut_status marginal_skip_enqueue(ccut_plan *p, const ccut_eval_opts *eo, const uint32_t *qubits, uint32_t nq,
                                   double *res) {
   ccut_ctx *c = p->ctx;
@@ -1746,11 +1857,17 @@ ccut_status marginal_enqueue(ccut_plan *p, const ccut_eval_opts *eo, const uint3
   const bool counts_ok = counts_contraction(pd, eo, nq);
   HeisRows H;
   Columns C;
+  std::vector<double *> nc_T;
+  std::vector<char> folded;
+  c->cur = c->use_aux ? c->aux : c->stream;  // (non-Clifford fragments' stream, see route)
+  if ((st = grouped_tensors(p, eo, reqs, g, nc_T, folded)) != CCUT_OK) return st;
   for (const Fragment &f : pd.frags) {
     route(c, f);
     const FragRequest &r = reqs[f.index];
-    double *dist = nullptr, *T = nullptr;
-    if ((int)f.index == ef) {
+    double *dist = nullptr, *T = nc_T[f.index];
+    if (T) {
+      // formed above
+    } else if ((int)f.index == ef) {
       if ((st = heis_size(c, f, 1ull << r.req_pos.size())) != CCUT_OK) return st;
       if ((st = heis_rows(p, f, r, eo->circuit, nullptr, H)) != CCUT_OK) return st;
     } else if ((int)f.index == cf) {
@@ -1816,7 +1933,7 @@ ccut_status marginal_enqueue(ccut_plan *p, const ccut_eval_opts *eo, const uint3
     return column_contract(c, args, C, true, res);
   }
   std::vector<FoldJob> fj;
-  fold_jobs(pd, g, args, fj);
+  fold_jobs(pd, g, args, fj, &folded);
   if (!fj.empty()) {
     FoldJob *d_fj = (FoldJob *)upload(c, fj.data(), fj.size() * sizeof(FoldJob));
     if (!d_fj) return fail(c, CCUT_E_OOM, "device allocation failed");
@@ -1993,9 +2110,14 @@ ccut_status zexpect_call(ccut_plan *p, const ccut_eval_opts *eo, const uint64_t 
   // (in fp32 only where a single term is left: its product rounds the same way)
   const int ef = exact_fragment(pd, eo, {}, true, 1, eo->precision == CCUT_FP64 ? kExactMaxFree : 0);
   HeisRows H;
+  std::vector<FragRequest> reqs;
+  for (const Fragment &f : pd.frags) reqs.push_back(zstring_request(f, anymask));
+  std::vector<double *> nc_dist;
+  c->cur = c->use_aux ? c->aux : c->stream;  // (non-Clifford fragments' stream, see route)
+  if ((st = grouped_tables(p, eo, reqs, nc_dist)) != CCUT_OK) return st;
   for (const Fragment &f : pd.frags) {
     route(c, f);
-    FragRequest r = zstring_request(f, anymask);
+    const FragRequest &r = reqs[f.index];
     const uint32_t nm = (uint32_t)r.meas.size();
     const uint64_t nv = f.n_variants;
     if (use_heisenberg(f, eo, 0)) {
@@ -2056,10 +2178,11 @@ ccut_status zexpect_call(ccut_plan *p, const ccut_eval_opts *eo, const uint64_t 
     if (!d_ext || !E) return fail(c, CCUT_E_OOM, "device allocation failed");
     const FragDev h = frag_desc(p, f, r, eo->circuit);
     if (!f.clifford) {
-      double *dist = aget<double>(c, nv << nm);
-      double *states = aget<double>(c, sv_states_bytes(h) / sizeof(double));
-      if (!dist || !states) return fail(c, CCUT_E_OOM, "device allocation failed");
-      {
+      double *dist = nc_dist[f.index];
+      if (!dist) {
+        double *states = aget<double>(c, sv_states_bytes(h) / sizeof(double));
+        dist = aget<double>(c, nv << nm);
+        if (!dist || !states) return fail(c, CCUT_E_OOM, "device allocation failed");
         KTimer t(c, CCUT_K_SV);
         HIP_TRY(c, launch_sv(h, dist, states, c->cur));
       }
@@ -3730,23 +3853,28 @@ ccut_status learned_enqueue(ccut_plan *p, const ccut_eval_opts *eo, const uint32
     LearnedDev &h = L->h;
     h.k = pd.k;
     h.n_frags = args.n_frags;
+    std::vector<FragRequest> reqs;
+    for (const Fragment &f : pd.frags) reqs.push_back(marginal_request(f, qubits, nq));
+    std::vector<double *> nc_T;
+    std::vector<char> folded;
+    if ((st = grouped_tensors(p, eo, reqs, -1, nc_T, folded)) != CCUT_OK) return st;
     for (const Fragment &f : pd.frags) {
-      FragRequest r = marginal_request(f, qubits, nq);
+      const FragRequest &r = reqs[f.index];
       const uint32_t a = (uint32_t)f.axes.size();
       const uint64_t ncols = 1ull << (2 * a);
       double *norm = aget<double>(c, ncols);
       double *part = aget<double>(c, (uint64_t)4 * std::max<uint32_t>(a, 1) * share_chunks(a));
       if (!norm || !part) return fail(c, CCUT_E_OOM, "device allocation failed");
-      double *dist = nullptr, *T = nullptr;
+      double *dist = nullptr, *T = nc_T[f.index];
       const bool columns = !L->by_columns && column_fragment(pd, eo, f, r.req_pos.size());
       if (columns) {  // its column norms come with the columns
         HIP_TRY(c, launch_fill_u32(reinterpret_cast<uint32_t *>(norm), 2 * ncols, 0u, c->cur));  // +0.0
         if ((st = column_set(p, f, r, eo->circuit, false, true, norm, L->cols)) != CCUT_OK) return st;
         T = L->cols.T;
         L->by_columns = true;
-      } else if (use_heisenberg(f, eo, r.req_pos.size())) {
+      } else if (!T && use_heisenberg(f, eo, r.req_pos.size())) {
         if ((st = heis_tensor(p, f, r, eo->circuit, nullptr, &T)) != CCUT_OK) return st;
-      } else {
+      } else if (!T) {
         if ((st = variant_dists(p, eo, f, r, &dist)) != CCUT_OK) return st;
         if ((st = pauli_passes(c, f, r, dist, 1ull << r.meas.size(), 0, &T)) != CCUT_OK) return st;
       }
