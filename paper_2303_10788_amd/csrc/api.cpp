@@ -106,6 +106,7 @@ struct ccut_ctx {
   uint64_t launches[CCUT_K_COUNT] = {};
   double total_ms[CCUT_K_COUNT] = {};
   std::vector<std::vector<char>> staged;  // host copies kept alive until the call's final sync
+  bool one_stream = false;   // this call's Clifford side is too short to overlap (reset by check_eval)
   bool use_aux = true;       // route non-Clifford fragments to the auxiliary stream
   bool replay_uploads = false;  // re-enqueue of an identical sequence: reuse earlier uploads, copy nothing
   // Pinned staging of host-to-device uploads: a ring of slots, one per call;
@@ -301,6 +302,7 @@ ccut_status check_eval(ccut_plan *p, const ccut_eval_opts *eo) {
   if (c->device < 0) return fail(c, CCUT_E_DEVICE, "host-only context: evaluation needs a device");
   HIP_TRY(c, hipSetDevice(c->device));
   c->cancel.store(0);
+  c->one_stream = false;
   c->arena.reset();
   c->staged.clear();
   c->call_upload_bytes = 0;
@@ -317,9 +319,12 @@ ccut_status check_eval(ccut_plan *p, const ccut_eval_opts *eo) {
   return ensure_ops(p);
 }
 
+// The non-Clifford fragments' stream.
+hipStream_t nc_stream(const ccut_ctx *c) { return c->use_aux && !c->one_stream ? c->aux : c->stream; }
+
 // Route the next launches of fragment f: non-Clifford fragments go to the
 // auxiliary stream so they overlap the Clifford chain.
-void route(ccut_ctx *c, const Fragment &f) { c->cur = (f.clifford || !c->use_aux) ? c->stream : c->aux; }
+void route(ccut_ctx *c, const Fragment &f) { c->cur = f.clifford ? c->stream : nc_stream(c); }
 
 // Join the auxiliary stream back into the caller's stream.
 ccut_status join(ccut_ctx *c) {
@@ -882,10 +887,12 @@ bool use_heisenberg(const Fragment &f, const ccut_eval_opts *eo, size_t req_bits
 struct HeisRows {
   uint32_t W = 0, n_in = 0, n_out = 0;
   uint64_t cin[8] = {};  // local qubits that are circuit inputs
-  uint64_t *rows = nullptr;
+  uint32_t n_rows = 0;
+  uint64_t *in = nullptr, *rows = nullptr;  // before and after the carry
 };
-ccut_status heis_rows(ccut_plan *p, const Fragment &f, const FragRequest &r, uint32_t circuit,
-                      const std::vector<std::vector<uint64_t>> *strings, HeisRows &H) {
+// The rows to carry (all but the carry itself).
+ccut_status heis_in(ccut_plan *p, const Fragment &f, const FragRequest &r,
+                    const std::vector<std::vector<uint64_t>> *strings, HeisRows &H) {
   ccut_ctx *c = p->ctx;
   const uint32_t W = H.W = row_words(f.m());
   if (!W) return fail(c, CCUT_E_UNSUPPORTED, "Clifford fragment wider than 512 qubits");
@@ -916,14 +923,30 @@ ccut_status heis_rows(ccut_plan *p, const Fragment &f, const FragRequest &r, uin
   if (H.n_out > 8) return fail(c, CCUT_E_UNSUPPORTED, "more than 8 quantum outputs on a Clifford fragment");
   for (uint32_t i = 0; i < f.m(); ++i)
     if (f.segs[i] == 0) H.cin[i >> 6] |= 1ull << (i & 63);
-  const uint32_t n_rows = (uint32_t)(rows.size() / RW);
+  H.n_rows = (uint32_t)(rows.size() / RW);
   if (rows.empty()) rows.assign(RW, 0);  // a fragment with nothing to carry back still gets a valid buffer
   H.rows = aget<uint64_t>(c, rows.size());
-  uint64_t *d_in = (uint64_t *)upload(c, rows.data(), rows.size() * 8);
-  if (!H.rows || !d_in) return fail(c, CCUT_E_OOM, "device allocation failed");
-  KTimer t(c, CCUT_K_HEISENBERG);
-  HIP_TRY(c, launch_rows(carry_desc(p, f, frag_desc(p, f, r, circuit)), W, d_in, H.rows, n_rows, c->cur));
+  H.in = (uint64_t *)upload(c, rows.data(), rows.size() * 8);
+  if (!H.rows || !H.in) return fail(c, CCUT_E_OOM, "device allocation failed");
   return CCUT_OK;
+}
+ccut_status heis_carry(ccut_plan *p, const Fragment &f, const FragRequest &r, uint32_t circuit, const HeisRows &H) {
+  ccut_ctx *c = p->ctx;
+  KTimer t(c, CCUT_K_HEISENBERG);
+  HIP_TRY(c, launch_rows(carry_desc(p, f, frag_desc(p, f, r, circuit)), H.W, H.in, H.rows, H.n_rows, c->cur));
+  return CCUT_OK;
+}
+ccut_status heis_rows(ccut_plan *p, const Fragment &f, const FragRequest &r, uint32_t circuit,
+                      const std::vector<std::vector<uint64_t>> *strings, HeisRows &H) {
+  const ccut_status st = heis_in(p, f, r, strings, H);
+  return st == CCUT_OK ? heis_carry(p, f, r, circuit, H) : st;
+}
+
+// Whether a Clifford fragment's marginal tensor is one launch (heis_tile_kernel).
+bool heis_tile(const ccut_plan *p, const Fragment &f, size_t req_bits) {
+  size_t n_in = 0;
+  for (const Axis &a : f.axes) n_in += a.side != 0;
+  return p->d_lanes[f.index] && heis_one_launch(f.m(), p->n_steps[f.index], n_in, f.axes.size() - n_in, req_bits);
 }
 
 // The size limit of a fragment's exact tensor (ncols outcomes or strings); it
@@ -948,9 +971,14 @@ ccut_status heis_tensor(ccut_plan *p, const Fragment &f, const FragRequest &r, u
   double *tau = aget<double>(c, total);
   if (!tau) return fail(c, CCUT_E_OOM, "device allocation failed");
   HeisRows H;
-  const ccut_status st = heis_rows(p, f, r, circuit, strings, H);
+  ccut_status st = heis_in(p, f, r, strings, H);
   if (st != CCUT_OK) return st;
-  {
+  if (!strings && heis_tile(p, f, nreq)) {
+    KTimer t(c, CCUT_K_HEISENBERG);
+    HIP_TRY(c, launch_heis_tile(carry_desc(p, f, frag_desc(p, f, r, circuit)), H.n_in, H.n_out, nreq, H.cin, H.in,
+                                H.n_rows, tau, c->cur));
+  } else {
+    if ((st = heis_carry(p, f, r, circuit, H)) != CCUT_OK) return st;
     KTimer t(c, CCUT_K_HEISENBERG);
     HIP_TRY(c, launch_heisenberg(frag_desc(p, f, r, circuit), H.W, H.n_in, H.n_out, strings ? 0 : nreq,
                                  strings ? (uint32_t)strings->size() : 0, H.cin, H.rows, tau, c->cur));
@@ -1859,7 +1887,18 @@ ccut_status marginal_enqueue(ccut_plan *p, const ccut_eval_opts *eo, const uint3
   Columns C;
   std::vector<double *> nc_T;
   std::vector<char> folded;
-  c->cur = c->use_aux ? c->aux : c->stream;  // (non-Clifford fragments' stream, see route)
+  // One stream where the Clifford side is a launch or two: a forked and joined
+  // replay starts later by more than they take (8 qubits 73 us, on one stream
+  // 60; with a sampled chain or the contraction's own kernels on the Clifford
+  // side the fork gains: 32 qubits sampled 71 us, on one stream 89).
+  uint32_t n_cliff = 0;
+  c->one_stream = ef < 0 && cf < 0;
+  for (const Fragment &f : pd.frags)
+    if (f.clifford) {
+      const size_t bits = reqs[f.index].req_pos.size();
+      c->one_stream = c->one_stream && ++n_cliff <= 2 && use_heisenberg(f, eo, bits) && heis_tile(p, f, bits);
+    }
+  c->cur = nc_stream(c);
   if ((st = grouped_tensors(p, eo, reqs, g, nc_T, folded)) != CCUT_OK) return st;
   for (const Fragment &f : pd.frags) {
     route(c, f);
@@ -2113,7 +2152,7 @@ ccut_status zexpect_call(ccut_plan *p, const ccut_eval_opts *eo, const uint64_t 
   std::vector<FragRequest> reqs;
   for (const Fragment &f : pd.frags) reqs.push_back(zstring_request(f, anymask));
   std::vector<double *> nc_dist;
-  c->cur = c->use_aux ? c->aux : c->stream;  // (non-Clifford fragments' stream, see route)
+  c->cur = nc_stream(c);
   if ((st = grouped_tables(p, eo, reqs, nc_dist)) != CCUT_OK) return st;
   for (const Fragment &f : pd.frags) {
     route(c, f);

@@ -427,6 +427,17 @@ hipError_t launch_affine_batch(const FragDev *descs, const uint32_t *desc_w, con
 hipError_t launch_heisenberg(const FragDev &F, uint32_t W, uint32_t n_in, uint32_t n_out, uint32_t r,
                              uint32_t n_str, const uint64_t *cin_mask, const uint64_t *rows, double *tau,
                              hipStream_t s);
+// The same from the rows before the carry (in), in one launch for a fragment
+// whose entries of one output Pauli fit a workgroup's tile.  Each workgroup
+// repeats the carry, so the program is short and the workgroups are few
+// enough to run at once (on 256 compute units); 16 KB of tile is eight
+// entries a thread.
+constexpr uint32_t kHeisTile = 2048, kHeisTileRows = 64;
+inline bool heis_one_launch(uint32_t m, uint32_t n_steps, uint64_t n_in, uint64_t n_out, uint64_t r) {
+  return m <= 64 && n_steps <= 256 && n_out <= 4 && r + 2 * n_in <= 11 && r + 2 * n_out <= kHeisTileRows;
+}
+hipError_t launch_heis_tile(const FragDev &F, uint32_t n_in, uint32_t n_out, uint32_t r, const uint64_t *cin_mask,
+                            const uint64_t *in, uint32_t n_rows, double *T, hipStream_t s);
 
 // A fragment tensor to be rewritten along cut axes `mask` (bit j = axis j)
 // into the preparation basis of the fragments downstream (launch_fold).

@@ -479,6 +479,76 @@ __global__ void fill_zero_kernel(double *p, uint64_t n) {
     p[i] = 0.0;
 }
 
+// A small fragment's whole tensor in one launch: workgroup P_out carries the
+// rows back itself (one wave, rows left in LDS), places its 4^n_in x 2^r
+// entries in an LDS tile, transforms the tile's rows over S (the additions
+// of the kernels above in the same order) and writes them out.  All of it is
+// latency: carry, clearing, entries and transform took 5 + 1 + 2 + 1 us as
+// launches of their own at 16 entries an output Pauli (8 qubits), 7 + 2 + 5 +
+// 3 us at 64 x 256 (17 qubits), with the gaps between them on top.  With one
+// stream for the call the waited marginals went from 71 to 53 us and from 64
+// to 43 us on MI355X.
+__global__ __launch_bounds__(256) void heis_tile_kernel(const FragDev F, const HeisArgs A,
+                                                        const uint64_t *__restrict__ in, uint32_t n_rows,
+                                                        double *__restrict__ T) {
+  __shared__ double tile[kHeisTile];
+  __shared__ uint64_t rows[kHeisTileRows * 3];
+  const uint32_t n = 1u << A.r, total = n << (2 * A.n_in), pc = blockIdx.x;
+  for (uint32_t i = threadIdx.x; i < total; i += 256) tile[i] = 0.0;
+  if (threadIdx.x < 64) carry_lanes_body<false>(F, 1, in, rows, n_rows, nullptr);
+  __syncthreads();
+  for (uint32_t col = threadIdx.x; col < n; col += 256) {
+    PAcc<1> acc;
+    pclear(acc);
+    for (uint32_t j = 0; j < A.r; ++j)
+      if ((col >> j) & 1u) pmul<1>(acc, rows + 3 * j);
+    for (uint32_t oc = 0; oc < A.n_out; ++oc) pmul_out<1>(acc, (pc >> (2 * oc)) & 3u, rows + 3 * (A.r + 2 * oc));
+    if (acc.x[0] & A.cin_mask[0]) continue;
+    uint32_t pin = 0, ic = 0;
+    for (uint32_t j = 0; j < A.n_axes; ++j)
+      if (A.axis_side[j] == 1) pin |= pdigit<1>(acc, A.axis_local[j]) << (2 * ic++);
+    tile[(pin << A.r) | col] = ldexp(psign<1>(acc) ? -1.0 : 1.0, (int)A.n_in);
+  }
+  __syncthreads();
+  for (uint32_t s = 0; s < A.r; ++s) {
+    for (uint32_t k = threadIdx.x; k < total / 2; k += 256) {
+      const uint32_t i0 = ((k >> s) << (s + 1)) | (k & ((1u << s) - 1)), i1 = i0 | (1u << s);
+      const double a = tile[i0], b = tile[i1];
+      tile[i0] = a + b;
+      tile[i1] = a - b;
+    }
+    __syncthreads();
+  }
+  for (uint32_t i = threadIdx.x; i < total; i += 256) {
+    uint64_t pf = 0;
+    uint32_t po = pc, pi = i >> A.r;
+    for (uint32_t j = 0; j < A.n_axes; ++j) {
+      uint32_t &d = A.axis_side[j] == 1 ? pi : po;
+      pf |= (uint64_t)(d & 3u) << (2 * j);
+      d >>= 2;
+    }
+    T[(pf << A.r) | (i & (n - 1))] = ldexp(tile[i], -(int)A.r);
+  }
+}
+
+HeisArgs heis_args(const FragDev &F, uint32_t W, uint32_t n_in, uint32_t n_out, uint32_t r, uint32_t n_str,
+                   const uint64_t *cin_mask) {
+  HeisArgs A{};
+  A.m = F.m;
+  A.W = W;
+  A.n_axes = F.n_axes;
+  A.n_in = n_in;
+  A.n_out = n_out;
+  A.r = r;
+  A.n_str = n_str;
+  for (uint32_t j = 0; j < F.n_axes; ++j) {
+    A.axis_side[j] = F.axis_side[j];
+    A.axis_local[j] = F.axis_local[j];
+  }
+  for (uint32_t w = 0; w < 8; ++w) A.cin_mask[w] = w < W ? cin_mask[w] : 0;
+  return A;
+}
+
 template <int W>
 hipError_t run_w(const HeisArgs &A, const uint64_t *rows, double *tau, uint64_t ncols, hipStream_t s) {
   hipError_t e;
@@ -555,19 +625,7 @@ hipError_t launch_carry_batch(const FragDev *descs, const CarryJob *jobs, uint32
 hipError_t launch_heisenberg(const FragDev &F, uint32_t W, uint32_t n_in, uint32_t n_out, uint32_t r,
                              uint32_t n_str, const uint64_t *cin_mask, const uint64_t *rows, double *tau,
                              hipStream_t s) {
-  HeisArgs A{};
-  A.m = F.m;
-  A.W = W;
-  A.n_axes = F.n_axes;
-  A.n_in = n_in;
-  A.n_out = n_out;
-  A.r = r;
-  A.n_str = n_str;
-  for (uint32_t j = 0; j < F.n_axes; ++j) {
-    A.axis_side[j] = F.axis_side[j];
-    A.axis_local[j] = F.axis_local[j];
-  }
-  for (uint32_t w = 0; w < 8; ++w) A.cin_mask[w] = w < W ? cin_mask[w] : 0;
+  const HeisArgs A = heis_args(F, W, n_in, n_out, r, n_str, cin_mask);
   const uint64_t ncols = n_str ? n_str : (1ull << r);
   hipError_t e;
   switch (W) {
@@ -596,6 +654,16 @@ hipError_t launch_heisenberg(const FragDev &F, uint32_t W, uint32_t n_in, uint32
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+hipError_t launch_heis_tile(const FragDev &F, uint32_t n_in, uint32_t n_out, uint32_t r, const uint64_t *cin_mask,
+                            const uint64_t *in, uint32_t n_rows, double *T, hipStream_t s) {
+  if (!F.lanes || F.n_steps % kCarryChunk || !in || n_rows != r + 2 * n_out || n_in + n_out != F.n_axes ||
+      !heis_one_launch(F.m, F.n_steps, n_in, n_out, r))
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(heis_tile_kernel, dim3(1u << (2 * n_out)), dim3(256), 0, s, F,
+                     heis_args(F, 1, n_in, n_out, r, 0, cin_mask), in, n_rows, T);
+  return hipGetLastError();
 }
 
 }  // namespace ccut
