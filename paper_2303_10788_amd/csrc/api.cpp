@@ -3880,15 +3880,10 @@ ccut_status learned_enqueue(ccut_plan *p, const ccut_eval_opts *eo, const uint32
     RecombArgs &args = L->args;
     args.n_frags = (uint32_t)pd.frags.size();
     args.k = pd.k;
-    uint64_t n_slots = 0;
-    std::vector<uint64_t> slot_off(pd.frags.size());
-    for (const Fragment &f : pd.frags) {
-      slot_off[f.index] = n_slots;
-      n_slots += 4 * f.axes.size();
-    }
-    double *shares = aget<double>(c, std::max<uint64_t>(n_slots, 1));
-    if (!shares) return fail(c, CCUT_E_OOM, "device allocation failed");
-    std::vector<int64_t> src(2 * pd.k, -1);
+    PhiSrc src;
+    std::fill(std::begin(src.slot), std::end(src.slot), (int8_t)-1);
+    std::vector<NormJob> jobs;
+    uint32_t tiles = 0, parts = 0, slots = 0;
     LearnedDev &h = L->h;
     h.k = pd.k;
     h.n_frags = args.n_frags;
@@ -3924,22 +3919,25 @@ ccut_status learned_enqueue(ccut_plan *p, const ccut_eval_opts *eo, const uint32
       rf.n_req = (uint32_t)r.req_pos.size();
       for (size_t j = 0; j < f.axes.size(); ++j) rf.axis_cut[j] = f.axes[j].cut;
       for (size_t i = 0; i < r.req_user.size(); ++i) rf.req_user[i] = r.req_user[i];
-      {
-        KTimer t(c, CCUT_K_TERMS);
-        if (!columns) HIP_TRY(c, launch_colnorm(T, rf.rows, ncols, norm, c->cur));
-        HIP_TRY(c, launch_shares(norm, a, part, shares + slot_off[f.index], c->cur));
-      }
+      const NormJob J{columns ? nullptr : T, norm, part, rf.rows, a, share_chunks(a), tiles, parts, slots};
       h.norm[f.index] = norm;
       h.n_axes[f.index] = a;
       for (uint32_t j = 0; j < a; ++j) {
         h.axis_cut[f.index][j] = f.axes[j].cut;
-        src[2 * f.axes[j].cut + f.axes[j].side] = (int64_t)(slot_off[f.index] + 4 * j);
+        src.slot[2 * f.axes[j].cut + f.axes[j].side] = (int8_t)(slots + 4 * j);
       }
+      jobs.push_back(J);
+      tiles += norm_tiles(J);
+      parts += 4 * a * J.chunks;
+      slots += 4 * a;
     }
-    int64_t *d_src = (int64_t *)upload(c, src.data(), src.size() * 8);
+    NormJob *d_jobs = (NormJob *)upload(c, jobs.data(), jobs.size() * sizeof(NormJob));
     double *phi = aget<double>(c, 8 * pd.k);
-    if (!d_src || !phi) return fail(c, CCUT_E_OOM, "device allocation failed");
-    HIP_TRY(c, launch_phi(shares, d_src, pd.k, phi, c->cur));
+    if (!d_jobs || !phi) return fail(c, CCUT_E_OOM, "device allocation failed");
+    {
+      KTimer t(c, CCUT_K_TERMS);
+      HIP_TRY(c, launch_norms(jobs.data(), d_jobs, (uint32_t)jobs.size(), src, pd.k, phi, c->cur));
+    }
     h.phi = phi;
     L->d = (LearnedDev *)upload(c, &h, sizeof(h));
     if (!L->d) return fail(c, CCUT_E_OOM, "device allocation failed");

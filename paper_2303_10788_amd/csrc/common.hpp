@@ -699,10 +699,22 @@ struct LearnedDev {
   uint32_t axis_cut[kMaxFrags][kMaxAxes];
   const double *phi;              // [cut][side: 0 up, 1 down][digit]
 };
-hipError_t launch_colnorm(const double *T, uint32_t rows, uint64_t ncols, double *out, hipStream_t s);
+// A fragment's column norms (formed from T; T null: they are there) and the
+// partial sums of its shares: its first tile of 64 columns, workgroup and
+// share slot in the launches over all fragments (one without axes has no share).
+struct NormJob {
+  const double *T;
+  double *norm, *part;
+  uint32_t rows, n_axes, chunks, tile0, block0, slot0;
+};
+constexpr uint32_t kPhiSlots = 128;  // 4 per cut and side, up to 12 cuts
+struct PhiSrc {
+  int8_t slot[kPhiSlots / 4];
+};
 uint32_t share_chunks(uint32_t n_axes);
-hipError_t launch_shares(const double *norm, uint32_t n_axes, double *part, double *shares, hipStream_t s);
-hipError_t launch_phi(const double *shares, const int64_t *src, uint32_t k, double *phi, hipStream_t s);
+uint32_t norm_tiles(const NormJob &J);
+hipError_t launch_norms(const NormJob *jobs, const NormJob *d_jobs, uint32_t n_jobs, const PhiSrc &src, uint32_t k,
+                        double *phi, hipStream_t s);
 hipError_t launch_features(const LearnedDev *L, const uint64_t *terms, uint64_t first, uint64_t n, uint32_t width,
                            uint16_t *X, hipStream_t s);
 // The whole forward pass over term rows [first, first + n) in one launch:

@@ -109,11 +109,19 @@ __global__ void colnorm_kernel(const double *__restrict__ T, uint32_t rows, uint
 
 // The same for up to 64 rows per column: a wave stages 64 whole columns
 // (contiguous in memory) through LDS with coalesced loads, all issued before
-// the first store, then each lane sums its column in row order as above.
-__global__ __launch_bounds__(64) void colnorm_tile_kernel(const double *__restrict__ T, uint32_t rows, uint64_t ncols,
-                                                          double *__restrict__ out) {
+// the first store, then each lane sums its column in row order as above.  The
+// tiles of all fragments are one launch, as those of their shares, whose ends
+// make the phi tables too: a launch is 2 us of work, and the five fragments'
+// were fourteen (ten-cut estimate 673 us; in three launches 644 us on MI355X).
+__global__ __launch_bounds__(64) void colnorm_tile_kernel(const NormJob *__restrict__ jobs, uint32_t n_jobs) {
   __shared__ double tile[64 * 65];  // column c at c * 65 (padded against bank conflicts)
-  const uint64_t p0 = (uint64_t)blockIdx.x * 64;
+  uint32_t f = 0;
+  while (f + 1 < n_jobs && blockIdx.x >= jobs[f + 1].tile0) ++f;
+  const double *__restrict__ T = jobs[f].T;
+  double *__restrict__ out = jobs[f].norm;
+  const uint32_t rows = jobs[f].rows;
+  const uint64_t ncols = 1ull << (2 * jobs[f].n_axes);
+  const uint64_t p0 = (uint64_t)(blockIdx.x - jobs[f].tile0) * 64;
   const uint32_t lane = threadIdx.x;
   const uint64_t cols = ncols - p0 < 64 ? ncols - p0 : 64;
   const uint32_t n = (uint32_t)(cols * rows);  // <= 4096 doubles
@@ -142,15 +150,19 @@ __global__ __launch_bounds__(64) void colnorm_tile_kernel(const double *__restri
   }
 }
 
-// shares[j][d] = sum_{p: digit j of p = d} n[p]^2 / sum_p n[p]^2 for one
+// shares[j][d] = sum_{p: digit j of p = d} n[p]^2 / sum_p n[p]^2 for each
 // fragment: slot 4 j + d sums the 4^(a-1) columns with that digit, in
 // chunks (partials in order, then a fixed-order tree), then the chunks in
 // order.
 constexpr uint32_t kShareChunk = 4096;
-__global__ __launch_bounds__(256) void share_partial_kernel(const double *__restrict__ norm, uint64_t per_slot,
-                                                            uint32_t chunks, double *__restrict__ part) {
+__global__ __launch_bounds__(256) void share_partial_kernel(const NormJob *__restrict__ jobs, uint32_t n_jobs) {
   __shared__ double red[256];
-  const uint32_t slot = blockIdx.y, chunk = blockIdx.x;
+  uint32_t f = 0;
+  while (f + 1 < n_jobs && blockIdx.x >= jobs[f + 1].block0) ++f;
+  const double *__restrict__ norm = jobs[f].norm;
+  const uint32_t local = blockIdx.x - jobs[f].block0, chunks = jobs[f].chunks;
+  const uint32_t slot = local / chunks, chunk = local % chunks;
+  const uint64_t per_slot = 1ull << (2 * (jobs[f].n_axes - 1));
   const uint32_t j = slot >> 2, d = slot & 3;
   const uint64_t low = (1ull << (2 * j)) - 1;
   const uint64_t e0 = (uint64_t)chunk * kShareChunk;
@@ -166,32 +178,45 @@ __global__ __launch_bounds__(256) void share_partial_kernel(const double *__rest
     if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
     __syncthreads();
   }
-  if (threadIdx.x == 0) part[(uint64_t)slot * chunks + chunk] = red[0];
-}
-__global__ void share_final_kernel(const double *__restrict__ part, uint32_t n_slots, uint32_t chunks,
-                                   double *__restrict__ shares) {
-  __shared__ double tot[4 * kMaxAxes];
-  const uint32_t slot = threadIdx.x;
-  if (slot < n_slots) {
-    double sum = 0.0;
-    for (uint32_t c = 0; c < chunks; ++c) sum += part[(uint64_t)slot * chunks + c];
-    tot[slot] = sum;
-  }
-  __syncthreads();
-  const double total = tot[0] + tot[1] + tot[2] + tot[3];
-  if (slot < n_slots) shares[slot] = tot[slot] / total;
+  if (threadIdx.x == 0) jobs[f].part[local] = red[0];
 }
 
-// phi tables of every cut: phi(s) = max(ln s, -40) / 40 of the share of the
-// fragment on each side (src holds, per cut and side, the offset of that
-// fragment's share row in `shares`, or -1 when the side has no fragment).
-__global__ void phi_kernel(const double *__restrict__ shares, const int64_t *__restrict__ src, uint32_t k,
-                           double *__restrict__ phi) {
-  const uint32_t i = threadIdx.x;  // i = (c * 2 + side) * 4 + d
-  if (i >= 8 * k) return;
-  const uint32_t cs = i >> 2, d = i & 3;
-  const int64_t o = src[cs];
-  const double s = o < 0 ? 0.0 : shares[o + d];
+// The shares and, from them, the phi tables of every cut: phi(s) =
+// max(ln s, -40) / 40 of the share of the fragment on each side (src.slot
+// holds, per cut and side, the slot of that fragment's share row, or -1 when
+// the side has no fragment).  One workgroup, a thread per slot.
+__global__ __launch_bounds__(kPhiSlots) void phi_kernel(const NormJob *__restrict__ jobs, uint32_t n_jobs,
+                                                        const PhiSrc src, uint32_t n_slots, uint32_t k,
+                                                        double *__restrict__ phi) {
+  __shared__ double tot[kPhiSlots], share[kPhiSlots];
+  const uint32_t i = threadIdx.x;
+  uint32_t f = 0;
+  if (i < n_slots) {
+    while (f + 1 < n_jobs && i >= jobs[f + 1].slot0) ++f;
+    const uint32_t chunks = jobs[f].chunks;
+    const double *__restrict__ part = jobs[f].part + (uint64_t)(i - jobs[f].slot0) * chunks;
+    double sum = 0.0;
+    uint32_t c = 0;
+    for (; c + 16 <= chunks; c += 16) {  // sixteen loads in flight, added in order
+      double v[16];
+#pragma unroll
+      for (uint32_t u = 0; u < 16; ++u) v[u] = part[c + u];
+#pragma unroll
+      for (uint32_t u = 0; u < 16; ++u) sum += v[u];
+    }
+    for (; c < chunks; ++c) sum += part[c];
+    tot[i] = sum;
+  }
+  __syncthreads();
+  if (i < n_slots) {
+    const double *t = tot + jobs[f].slot0;
+    const double total = t[0] + t[1] + t[2] + t[3];
+    share[i] = tot[i] / total;
+  }
+  __syncthreads();
+  if (i >= 8 * k) return;  // i = (c * 2 + side) * 4 + d
+  const int o = src.slot[i >> 2];
+  const double s = o < 0 ? 0.0 : share[o + (i & 3)];
   phi[i] = (s > 0.0 ? fmax(log(s), -40.0) : -40.0) / 40.0;
 }
 
@@ -587,34 +612,35 @@ hipError_t launch_head_forward(const uint16_t *H, uint32_t width, uint64_t rows,
   return hipGetLastError();
 }
 
-hipError_t launch_colnorm(const double *T, uint32_t rows, uint64_t ncols, double *out, hipStream_t s) {
-  if (rows <= 64)
-    hipLaunchKernelGGL(colnorm_tile_kernel, dim3(blocks(ncols, 64)), dim3(64), 0, s, T, rows, ncols, out);
-  else
-    hipLaunchKernelGGL(colnorm_kernel, dim3(blocks(ncols, 256)), dim3(256), 0, s, T, rows, ncols, out);
+hipError_t launch_norms(const NormJob *jobs, const NormJob *d_jobs, uint32_t n_jobs, const PhiSrc &src, uint32_t k,
+                        double *phi, hipStream_t s) {
+  uint32_t tiles = 0, parts = 0, slots = 0;
+  for (uint32_t f = 0; f < n_jobs; ++f) {
+    const NormJob &J = jobs[f];
+    if (J.n_axes > (uint32_t)kMaxAxes || J.tile0 != tiles || J.block0 != parts || J.slot0 != slots)
+      return hipErrorInvalidValue;
+    const uint64_t ncols = 1ull << (2 * J.n_axes);
+    tiles += norm_tiles(J);
+    parts += 4 * J.n_axes * J.chunks;
+    slots += 4 * J.n_axes;
+    if (J.T && norm_tiles(J) == 0)
+      hipLaunchKernelGGL(colnorm_kernel, dim3(blocks(ncols, 256)), dim3(256), 0, s, J.T, J.rows, ncols, J.norm);
+  }
+  if (slots > kPhiSlots || 8 * k > kPhiSlots) return hipErrorInvalidValue;
+  if (tiles) hipLaunchKernelGGL(colnorm_tile_kernel, dim3(tiles), dim3(64), 0, s, d_jobs, n_jobs);
+  if (parts) hipLaunchKernelGGL(share_partial_kernel, dim3(parts), dim3(256), 0, s, d_jobs, n_jobs);
+  hipLaunchKernelGGL(phi_kernel, dim3(1), dim3(kPhiSlots), 0, s, d_jobs, n_jobs, src, slots, k, phi);
   return hipGetLastError();
 }
 
-hipError_t launch_shares(const double *norm, uint32_t n_axes, double *part, double *shares, hipStream_t s) {
-  if (n_axes == 0) return hipSuccess;
-  if (n_axes > (uint32_t)kMaxAxes) return hipErrorInvalidValue;
-  const uint64_t per_slot = 1ull << (2 * (n_axes - 1));
-  const uint32_t chunks = share_chunks(n_axes);
-  hipLaunchKernelGGL(share_partial_kernel, dim3(chunks, 4 * n_axes), dim3(256), 0, s, norm, per_slot, chunks, part);
-  hipLaunchKernelGGL(share_final_kernel, dim3(1), dim3(4 * kMaxAxes), 0, s, part, 4 * n_axes, chunks, shares);
-  return hipGetLastError();
+uint32_t norm_tiles(const NormJob &J) {
+  return J.T && J.rows <= 64 ? (uint32_t)(((1ull << (2 * J.n_axes)) + 63) / 64) : 0;
 }
 
 uint32_t share_chunks(uint32_t n_axes) {
   if (n_axes == 0) return 1;
   const uint64_t per_slot = 1ull << (2 * (n_axes - 1));
   return (uint32_t)((per_slot + kShareChunk - 1) / kShareChunk);
-}
-
-hipError_t launch_phi(const double *shares, const int64_t *src, uint32_t k, double *phi, hipStream_t s) {
-  if (8 * k > 1024) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(phi_kernel, dim3(1), dim3(8 * k), 0, s, shares, src, k, phi);
-  return hipGetLastError();
 }
 
 hipError_t launch_features(const LearnedDev *L, const uint64_t *terms, uint64_t first, uint64_t n, uint32_t width,
