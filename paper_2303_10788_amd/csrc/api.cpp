@@ -452,6 +452,7 @@ FragDev frag_desc(ccut_plan *p, const Fragment &f, const FragRequest &r, uint32_
   FragDev h = make_frag_dev(f, r, ((uint64_t)circuit << 40) | ((uint64_t)f.index << 32));
   h.ops = p->d_ops[f.index];
   h.mats = p->d_mats[f.index];
+  h.sv_halves = f.sv_halves;
   return h;
 }
 

@@ -172,6 +172,7 @@ struct FragDev {
   // two values in the stored states, the outcome bit (outputs; else 0) and the
   // stride in the variant index
   uint32_t in_axes, req_mask, rest_mask;
+  uint32_t sv_halves;  // factors 1/2 the states' probabilities still take
   uint32_t axis_dist[kMaxAxes], axis_obit[kMaxAxes], axis_stride[kMaxAxes];
 };
 

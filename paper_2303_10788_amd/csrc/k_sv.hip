@@ -219,7 +219,7 @@ __device__ __attribute__((always_inline)) void sv_combine(D &F, double *__restri
   // choices along the axes beyond the first two (three bits each)
   uint64_t kinds = 0;
   uint32_t v = 0;
-  int halves = 0;
+  int halves = (int)F.sv_halves;
 #pragma unroll 1
   for (uint32_t j = 2; j < n_axes; ++j) {
     const bool in = ins >> j & 1u;

@@ -207,10 +207,62 @@ void sv_block_matrix(const Fragment &F, const SvBlock &B, cplx (&U)[8][8]) {
 // A[l % 16][4 c + l / 16], c < 4.  The block's qubits are lane bits 4 and 5 and
 // the register; the other qubits fill lane bits 0-3 (residues 0, 1, 2, 3 mod 4
 // where they can: different LDS banks), then the tile.
+// Puts a block's matrix, times sqrt2 if the result says so, on exact values
+// where it has them: every component (a + b / sqrt2) / 64 with whole a, b
+// (Clifford gates and T), of the two scalings the one with fewer entries of b.  Whole
+// multiples of powers of two keep the products of a step exact, so amplitudes
+// that cancel cancel to zero rather than to a rounding residue.  Other
+// matrices (general rotations) stay as they are.
+bool sv_exact_matrix(cplx (&U)[8][8]) {
+  const double r = 0.70710678118654752440, tol = 64.0 * 2e-14;
+  struct Value {
+    double u, out[2];  // a magnitude, its exact value as it is and times sqrt2
+    bool root[2];
+  };
+  Value seen[16];  // a block has a few magnitudes; one with more is not of this form
+  uint32_t n_seen = 0, roots[2] = {};
+  uint8_t at[128];
+  const double *flat = reinterpret_cast<const double *>(U);
+  for (uint32_t i = 0; i < 128; ++i) {
+    const double u = std::fabs(flat[i]);
+    uint32_t k = 0;
+    while (k < n_seen && std::fabs(seen[k].u - u) > 2e-14) ++k;
+    if (k == n_seen) {
+      if (n_seen == 16) return false;
+      Value &x = seen[n_seen++];
+      x.u = u;
+      for (int odd = 0; odd < 2; ++odd) {
+        const double v = 64.0 * u * (odd ? 2.0 * r : 1.0);
+        bool found = false;
+        for (int t = 0; t <= 192 && !found; ++t) {  // no root, roots alone, then both
+          double a = 0.0, b = 0.0;
+          if (t == 1) b = std::floor(v / r + 0.5);
+          if (t >= 2) b = t & 1 ? -(t / 2) : t / 2;
+          if (t != 1) a = std::floor(v - b * r + 0.5);
+          if (std::fabs(v - (a + b * r)) > tol) continue;
+          found = true;
+          x.out[odd] = (double)((a + b * 0.70710678118654752440084436210485L) / 64.0L);
+          x.root[odd] = b != 0.0;
+        }
+        if (!found) return false;
+      }
+    }
+    at[i] = (uint8_t)k;
+  }
+  for (uint32_t e = 0; e < 64; ++e)  // entries; column 0 (where a run starts) decides a draw
+    for (int odd = 0; odd < 2; ++odd)
+      roots[odd] += seen[at[2 * e]].root[odd] || seen[at[2 * e + 1]].root[odd] ? (e % 8 == 0 ? 65u : 64u) : 0u;
+  const bool odd = roots[1] < roots[0];
+  double *to = reinterpret_cast<double *>(U);
+  for (uint32_t i = 0; i < 128; ++i) to[i] = std::copysign(seen[at[i]].out[odd], flat[i]);
+  return odd;
+}
+
 void build_sv_program(Fragment &F) {
   const uint32_t m = F.m(), mm = std::max(m, 3u);
   std::vector<SvBlock> blocks;
   sv_blocks(F, mm, blocks);
+  F.sv_halves = 0;
   F.sv_prog.reserve(256 * blocks.size());
   F.sv_prog_mats.reserve(256 * blocks.size());
   auto slot = [](uint32_t p) { return ((1u << p) | (p >= 4 ? 1u << (p & 3u) : 0u)) * 16u; };  // p < 12: sv_slot(2^p)
@@ -242,10 +294,15 @@ void build_sv_program(Fragment &F) {
     }
     cplx U[8][8];
     sv_block_matrix(F, B, U);
+    // every second factor sqrt2 takes the one before it out with 1/2; one
+    // that is left halves the probabilities (sv_combine)
+    const bool odd = sv_exact_matrix(U);
+    const double half = odd && F.sv_halves ? 0.5 : 1.0;
+    F.sv_halves ^= odd;
     for (uint32_t l = 0; l < 64; ++l)
       for (uint32_t c = 0; c < 4; ++c) {
         const uint32_t row = l % 16, k = 4 * c + l / 16;
-        const cplx u = U[row & 7u][k & 7u];
+        const cplx u = half * U[row & 7u][k & 7u];
         F.sv_prog_mats.push_back(row < 8 ? (k < 8 ? u.real() : -u.imag()) : (k < 8 ? u.imag() : u.real()));
       }
   }

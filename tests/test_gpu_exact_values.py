@@ -1,0 +1,40 @@
+"""State vectors of Clifford gates give whole multiples of 2^-n, to the bit: the
+three-qubit steps' matrices are whole multiples of powers of two, with the roots of
+two left over taken out of the probabilities.  A T gate on a qubit that stays in
+|0> makes the fragment non-Clifford; expected are the oracle's values rounded to
+multiples of 2^-n (they are such multiples, known to 1e-14 of at least 2^-12), so
+the comparison is for equality."""
+import numpy as np
+import pytest
+
+import paper_2303_10788_amd as cc
+import workloads as W
+from oracle import statevector as SV
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [3, 4, 7, 9, 12])
+@pytest.mark.parametrize("seed", [1, 2, 3])
+def test_clifford_states_to_the_bit(n, seed):
+    import torch
+    assert torch.cuda.is_available()
+    ctx = cc.Context()
+    rng = np.random.default_rng([n, seed])
+    ops = [("T", n - 1, -1, 0.0)]
+    for k, a, b, th in W.random_circuit(n - 1, 12 * n + seed, seed, kinds=["H", "S", "SDG", "X", "CX", "CZ"]):
+        ops.append((k, a, b, th))
+        if rng.random() < 0.2:
+            ops.append(("CZ", int(rng.integers(n - 1)), n - 1, 0.0))
+    print(f"values n={n} seed={seed} H={sum(o[0] == 'H' for o in ops)}", flush=True)
+    plan = cc.Plan(ctx, n, ops, [])
+    assert [f["clifford"] for f in plan.fragments()] == [0]
+    qubits = list(range(n))
+    ref = SV.uncut_marginal(n, ops, qubits)
+    want = np.round(ref * 2.0 ** n) / 2.0 ** n
+    assert np.abs(want - ref).max() <= 1e-12
+    assert np.array_equal(plan.marginal(qubits), want)
+    masks = rng.integers(0, 1 << n, size=20).astype(np.uint64)
+    par = np.array([[bin(int(x) & int(m)).count("1") & 1 for x in range(1 << n)] for m in masks])
+    z = np.array([(want * (1 - 2 * p)).sum() for p in par])
+    assert np.array_equal(plan.zexpect(masks), np.round(z))  # -1, 0 or 1
