@@ -1430,7 +1430,7 @@ ccut_status ccut_fragment_ops(const ccut_plan *p, uint32_t f, uint32_t *n_one, u
   if (!p || f >= p->pd.frags.size()) return CCUT_E_INVALID;
   const Fragment &F = p->pd.frags[f];
   const std::vector<uint32_t> &w = F.clifford ? F.cl_words : F.sv_words;
-  uint32_t one = 0, two = 0;
+  uint32_t one = F.clifford ? 0u : F.sv_left_out, two = 0;
   for (uint32_t x : w) {
     const uint32_t k = op_kind(x);
     if (k == G_CX || k == G_CZ)

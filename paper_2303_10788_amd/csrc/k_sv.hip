@@ -180,7 +180,9 @@ __device__ inline C2 sv_value(C2 a, C2 b, uint32_t k) {
 __device__ inline uint32_t sv_kind(bool input, uint32_t d) {
   return input ? (d == 3 ? 5u : d) : (d < 4 ? d + 2 : d - 4);
 }
-__device__ inline double sv_prob(C2 a) { return __builtin_fma(a.re, a.re, a.im * a.im); }
+// both squares rounded: (x, y) and (y, x) have the same probability, so values
+// that are zero by such a symmetry come out as zero
+__device__ inline double sv_prob(C2 a) { return a.re * a.re + a.im * a.im; }
 
 // lds: 36 x 64 doubles, the wave's sums on their way out (one short loop
 // stores them all: written out 36 times, the stores took as long to fetch as

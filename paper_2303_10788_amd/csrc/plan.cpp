@@ -68,9 +68,25 @@ M2 gate_matrix(uint32_t kind, double theta) {
 // the two-qubit gates that do not touch them, so emitting a run just before
 // the first two-qubit gate on its qubit preserves the circuit.  A run that
 // is diagonal so far also commutes with a CZ on its qubit and with a CX it
-// controls, so it continues past them.
+// controls, so it continues past them.  Diagonal gates that end a qubit which
+// goes into no cut change no outcome (it is measured in Z or summed over) and
+// are left out: a T there would only round amplitudes of equal magnitude
+// differently.
 void fuse_one_qubit_runs(Fragment &F) {
   const uint32_t m = F.m();
+  std::vector<char> end(m, 1), skip(F.op_words.size(), 0);
+  for (const Axis &a : F.axes)
+    if (a.side == 0) end[a.local] = 0;
+  for (size_t g = F.op_words.size(); g-- > 0;) {
+    const uint32_t k = op_kind(F.op_words[g]), q = op_q0(F.op_words[g]);
+    if (is_two_qubit(k)) {
+      end[q] = end[op_q1(F.op_words[g])] = 0;
+    } else {
+      const M2 M = gate_matrix(k, F.op_theta[g]);
+      end[q] = end[q] && M.b == 0.0 && M.c == 0.0;
+      skip[g] = end[q];
+    }
+  }
   std::vector<M2> pend(m, M2{1, 0, 0, 1});
   std::vector<char> has(m, 0);
   auto flush = [&](uint32_t q) {
@@ -87,6 +103,7 @@ void fuse_one_qubit_runs(Fragment &F) {
   };
   for (size_t g = 0; g < F.op_words.size(); ++g) {
     const uint32_t w = F.op_words[g], k = op_kind(w), a = op_q0(w), b = op_q1(w);
+    if (skip[g]) continue;
     if (is_two_qubit(k)) {
       // a diagonal run commutes with a CZ on its qubit and with a CX it
       // controls, so it stays pending and merges with the next run
@@ -99,6 +116,18 @@ void fuse_one_qubit_runs(Fragment &F) {
       pend[a] = mul(gate_matrix(k, F.op_theta[g]), pend[a]);
       has[a] = 1;
     }
+  }
+  for (size_t g = 0; g < skip.size(); ++g)  // a run left out as a whole still counts as one (ccut_fragment_ops)
+    if (skip[g] && !has[op_q0(F.op_words[g])]) has[op_q0(F.op_words[g])] = 2;
+  F.sv_left_out = 0;
+  for (uint32_t q = 0; q < m; ++q)
+    if (has[q] == 2) {
+      ++F.sv_left_out;
+      has[q] = 0;
+    }
+  if (F.sv_left_out && F.sv_words.empty() && std::count(has.begin(), has.end(), 1) == 0) {
+    --F.sv_left_out;  // a program has a step: one of them as the identity
+    has[0] = 1;
   }
   for (uint32_t q = 0; q < m; ++q) flush(q);
 }

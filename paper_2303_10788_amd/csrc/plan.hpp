@@ -46,6 +46,7 @@ struct Fragment {
   // words and 256 doubles a step, build_sv_program)
   std::vector<uint32_t> sv_prog;
   std::vector<double> sv_prog_mats;
+  uint32_t sv_left_out = 0;  // runs that change no outcome and are not in sv_words
   uint32_t sv_halves = 0;  // factors 1/2 its states' probabilities still take (0 or 1)
   bool clifford = true;
   std::vector<Axis> axes;

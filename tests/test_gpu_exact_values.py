@@ -38,3 +38,23 @@ def test_clifford_states_to_the_bit(n, seed):
     par = np.array([[bin(int(x) & int(m)).count("1") & 1 for x in range(1 << n)] for m in masks])
     z = np.array([(want * (1 - 2 * p)).sum() for p in par])
     assert np.array_equal(plan.zexpect(masks), np.round(z))  # -1, 0 or 1
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 6, 12])
+def test_diagonal_gates_at_the_end(n):
+    """T gates that end every qubit change no outcome: the values are those of the Clifford circuit before them, to the
+    bit (n = 1: nothing but a T), and the gates still count."""
+    import torch
+    assert torch.cuda.is_available()
+    ctx = cc.Context()
+    cliff = list(W.random_circuit(n, 10 * n, n, kinds=["H", "S", "X", "CX", "CZ"])) if n > 1 else []
+    ops = cliff + [("T", q, -1, 0.0) for q in range(n)] + [("S", 0, -1, 0.0)]
+    print(f"end n={n}", flush=True)
+    plan = cc.Plan(ctx, n, ops, [])
+    qubits = list(range(n))
+    ref = SV.uncut_marginal(n, ops, qubits)
+    want = np.round(ref * 2.0 ** n) / 2.0 ** n
+    assert np.abs(want - ref).max() <= 1e-12
+    assert np.array_equal(plan.marginal(qubits), want)
+    one, two = cc.ccut_fragment_ops(plan.handle, 0)
+    assert two == sum(o[0] in ("CX", "CZ") for o in ops) and n <= one <= len(ops) - two
