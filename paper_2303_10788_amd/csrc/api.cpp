@@ -2968,9 +2968,11 @@ ccut_status batch_enqueue(ccut_batch *b, bool tune) {
   // The plans' remaining steps.  Work that the batched launches below do
   // not cover (Heisenberg tensors, tables outside the pre-pass, transforms
   // too large to tile, contractions of more than 8 fragments) runs per plan,
-  // plan i on pool stream i mod P; then, on the batch stream, one tiled
-  // transform launch for every other fragment, one plain and one MFMA
-  // contraction launch for all plans.  Each plan takes the same transform
+  // plan i on pool stream i mod P.  The transforms of every other fragment are
+  // one launch per kind, those into counts on the batch stream and those into
+  // values on the first pool stream, which waits for the other pool streams
+  // where these wrote one of their tables.  Then, on the batch stream again,
+  // the contractions of all plans.  Each plan takes the same transform
   // and contraction as a call of its own, so the results are the same bits.
   const size_t P = b->pool.size(), np = b->plans.size();
   HIP_TRY(c, hipEventRecord(b->fork_ev, b->stream));
@@ -2983,6 +2985,7 @@ ccut_status batch_enqueue(ccut_batch *b, bool tune) {
   std::vector<uint8_t> kind(np);  // 0 plain (batched), 1 plain (own launch), 2 MFMA, 3 exact through a fragment (own launch)
   std::vector<int> exact_of(np, -1);
   std::vector<HeisRows> exact_rows(np);
+  bool pool_tables = false;  // some tile job reads a table that its plan's pool stream writes
   for (size_t i = 0; i < np; ++i) {
     ccut_plan *p = b->plans[i];
     const PlanData &pd = p->pd;
@@ -3018,7 +3021,8 @@ ccut_status batch_enqueue(ccut_batch *b, bool tune) {
         double *dist = pre_dist[i][f.index];
         uint16_t *cnt = pre_cnt[i][f.index];
         uint64_t *pm = b->model_off[i][f.index] >= 0 ? d_models + b->model_off[i][f.index] : nullptr;
-        st = (dist || cnt) ? CCUT_OK : variant_dists(p, &eo, f, r, &dist, pm);
+        const bool own_table = !dist && !cnt;
+        st = own_table ? variant_dists(p, &eo, f, r, &dist, pm) : CCUT_OK;
         const uint64_t xsize = 1ull << r.meas.size();
         TileJob J;
         if (st == CCUT_OK && (int)f.index == g) {
@@ -3035,6 +3039,7 @@ ccut_status batch_enqueue(ccut_batch *b, bool tune) {
           J.shots = (double)eo.shots_per_variant;
           J.fold = fold_mask(pd, g, f);  // the fold of fold_jobs, applied in the tile
           folded[f.index] = 1;
+          pool_tables |= own_table;
           const TileKind tk = !whole ? kTileF64 : counts_contraction(pd, &eo, nq) ? kTileCounts : kTileCountsF64;
           J.out = T = (double *)c->arena.get((J.x_out << (2 * f.axes.size())) *
                                              (tk == kTileCounts ? sizeof(int32_t) : sizeof(double)));
@@ -3069,7 +3074,13 @@ ccut_status batch_enqueue(ccut_batch *b, bool tune) {
     // the contraction recombine() would take
     kind[i] = ef >= 0 ? 3 : plain_contraction(args, nq, fp32) ? (args.n_frags <= 8 ? 0 : 1) : 2;
   }
-  // the transforms: into counts on the batch stream, the others beside them
+  // the transforms: into counts on the batch stream (their tables were all
+  // written there), the others beside them
+  if (pool_tables)
+    for (size_t k = 1; k < P; ++k) {
+      HIP_TRY(c, hipEventRecord(b->join_ev[k], b->pool[k]));
+      HIP_TRY(c, hipStreamWaitEvent(b->pool[0], b->join_ev[k], 0));
+    }
   for (int values = 0; values < 2; ++values) {
     std::vector<OutJob> &list = ojobs[values];
     if (list.empty()) continue;
