@@ -71,7 +71,8 @@ M2 gate_matrix(uint32_t kind, double theta) {
 // controls, so it continues past them.  Diagonal gates that end a qubit which
 // goes into no cut change no outcome (it is measured in Z or summed over) and
 // are left out: a T there would only round amplitudes of equal magnitude
-// differently.
+// differently.  (An angle that is no number is not left out: what it makes of
+// the outcomes is no number either.)
 void fuse_one_qubit_runs(Fragment &F) {
   const uint32_t m = F.m();
   std::vector<char> end(m, 1), skip(F.op_words.size(), 0);
@@ -83,7 +84,7 @@ void fuse_one_qubit_runs(Fragment &F) {
       end[q] = end[op_q1(F.op_words[g])] = 0;
     } else {
       const M2 M = gate_matrix(k, F.op_theta[g]);
-      end[q] = end[q] && M.b == 0.0 && M.c == 0.0;
+      end[q] = end[q] && M.b == 0.0 && M.c == 0.0 && std::isfinite(M.d.real()) && std::isfinite(M.d.imag());
       skip[g] = end[q];
     }
   }
@@ -254,6 +255,7 @@ bool sv_exact_matrix(cplx (&U)[8][8]) {
   const double *flat = reinterpret_cast<const double *>(U);
   for (uint32_t i = 0; i < 128; ++i) {
     const double u = std::fabs(flat[i]);
+    if (!std::isfinite(u)) return false;  // (an angle that is no number; it would compare equal to any magnitude)
     uint32_t k = 0;
     while (k < n_seen && std::fabs(seen[k].u - u) > 2e-14) ++k;
     if (k == n_seen) {

@@ -15,6 +15,7 @@ std::string g_log;
 std::map<const void *, std::string> g_kernels;
 long g_ids = 0;
 const char *g_fail = "";  // allocations by this name fail
+std::string g_copied;     // what the last hipMemcpy copied (a plan's programs)
 struct {
   dim3 grid, block;
   size_t shmem;
@@ -41,6 +42,7 @@ std::string fail_name;
 extern "C" {
 const char *host_hip_log() { return g_log.c_str(); }
 void host_hip_clear() { g_log.clear(); }
+const char *host_hip_copied(size_t *n) { return *n = g_copied.size(), g_copied.data(); }
 void host_hip_fail(const char *name) {
   fail_name = name;
   g_fail = fail_name.c_str();
@@ -72,7 +74,10 @@ hipError_t hipMalloc(void **p, size_t n) { return allocate("hipMalloc", p, n); }
 hipError_t hipHostMalloc(void **p, size_t n, unsigned) { return allocate("hipHostMalloc", p, n); }
 hipError_t hipFree(void *p) { return std::free(p), hipSuccess; }
 hipError_t hipHostFree(void *p) { return std::free(p), hipSuccess; }
-hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { return std::memcpy(d, s, n), hipSuccess; }
+hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) {
+  g_copied.assign((const char *)s, n);
+  return std::memcpy(d, s, n), hipSuccess;
+}
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t stream) {
   put("copy %p %zu", (void *)stream, n);
   return std::memcpy(d, s, n), hipSuccess;

@@ -1,8 +1,9 @@
 """The library's host side on the CPU, over the recording runtime of
 _host_hip.cpp (not collected).  run(code) executes `code` in a process of its
-own, where `cc` is the binding, `ctx` a context on the recorded device, and
+own, where `cc` is the binding, `ctx` a context on the recorded device,
 log() / clear() / fail(name) read and reset the record or make an allocation
-fail; what `code` leaves in `result` comes back."""
+fail and copied() is what the last synchronous copy moved (a plan's programs);
+what `code` leaves in `result` comes back."""
 import json
 import os
 import subprocess
@@ -35,6 +36,13 @@ def new_context(**fields):
 log = lambda: [l.split() for l in _rt.host_hip_log().decode().splitlines()]
 clear = _rt.host_hip_clear
 fail = lambda name: _rt.host_hip_fail(name.encode())
+
+def copied():
+    n = ctypes.c_size_t()
+    _rt.host_hip_copied.restype = ctypes.c_void_p
+    p = _rt.host_hip_copied(ctypes.byref(n))
+    return ctypes.string_at(p, n.value)
+
 ctx = new_context()
 result = None
 """

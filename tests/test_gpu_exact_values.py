@@ -58,3 +58,20 @@ def test_diagonal_gates_at_the_end(n):
     assert np.array_equal(plan.marginal(qubits), want)
     one, two = cc.ccut_fragment_ops(plan.handle, 0)
     assert two == sum(o[0] in ("CX", "CZ") for o in ops) and n <= one <= len(ops) - two
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_an_angle_that_is_no_number_shows(bad):
+    """Nothing that such a gate reaches is a number: in the circuit's middle every outcome, at a qubit's end those of
+    outcome 1 (the matrix there is diag(1, nan))."""
+    import torch
+    assert torch.cuda.is_available()
+    ctx = cc.Context()
+    print(f"angle {bad}", flush=True)
+    mid = [("H", 0, -1, 0.0), ("RZ", 0, -1, bad)] + [("CX", 0, t, 0.0) for t in (1, 2, 3)] + [("H", 0, -1, 0.0)]
+    plan = cc.Plan(ctx, 4, mid, [])
+    assert np.isnan(plan.marginal([0, 1, 2, 3])).all() and np.isnan(plan.marginal([2])).all()
+    assert np.isnan(plan.zexpect(np.array([1, 2], dtype=np.uint64))).all()
+    end = [("H", 0, -1, 0.0), ("T", 0, -1, 0.0), ("CX", 0, 1, 0.0), ("RZ", 1, -1, bad)]
+    got = cc.Plan(ctx, 2, end, []).marginal([0, 1])
+    assert np.array_equal(np.isnan(got), [False, False, True, True])
