@@ -30,22 +30,23 @@ typedef __attribute__((address_space(4))) const uint64_t c_u64;
 typedef __attribute__((address_space(4))) const RecombArgs c_RecombArgs;
 typedef __attribute__((address_space(1))) const double g_f64;
 
-// Column of fragment f's tensor under cut term P (two bits per cut).
+// Column of fragment f's tensor under cut term P (two bits per cut; up to
+// kMaxAxes + kExactMaxFree = 19 cuts pass through one fragment, so 38 bits).
 template <class F>
-__device__ inline uint32_t frag_column(F &f, uint32_t P) {
+__device__ inline uint32_t frag_column(F &f, uint64_t P) {
   uint32_t p = 0;
-  for (uint32_t j = 0; j < f.n_axes; ++j) p |= ((P >> (2 * f.axis_cut[j])) & 3u) << (2 * j);
+  for (uint32_t j = 0; j < f.n_axes; ++j) p |= ((uint32_t)(P >> (2 * f.axis_cut[j])) & 3u) << (2 * j);
   return p;
 }
 
 // The free Paulis' share of the cut term, and C's output Paulis among them
 // applied to `acc`.
 template <int W>
-__device__ inline uint32_t free_paulis(const ExactArgs &A, uint32_t t, PAcc<W> &acc, c_u64 *rows) {
-  uint32_t P = 0;
+__device__ inline uint64_t free_paulis(const ExactArgs &A, uint32_t t, PAcc<W> &acc, c_u64 *rows) {
+  uint64_t P = 0;
   for (uint32_t i = 0; i < A.n_free; ++i) {
     const uint32_t d = (t >> (2 * i)) & 3u;
-    P |= d << (2 * A.free_cut[i]);
+    P |= (uint64_t)d << (2 * A.free_cut[i]);
     if (A.free_row[i] != ~0u) pmul_out<W>(acc, d, rows + (size_t)A.free_row[i] * (2 * W + 1));
   }
   return P;
@@ -54,12 +55,12 @@ __device__ inline uint32_t free_paulis(const ExactArgs &A, uint32_t t, PAcc<W> &
 // C's input Paulis as bits of the cut term; false if a circuit input carries
 // X or Y (the expectation vanishes).
 template <int W>
-__device__ inline bool input_paulis(const ExactArgs &A, const PAcc<W> &acc, uint32_t &P) {
+__device__ inline bool input_paulis(const ExactArgs &A, const PAcc<W> &acc, uint64_t &P) {
   uint64_t bad = 0;
 #pragma unroll
   for (int w = 0; w < W; ++w) bad |= acc.x[w] & A.cin_mask[w];
   if (bad) return false;
-  for (uint32_t i = 0; i < A.n_in; ++i) P |= pdigit<W>(acc, A.in_local[i]) << (2 * A.in_cut[i]);
+  for (uint32_t i = 0; i < A.n_in; ++i) P |= (uint64_t)pdigit<W>(acc, A.in_local[i]) << (2 * A.in_cut[i]);
   return true;
 }
 
@@ -98,7 +99,7 @@ __global__ __launch_bounds__(kExactThreads) void exact_marginal_kernel(const Exa
     double sum = 0.0;
     for (uint32_t t = 0; t < 1u << (2 * A.n_free); ++t) {
       PAcc<W> o = acc;
-      uint32_t P = free_paulis<W>(A, t, o, rows);
+      uint64_t P = free_paulis<W>(A, t, o, rows);
       if (!live || !input_paulis<W>(A, o, P)) continue;
       double v = psign<W>(o) ? -1.0 : 1.0;
       uint32_t shift = 0;
@@ -158,7 +159,7 @@ __global__ __launch_bounds__(64) void exact_strings_kernel(const ExactArgs A, co
   double sum = 0.0;
   for (uint32_t t = 0; t < 1u << (2 * A.n_free); ++t) {
     PAcc<W> o = acc;
-    uint32_t P = free_paulis<W>(A, t, o, rows);
+    uint64_t P = free_paulis<W>(A, t, o, rows);
     if (!input_paulis<W>(A, o, P)) continue;
     double v = psign<W>(o) ? -1.0 : 1.0;
     float hi = (float)v, corr = 0.f;
@@ -236,8 +237,9 @@ __global__ __launch_bounds__(kColThreads) void columns_kernel(const ExactArgs A,
     pclear(acc);
     for (uint32_t j = 0; j < A.r; ++j)
       if (e >> j & 1u) pmul<W>(acc, rows + (size_t)j * (2 * W + 1));
-    uint32_t P = free_paulis<W>(A, e >> A.r, acc, rows);
-    if (!input_paulis<W>(A, acc, P)) continue;
+    uint64_t term = free_paulis<W>(A, e >> A.r, acc, rows);
+    if (!input_paulis<W>(A, acc, term)) continue;
+    const uint32_t P = (uint32_t)term;  // (at most kMaxColumnCuts cuts here)
     pair[i] = P | psign<W>(acc) << 31;
     atomicOr(&mask[col_at(P >> 5, per)], 1u << (P & 31));
   }
@@ -355,7 +357,7 @@ __global__ __launch_bounds__(kColThreads) void column_support_kernel(const Recom
     for (uint32_t f = 0; ok && f < R.n_frags; ++f) {
       if (f == A.frag) continue;
       auto &F = R.f[f];
-      ok = nz[sa.off[f] + frag_column(F, (uint32_t)P)] != 0;
+      ok = nz[sa.off[f] + frag_column(F, P)] != 0;
     }
     const uint32_t incl = block_scan(ok ? 1u : 0u, wave_sum);
     uint32_t total = 0;

@@ -179,3 +179,45 @@ def test_columns_fp32_and_learned(ctx, exits, n):
                 v = v * tens[f][p][b]
             exp += c * v / (700 * qh[P])
         assert np.abs(est - exp).max() <= 1e-10 * max(1.0, np.abs(exp).max())
+
+
+@pytest.mark.parametrize("n_in,out,chain,turned", [(13, False, 3, False), (14, False, 3, False), (14, False, 3, True),
+                                                   (15, True, 1, False), (15, True, 2, True)])
+def test_many_cuts(n_in, out, chain, turned):
+    """16 to 18 cuts: n_in one-qubit fragments with a T feed a Clifford part (`out`: one of its wires goes on to a T), and
+    `chain` cuts follow one another on a wire of their own; the cuts numbered along the circuit or the other way round."""
+    ctx = cc.Context(max_cuts=20)
+    rng = np.random.default_rng([n_in, chain])
+    n, ops, cuts = n_in + 1, [], []
+
+    def block(q):
+        for k in ("H", "T", "H"):
+            ops.append((k, q, -1, 0.0))
+
+    for q in range(n_in):
+        block(q)
+        cuts.append((q, len(ops) - 1))
+    for a in range(n_in - 1):
+        ops.append(("CX", a, a + 1, 0.0))
+    ops.extend(W.random_circuit(n_in, 40, int(rng.integers(1 << 30)), kinds=CLIFF))
+    for a in range(n_in - 1):
+        ops.append(("CZ", a, a + 1, 0.0))
+    if out:
+        cuts.append((0, len(ops) - 1 - (n_in - 2)))
+        block(0)
+    for i in range(chain):
+        block(n_in)
+        cuts.append((n_in, len(ops) - 1))
+    block(n_in)
+    if turned:
+        cuts = cuts[::-1]
+    print(f"many cuts k={len(cuts)}", flush=True)
+    plan = cc.Plan(ctx, n, ops, cuts)
+    assert plan.info()[0] == n_in + 1 + out + chain + 1
+    full = SV.uncut_marginal(n, ops, list(range(n)))
+    idx = np.arange(1 << n, dtype=np.uint64)
+    masks = np.array([(1 << n) - 1, 1 << n_in | 1, 1 << (n_in - 1), int(rng.integers(1, 1 << n))], dtype=np.uint64)
+    par = np.array([[bin(int(x & m)).count("1") & 1 for x in idx] for m in masks])
+    assert np.abs(plan.zexpect(masks) - (full * (1 - 2 * par)).sum(axis=1)).max() <= 1e-10
+    for qubits in ([0, n_in], [n_in - 1, n_in, 3], [n_in]):
+        assert np.abs(plan.marginal(qubits) - SV.uncut_marginal(n, ops, qubits)).max() <= 1e-10
