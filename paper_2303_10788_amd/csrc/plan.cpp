@@ -89,18 +89,19 @@ void fuse_one_qubit_runs(Fragment &F) {
     }
   }
   std::vector<M2> pend(m, M2{1, 0, 0, 1});
-  std::vector<char> has(m, 0);
+  std::vector<char> has(m, 0), rz(m, 0);  // rz: an RZ is in the run
   auto flush = [&](uint32_t q) {
     if (!has[q]) return;
     const M2 &M = pend[q];
     F.sv_words.push_back(pack_op(G_U2, q, 0));
+    F.sv_rz.push_back(rz[q]);
     const cplx e[4] = {M.a, M.b, M.c, M.d};
     for (auto &z : e) {
       F.sv_mats.push_back(z.real());
       F.sv_mats.push_back(z.imag());
     }
     pend[q] = M2{1, 0, 0, 1};
-    has[q] = 0;
+    has[q] = rz[q] = 0;
   };
   for (size_t g = 0; g < F.op_words.size(); ++g) {
     const uint32_t w = F.op_words[g], k = op_kind(w), a = op_q0(w), b = op_q1(w);
@@ -112,10 +113,12 @@ void fuse_one_qubit_runs(Fragment &F) {
       if (!(diag(a) && (k == G_CZ || k == G_CX))) flush(a);
       if (!(diag(b) && k == G_CZ)) flush(b);
       F.sv_words.push_back(w);
+      F.sv_rz.push_back(0);
       for (int t = 0; t < 8; ++t) F.sv_mats.push_back(0.0);
     } else {
       pend[a] = mul(gate_matrix(k, F.op_theta[g]), pend[a]);
       has[a] = 1;
+      rz[a] |= k == G_RZ;
     }
   }
   for (size_t g = 0; g < skip.size(); ++g)  // a run left out as a whole still counts as one (ccut_fragment_ops)
@@ -237,12 +240,14 @@ void sv_block_matrix(const Fragment &F, const SvBlock &B, cplx (&U)[8][8]) {
 // A[l % 16][4 c + l / 16], c < 4.  The block's qubits are lane bits 4 and 5 and
 // the register; the other qubits fill lane bits 0-3 (residues 0, 1, 2, 3 mod 4
 // where they can: different LDS banks), then the tile.
-// Puts a block's matrix, times sqrt2 if the result says so, on exact values
-// where it has them: every component (a + b / sqrt2) / 64 with whole a, b
-// (Clifford gates and T), of the two scalings the one with fewer entries of b.  Whole
+// Puts the matrix of a block of Clifford gates and T, times sqrt2 if the result
+// says so, on its exact values where these are of the form (a + b / sqrt2) / 64
+// with whole a, b (found from the product of the gates, which is within 2e-14
+// of them), of the two scalings the one with fewer entries of b.  Whole
 // multiples of powers of two keep the products of a step exact, so amplitudes
-// that cancel cancel to zero rather than to a rounding residue.  Other
-// matrices (general rotations) stay as they are.
+// that cancel cancel to zero rather than to a rounding residue.  The angle of an
+// RZ is the caller's, however close to a multiple of pi / 4 (or no number at
+// all): a block that holds one stays as it is.
 bool sv_exact_matrix(cplx (&U)[8][8]) {
   const double r = 0.70710678118654752440, tol = 64.0 * 2e-14;
   struct Value {
@@ -255,7 +260,6 @@ bool sv_exact_matrix(cplx (&U)[8][8]) {
   const double *flat = reinterpret_cast<const double *>(U);
   for (uint32_t i = 0; i < 128; ++i) {
     const double u = std::fabs(flat[i]);
-    if (!std::isfinite(u)) return false;  // (an angle that is no number; it would compare equal to any magnitude)
     uint32_t k = 0;
     while (k < n_seen && std::fabs(seen[k].u - u) > 2e-14) ++k;
     if (k == n_seen) {
@@ -327,7 +331,8 @@ void build_sv_program(Fragment &F) {
     sv_block_matrix(F, B, U);
     // every second factor sqrt2 takes the one before it out with 1/2; one
     // that is left halves the probabilities (sv_combine)
-    const bool odd = sv_exact_matrix(U);
+    const bool rz = std::any_of(B.ops.begin(), B.ops.end(), [&](size_t g) { return F.sv_rz[g] != 0; });
+    const bool odd = !rz && sv_exact_matrix(U);
     const double half = odd && F.sv_halves ? 0.5 : 1.0;
     F.sv_halves ^= odd;
     for (uint32_t l = 0; l < 64; ++l)

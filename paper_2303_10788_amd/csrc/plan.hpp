@@ -42,6 +42,7 @@ struct Fragment {
   // qubit fused into one 2x2 unitary (G_U2) for the state-vector kernel
   std::vector<uint32_t> sv_words;
   std::vector<double> sv_mats;              // 8 doubles per sv word
+  std::vector<char> sv_rz;                  // per sv word: an RZ is in it
   // the same stream as three-qubit unitaries for the state-vector kernel (256
   // words and 256 doubles a step, build_sv_program)
   std::vector<uint32_t> sv_prog;

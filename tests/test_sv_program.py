@@ -66,3 +66,24 @@ def _product(ops):
 def test_an_angle_that_is_no_number_stays(n, pre, post, bad):
     steps = _steps(n, pre + [("RZ", 0, 0, bad)] + post)
     assert any(np.isnan(M).any() for M in steps)
+
+
+@pytest.mark.parametrize("theta", [1e-14, -1.5e-14, np.pi / 4 + 1e-14, np.pi / 2 - 1.5e-14, np.pi + 2e-14, 1.0])
+@pytest.mark.parametrize("pre,post", [(["H"], ["H"]), (["H"], ["SDG", "H"]), (["H", "T"], ["H"])])
+def test_an_angle_near_pi_over_four_is_kept(pre, post, theta):
+    """The caller's angle, not the multiple of pi / 4 that it lies near.  Tolerance: the products of at most four gates'
+    entries of magnitude <= 1 round to within 4 x 2 x 2^-53 < 1e-15; the angles differ by 1e-14 and more, half of it in an
+    entry."""
+    ops = [(k, 0, 0, 0.0) for k in pre] + [("RZ", 0, 0, theta)] + [(k, 0, 0, 0.0) for k in post]
+    (M,) = _steps(1, ops)
+    assert np.abs(M - _product(ops)).max() <= 1e-15
+
+
+def test_clifford_and_t_steps_stay_exact():
+    """Matrices of gates without an angle, times sqrt2 where that is so, have the values (a + b / sqrt2) / 64 exactly."""
+    ops = [("H", 0, 0, 0.0), ("T", 0, 0, 0.0), ("CX", 0, 1, 0.0), ("H", 1, 0, 0.0), ("T", 1, 0, 0.0), ("H", 0, 0, 0.0),
+           ("CX", 1, 2, 0.0), ("T", 2, 0, 0.0), ("H", 2, 0, 0.0)]
+    grid = {float(np.float64((a + b * np.longdouble(0.5) ** np.longdouble(0.5)) / 64)) for a in range(-64, 65)
+            for b in range(-64, 65)}
+    for M in _steps(3, ops):
+        assert {float(x) for x in np.concatenate([M.real.ravel(), M.imag.ravel()])} <= grid
