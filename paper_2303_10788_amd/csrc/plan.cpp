@@ -151,41 +151,48 @@ struct SvBlock {
 void sv_blocks(const Fragment &F, uint32_t mm, std::vector<SvBlock> &blocks) {
   const size_t n = F.sv_words.size();
   std::vector<uint32_t> mask(n);
-  std::vector<char> two(n);
+  std::vector<std::vector<size_t>> on(mm);  // each qubit's ops in order
+  std::vector<size_t> head(mm, 0);          // of them taken: always the first ones
   for (size_t g = 0; g < n; ++g) {
     const uint32_t w = F.sv_words[g];
-    two[g] = is_two_qubit(op_kind(w));
-    mask[g] = 1u << op_q0(w) | (two[g] ? 1u << op_q1(w) : 0u);
+    mask[g] = 1u << op_q0(w) | (is_two_qubit(op_kind(w)) ? 1u << op_q1(w) : 0u);
+    for (uint32_t r = mask[g]; r; r &= r - 1) on[__builtin_ctz(r)].push_back(g);
   }
-  std::vector<char> done(n, 0);
-  auto scan = [&](size_t g0, uint32_t set, std::vector<size_t> *take) {
-    uint32_t blocked = 0;
-    size_t count = 0;
-    for (size_t g = g0; g < n && (set & ~blocked); ++g) {
-      if (done[g]) continue;
-      if (!(mask[g] & blocked) && !(mask[g] & ~set)) {
+  // the ops on `set` that a block may take, in order; only ops that touch a
+  // qubit of it which is not blocked yet are looked at
+  auto scan = [&](uint32_t set, std::vector<size_t> *take) {
+    size_t at[32], count = 0;
+    for (uint32_t r = set; r; r &= r - 1) at[__builtin_ctz(r)] = head[__builtin_ctz(r)];
+    for (uint32_t open = set;;) {
+      size_t g = n;
+      for (uint32_t r = open; r; r &= r - 1) {
+        const uint32_t q = __builtin_ctz(r);
+        if (at[q] < on[q].size()) g = std::min(g, on[q][at[q]]);
+      }
+      if (g == n) return count;
+      if (!(mask[g] & ~open)) {
         ++count;
         if (take) take->push_back(g);
+        for (uint32_t r = mask[g]; r; r &= r - 1) ++at[__builtin_ctz(r)];
       } else {
-        blocked |= mask[g];
+        open &= ~mask[g];
       }
     }
-    return count;
   };
+  std::vector<char> done(n, 0);
   for (size_t g0 = 0; g0 < n; ++g0) {
     if (done[g0]) continue;
     uint32_t pair = mask[g0];
-    for (size_t g = g0 + 1; g < n && !two[g0]; ++g)
-      if (!done[g] && two[g] && (mask[g] & pair)) {
-        pair |= mask[g];
-        break;
-      }
+    if (__builtin_popcount(pair) == 1) {
+      const uint32_t q = __builtin_ctz(pair);
+      for (size_t i = head[q]; i < on[q].size() && __builtin_popcount(pair) == 1; ++i) pair |= mask[on[q][i]];
+    }
     for (uint32_t q = 0; __builtin_popcount(pair) < 2; ++q) pair |= 1u << q;
     uint32_t best = 0;
     size_t most = 0;
     for (uint32_t q = 0; q < mm; ++q) {
       if (pair >> q & 1u) continue;
-      const size_t c = scan(g0, pair | 1u << q, nullptr);
+      const size_t c = scan(pair | 1u << q, nullptr);
       if (c > most) {
         most = c;
         best = q;
@@ -195,8 +202,11 @@ void sv_blocks(const Fragment &F, uint32_t mm, std::vector<SvBlock> &blocks) {
     SvBlock B;
     for (uint32_t q = 0, i = 0; q < mm; ++q)
       if (set >> q & 1u) B.q[i++] = q;
-    scan(g0, set, &B.ops);
-    for (size_t g : B.ops) done[g] = 1;
+    scan(set, &B.ops);
+    for (size_t g : B.ops) {
+      done[g] = 1;
+      for (uint32_t r = mask[g]; r; r &= r - 1) ++head[__builtin_ctz(r)];
+    }
     blocks.push_back(std::move(B));
   }
 }
