@@ -143,6 +143,7 @@ struct CallGraph {
   size_t pin_cap = 0, pin_used = 0, upload_bytes = 0;
   const double *res = nullptr;  // a host-output call's result on the device (in the context's scratch)
   bool no_graph = false;  // capture failed once: stay eager
+  bool on_device = false;  // the call's output
   uint64_t last_use = 0;
   void release() {
     if (exec) (void)hipGraphExecDestroy(exec);
@@ -164,7 +165,9 @@ struct ccut_plan {
   std::vector<const uint32_t *> d_lanes;  // carry-back lane program, or
   std::vector<const uint32_t *> d_back, d_back_layers;  // layered stream
   std::vector<uint32_t> n_steps, n_back, n_back_layers;
-  std::vector<CallGraph> graphs;  // least recently used first out, at most kMaxCallGraphs
+  // at most kMaxCallGraphs of calls with a device output and as many of calls
+  // with a host output, of each kind the least recently used first out
+  std::vector<CallGraph> graphs;
   uint64_t graph_tick = 0;
   static constexpr size_t kMaxCallGraphs = 8;
   ~ccut_plan() {
@@ -2048,16 +2051,24 @@ ccut_status graph_call(ccut_plan *p, std::vector<uint8_t> &&key, double *out, si
   if (!g) {  // first sighting: eager, remembered only if it succeeds
     ccut_status st = impl();
     if (st != CCUT_OK) return st;
-    if (p->graphs.size() >= ccut_plan::kMaxCallGraphs) {
-      auto lru = std::min_element(p->graphs.begin(), p->graphs.end(),
-                                  [](const CallGraph &a, const CallGraph &b) { return a.last_use < b.last_use; });
-      (void)hipStreamSynchronize(c->stream);  // a replay of it may still be running
+    // each kind of output has its own: requests that a program reads back once
+    // do not push out the graphs of its device calls
+    size_t kept = 0;
+    auto lru = p->graphs.end();
+    for (auto it = p->graphs.begin(); it != p->graphs.end(); ++it) {
+      if (it->on_device != (on_device != 0)) continue;
+      ++kept;
+      if (lru == p->graphs.end() || it->last_use < lru->last_use) lru = it;
+    }
+    if (kept >= ccut_plan::kMaxCallGraphs) {
+      if (lru->exec) (void)hipStreamSynchronize(c->stream);  // a replay of it may still be running
       lru->release();
       p->graphs.erase(lru);
     }
     p->graphs.emplace_back();
     CallGraph &e = p->graphs.back();
     e.key = std::move(key);
+    e.on_device = on_device != 0;
     e.upload_bytes = c->call_upload_bytes;
     e.last_use = ++p->graph_tick;
     return CCUT_OK;
