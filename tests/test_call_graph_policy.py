@@ -44,3 +44,13 @@ result += [call(0, 0)]
 """)
     assert r[:16] == [[0, 1]] * 16
     assert r[16][2] == 1 and r[17][2] == 0
+
+
+def test_a_host_call_asked_twice_is_not_captured():
+    """A capture costs about what two replays save: a host call is captured when it comes a third time, a device call the
+    second."""
+    r = H.run(SETUP + """
+result = [[call(3, device) for _ in range(5)] for device in (0, 1)]
+""")
+    eager, capture, replay = [0, 0, 0, 0], [0, 1, 1, 0], [0, 0, 1, 0]
+    assert r == [[eager, eager, capture, replay, replay], [eager, capture, replay, replay, replay]]
