@@ -2089,12 +2089,19 @@ ccut_status graph_call(ccut_plan *p, std::vector<uint8_t> &&key, double *out, si
   }
   g->pin_cap = std::max<size_t>(g->upload_bytes, 256);
   g->pin_used = 0;
-  HIP_TRY(c, hipHostMalloc((void **)&g->pin, g->pin_cap, hipHostMallocDefault));
-  HIP_TRY(c, hipMalloc((void **)&g->dev, g->pin_cap));
+  auto stay_eager = [&] {
+    g->release();
+    g->no_graph = true;
+    (void)hipGetLastError();
+    return impl();
+  };
+  if (hipHostMalloc((void **)&g->pin, g->pin_cap, hipHostMallocDefault) != hipSuccess ||
+      hipMalloc((void **)&g->dev, g->pin_cap) != hipSuccess)
+    return stay_eager();
   // captured on a private stream (the caller's may be the legacy default
   // stream, which cannot be captured) and launched on the caller's
-  if (!c->cap_stream) HIP_TRY(c, hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
-  HIP_TRY(c, hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeRelaxed));
+  if (!c->cap_stream && hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking) != hipSuccess) return stay_eager();
+  if (hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeRelaxed) != hipSuccess) return stay_eager();
   const hipStream_t caller = c->stream;
   c->stream = c->cap_stream;
   c->capturing = g;
@@ -2112,10 +2119,7 @@ ccut_status graph_call(ccut_plan *p, std::vector<uint8_t> &&key, double *out, si
   if (graph) (void)hipGraphDestroy(graph);
   if (st != CCUT_OK || e_inst != hipSuccess) {
     // stay eager for this key; the capture enqueued nothing, so run the call now
-    g->release();
-    g->no_graph = true;
-    (void)hipGetLastError();
-    return impl();
+    return stay_eager();
   }
   if (g->pin_used) HIP_TRY(c, hipMemcpyAsync(g->dev, g->pin, g->pin_used, hipMemcpyHostToDevice, c->stream));
   return replay(*g);

@@ -54,3 +54,21 @@ result = [[call(3, device) for _ in range(5)] for device in (0, 1)]
 """)
     eager, capture, replay = [0, 0, 0, 0], [0, 1, 1, 0], [0, 0, 1, 0]
     assert r == [[eager, eager, capture, replay, replay], [eager, capture, replay, replay, replay]]
+
+
+@pytest.mark.parametrize("device", [0, 1])
+@pytest.mark.parametrize("name", ["hipMalloc", "hipHostMalloc"])
+def test_a_capture_that_finds_no_memory(name, device):
+    """The call runs eagerly instead, and the memory is not asked for again."""
+    r = H.run(SETUP + f"""
+for seed in range(100, 106):  # the ring of pinned uploads is there
+    call(seed, {device})
+for _ in range({1 if device else 2}):
+    call(7, {device})
+fail({name!r})
+result = [call(7, {device})]
+fail("")
+clear()
+result += [call(7, {device}), [e[0] for e in log()].count({name!r})]
+""")
+    assert r == [[0, 0, 0, 0], [0, 0, 0, 0], 0]
