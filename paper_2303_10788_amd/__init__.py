@@ -13,13 +13,14 @@ from __future__ import annotations
 
 import ctypes
 import os
+import sysconfig
 from typing import Optional, Sequence
 
 import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libccut.so")
-PACK_PATH = os.path.join(_HERE, "libccut_pack.so")
+PACK_PATH = os.path.join(_HERE, "libccut_pack" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 GATES = {"H": 0, "S": 1, "SDG": 2, "X": 3, "Y": 4, "Z": 5, "CX": 6, "CZ": 7, "T": 8, "TDG": 9, "RZ": 10}
 CCUT_OK, CCUT_E_INVALID, CCUT_E_OOM, CCUT_E_DEVICE = 0, -1, -2, -3
@@ -184,28 +185,30 @@ def ccut_cancel(ctx) -> None:
     lib().ccut_cancel(ctx)
 
 
+_PACK = None  # the native conversion, or False where it is not there
+
+
 def _pack_lib():
     global _PACK
     if _PACK is None:
-        if not os.path.exists(PACK_PATH):
-            raise ImportError(f"{PACK_PATH} is missing: build it with python -m paper_2303_10788_amd.build")
-        f = ctypes.PyDLL(PACK_PATH).ccut_pack_ops
-        f.argtypes = [ctypes.py_object, ctypes.py_object, ctypes.c_ssize_t, ctypes.POINTER(ccut_op)]
-        f.restype = ctypes.c_int
-        _PACK = f
+        try:
+            f = ctypes.PyDLL(PACK_PATH).ccut_pack_ops
+            f.argtypes = [ctypes.py_object, ctypes.py_object, ctypes.c_ssize_t, ctypes.POINTER(ccut_op)]
+            f.restype = ctypes.c_int
+            _PACK = f
+        except (OSError, AttributeError):
+            _PACK = False
     return _PACK
-
-
-_PACK = None
 
 
 def _ops_array(ops):
     """The ops as a ccut_op array.  A ctypes structure built for each op took
     2.1 ms for the 4994 ops of a 100-qubit circuit, native code takes 0.04;
     it leaves what is not a list of (name, int, int, float) tuples to the
-    loop here, with its conversions and errors."""
+    loop here, with its conversions and errors, as does a package without it."""
     arr = (ccut_op * max(len(ops), 1))()
-    if type(ops) is list and _pack_lib()(ops, GATES, len(ops), arr) == 0:
+    pack = _pack_lib()
+    if pack and type(ops) is list and pack(ops, GATES, len(ops), arr) == 0:
         return arr
     for i, (k, a, b, th) in enumerate(ops):
         arr[i] = ccut_op(GATES[k] if isinstance(k, str) else int(k), int(a), int(b) if b >= 0 else 0, 0,

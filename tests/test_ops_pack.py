@@ -52,3 +52,32 @@ def test_native_path_taken():
     assert pack(ops, cc.GATES, len(ops), arr) == 0
     assert pack(ops, cc.GATES, len(ops) - 1, arr) == 1
     assert pack(tuple(ops), cc.GATES, len(ops), arr) == 1
+
+
+def test_without_the_native_library(monkeypatch, tmp_path):
+    """A missing library, or one that does not load, leaves the conversion to the loop."""
+    broken = tmp_path / "broken.so"
+    broken.write_bytes(b"not a library")
+    for path in (tmp_path / "missing.so", broken):
+        monkeypatch.setattr(cc, "PACK_PATH", str(path))
+        monkeypatch.setattr(cc, "_PACK", None)
+        for ops in GOOD:
+            assert bytes(cc._ops_array(ops)) == bytes(_by_op(ops))
+
+
+def test_the_library_carries_the_interpreter_in_its_name():
+    import sysconfig
+    from paper_2303_10788_amd import build as B
+    assert cc.PACK_PATH == B.PACK_OUT and cc.PACK_PATH.endswith(sysconfig.get_config_var("EXT_SUFFIX"))
+
+
+def test_a_build_without_the_interpreters_headers(monkeypatch, tmp_path, capfd):
+    """It says so, leaves no library of an earlier build behind, and goes on."""
+    from paper_2303_10788_amd import build as B
+    old = tmp_path / "pack.so"
+    old.write_bytes(b"an earlier build")
+    monkeypatch.setattr(B, "PACK_OUT", str(old))
+    monkeypatch.setattr(B.sysconfig, "get_paths", lambda: {"include": str(tmp_path / "nowhere")})
+    B._build_pack()
+    assert not old.exists() and list(tmp_path.iterdir()) == []
+    assert "Python.h" in capfd.readouterr().err
