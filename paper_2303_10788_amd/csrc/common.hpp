@@ -563,7 +563,7 @@ hipError_t launch_column_weights(const ColumnSet &S, const uint64_t *terms, uint
                                  uint32_t *counts, double *scale, double *scale2, hipStream_t s);
 constexpr uint32_t kRcChunkOut = 128;  // outputs per workgroup of the plain recombination
 // Z strings: fp64 products and sum, or (fp32 = true) fp32 products summed
-// in fp32 over chunks of 32 terms and in fp64 across chunks.
+// in fp32 over 8 consecutive terms and those sums in fp64.
 uint32_t zrecombine_splits(uint32_t k, uint32_t n_strings);
 hipError_t launch_zrecombine(const RecombArgs *d_args, uint32_t n_frags, uint32_t k, uint32_t n_strings, bool fp32,
                              double *partial, uint32_t splits, double *out, hipStream_t s);

@@ -729,10 +729,11 @@ __global__ void zrecombine_kernel(const RecombArgs *__restrict__ A, uint32_t n_s
   partial[(uint64_t)blockIdx.y * n_strings + s] = acc;
 }
 
-// The same for at most 8 fragments (same operations, same order): the
+// The same for at most 8 fragments: the
 // column offsets of each chunk of 64 terms are computed once per workgroup
-// into LDS and its waves take equal shares of the chunk (multiples of 8 terms, so
-// fp32 groups stay whole), their sums added in order at the end; with a single
+// into LDS and its waves take equal shares of the chunk (8 terms, so
+// fp32 groups stay whole), their sums added in order at the end (the same
+// products, regrouped by wave where there are eight); with a single
 // term range the result is written directly (scaled by 2^-k) and no final pass is
 // needed.  Bound by the latency of the gathers: 64 strings of 3 cuts 5 us,
 // 18.5 us with one wave for the chunk.
@@ -996,7 +997,9 @@ hipError_t launch_zrecombine(const RecombArgs *d_args, uint32_t n_frags, uint32_
   const dim3 grid(blocks_for(n_strings, 64), splits);
   if (n_frags <= kRcFrags) {
     double *direct = splits == 1 ? out : nullptr;
-    const uint32_t waves = per >= 64 ? 8 : per >= 32 ? 4 : per >= 16 ? 2 : 1;  // shares of 8 terms or more
+    // one or two cuts are less than a chunk (4 or 16 terms): one wave, a second
+    // one would have none of them; from three cuts on a range is whole chunks
+    const uint32_t waves = per >= 64 ? kZrWaves : 1;
     const dim3 block(64 * waves);
     if (fp32)
       hipLaunchKernelGGL(zrecombine_small_kernel<true>, grid, block, 0, s, d_args, n_strings, per, partial, direct);

@@ -37,3 +37,22 @@ def test_transforms_follow_their_tables(n, wide, method, shots, graph):
         if any(w in name for w in writers):
             tables.add(i)
     assert transforms and tables
+
+
+@pytest.mark.parametrize("k,waves", [(1, 1), (2, 1), (3, 8), (4, 8)])
+def test_waves_of_a_string_sum(k, waves):
+    """A chunk of 64 terms is shared by eight waves; the 4 or 16 terms of one or two cuts are one wave's."""
+    log = H.run(f"""
+ops, cuts = [], []
+for i in range({k} + 1):
+    ops += [("H", i, 0, 0.0), ("CX", i, i + 1, 0.0)]
+    if i < {k}:
+        cuts.append((i + 1, len(ops) - 1))
+p = cc.Plan(ctx, {k} + 2, ops, cuts)
+clear()
+out = np.zeros(5)
+cc.ccut_zexpect(p.handle, ctx.handle, cc._eval_opts(100, 1), np.arange(5, dtype=np.uint64)[:, None], out)
+result = log()
+""")
+    (block,) = [b for _, name, _, b, _ in H.launches_before(log) if "zrecombine_small" in name]
+    assert block == 64 * waves
