@@ -392,6 +392,7 @@ __global__ __launch_bounds__(256) void hist_reduce_batch_kernel(const SampleJob 
   const uint64_t n_e = J.nv * bins;
   const uint64_t e0 = (uint64_t)(blockIdx.x - J.rb0) * kReduceChunk;
   const uint64_t e1 = e0 + kReduceChunk < n_e ? e0 + kReduceChunk : n_e;
+  const double inv = 1.0 / (double)J.shots;  // a table entry is count x fl(1/shots)
   for (uint64_t e = e0 + threadIdx.x; e < e1; e += 256) {
     const uint64_t v = e / bins, b = e % bins;
     uint64_t c = 0;
@@ -399,7 +400,7 @@ __global__ __launch_bounds__(256) void hist_reduce_batch_kernel(const SampleJob 
     if (J.cnt16)
       J.cnt16[e] = (uint16_t)c;
     else
-      J.dist[e] = (double)c / (double)J.shots;
+      J.dist[e] = (double)c * inv;
   }
 }
 

@@ -100,3 +100,18 @@ def test_batch_equals_calls(ctx):
     got = cc.Batch(ctx, plans, qubits, shots=shots, seed=7).run()
     for i, (p, q) in enumerate(zip(plans, qubits)):
         assert np.array_equal(got[i], p.marginal(q, shots=shots, seed=7, circuit=i)), i
+
+
+@pytest.mark.parametrize("shots", [20000, 70000])
+def test_batch_equals_calls_over_several_shot_blocks(ctx, shots):
+    """A variant's shots in more than one block (their counts reduced by a launch over the batch), as 16-bit counts and,
+    from 2^16 shots on or as a small plain sum's fold target, as values."""
+    print(f"counts batch of {shots} shots", flush=True)
+    plans, qubits = [], []
+    for i, (n, outs, ins) in enumerate([(6, 1, 0), (7, 2, 0), (8, 4, 0), (9, 2, 1), (9, 1, 2), (8, 1, 1), (7, 0, 2), (6, 0, 3)]):
+        ops, cuts = _circuit(n, outs, ins, 40 + i)
+        plans.append(cc.Plan(ctx, n, ops, cuts))
+        qubits.append(list(range(n)))
+    got = cc.Batch(ctx, plans, qubits, shots=shots, seed=7).run()
+    for i, (p, q) in enumerate(zip(plans, qubits)):
+        assert np.array_equal(got[i], p.marginal(q, shots=shots, seed=7, circuit=i)), i
