@@ -277,7 +277,7 @@ ccut_status ccut_zexpect(ccut_plan *plan, const ccut_eval_opts *eo, const uint64
 /* Call graphs (default on).  A ccut_marginal or ccut_zexpect call
  * that repeats an earlier call on the same plan exactly (same
  * options, request and, on the device, output address) is captured as a HIP
- * graph on its second occurrence (with a host output on its third) and
+ * graph on its second occurrence (with a host output on its sixth) and
  * replayed from then on: every kernel and copy runs again, only the host-side planning and launch overhead is saved.
  * Up to 8 graphs per plan of calls with a device output and 8 of calls with
  * a host output (least recently used out).  Calls with

@@ -2013,13 +2013,17 @@ std::vector<uint8_t> call_key(uint32_t entry, const ccut_eval_opts *eo, const vo
   return k;
 }
 
-// A host-output call runs eagerly twice before it is captured: the capture
-// costs some 100 us (8 qubits: 201..234 us with it, about 110 eager and 60
-// replayed), so a request that is asked but twice is better off without.
-constexpr uint32_t kHostEager = 2;
+// A host-output call runs eagerly five times before it is captured.  Its capture
+// (the graph of a request that came before released, upload blocks, the graph
+// instantiated) takes some 210 us more than the eager call, a replay saves some
+// 45, so from there on a program that asks each request a few times and goes on
+// to the next (seeds, say) loses little, and one that stays with a request gains.
+// Measured, us a call, sampled strings of 32 qubits, each seed asked 2, 3, 6, 12 or
+// 30 times: 136, 136, 171, 140, 116; captured at the second: 219, 199, 152, 127, 111.
+constexpr uint32_t kHostEager = 5;
 
 // Run a call through the plan's call graphs: the first call with a given key
-// runs eagerly (a host-output one twice), the next is captured (every launch and
+// runs eagerly (a host-output one the first five), the next is captured (every launch and
 // copy it enqueues, on both streams) and replayed, later ones only replay.
 // Calls with kernel timing on, or issued while the caller's stream is itself
 // being captured always run eagerly.  The graph's

@@ -71,3 +71,23 @@ def test_errors_stay(ctx):
             plan.marginal([0, 0])
         with pytest.raises(cc.CcutError):
             plan.marginal(w.qubits, flags=cc.CCUT_FLAG_SETTLE)
+
+
+@pytest.mark.parametrize("shots", [0, 700])
+def test_many_repeats(ctx, shots):
+    """Twelve equal calls of each kind (eager, captured, replayed), other requests and device calls between them."""
+    import torch
+    print(f"host graphs, twelve repeats, shots={shots}", flush=True)
+    w, other = W.mid(shots=shots), W.tiny()
+    p, q = cc.Plan(ctx, w.n, w.ops, w.cuts), cc.Plan(ctx, other.n, other.ops, other.cuts)
+    masks = w.zmask_words()
+    ref_m = _eager(ctx, lambda: p.marginal(w.qubits, shots=shots, seed=3))
+    ref_z = _eager(ctx, lambda: p.zexpect(masks, shots=shots, seed=3))
+    dev = torch.empty(ref_m.size, dtype=torch.float64, device="cuda")
+    for rep in range(12):
+        assert np.array_equal(p.marginal(w.qubits, shots=shots, seed=3), ref_m), rep
+        assert np.array_equal(p.zexpect(masks, shots=shots, seed=3), ref_z), rep
+        q.marginal(other.qubits, shots=shots, seed=rep)
+        p.marginal(w.qubits, shots=shots, seed=3, out=dev)
+        torch.cuda.synchronize()
+        assert np.array_equal(dev.cpu().numpy(), ref_m), rep
