@@ -25,6 +25,7 @@
 // combination mask of the measurements folded into it.  Elimination is
 // n_meas broadcast steps (readlane), no LDS and no barrier.
 #include "common.hpp"
+#include "pauli.hpp"
 
 namespace ccut {
 
@@ -271,17 +272,7 @@ __global__ __launch_bounds__(1024) void affine_batch_kernel(const FragDev *__res
 // accumulating, since the product's x part is known from its z part.  Bound by
 // the chain of instructions of one wave (about 70 a column).  Measured for 64
 // variants of 161 measurements on 161 qubits: 52 us, 122 us by measurements.
-// The transpose of the 64 x 64 bit matrix with row l in lane l.
-__device__ inline uint64_t transpose64(uint64_t x, uint32_t lane) {
-#pragma unroll
-  for (uint32_t s = 32; s; s >>= 1) {
-    const uint64_t low = ~0ull / ((1ull << s) + 1);  // positions without bit s
-    const uint64_t t = __shfl_xor(x, (int)s);
-    x = lane & s ? (x & ~low) | ((t & ~low) >> s) : (x & low) | ((t & low) << s);
-  }
-  return x;
-}
-
+//
 // W: words of the qubits (64 rows of the matrix to a lane each); ld: words of x
 // and of z in a carried-back row.
 template <int W>

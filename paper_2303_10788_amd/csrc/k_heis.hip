@@ -236,20 +236,6 @@ __global__ __launch_bounds__(64 * kCarryWaves) void sliced_batch_kernel(const Fr
   rows_sliced_body(F, J.W, in + J.in_off, out + J.out_off, J.n_rows, cols);
 }
 
-// 64 x 64 bits held one row per lane, transposed: bit c of lane r goes to bit
-// r of lane c (swaps of the index bits, one lane exchange each).
-__device__ inline uint64_t transpose64(uint64_t v, uint32_t lane) {
-  constexpr uint64_t low[6] = {0x5555555555555555ull, 0x3333333333333333ull, 0x0F0F0F0F0F0F0F0Full,
-                               0x00FF00FF00FF00FFull, 0x0000FFFF0000FFFFull, 0x00000000FFFFFFFFull};
-#pragma unroll
-  for (int b = 5; b >= 0; --b) {
-    const uint32_t j = 1u << b;
-    const uint64_t p = __shfl_xor((unsigned long long)v, j);
-    v = lane & j ? (v & ~low[b]) | ((p & ~low[b]) >> j) : (v & low[b]) | ((p & low[b]) << j);
-  }
-  return v;
-}
-
 // One bit of a program word as a mask (0 or all ones).
 __device__ inline uint64_t word_mask(uint32_t w, uint32_t bit) {
   return (uint64_t)(int64_t)((int32_t)(w << (31 - bit)) >> 31);

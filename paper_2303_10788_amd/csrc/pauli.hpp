@@ -1,4 +1,5 @@
-// Phase-tracked products of Pauli rows on the device.
+// Phase-tracked products of Pauli rows on the device, and the transpose of 64
+// rows of 64 bits.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -68,6 +69,20 @@ __device__ inline uint32_t psign(const PAcc<W> &L) {
 #pragma unroll
   for (int w = 0; w < W; ++w) pxz += __popcll(L.x[w] & L.z[w]);
   return ((L.a - pxz) & 3u) >> 1;
+}
+
+// 64 x 64 bits held one row per lane, transposed: bit c of lane r goes to bit
+// r of lane c (swaps of the index bits, one lane exchange each).
+__device__ inline uint64_t transpose64(uint64_t v, uint32_t lane) {
+  constexpr uint64_t low[6] = {0x5555555555555555ull, 0x3333333333333333ull, 0x0F0F0F0F0F0F0F0Full,
+                               0x00FF00FF00FF00FFull, 0x0000FFFF0000FFFFull, 0x00000000FFFFFFFFull};
+#pragma unroll
+  for (int b = 5; b >= 0; --b) {
+    const uint32_t j = 1u << b;
+    const uint64_t p = __shfl_xor((unsigned long long)v, j);
+    v = lane & j ? (v & ~low[b]) | ((p & ~low[b]) >> j) : (v & low[b]) | ((p & low[b]) << j);
+  }
+  return v;
 }
 
 }  // namespace ccut
