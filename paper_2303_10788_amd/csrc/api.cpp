@@ -1497,9 +1497,6 @@ ccut_status ccut_fragment_tensor(ccut_plan *p, const ccut_eval_opts *eo, const u
 }  // extern "C"
 
 namespace {
-// Enqueue the whole marginal evaluation of one plan (no final copy, no
-// sync); res receives 2^nq doubles.  pre_models[f], if given, holds the
-// already computed sample models of Clifford fragment f.
 // The fragment whose variant tables stand in for its Pauli-basis tensor:
 // the fragment with the most requested outputs (the contraction's column
 // side, the largest tensor) when every cut axis of it is a quantum input
@@ -1865,9 +1862,10 @@ ccut_status marginal_skip_enqueue(ccut_plan *p, const ccut_eval_opts *eo, const 
   return contract_terms(c, args, dargs, nq, fp32, res, terms, count);
 }
 
+// Enqueue the whole marginal evaluation of one plan (no final copy, no
+// sync); res receives 2^nq doubles.
 ccut_status marginal_enqueue(ccut_plan *p, const ccut_eval_opts *eo, const uint32_t *qubits, uint32_t nq,
-                             double *res, const std::vector<uint64_t *> *pre_models,
-                             const std::vector<double *> *pre_dist = nullptr) {
+                             double *res) {
   ccut_ctx *c = p->ctx;
   ccut_status st;
   const PlanData &pd = p->pd;
@@ -1920,12 +1918,10 @@ ccut_status marginal_enqueue(ccut_plan *p, const ccut_eval_opts *eo, const uint3
     } else if (use_heisenberg(f, eo, r.req_pos.size())) {
       if ((st = heis_tensor(p, f, r, eo->circuit, nullptr, &T)) != CCUT_OK) return st;
     } else {
-      uint64_t *pm = pre_models ? (*pre_models)[f.index] : nullptr;
-      dist = pre_dist ? (*pre_dist)[f.index] : nullptr;
       uint16_t *cnt = nullptr;
-      const bool whole = !dist && (int)f.index != g && counts_transform(pd, eo, reqs, f, nq, qubits);
+      const bool whole = (int)f.index != g && counts_transform(pd, eo, reqs, f, nq, qubits);
       const bool counts = ((int)f.index == g && counts_ok) || whole;
-      if (!dist && (st = variant_dists(p, eo, f, r, &dist, pm, counts ? &cnt : nullptr)) != CCUT_OK) return st;
+      if ((st = variant_dists(p, eo, f, r, &dist, nullptr, counts ? &cnt : nullptr)) != CCUT_OK) return st;
       if ((int)f.index == g)
         T = cnt ? reinterpret_cast<double *>(cnt) : dist;  // tables [preparations][outcomes]: the tensor's layout
       else if (cnt) {
@@ -2146,10 +2142,10 @@ ccut_status marginal_call(ccut_plan *p, const ccut_eval_opts *eo, const uint32_t
       return fail(c, CCUT_E_UNSUPPORTED, "the maximum-likelihood correction needs every variant (no skipping)");
     std::vector<FragRequest> reqs;
     for (const Fragment &f : p->pd.frags) reqs.push_back(marginal_request(f, qubits, nq));
-    st = exact_marginal_fragment(p->pd, eo, reqs, nq) >= 0 ? marginal_enqueue(p, eo, qubits, nq, res, nullptr)
+    st = exact_marginal_fragment(p->pd, eo, reqs, nq) >= 0 ? marginal_enqueue(p, eo, qubits, nq, res)
                                                            : marginal_skip_enqueue(p, eo, qubits, nq, res);
   } else {
-    st = marginal_enqueue(p, eo, qubits, nq, res, nullptr);
+    st = marginal_enqueue(p, eo, qubits, nq, res);
   }
   if (st != CCUT_OK) return st;
   if (left) *left = res;
