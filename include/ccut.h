@@ -310,9 +310,11 @@ ccut_status ccut_variant_tables(ccut_plan *plan, const ccut_eval_opts *eo, const
 ccut_status ccut_fragment_tensor(ccut_plan *plan, const ccut_eval_opts *eo, const uint32_t *qubits,
                                  uint32_t nq, uint32_t fragment, double *out, int out_on_device);
 
-/* The op stream the kernels run for fragment f: number of one-qubit words
+/* The fused op stream of fragment f: number of one-qubit words
  * (fused runs: 2x2 unitaries on non-Clifford fragments, GF(2) maps on
- * Clifford ones) and of two-qubit gates. */
+ * Clifford ones) and of two-qubit gates.  Runs that no outcome depends on
+ * (diagonal ones that end a qubit without a cut) count, although the kernels
+ * do not run them. */
 ccut_status ccut_fragment_ops(const ccut_plan *plan, uint32_t f, uint32_t *n_one, uint32_t *n_two);
 
 /* Number of measured qubits and requested outputs of fragment `fragment`

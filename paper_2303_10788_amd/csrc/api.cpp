@@ -493,10 +493,6 @@ std::vector<uint64_t> measured_rows(const FragDev &h, uint32_t W) {
   return rows;
 }
 
-// Affine sample models of variants [v0, v0 + nv) of a Clifford fragment:
-// its measured Paulis are carried back through the fragment once (the
-// reversed stream of inverse gates), then one wave per variant eliminates
-// them against the variant's prepared product state (Heisenberg picture).
 // The same rows for a measured set of any size (meas: local qubits in
 // measured order); row_of[j] = the first row of measurement j, meas_axis[j]
 // = the axis of a quantum output, else -1.
@@ -521,6 +517,10 @@ std::vector<uint64_t> measured_rows(const Fragment &f, const std::vector<uint32_
   return rows;
 }
 
+// Affine sample models of variants [v0, v0 + nv) of a Clifford fragment:
+// its measured Paulis are carried back through the fragment once (the
+// reversed stream of inverse gates), then one wave per variant eliminates
+// them against the variant's prepared product state (Heisenberg picture).
 // vmask (device, one byte per variant of the fragment, optional): variants
 // with vmask[v] == 0 get no model (64 measured qubits or fewer; wider
 // fragments model every variant)
@@ -556,9 +556,6 @@ ccut_status tableau_models(ccut_plan *p, const Fragment &f, const FragDev &h, co
   return CCUT_OK;
 }
 
-// Per-variant outcome distributions dist[v][x] over the measured set.
-// cnt_out (sampled Clifford fragments, fewer than 2^16 shots): the tables
-// as 16-bit shot counts into *cnt_out instead (*dist_out null).
 // Maximum-likelihood correction of a fragment's variant tables, in place
 // (Sec. V-C, distribution builder; launch_ml_correct).  Fragments without
 // quantum outputs keep their tables: sampled histograms already are
@@ -594,6 +591,9 @@ ccut_status ml_correct(ccut_ctx *c, const Fragment &f, const FragRequest &r, dou
   return CCUT_OK;
 }
 
+// Per-variant outcome distributions dist[v][x] over the measured set.
+// cnt_out (sampled Clifford fragments, fewer than 2^16 shots): the tables
+// as 16-bit shot counts into *cnt_out instead (*dist_out null).
 // vmask (device, one byte per variant, optional): sampled Clifford variants
 // with vmask[v] == 0 draw no shots (all-zero tables)
 ccut_status variant_dists(ccut_plan *p, const ccut_eval_opts *eo, const Fragment &f,
@@ -677,13 +677,9 @@ ccut_status variant_dists(ccut_plan *p, const ccut_eval_opts *eo, const Fragment
   return cancelled(c);
 }
 
-// Per-axis Pauli-basis passes: data[v][x] -> T[p_f][rest], where rest is
-// the x part with the output bits removed (mode 1) or the J part consumed
-// (mode 2, parity tables laid out [v][J][string]).
 // Tile plan of a fragment's marginal-mode transform (variant data in, T out):
 // false when the fragment has no axes, more than kMaxTileAxes, or variant
-// data per x_out entry beyond kTileElems.
-// elems: of a tile of this launch (every kind takes the same fragments).
+// data per x_out entry beyond kTileElems.  elems: of a tile of this launch (every kind takes the same fragments).
 bool tile_job(const Fragment &f, const FragRequest &r, const double *in, uint64_t xsize, double *out, TileJob &J,
               uint32_t elems = kTileElems) {
   const uint32_t a = (uint32_t)f.axes.size();
@@ -797,6 +793,9 @@ ccut_status counts_passes(ccut_ctx *c, const Fragment &f, const FragRequest &r, 
   return CCUT_OK;
 }
 
+// Per-axis Pauli-basis passes: data[v][x] -> T[p_f][rest], where rest is
+// the x part with the output bits removed (mode 1) or the J part consumed
+// (mode 2, parity tables laid out [v][J][string]).
 ccut_status pauli_passes(ccut_ctx *c, const Fragment &f, const FragRequest &r, double *data,
                          uint64_t xsize, uint64_t mode2_lo, double **out) {
   const uint32_t a = (uint32_t)f.axes.size();
@@ -1168,11 +1167,6 @@ ccut_status column_contract(ccut_ctx *c, const RecombArgs &args, const Columns &
   return run_gemm(c, g, fp32, res);
 }
 
-// The sparse contraction: the support (cut terms whose column is nonzero in
-// every fragment) is found on the device, its size read back, and only its
-// terms are summed: the plain sum in ascending order when it is small (the
-// same operations as the dense plain sum minus its zero terms), else the
-// term-list contraction.
 // The contraction over a term list (device, ascending, count terms): the
 // plain fp64 sum over the terms when small, else the matrix paths.
 ccut_status contract_terms(ccut_ctx *c, const RecombArgs &args, const RecombArgs *dargs, uint32_t nq, bool fp32,
@@ -1193,6 +1187,11 @@ ccut_status contract_terms(ccut_ctx *c, const RecombArgs &args, const RecombArgs
   return run_gemm(c, g, fp32, res, true);
 }
 
+// The sparse contraction: the support (cut terms whose column is nonzero in
+// every fragment) is found on the device, its size read back, and only its
+// terms are summed: the plain sum in ascending order when it is small (the
+// same operations as the dense plain sum minus its zero terms), else the
+// term-list contraction.
 ccut_status recombine_sparse(ccut_ctx *c, const RecombArgs &args, uint32_t nq, bool fp32, double *res) {
   const uint64_t K = 1ull << (2 * args.k);
   SupportArgs sa{};
@@ -1218,9 +1217,6 @@ ccut_status recombine_sparse(ccut_ctx *c, const RecombArgs &args, uint32_t nq, b
   return contract_terms(c, args, dargs, nq, fp32, res, terms, count);
 }
 
-// Contract the fragment tensors into out[2^nq].  fp64 with at most 2^20
-// term-outputs: the plain ascending sum; otherwise the K-split MFMA contraction
-// (fp32 products with fp64 across K-chunks, or fp64 MFMA).
 // The plain fp64 sum (per output, every term's product, ascending) for
 // small contractions of more than two fragments; two fragments always take
 // the matrix paths (the skinny kernel's ascending sum of products is the
@@ -1230,6 +1226,9 @@ bool plain_contraction(const RecombArgs &args, uint32_t nq, bool fp32) {
   return !fp32 && args.n_frags > 2 && (K << nq) <= (1ull << 20);
 }
 
+// Contract the fragment tensors into out[2^nq].  fp64 with at most 2^20
+// term-outputs: the plain ascending sum; otherwise the K-split MFMA contraction
+// (fp32 products with fp64 across K-chunks, or fp64 MFMA).
 ccut_status recombine(ccut_ctx *c, const RecombArgs &args, uint32_t nq, bool fp32, double *res,
                       bool sparse = false) {
   if (sparse) return recombine_sparse(c, args, nq, fp32, res);
@@ -1580,12 +1579,6 @@ void fold_jobs(const PlanData &pd, int g, const RecombArgs &args, std::vector<Fo
   }
 }
 
-// Sec. IX, fewer downstream evaluations (CCUT_FLAG_SKIP): the support is
-// fixed first from the Clifford fragments' exact Pauli tensors (Heisenberg
-// picture where it applies, else exact variant tables); every sampled
-// Clifford variant no term of the support reads draws no shots; the
-// tensors are formed in the Pauli basis (no fold) and only the support's
-// terms are summed.  The support size is read back (the call synchronizes).
 // The variant tables of the non-Clifford fragments of a call, where it has at
 // least two: one launch evolves all their states of a launch shape and one
 // combines them, where each fragment took two launches of its own, mostly
@@ -1697,6 +1690,12 @@ ccut_status grouped_tensors(ccut_plan *p, const ccut_eval_opts *eo, const std::v
   return CCUT_OK;
 }
 
+// Sec. IX, fewer downstream evaluations (CCUT_FLAG_SKIP): the support is
+// fixed first from the Clifford fragments' exact Pauli tensors (Heisenberg
+// picture where it applies, else exact variant tables); every sampled
+// Clifford variant no term of the support reads draws no shots; the
+// tensors are formed in the Pauli basis (no fold) and only the support's
+// terms are summed.  The support size is read back (the call synchronizes).
 ccut_status marginal_skip_enqueue(ccut_plan *p, const ccut_eval_opts *eo, const uint32_t *qubits, uint32_t nq,
                                   double *res) {
   ccut_ctx *c = p->ctx;
@@ -2641,8 +2640,6 @@ void tune_store(const std::string &key, const TuneEntry &e) {
   }
 }
 
-// Enqueue one whole batch evaluation on the batch stream (inside a
-// BatchScope).  Allocation order is fixed, so a replay reuses the same memory.
 std::string tune_key(ccut_ctx *c, const ccut_batch *b) {
   hipDeviceProp_t prop{};
   (void)hipGetDeviceProperties(&prop, c->device);
@@ -2662,6 +2659,8 @@ std::string tune_key(ccut_ctx *c, const ccut_batch *b) {
 
 constexpr uint32_t kCtrKey = 1u << 20;  // contraction classes' keys in the measured durations (above any width)
 
+// Enqueue one whole batch evaluation on the batch stream (inside a
+// BatchScope).  Allocation order is fixed, so a replay reuses the same memory.
 ccut_status batch_enqueue(ccut_batch *b, bool tune) {
   ccut_ctx *c = b->ctx;
   ccut_status st;

@@ -242,9 +242,8 @@ inline size_t sample_lds_bytes(uint32_t n_meas, bool hist, bool sliced = false) 
 }
 constexpr size_t kSampleLdsMax = 8 * 256 * 8 + (size_t(2) << kLdsHistBits);
 
-// One non-Clifford fragment in a batched state-vector launch: descriptor
-// descs[desc], tables in dist, wg0 = its first workgroup.
-// One fragment's evolve or combine pass in a batched state-vector launch.
+// One non-Clifford fragment's evolve or combine pass in a batched state-vector
+// launch: descriptor descs[desc], tables in dist, wg0 = its first workgroup.
 struct SvJob {
   uint32_t desc, pad_;
   uint64_t wg0;

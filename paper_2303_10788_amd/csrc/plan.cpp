@@ -244,12 +244,6 @@ void sv_block_matrix(const Fragment &F, const SvBlock &B, cplx (&U)[8][8]) {
   }
 }
 
-// Per step four words and four doubles a lane (sv_prog, sv_prog_mats).  Words:
-// LDS byte offsets (16 bits each) of the lane's index bits and of the register
-// bit, then of tile bits 0-1, 2-3 and 4.  Doubles: lane l's matrix elements
-// A[l % 16][4 c + l / 16], c < 4.  The block's qubits are lane bits 4 and 5 and
-// the register; the other qubits fill lane bits 0-3 (residues 0, 1, 2, 3 mod 4
-// where they can: different LDS banks), then the tile.
 // Puts the matrix of a block of Clifford gates and T, times sqrt2 if the result
 // says so, on its exact values where these are of the form (a + b / sqrt2) / 64
 // with whole a, b (found from the product of the gates, which is within 2e-14
@@ -303,6 +297,12 @@ bool sv_exact_matrix(cplx (&U)[8][8]) {
   return odd;
 }
 
+// Per step four words and four doubles a lane (sv_prog, sv_prog_mats).  Words:
+// LDS byte offsets (16 bits each) of the lane's index bits and of the register
+// bit, then of tile bits 0-1, 2-3 and 4.  Doubles: lane l's matrix elements
+// A[l % 16][4 c + l / 16], c < 4.  The block's qubits are lane bits 4 and 5 and
+// the register; the other qubits fill lane bits 0-3 (residues 0, 1, 2, 3 mod 4
+// where they can: different LDS banks), then the tile.
 void build_sv_program(Fragment &F) {
   const uint32_t m = F.m(), mm = std::max(m, 3u);
   std::vector<SvBlock> blocks;
