@@ -162,10 +162,13 @@ __device__ __attribute__((always_inline)) void sv_evolve(D &F, uint32_t blk, C2 
 // axes beyond four summed in as they are read), reduces them to the first two
 // axes and adds up all 36 probabilities in registers, so a state is read
 // 4^-2 (inputs) or 6^-2 (outputs) as often as there are variants.  The lanes
-// that share an outcome add up in a fixed order.  Bound by fp64 adds and
+// that share an outcome add up in a fixed order; with few outcomes (four lanes
+// or more each) the 36 sums are spread over the wave.  Bound by fp64 adds and
 // the loads from L2.  Measured for the 11- and 12-qubit fragments of a
 // 256-circuit batch: 277 -> 118 us against one workgroup per variant (state
-// combined and rotated in LDS, a barrier per rotation and unmeasured qubit).
+// combined and rotated in LDS, a barrier per rotation and unmeasured qubit); for
+// 10 qubits, two outputs and no requested qubit 7 us (30 to 38 where one lane
+// added up all 36), with 6 to 8 requested ones 5 us.
 __device__ inline C2 sv_value(C2 a, C2 b, uint32_t k) {
   switch (k) {
     case 0: return a;
@@ -184,9 +187,11 @@ __device__ inline uint32_t sv_kind(bool input, uint32_t d) {
 // that are zero by such a symmetry come out as zero
 __device__ inline double sv_prob(C2 a) { return a.re * a.re + a.im * a.im; }
 
-// lds: 36 x 64 doubles, the wave's sums on their way out (one short loop
+// lds: 36 rows of kSvRow doubles, the wave's sums on their way out (one short loop
 // stores them all: written out 36 times, the stores took as long to fetch as
 // the rest of a small call to run)
+constexpr uint32_t kSvRow = 65;    // (64 lanes, padded: lanes that read different rows meet different banks)
+constexpr uint32_t kSvSpread = 2;  // see the end of sv_combine
 template <int L, class D>
 __device__ __attribute__((always_inline)) void sv_combine(D &F, double *__restrict__ dist, uint32_t unit,
                                                           const C2 *__restrict__ states, double *lds) {
@@ -326,15 +331,35 @@ __device__ __attribute__((always_inline)) void sv_combine(D &F, double *__restri
 #pragma unroll
   for (uint32_t k1 = 0; k1 < n1; ++k1)
 #pragma unroll
-    for (uint32_t k0 = 0; k0 < n0; ++k0) lds[(k1 * n0 + k0) * 64 + lane] = acc[k1][k0];
+    for (uint32_t k0 = 0; k0 < n0; ++k0) lds[(k1 * n0 + k0) * kSvRow + lane] = acc[k1][k0];
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
-  if (lane >= 1u << lr) return;
   __attribute__((address_space(1))) double *o = (__attribute__((address_space(1))) double *)dist;
   const bool in0 = ins & 1u, in1 = ins >> 1 & 1u;
   const uint32_t e1 = L > 1 ? (in1 ? 4u : 6u) : 1u, e0 = L > 0 ? (in0 ? 4u : 6u) : 1u;
   const uint32_t st0 = L > 0 ? F.axis_stride[0] : 0u, st1 = L > 1 ? F.axis_stride[1] : 0u;
   const uint32_t ob0 = L > 0 ? F.axis_obit[0] : 0u, ob1 = L > 1 ? F.axis_obit[1] : 0u;
+  if (lu >= kSvSpread) {
+    // few outcomes of many lanes each: the choices along the two axes go to
+    // the lanes too, each summing the lanes that share its outcome in order (the
+    // same sums as below; from four lanes to an outcome on, as with two the
+    // sums below take one more read each)
+    const double *src = lds + (lane & ((1u << lr) - 1));
+#pragma unroll 1
+    for (uint32_t d = lane >> lr; d < e1 * e0; d += 64u >> lr) {
+      const uint32_t d1 = d / e0, d0 = d - d1 * e0;
+      const uint32_t k1 = L > 1 ? sv_kind(in1, d1) : 0u, k0 = L > 0 ? sv_kind(in0, d0) : 0u;
+      const double *row = src + (k1 * n0 + k0) * kSvRow;
+      double p = row[0];
+#pragma unroll 8
+      for (uint32_t t = 1; t < 1u << lu; ++t) p += row[t << lr];
+      const uint32_t vv = v + (in1 ? d1 : d1 >> 1) * st1 + (in0 ? d0 : d0 >> 1) * st0;
+      const uint32_t oo = out | (d1 & 1u ? ob1 : 0u) | (d0 & 1u ? ob0 : 0u);
+      o[((size_t)vv << nm) + oo] = ldexp(p, -(halves + (k1 >= 2) + (k0 >= 2)));
+    }
+    return;
+  }
+  if (lane >= 1u << lr) return;
 #pragma unroll 1
   for (uint32_t d1 = 0; d1 < e1; ++d1) {
     uint32_t v1 = v, o1 = out, k1 = 0;
@@ -345,13 +370,13 @@ __device__ __attribute__((always_inline)) void sv_combine(D &F, double *__restri
       v1 += (in1 ? d1 : d1 >> 1) * st1;
       o1 |= d1 & 1u ? ob1 : 0u;  // (0 for an input)
     }
-    const double *src1 = lds + k1 * n0 * 64 + lane;
+    const double *src1 = lds + k1 * n0 * kSvRow + lane;
     double p[n0];
 #pragma unroll
-    for (uint32_t d0 = 0; d0 < n0; ++d0) p[d0] = src1[(L > 0 ? sv_kind(in0, d0) : 0u) * 64];
+    for (uint32_t d0 = 0; d0 < n0; ++d0) p[d0] = src1[(L > 0 ? sv_kind(in0, d0) : 0u) * kSvRow];
     for (uint32_t t = 1; t < 1u << lu; ++t)  // the lanes that share the outcome, in order
 #pragma unroll
-      for (uint32_t d0 = 0; d0 < n0; ++d0) p[d0] += src1[(L > 0 ? sv_kind(in0, d0) : 0u) * 64 + (t << lr)];
+      for (uint32_t d0 = 0; d0 < n0; ++d0) p[d0] += src1[(L > 0 ? sv_kind(in0, d0) : 0u) * kSvRow + (t << lr)];
 #pragma unroll
     for (uint32_t d0 = 0; d0 < n0; ++d0) {
       if (d0 >= e0) continue;
@@ -387,7 +412,7 @@ __global__ __launch_bounds__(1024, 8) void sv_evolve_kernel(const FragDev F, C2 
 
 __global__ __launch_bounds__(64) void sv_combine_kernel(const FragDev F, double *__restrict__ dist,
                                                         const C2 *__restrict__ states) {
-  __shared__ double lds[36 * 64];
+  __shared__ double lds[36 * kSvRow];
   sv_combine_any(F, dist, blockIdx.x, states, lds);
 }
 
@@ -414,7 +439,7 @@ __global__ __launch_bounds__(1024, 8) void sv_evolve_batch_kernel(const FragDev 
 
 __global__ __launch_bounds__(64) void sv_combine_batch_kernel(const FragDev *__restrict__ descs,
                                                               const SvJob *__restrict__ jobs, uint32_t n_jobs) {
-  __shared__ double lds[36 * 64];
+  __shared__ double lds[36 * kSvRow];
   const SvJob &J = sv_job(jobs, n_jobs);
   const uint32_t desc = __builtin_amdgcn_readfirstlane(J.desc);
   const uint32_t unit = __builtin_amdgcn_readfirstlane((uint32_t)(blockIdx.x - J.wg0));
