@@ -21,15 +21,14 @@
 //     diagonalise it (cyclic complex Jacobi in registers), store the
 //     eigenvalues;
 //  2. one workgroup per s: the simplex shift tau_s of the joint spectrum by
-//     Michelot's iteration (tau = (sum of the active values - 1) / their
-//     count, active = the values above the previous tau, until the active
-//     set stops shrinking), sums in a fixed order;
+//     Michelot's iteration (simplex.hpp), sums in a fixed order;
 //  3. one thread per (s, x): the same diagonalisation again (the same code
 //     on the same data: the same bits), eigenvalues max(mu - tau_s, 0),
 //     rho'_x, its Pauli coefficients, the corrected table entries.
 #include <cmath>
 
 #include "common.hpp"
+#include "simplex.hpp"
 
 #pragma clang fp contract(off)
 
@@ -269,13 +268,12 @@ __global__ __launch_bounds__(kTauThreads) void ml_tau_kernel(const MlJob *__rest
   const uint64_t n = J.nx * d;
   const double *mu = J.eig + (uint64_t)s * n;
   // the active set starts as every value: tau below all of them
-  double tau = -INFINITY;
-  uint64_t prev = n + 1;
-  for (;;) {
+  SimplexShift S{-INFINITY, n + 1};
+  for (bool more = true; more;) {
     double sum = 0.0;
     uint64_t cnt = 0;
     for (uint64_t i = tid; i < n; i += kTauThreads)
-      if (mu[i] > tau) {
+      if (mu[i] > S.tau) {
         sum += mu[i];
         ++cnt;
       }
@@ -292,11 +290,9 @@ __global__ __launch_bounds__(kTauThreads) void ml_tau_kernel(const MlJob *__rest
     const double tot = s_sum[0];
     const uint64_t c = s_cnt[0];
     __syncthreads();  // every thread has read the totals
-    if (c == prev || c == 0) break;  // the active set stopped shrinking (c >= 1 always)
-    tau = (tot - 1.0) / (double)c;
-    prev = c;
+    more = S.round(tot, c);
   }
-  if (tid == 0) J.tau[s] = tau;
+  if (tid == 0) J.tau[s] = S.tau;
 }
 
 }  // namespace

@@ -127,3 +127,26 @@ def test_refusals(ctx):
     with pytest.raises(cc.CcutError) as e:
         p2.zexpect(np.array([1], dtype=np.uint64), shots=100, flags=cc.CCUT_FLAG_ML)
     assert e.value.status == cc.CCUT_E_UNSUPPORTED
+
+
+@pytest.mark.parametrize("m,n_out,n_req", [(4, 1, 3), (5, 2, 3), (6, 2, 4), (8, 1, 7), (9, 2, 7), (12, 2, 10)])
+def test_state_vector_tables_are_a_fixed_point(ctx, m, n_out, n_req):
+    """Physical models whose states have zero eigenvalues (known to rounding): the correction ends and changes nothing."""
+    for seed in range(6):
+        rng = np.random.default_rng([m, n_out, seed])
+        ops = [("H", q, -1, 0.0) for q in range(m)] + [("CX", q, q + 1, 0.0) for q in range(m - 1)]
+        ops += W.random_circuit(m, 6 * m, 70 + seed) + [("T", 0, -1, 0.0)]
+        outs = sorted(int(q) for q in rng.choice(m, size=n_out, replace=False))
+        cuts = []
+        for q in outs:
+            ops.append(("H", q, -1, 0.0))
+            cuts.append((q, len(ops) - 1))
+        ops += [("CX", q, m, 0.0) for q in outs]
+        qubits = [q for q in range(m) if q not in outs][:n_req]
+        _log(f"fixed point m={m} out={n_out} requested={len(qubits)} seed={seed}")
+        plan = cc.Plan(ctx, m + 1, ops, cuts)
+        for f, fr in enumerate(plan.fragments()):
+            if not fr["clifford"]:
+                raw = plan.variant_tables(qubits, f)
+                cor = plan.variant_tables(qubits, f, flags=cc.CCUT_FLAG_ML)
+                assert np.max(np.abs(cor - raw)) <= 1e-12
