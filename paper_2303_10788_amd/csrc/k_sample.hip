@@ -355,8 +355,12 @@ __global__ __launch_bounds__(kSampleBlock) void sample_batch_kernel(const Sample
 
 // dist[v][b] = (sum over shot blocks of counts) x fl(1/shots).  `slices`
 // (1, 2, 4 or 8) threads to an entry, each adding every slices-th block: bound
-// by the latency of their loads (49 blocks of 16 x 64 entries one thread to an
-// entry: 16 us; eight to an entry: 4 us).
+// by the latency of their loads where the entries are few (49 blocks of 16 x 64
+// entries one thread to an entry: 16 us; eight to an entry: 4 us) and by memory
+// where they are many (15 blocks of 4096 x 1024: 93 us with eight threads to an
+// entry, which read 128 bytes in a row, 50 with one): as many threads as
+// kReduceFill allows.
+constexpr uint64_t kReduceFill = 1u << 17;
 __global__ __launch_bounds__(256) void hist_reduce_kernel(const uint32_t *__restrict__ partial, uint64_t nv,
                                                           uint32_t nblk, uint32_t bins, uint64_t shots, uint32_t slices,
                                                           double *__restrict__ dist, uint16_t *__restrict__ cnt16) {
@@ -894,7 +898,8 @@ hipError_t launch_hist_reduce(const uint32_t *partial, uint64_t nv, uint32_t nbl
                               uint64_t shots, double *dist, hipStream_t s, uint16_t *cnt16) {
   const uint64_t n = nv * bins;
   if (cnt16 && shots > 0xFFFFull) return hipErrorInvalidValue;
-  const uint32_t slices = nblk >= 8 ? 8 : nblk >= 4 ? 4 : nblk >= 2 ? 2 : 1;
+  uint32_t slices = 1;
+  while (slices < 8 && 2 * slices <= nblk && n * slices < kReduceFill) slices *= 2;
   hipLaunchKernelGGL(hist_reduce_kernel, dim3(blocks_for(n, 256 / slices)), dim3(256), 0, s, partial, nv, nblk, bins,
                      shots, slices, dist, cnt16);
   return hipGetLastError();

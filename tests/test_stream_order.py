@@ -56,3 +56,26 @@ result = log()
 """)
     (block,) = [b for _, name, _, b, _ in H.launches_before(log) if "zrecombine_small" in name]
     assert block == 64 * waves
+
+
+@pytest.mark.parametrize("inputs,request_,slices", [(1, 4, 8), (2, 6, 8), (3, 8, 8), (4, 8, 2), (6, 9, 1), (6, 10, 1)])
+def test_slices_of_a_histogram_reduction(inputs, request_, slices):
+    """Few table entries (4^inputs variants of 2^request_) share their shot blocks between up to eight threads each; tables
+    that fill the chip by themselves take a thread to an entry."""
+    log = H.run(f"""
+n = 14
+ops, cuts = [], []
+for q in range({inputs}):
+    ops += [("H", q, 0, 0.0), ("T", q, 0, 0.0), ("H", q, 0, 0.0)]
+    cuts.append((q, len(ops) - 1))
+for q in range(n - 1):
+    ops.append(("CX", q, q + 1, 0.0))
+p = cc.Plan(ctx, n, ops, cuts)
+clear()
+out = np.zeros(1 << {request_})
+cc.ccut_marginal(p.handle, ctx.handle, cc._eval_opts(60000, 1), list(range({request_})), out)
+result = log()
+""")
+    (grid,) = [g for _, name, g, _, _ in H.launches_before(log) if "hist_reduce" in name]
+    entries = 4 ** inputs << request_
+    assert grid == (entries * slices + 255) // 256
