@@ -1029,6 +1029,14 @@ int exact_marginal_fragment(const PlanData &pd, const ccut_eval_opts *eo, const 
   return exact_fragment(pd, eo, reqs, false, 3, kExactMaxFree);
 }
 
+// The most free cuts with which Z strings go through exact_fragment.  A thread
+// sums a string's 4^free terms one after another (three free cuts: up to 100 us),
+// where the dense sum spreads its 4^k terms over waves and needs about 90 us up
+// to six cuts, then 200 and more.  Measured for 64 strings, exact against dense
+// sum: two free cuts 53 and 78 us at 3 cuts, 92 and 102 at 6; three free cuts 84 to
+// 168 and 88 to 99 at 4 and 5, 91 to 191 and 104 to 112 at 6, 123 to 216 and 254 to 261 at 7.
+uint32_t exact_strings_free(uint32_t k) { return k >= 7 ? 3 : 2; }
+
 ExactArgs exact_args(const PlanData &pd, const Fragment &f, const HeisRows &H, uint32_t first_out_row, uint32_t r,
                      uint32_t nq) {
   ExactArgs A{};
@@ -2174,7 +2182,7 @@ ccut_status zexpect_call(ccut_plan *p, const ccut_eval_opts *eo, const uint64_t 
   args.k = pd.k;
   args.lo_parts = eo->precision == CCUT_FP32X3_MFMA_FP64SUM;
   // (in fp32 only where a single term is left: its product rounds the same way)
-  const int ef = exact_fragment(pd, eo, {}, true, 1, eo->precision == CCUT_FP64 ? kExactMaxFree : 0);
+  const int ef = exact_fragment(pd, eo, {}, true, 1, eo->precision == CCUT_FP64 ? exact_strings_free(pd.k) : 0);
   HeisRows H;
   std::vector<FragRequest> reqs;
   for (const Fragment &f : pd.frags) reqs.push_back(zstring_request(f, anymask));

@@ -79,3 +79,30 @@ result = log()
     (grid,) = [g for _, name, g, _, _ in H.launches_before(log) if "hist_reduce" in name]
     entries = 4 ** inputs << request_
     assert grid == (entries * slices + 255) // 256
+
+
+@pytest.mark.parametrize("n_in,chain,exact", [(1, 0, True), (1, 2, True), (1, 3, False), (3, 3, False), (4, 2, True),
+                                              (4, 3, True)])
+def test_strings_through_one_fragment(n_in, chain, exact):
+    """Strings take the sum through one Clifford fragment where it is the shorter one: up to two cuts that are not its
+    inputs, three from seven cuts on."""
+    log = H.run(f"""
+n, ops, cuts = {n_in} + 3, [], []
+block = lambda q: ops.extend([("H", q, 0, 0.0), ("T", q, 0, 0.0), ("H", q, 0, 0.0)])
+for q in range({n_in}):
+    block(q)
+    cuts.append((q, len(ops) - 1))
+for q in range(n - 2):
+    ops.append(("CX", q, q + 1, 0.0))
+for i in range({chain}):
+    block(n - 1)
+    cuts.append((n - 1, len(ops) - 1))
+block(n - 1)
+p = cc.Plan(ctx, n, ops, cuts)
+clear()
+out = np.zeros(5)
+cc.ccut_zexpect(p.handle, ctx.handle, cc._eval_opts(), np.arange(5, dtype=np.uint64)[:, None], out)
+result = log()
+""")
+    names = " ".join(name for _, name, _, _, _ in H.launches_before(log))
+    assert ("exact_strings" in names) == exact and ("zrecombine" in names) == (not exact)
