@@ -1604,55 +1604,51 @@ ccut_status grouped_tables(ccut_plan *p, const ccut_eval_opts *eo, const std::ve
     if (!f.clifford && nm <= (size_t)kMaxTableBits && (f.n_variants << nm) <= (uint64_t(1) << 34)) nc.push_back(&f);
   }
   if (nc.size() < 2 || (eo->flags & CCUT_FLAG_ML)) return CCUT_OK;
-  // descriptors, then the classes' evolve and combine jobs, in one upload
-  std::stable_sort(nc.begin(), nc.end(), [](const Fragment *x, const Fragment *y) { return sv_waves(x->m()) < sv_waves(y->m()); });
-  std::vector<FragDev> descs;
-  std::vector<SvJob> jobs[2];
-  struct Class {
-    uint32_t first, count, m;
-    uint64_t wg[2];
-    size_t lds[2];
+  // the launches: evolve passes by their number of waves (1, 2, 4, 8 or 16), then
+  // combine passes by theirs; the descriptors and all jobs in one upload
+  struct Pass {
+    std::vector<SvJob> jobs;
+    SvShape shape;
+    size_t at = 0;  // of the jobs in the upload
   };
-  std::vector<Class> classes;
+  constexpr uint32_t kEvolve = 5;
+  Pass pass[kEvolve + kSvShapes];
+  std::vector<FragDev> descs;
   for (const Fragment *f : nc) {
     const FragRequest &r = reqs[f->index];
     const FragDev h = frag_desc(p, *f, r, eo->circuit);
-    if (classes.empty() || sv_waves(classes.back().m) != sv_waves(h.m))
-      classes.push_back(Class{(uint32_t)descs.size(), 0, h.m, {0, 0}, {0, 0}});
-    Class &C = classes.back();
     double *d = aget<double>(c, f->n_variants << r.meas.size());
     double *states = aget<double>(c, sv_states_bytes(h) / sizeof(double));
     if (!d || !states) return fail(c, CCUT_E_OOM, "device allocation failed");
-    for (int k = 0; k < 2; ++k) {  // evolve, combine
-      uint64_t n_wg;
-      size_t lds;
-      sv_pass_shape(h, k == 1, n_wg, lds);
+    for (const bool combine : {false, true}) {
+      const SvShape S = sv_pass_shape(h, combine);
+      Pass &P = pass[(combine ? kEvolve : 0) + __builtin_ctz(S.threads / 64)];
       SvJob J{};
       J.desc = (uint32_t)descs.size();
-      J.wg0 = C.wg[k];
+      J.wg0 = P.shape.add(S);
       J.dist = d;
       J.states = states;
-      C.wg[k] += n_wg;
-      C.lds[k] = std::max(C.lds[k], lds);
-      jobs[k].push_back(J);
+      P.jobs.push_back(J);
     }
-    C.m = std::max(C.m, h.m);
-    ++C.count;
     descs.push_back(h);
     dist[f->index] = d;
   }
-  const size_t nd = descs.size(), db = (nd * sizeof(FragDev) + 255) & ~size_t(255), jb = nd * sizeof(SvJob);
-  std::vector<char> block(db + 2 * jb, 0);
-  std::memcpy(block.data(), descs.data(), nd * sizeof(FragDev));
-  for (int k = 0; k < 2; ++k) std::memcpy(block.data() + db + k * jb, jobs[k].data(), jb);
+  std::vector<char> block(descs.size() * sizeof(FragDev));
+  std::memcpy(block.data(), descs.data(), block.size());
+  for (Pass &P : pass) {
+    P.at = (block.size() + 255) & ~size_t(255);
+    block.resize(P.at + P.jobs.size() * sizeof(SvJob), 0);
+    if (!P.jobs.empty()) std::memcpy(block.data() + P.at, P.jobs.data(), P.jobs.size() * sizeof(SvJob));
+  }
   char *d_block = (char *)upload(c, block.data(), block.size());
   if (!d_block) return fail(c, CCUT_E_OOM, "device allocation failed");
-  for (const Class &C : classes)
-    for (int k = 0; k < 2; ++k) {
-      KTimer t(c, CCUT_K_SV);
-      HIP_TRY(c, launch_sv_batch((const FragDev *)d_block, (const SvJob *)(d_block + db + k * jb) + C.first, C.count,
-                                 C.wg[k], k == 1, C.m, C.lds[k], c->cur));
-    }
+  for (uint32_t k = 0; k < kEvolve + kSvShapes; ++k) {
+    const Pass &P = pass[k];
+    if (P.jobs.empty()) continue;
+    KTimer t(c, CCUT_K_SV);
+    HIP_TRY(c, launch_sv_batch((const FragDev *)d_block, (const SvJob *)(d_block + P.at), (uint32_t)P.jobs.size(), P.shape,
+                               k >= kEvolve, c->cur));
+  }
   return CCUT_OK;
 }
 
@@ -2727,14 +2723,16 @@ ccut_status batch_enqueue(ccut_batch *b, bool tune) {
   // durations)
   struct SvClass {
     uint32_t m;
-    std::vector<SvJob> jobs[2];
-    SvJob *d_jobs[2] = {nullptr, nullptr};
-    uint64_t wg[2] = {0, 0};
-    size_t lds[2] = {0, 0};
+    struct Pass {
+      std::vector<SvJob> jobs;
+      SvJob *d_jobs = nullptr;
+      SvShape shape;
+    } pass[1 + kSvShapes];  // evolve, then combine by its number of waves
     double cost = 0.0;
   };
-  // one class per launch shape (number of waves): every state of up to 7
-  // qubits shares one, and those of 11 and 12; C.m is the class's widest state
+  // one class per launch shape of the evolve pass (number of waves): every state
+  // of up to 7 qubits shares one, and those of 11 and 12; C.m is the class's
+  // widest state
   std::vector<SvClass> classes;
   for (uint32_t m = 1; m <= (uint32_t)kMaxNcQubits; ++m) {
     if (m > 1 && sv_waves(m - 1) == sv_waves(m)) continue;  // handled with the class's first width
@@ -2748,40 +2746,37 @@ ccut_status batch_enqueue(ccut_batch *b, bool tune) {
       double *states = aget<double>(c, sv_states_bytes(h) / sizeof(double));
       if (!dist || !states) return fail(c, CCUT_E_OOM, "device allocation failed");
       pre_dist[ref.plan][ref.frag] = dist;
-      for (int k = 0; k < 2; ++k) {  // evolve, combine
-        uint64_t n_wg;
-        size_t l;
-        sv_pass_shape(h, k == 1, n_wg, l);
+      for (const bool combine : {false, true}) {
+        const SvShape S = sv_pass_shape(h, combine);
+        SvClass::Pass &P = C.pass[combine ? 1 + __builtin_ctz(S.threads / 64) : 0];
         SvJob J{};
         J.desc = ref.desc;
-        J.wg0 = C.wg[k];
+        J.wg0 = P.shape.add(S);
         J.dist = dist;
         J.states = states;
-        C.wg[k] += n_wg;
-        C.lds[k] = std::max(C.lds[k], l);
-        C.cost += k ? (double)n_wg * 1024 : (double)n_wg * (double)(1u << h.m) * (double)h.n_ops;
-        C.jobs[k].push_back(J);
+        C.cost += combine ? (double)S.n_wg * 1024 : (double)S.n_wg * (double)(1u << h.m) * (double)h.n_ops;
+        P.jobs.push_back(J);
       }
     }
-    if (!C.jobs[0].empty()) classes.push_back(std::move(C));
+    if (!C.pass[0].jobs.empty()) classes.push_back(std::move(C));
   }
   // the job lists go up in the classes' fixed order (a re-enqueue reuses
   // the first run's uploads in place: the order must not depend on the
   // launch order below)
   for (SvClass &C : classes)
-    for (int k = 0; k < 2; ++k) {
-      if (C.jobs[k].empty()) continue;
-      C.d_jobs[k] = (SvJob *)upload(c, C.jobs[k].data(), C.jobs[k].size() * sizeof(SvJob));
-      if (!C.d_jobs[k]) return fail(c, CCUT_E_OOM, "device allocation failed");
+    for (SvClass::Pass &P : C.pass) {
+      if (P.jobs.empty()) continue;
+      P.d_jobs = (SvJob *)upload(c, P.jobs.data(), P.jobs.size() * sizeof(SvJob));
+      if (!P.d_jobs) return fail(c, CCUT_E_OOM, "device allocation failed");
     }
   if (!b->nc.empty() && n_sv_streams) HIP_TRY(c, hipEventRecord(b->fork_ev, b->stream));
   auto sv_pass = [&]() -> ccut_status {
     if (!b->nc.empty()) {
       // (the fork point was recorded before the sampling chain)
       for (size_t k = 0; k < n_sv_streams; ++k) HIP_TRY(c, hipStreamWaitEvent(b->pool[k], b->fork_ev, 0));
-      // two launches per shape class: the computational-basis inputs evolved,
-      // then combined into every variant's outcomes; the
-      // classes go to the streams longest first, each to the stream with the
+      // per shape class the computational-basis inputs evolved in one launch,
+      // then combined into every variant's outcomes (a launch per number of
+      // waves); the classes go to the streams longest first, each to the stream with the
       // least work so far (work: amplitudes times program length, summed over
       // workgroups)
       // measured durations (ms) replace the estimates once the creation run has timed the classes
@@ -2801,11 +2796,10 @@ ccut_status batch_enqueue(ccut_batch *b, bool tune) {
           sv_used[k] = 1;
         }
         const int sp = span_begin(C.m, c->cur);
-        for (int k = 0; k < 2; ++k) {
-          if (C.jobs[k].empty()) continue;
+        for (const SvClass::Pass &P : C.pass) {
+          if (P.jobs.empty()) continue;
           KTimer tm(c, CCUT_K_SV);
-          HIP_TRY(c, launch_sv_batch(d_sv, C.d_jobs[k], (uint32_t)C.jobs[k].size(), C.wg[k], k == 1, C.m, C.lds[k],
-                                     c->cur));
+          HIP_TRY(c, launch_sv_batch(d_sv, P.d_jobs, (uint32_t)P.jobs.size(), P.shape, &P != C.pass, c->cur));
         }
         span_end(sp, c->cur);
       }

@@ -291,12 +291,25 @@ hipError_t launch_exact_tables(const uint64_t *models, uint32_t n_meas, uint64_t
 hipError_t launch_sv(const FragDev &frag, double *dist, void *states, hipStream_t s);
 uint32_t sv_inputs(const FragDev &h);
 size_t sv_states_bytes(const FragDev &h);
-// Workgroups and LDS of one pass of a fragment.
-void sv_pass_shape(const FragDev &h, bool combine, uint64_t &n_wg, size_t &lds);
-// One pass of many non-Clifford fragments of one shape (same number of waves;
-// m: the widest) in one launch; lds = the largest of theirs.
-hipError_t launch_sv_batch(const FragDev *descs, const SvJob *jobs, uint32_t n_jobs, uint64_t total_wg, bool combine,
-                           uint32_t m, size_t lds, hipStream_t s);
+// Workgroups of one pass of a fragment, or of many fragments' in one launch: of the
+// same number of threads each, with the largest LDS of theirs.
+struct SvShape {
+  uint64_t n_wg = 0;
+  uint32_t threads = 0;
+  size_t lds = 0;
+  // takes in another fragment's pass; its first workgroup
+  uint64_t add(const SvShape &o) {
+    const uint64_t first = n_wg;
+    n_wg += o.n_wg;
+    threads = o.threads;
+    lds = lds > o.lds ? lds : o.lds;
+    return first;
+  }
+};
+SvShape sv_pass_shape(const FragDev &h, bool combine);
+constexpr uint32_t kSvShapes = 4;  // thread counts of a combine pass: 64 << 0 .. 3
+hipError_t launch_sv_batch(const FragDev *descs, const SvJob *jobs, uint32_t n_jobs, const SvShape &S, bool combine,
+                           hipStream_t s);
 // Batched sampling over jobs (see SampleJob; wg0 numbers the units of this
 // launch's jobs from 0); lds = the largest sample_lds_bytes among them.  The
 // reduction runs over all jobs of a batch (rb0 numbering) in one launch.

@@ -190,15 +190,32 @@ __device__ inline double sv_prob(C2 a) { return a.re * a.re + a.im * a.im; }
 // lds: 36 rows of kSvRow doubles, the wave's sums on their way out (one short loop
 // stores them all: written out 36 times, the stores took as long to fetch as
 // the rest of a small call to run)
+// A walk is a serial chain of loads, and few outcomes make few units: the waves
+// of a unit take equal shares of the configurations that a lane walks through
+// (sv_share_bits: at most eight waves, a lone one for walks of up to eight, which
+// a second wave's sums through LDS would not shorten), and add their sums up
+// pairwise in a fixed order.  Calls on 12 qubits with one requested: four inputs
+// 248 -> 155 us, three 129 -> 73, four outputs 80 -> 52; 11 qubits, three inputs
+// 100 -> 66.
 constexpr uint32_t kSvRow = 65;    // (64 lanes, padded: lanes that read different rows meet different banks)
 constexpr uint32_t kSvSpread = 2;  // see the end of sv_combine
+constexpr uint32_t kSvShareBits = 3;
+__host__ __device__ inline uint32_t sv_lane_bits(uint32_t r, uint32_t nu) {  // of configurations, beside the outcome's
+  const uint32_t lr = r < 6 ? r : 6;
+  return nu < 6 - lr ? nu : 6 - lr;
+}
+__host__ __device__ inline uint32_t sv_share_bits(uint32_t r, uint32_t nu) {
+  const uint32_t walk = nu - sv_lane_bits(r, nu);
+  return walk <= 3 ? 0 : walk - 3 < kSvShareBits ? walk - 3 : kSvShareBits;
+}
 template <int L, class D>
 __device__ __attribute__((always_inline)) void sv_combine(D &F, double *__restrict__ dist, uint32_t unit,
                                                           const C2 *__restrict__ states, double *lds) {
   const uint32_t n_axes = F.n_axes, nm = F.n_meas, ins = F.in_axes, rmask = F.req_mask, umask = F.rest_mask;
-  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t lane = threadIdx.x & 63, share = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t r = __popc(rmask), nu = __popc(umask);
-  const uint32_t lr = r < 6 ? r : 6, lu = nu < 6 - lr ? nu : 6 - lr;  // lane bits: outcome, configuration
+  const uint32_t lr = r < 6 ? r : 6, lu = sv_lane_bits(r, nu);  // lane bits: outcome, configuration
+  const uint32_t sb = sv_share_bits(r, nu);
   const uint32_t xb = r - lr;
   uint32_t group = unit >> xb;
   // this lane's amplitude index and outcome, bit by bit over the qubits
@@ -221,6 +238,11 @@ __device__ __attribute__((always_inline)) void sv_combine(D &F, double *__restri
       }
       pos += mmask >> q & 1u;
     }
+  }
+  for (uint32_t i = sb; i-- > 0;) {  // the share: the highest of the bits walked through
+    const uint32_t q = 31u - (uint32_t)__builtin_clz(uhi);
+    base |= (share >> i & 1u) << q;
+    uhi &= ~(1u << q);
   }
   const bool live = lane < 1u << (lr + lu);
   // choices along the axes beyond the first two (three bits each)
@@ -328,6 +350,20 @@ __device__ __attribute__((always_inline)) void sv_combine(D &F, double *__restri
     uc = un;
   } while (uc);
   constexpr uint32_t n1 = L > 1 ? 6 : 1, n0 = L > 0 ? 6 : 1;
+  for (uint32_t h = 1u << sb >> 1; h; h >>= 1) {  // the upper half of the waves hands its sums to the lower half
+    double *to = lds + (share & (h - 1)) * (36 * kSvRow) + lane;
+    if (share >= h && share < 2 * h) {
+#pragma unroll
+      for (uint32_t k = 0; k < n1 * n0; ++k) to[k * kSvRow] = acc[k / n0][k % n0];
+    }
+    __syncthreads();
+    if (share < h) {
+#pragma unroll
+      for (uint32_t k = 0; k < n1 * n0; ++k) acc[k / n0][k % n0] += to[k * kSvRow];
+    }
+    __syncthreads();
+  }
+  if (share) return;
 #pragma unroll
   for (uint32_t k1 = 0; k1 < n1; ++k1)
 #pragma unroll
@@ -410,9 +446,10 @@ __global__ __launch_bounds__(1024, 8) void sv_evolve_kernel(const FragDev F, C2 
   sv_evolve(F, blockIdx.x, smem, states);
 }
 
-__global__ __launch_bounds__(64) void sv_combine_kernel(const FragDev F, double *__restrict__ dist,
-                                                        const C2 *__restrict__ states) {
-  __shared__ double lds[36 * kSvRow];
+// One unit a workgroup, 2^sv_share_bits waves.
+__global__ __launch_bounds__(64 << kSvShareBits) void sv_combine_kernel(const FragDev F, double *__restrict__ dist,
+                                                                        const C2 *__restrict__ states) {
+  extern __shared__ double lds[];
   sv_combine_any(F, dist, blockIdx.x, states, lds);
 }
 
@@ -437,9 +474,10 @@ __global__ __launch_bounds__(1024, 8) void sv_evolve_batch_kernel(const FragDev 
   sv_evolve(const_desc(descs, desc), blk, smem, reinterpret_cast<C2 *>(const_cast<double *>(uniform_ptr(J.states))));
 }
 
-__global__ __launch_bounds__(64) void sv_combine_batch_kernel(const FragDev *__restrict__ descs,
-                                                              const SvJob *__restrict__ jobs, uint32_t n_jobs) {
-  __shared__ double lds[36 * kSvRow];
+__global__ __launch_bounds__(64 << kSvShareBits) void sv_combine_batch_kernel(const FragDev *__restrict__ descs,
+                                                                              const SvJob *__restrict__ jobs,
+                                                                              uint32_t n_jobs) {
+  extern __shared__ double lds[];
   const SvJob &J = sv_job(jobs, n_jobs);
   const uint32_t desc = __builtin_amdgcn_readfirstlane(J.desc);
   const uint32_t unit = __builtin_amdgcn_readfirstlane((uint32_t)(blockIdx.x - J.wg0));
@@ -457,7 +495,7 @@ uint32_t sv_inputs(const FragDev &h) {
 
 size_t sv_states_bytes(const FragDev &h) { return ((size_t)1 << (sv_inputs(h) + h.m)) * sizeof(C2); }
 
-// Waves of the combine pass: blocks of 64 outcomes of the requested qubits
+// Units of the combine pass: blocks of 64 outcomes of the requested qubits
 // times the choices along the axes beyond the first two.
 static uint64_t combine_units(const FragDev &h) {
   const uint32_t n_in = sv_inputs(h), n_out = h.n_axes - n_in, r = h.n_meas - n_out;
@@ -466,46 +504,51 @@ static uint64_t combine_units(const FragDev &h) {
   return u;
 }
 
-// Workgroups and LDS bytes of the evolve pass (one workgroup per
-// computational-basis input, its state in LDS) and of the combine pass.
-void sv_pass_shape(const FragDev &h, bool combine, uint64_t &n_wg, size_t &lds) {
-  n_wg = combine ? combine_units(h) : 1ull << sv_inputs(h);
-  lds = combine ? 0 : ((size_t)1 << (h.m < 3 ? 3 : h.m)) * sizeof(C2);
-}
-
-static hipError_t evolve_lds(const void *kernel, size_t lds) {
-  if (lds > 160 * 1024) return hipErrorInvalidValue;
-  return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-}
-
-hipError_t launch_sv_batch(const FragDev *descs, const SvJob *jobs, uint32_t n_jobs, uint64_t total_wg, bool combine,
-                           uint32_t m, size_t lds, hipStream_t s) {
-  if (n_jobs == 0) return hipSuccess;
-  if (m == 0 || m > (uint32_t)kMaxNcQubits || total_wg > 0x7FFFFFFFull) return hipErrorInvalidValue;
-  if (combine) {
-    hipLaunchKernelGGL(sv_combine_batch_kernel, dim3((unsigned)total_wg), dim3(64), 0, s, descs, jobs, n_jobs);
-    return hipGetLastError();
+// Workgroups of a pass, with their threads and LDS bytes: evolve (one workgroup
+// per computational-basis input, its state in LDS) or combine (one per unit).
+SvShape sv_pass_shape(const FragDev &h, bool combine) {
+  SvShape S;
+  if (!combine) {
+    S.n_wg = 1ull << sv_inputs(h);
+    S.threads = 64 * sv_waves(h.m);
+    S.lds = ((size_t)1 << (h.m < 3 ? 3 : h.m)) * sizeof(C2);
+  } else {
+    const uint32_t sb = sv_share_bits(__builtin_popcount(h.req_mask), __builtin_popcount(h.rest_mask));
+    S.n_wg = combine_units(h);
+    S.threads = 64u << sb;
+    S.lds = (sb > 1 ? 1u << (sb - 1) : 1u) * (36 * kSvRow * sizeof(double));
   }
-  const hipError_t e = evolve_lds((const void *)sv_evolve_batch_kernel, lds);
+  return S;
+}
+
+static hipError_t set_lds(const void *kernel, const SvShape &S) {
+  if (S.lds > 160 * 1024 || S.n_wg > 0x7FFFFFFFull || S.threads == 0 || S.threads > 1024) return hipErrorInvalidValue;
+  if (S.lds <= 64 * 1024) return hipSuccess;  // (what every launch may ask for)
+  return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)S.lds);
+}
+
+hipError_t launch_sv_batch(const FragDev *descs, const SvJob *jobs, uint32_t n_jobs, const SvShape &S, bool combine,
+                           hipStream_t s) {
+  if (n_jobs == 0) return hipSuccess;
+  const hipError_t e = set_lds(combine ? (const void *)sv_combine_batch_kernel : (const void *)sv_evolve_batch_kernel, S);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(sv_evolve_batch_kernel, dim3((unsigned)total_wg), dim3(64 * sv_waves(m)), lds, s, descs, jobs,
-                     n_jobs);
+  if (combine)
+    hipLaunchKernelGGL(sv_combine_batch_kernel, dim3((unsigned)S.n_wg), dim3(S.threads), S.lds, s, descs, jobs, n_jobs);
+  else
+    hipLaunchKernelGGL(sv_evolve_batch_kernel, dim3((unsigned)S.n_wg), dim3(S.threads), S.lds, s, descs, jobs, n_jobs);
   return hipGetLastError();
 }
 
 hipError_t launch_sv(const FragDev &h, double *dist, void *states, hipStream_t s) {
   if (h.m == 0 || h.m > (uint32_t)kMaxNcQubits || h.n_meas > h.m || !states) return hipErrorInvalidValue;
-  uint64_t n_wg;
-  size_t lds;
-  sv_pass_shape(h, false, n_wg, lds);
-  hipError_t e = evolve_lds((const void *)sv_evolve_kernel, lds);
+  SvShape S = sv_pass_shape(h, false);
+  hipError_t e = set_lds((const void *)sv_evolve_kernel, S);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(sv_evolve_kernel, dim3((unsigned)n_wg), dim3(64 * sv_waves(h.m)), lds, s, h,
-                     static_cast<C2 *>(states));
+  hipLaunchKernelGGL(sv_evolve_kernel, dim3((unsigned)S.n_wg), dim3(S.threads), S.lds, s, h, static_cast<C2 *>(states));
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  sv_pass_shape(h, true, n_wg, lds);
-  if (n_wg > 0x7FFFFFFFull) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(sv_combine_kernel, dim3((unsigned)n_wg), dim3(64), 0, s, h, dist,
+  S = sv_pass_shape(h, true);
+  if ((e = set_lds((const void *)sv_combine_kernel, S)) != hipSuccess) return e;
+  hipLaunchKernelGGL(sv_combine_kernel, dim3((unsigned)S.n_wg), dim3(S.threads), S.lds, s, h, dist,
                      static_cast<const C2 *>(states));
   return hipGetLastError();
 }

@@ -95,3 +95,10 @@ def test_few_requested_outcomes_take_no_longer(ctx, m, n_out):
         ctx.timing(False)
         least.append(min(times))
     assert least[0] <= 1.25 * least[1], least
+
+
+@pytest.mark.parametrize("m,n_in,n_out,n_req", [(10, 2, 0, 0), (11, 0, 1, 0), (11, 4, 0, 2), (12, 5, 0, 0), (12, 1, 2, 1),
+                                                (12, 4, 0, 7)])
+def test_variant_tables_of_shared_walks(ctx, m, n_in, n_out, n_req):
+    """Two, four and eight waves that share the configurations of the qubits that are not asked for (one where 7 are)."""
+    test_variant_tables(ctx, m, n_in, n_out, n_req)

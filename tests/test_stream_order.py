@@ -106,3 +106,29 @@ result = log()
 """)
     names = " ".join(name for _, name, _, _, _ in H.launches_before(log))
     assert ("exact_strings" in names) == exact and ("zrecombine" in names) == (not exact)
+
+
+@pytest.mark.parametrize("m,inputs,request_,waves", [(9, 0, 0, 1), (10, 2, 0, 2), (11, 4, 3, 4), (12, 4, 0, 8), (12, 5, 6, 8),
+                                                     (12, 1, 9, 1), (12, 0, 12, 1)])
+def test_waves_of_a_combined_state(m, inputs, request_, waves):
+    """The configurations of the qubits that are not asked for which a lane walks through (beyond the six bits of the lanes)
+    are shared by up to eight waves, eight or more each."""
+    log = H.run(f"""
+ops, cuts = [], []
+for q in range({inputs}):
+    ops += [("H", q, 0, 0.0)]
+    cuts.append((q, len(ops) - 1))
+for q in range({m}):
+    ops += [("H", q, 0, 0.0), ("T", q, 0, 0.0), ("H", q, 0, 0.0)]
+for q in range({m} - 1):
+    ops.append(("CX", q, q + 1, 0.0))
+ops.append(("H", {m}, 0, 0.0))
+p = cc.Plan(ctx, {m} + 1, ops, cuts)
+clear()
+qubits = list(range({request_})) + [{m}]
+out = np.zeros(1 << len(qubits))
+cc.ccut_marginal(p.handle, ctx.handle, cc._eval_opts(), qubits, out)
+result = log()
+""")
+    (block,) = [b for _, name, _, b, _ in H.launches_before(log) if "sv_combine" in name]
+    assert block == 64 * waves
