@@ -358,9 +358,11 @@ __global__ __launch_bounds__(kSampleBlock) void sample_batch_kernel(const Sample
 // by the latency of their loads where the entries are few (49 blocks of 16 x 64
 // entries one thread to an entry: 16 us; eight to an entry: 4 us) and by memory
 // where they are many (15 blocks of 4096 x 1024: 93 us with eight threads to an
-// entry, which read 128 bytes in a row, 50 with one): as many threads as
-// kReduceFill allows.
-constexpr uint64_t kReduceFill = 1u << 17;
+// entry, which read 128 bytes in a row, 51 with one): as many threads as
+// kReduceFill allows.  49 blocks of 64 x 1024, 64 x 4096 and 256 x 2048 entries:
+// 11.2, 12.8 and 22.6 us for 2^17 threads, 7.5, 9.5 and 22.6 for 2^19, 7.5, 13.2
+// and 25.4 for 2^21.
+constexpr uint64_t kReduceFill = 1u << 19;
 __global__ __launch_bounds__(256) void hist_reduce_kernel(const uint32_t *__restrict__ partial, uint64_t nv,
                                                           uint32_t nblk, uint32_t bins, uint64_t shots, uint32_t slices,
                                                           double *__restrict__ dist, uint16_t *__restrict__ cnt16) {

@@ -58,7 +58,8 @@ result = log()
     assert block == 64 * waves
 
 
-@pytest.mark.parametrize("inputs,request_,slices", [(1, 4, 8), (2, 6, 8), (3, 8, 8), (4, 8, 2), (6, 9, 1), (6, 10, 1)])
+@pytest.mark.parametrize("inputs,request_,slices", [(1, 4, 8), (2, 6, 8), (3, 8, 8), (4, 8, 8), (4, 9, 4), (4, 10, 2),
+                                                     (5, 9, 1), (6, 10, 1)])
 def test_slices_of_a_histogram_reduction(inputs, request_, slices):
     """Few table entries (4^inputs variants of 2^request_) share their shot blocks between up to eight threads each; tables
     that fill the chip by themselves take a thread to an entry."""
