@@ -278,11 +278,11 @@ ccut_status ccut_zexpect(ccut_plan *plan, const ccut_eval_opts *eo, const uint64
  * that repeats an earlier call on the same plan exactly (same
  * options, request and, on the device, output address) is captured as a HIP
  * graph on its second occurrence (with a host output on its sixth) and
- * replayed from then on: every kernel and copy runs again, only the host-side planning and launch overhead is saved.
- * Up to 8 graphs per plan of calls with a device output and 8 of calls with
- * a host output (least recently used out).  Calls with
- * kernel timing enabled, or issued while the context's stream is being
- * captured by the caller always run eagerly.  enable = 0 turns replay off
+ * replayed from then on: every kernel and copy runs again, only the host-side
+ * planning and launch overhead is saved.  Up to 8 graphs per plan of calls with a
+ * device output and 8 of calls with a host output (least recently used out).
+ * Calls with kernel timing enabled, or issued while the context's stream is
+ * being captured by the caller always run eagerly.  enable = 0 turns replay off
  * (captured graphs are kept until their plan is destroyed).  Errors:
  * CCUT_E_INVALID (NULL context). */
 ccut_status ccut_call_graphs(ccut_ctx *ctx, int enable);
